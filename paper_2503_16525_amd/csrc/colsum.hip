@@ -20,6 +20,11 @@
 // shift that centres the fp32 exponent range); if a sum
 // ends above 2^100 the workgroup finds the exact row maxima in a score-only sweep and repeats.
 // Sweep 2 needs none: exp(score - lse) <= 1.  No atomics: the result is identical from run to run.
+//
+// A sweep whose blocks of fixed rows are few, or of very different length (the first keys are seen by every
+// query row, the last by a handful), leaves most of the chip waiting for its longest block.  Such a sweep is
+// cut along the streamed side into pieces of `chunk` tiles, the same absolute ranges for every block; the
+// pieces leave their log-sum-exps / column sums in the workspace and a small kernel combines them in order.
 #include "kvs_internal.h"
 
 #include <math.h>
@@ -41,9 +46,19 @@ constexpr int TILE_B = TS * ROW_B;
 constexpr int SLOT_B = TILE_B + 256;    // a tile and the 32 log-sum-exps of its rows (sweep 2)
 constexpr int RING = 4;                 // slots; tiles are requested RING - 1 steps ahead
 constexpr int LDS_BYTES = RING * SLOT_B;
+// How a sweep is cut (plan_cut).  Three workgroups are resident per compute unit, 768 on the chip.  Measured, whole
+// call, uncut -> cut: Qwen-shaped 8192 tokens 1685 -> 522 us (sweep 2 was 128 workgroups of 1 to 1792 tiles: 1450 us),
+// 4296 tokens 876 -> 180, 600 tokens 150 -> 27; Llama-shaped 20000 tokens 3790 -> 3000; Yi-shaped 24000 7140 -> 4300.
+constexpr int kCutResident = 768;
+constexpr int kCutUnits = 3072;         // a large sweep aims at this many pieces, four rounds: the last one is then short
+                                        // (8192 tokens: 528 us with two rounds, 522 with four, 535 with eight)
+constexpr int kCutSmallUnits = 512;     // a small one at less than one round, of pieces of
+constexpr int kCutMinChunk = 4;         // this many tiles (1500 tokens: 45 us with pieces of 8, 56 with 5; 600 tokens: 27 with 4, 31 with 8)
+constexpr int kCutRoundChunk = 16;      // to this many (3001 tokens: 112 us with 16, 123 with 24, 133 with 8)
 // base-2 offset of sweep 1's fixed reference above the first tile's maximum: the row sums are then
 // taken around 2^-60, where fp32 is as precise as around 1, and only overflow for a logit 160 above
 constexpr float kRefShift = 60.0f;
+constexpr float kNoKey = -1.0e30f;      // stands for the maximum of a row that sees no key of a piece
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -54,14 +69,35 @@ __device__ __forceinline__ int tile_row(int r, int hf) { return 8 * (r >> 2) + 4
 #define KVS_CS_BARRIER_(in_flight) asm volatile("s_waitcnt vmcnt(" #in_flight ")\n\ts_barrier" ::: "memory")
 #define KVS_CS_BARRIER(in_flight) KVS_CS_BARRIER_(in_flight)
 
+// Blocks of fixed rows that have streamed tiles in piece p of a cut sweep, 0 past the last piece.
+// Sweep 1: block b reaches tile p * chunk if its last query row's token is at least 32 p chunk, i.e. from
+// b = p * chunk * grp / 8 on.  Sweep 2: block b streams the last tiles(b) = n_tiles - 8 grp b tiles.
+template <int SWEEP>
+__host__ __device__ __forceinline__ int blocks_in_piece(int n, int grp, int n_blocks, int chunk, int p)
+{
+    static_assert(FIXED / TS == 8, "the arithmetic below");
+    if (SWEEP == 1) {
+        const int tiles = (n + TS - 1) / TS;
+        const int64_t first = (int64_t)p * chunk * grp / 8;
+        return (int64_t)p * chunk < tiles && first < n_blocks ? n_blocks - (int)first : 0;
+    }
+    const int64_t left = ((int64_t)n * grp + TS - 1) / TS - (int64_t)p * chunk;
+    if (left <= 0) return 0;
+    const int64_t b = (left + 8 * grp - 1) / (8 * grp);
+    return b < n_blocks ? (int)b : n_blocks;
+}
+
 // SWEEP 1: fixed = query rows, streamed = keys, writes lse2[g][row] (base-2, scale included).
 // SWEEP 2: fixed = keys, streamed = query rows, reads lse2, writes alpha[g][key].
 // Rows of a KV head's queries are flattened as row = token * grp + head-in-group.
+// chunk > 0: the streamed side is cut into pieces of that many tiles; piece p of the results goes to
+// part[p * n_kv_heads * (rows of `lse2` / columns of `alpha` per head)].
 template <int SWEEP>
 __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int n_kv_heads,
                                                        const uint16_t *__restrict__ q,
                                                        const uint16_t *__restrict__ k, float scale_log2,
-                                                       float *__restrict__ lse2, float *__restrict__ alpha)
+                                                       const float *__restrict__ lse2, float *__restrict__ result,
+                                                       int chunk)
 {
     extern __shared__ __attribute__((aligned(16))) char lds_b[];
     __shared__ int redo_flag;
@@ -74,11 +110,19 @@ __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int
     const uint32_t grp_magic = 0xffffffffu / (uint32_t)grp + 1u;
     auto div_grp = [&](uint32_t x) -> uint32_t { return grp == 1 ? x : __umulhi(x, grp_magic); };
     const int g = blockIdx.x % n_kv_heads;
-    const int blk = blockIdx.x / n_kv_heads;
+    int blk = blockIdx.x / n_kv_heads;
     const int n_qrows = n * grp;
     const int n_fixed = SWEEP == 1 ? n_qrows : n;
     const int n_stream = SWEEP == 1 ? n : n_qrows;
     const int n_blocks = (n_fixed + FIXED - 1) / FIXED;
+    // which piece: the blocks that reach a piece are a run at the heavy end of the order below
+    int piece = 0;
+    if (chunk > 0) {
+        for (int c = blocks_in_piece<SWEEP>(n, grp, n_blocks, chunk, 0); blk >= c; c = blocks_in_piece<SWEEP>(n, grp, n_blocks, chunk, piece)) {
+            blk -= c;
+            ++piece;
+        }
+    }
     // heaviest first: the last query rows see the most keys, the first keys are seen by the most rows
     const int fb = (SWEEP == 1 ? n_blocks - 1 - blk : blk) * FIXED;
 
@@ -114,8 +158,13 @@ __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int
     // sweep 1: key tiles 0 .. (last token of the workgroup) / 32; sweep 2: query-row tiles from the
     // workgroup's first key on
     const int last_fixed = min(fb + FIXED, n_fixed) - 1;
-    const int t_begin = SWEEP == 1 ? 0 : (int)(((int64_t)fb * grp) / TS);
-    const int t_end = SWEEP == 1 ? (int)div_grp((uint32_t)last_fixed) / TS + 1 : (n_stream + TS - 1) / TS;
+    int t_begin = SWEEP == 1 ? 0 : (int)(((int64_t)fb * grp) / TS);
+    int t_end = SWEEP == 1 ? (int)div_grp((uint32_t)last_fixed) / TS + 1 : (n_stream + TS - 1) / TS;
+    if (chunk > 0) {
+        // pieces count from the end of the streamed tensor at which a sweep starts (see tile_of)
+        if (SWEEP == 1) { t_begin = piece * chunk; t_end = min(t_end, t_begin + chunk); }
+        else { t_end -= piece * chunk; t_begin = max(t_begin, t_end - chunk); }
+    }
     const int n_tiles = t_end - t_begin;
     // Step k of a sweep takes tile t_begin + k in sweep 1 and tile t_end - 1 - k in sweep 2: every
     // workgroup of a KV head then starts at the same end of the streamed tensor (key 0 / the last
@@ -281,19 +330,20 @@ __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int
                         for (int r = 0; r < 16; ++r) ref[nb] = fmaxf(ref[nb], s[nb][r]);
                 });
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) ref[nb] = fmaxf(ref[nb], __shfl_xor(ref[nb], 32)) * scale_log2;
+                for (int nb = 0; nb < NB; ++nb) ref[nb] = fmaxf(fmaxf(ref[nb], __shfl_xor(ref[nb], 32)) * scale_log2, kNoKey);
             }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[nb] = 0.f;
             sweep([&](int k, int, floatx16 (&s)[NB]) {
                 if (pass == 0 && k == 0) {
-                    // the reference: the largest score of the row's first tile (key 0 is never masked)
+                    // the reference: the largest score of the row's first tile, whose first key a row sees if it
+                    // sees any of the piece (a row that sees none keeps a finite reference and a sum of 0)
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         float mx = s[nb][0];
 #pragma unroll
                         for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[nb][r]);
-                        ref[nb] = fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2 + kRefShift;
+                        ref[nb] = fmaxf(fmaxf(mx, __shfl_xor(mx, 32)) * scale_log2, kNoKey) + kRefShift;
                     }
                 }
 #pragma unroll
@@ -317,7 +367,13 @@ __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
-            if (hf == 0 && frow[nb] < n_fixed) lse2[(int64_t)g * n_qrows + frow[nb]] = ref[nb] + __builtin_amdgcn_logf(acc[nb]);
+            // the sum is taken around 2^-kRefShift: scaled back first (exactly), its logarithm is small and so is that
+            // logarithm's last place (with log2(acc) near -50 the column sums of 8192 tokens were 1.7e-6 off)
+            if (hf == 0 && frow[nb] < n_fixed) {
+                const bool low = acc[nb] < 1.0f;
+                const float l = (low ? ref[nb] - kRefShift : ref[nb]) + __builtin_amdgcn_logf(low ? acc[nb] * 0x1p60f : acc[nb]);
+                result[((int64_t)piece * n_kv_heads + g) * n_qrows + frow[nb]] = l;    // -inf for a sum of 0
+            }
     } else {
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[nb] = 0.f;
@@ -337,14 +393,68 @@ __global__ __launch_bounds__(NT, 2) void colsum_kernel(int n, int n_q_heads, int
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             acc[nb] += __shfl_xor(acc[nb], 32);
-            if (hf == 0 && frow[nb] < n_fixed) alpha[(int64_t)g * n + frow[nb]] = acc[nb];
+            if (hf == 0 && frow[nb] < n_fixed) result[((int64_t)piece * n_kv_heads + g) * n + frow[nb]] = acc[nb];
         }
     }
 }
 
+// lse2[g][row] of the pieces' log-sum-exps: m + log2(sum_p 2^(l_p - m)), pieces in order
+__global__ __launch_bounds__(256) void colsum_join_rows(int n_qrows, int n_kv_heads, int grp, int chunk, const float *__restrict__ part,
+                                                        float *__restrict__ lse2)
+{
+    const int row = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;
+    if (row >= n_qrows) return;
+    const int64_t at = (int64_t)g * n_qrows + row, stride = (int64_t)n_kv_heads * n_qrows;
+    const int pieces = row / grp / TS / chunk + 1;              // up to the row's own token
+    float m = -INFINITY, sum = 0.f;
+    for (int p = 0; p < pieces; ++p) m = fmaxf(m, part[p * stride + at]);
+    for (int p = 0; p < pieces; ++p) sum += __builtin_amdgcn_exp2f(part[p * stride + at] - m);
+    lse2[at] = m + __builtin_amdgcn_logf(sum);
+}
+
+// alpha[g][key] of the pieces' column sums, in order
+__global__ __launch_bounds__(256) void colsum_join_cols(int n, int n_kv_heads, int grp, int chunk, const float *__restrict__ part,
+                                                        float *__restrict__ alpha)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x, g = blockIdx.y;   // a workgroup is a block of fixed keys
+    static_assert(FIXED == 256, "one block of keys per workgroup");
+    if (i >= n) return;
+    const int64_t at = (int64_t)g * n + i, stride = (int64_t)n_kv_heads * n;
+    const int tiles = (int)(((int64_t)n * grp + TS - 1) / TS) - (int)blockIdx.x * 8 * grp;
+    const int pieces = (tiles + chunk - 1) / chunk;
+    float sum = 0.f;
+#pragma unroll 8
+    for (int p = 0; p < pieces; ++p) sum += part[p * stride + at];
+    alpha[at] = sum;
+}
+
+// How a sweep is cut: tiles per piece (0: not at all), pieces, workgroups per KV head.
+struct Cut {
+    int chunk, pieces, units;
+};
+template <int SWEEP>
+Cut plan_cut(const kvs_shape *shape, int64_t n)
+{
+    const int grp = shape->n_q_heads / shape->n_kv_heads;
+    const int64_t n_fixed = SWEEP == 1 ? n * grp : n, n_stream = SWEEP == 1 ? n : n * grp;
+    const int64_t blocks = (n_fixed + FIXED - 1) / FIXED, tiles = (n_stream + TS - 1) / TS;
+    const Cut whole = {0, 1, (int)blocks};
+    if (SWEEP == 1 && blocks * shape->n_kv_heads >= kCutResident) return whole;   // its blocks are many (every query head's rows) and fill the chip
+    // (causal: a block has half the tiles on average)
+    const int64_t work = blocks * tiles / 2 * shape->n_kv_heads;
+    int64_t chunk = work / kCutSmallUnits;
+    if (chunk > kCutRoundChunk) chunk = kCutRoundChunk;
+    if (chunk < work / kCutUnits) chunk = work / kCutUnits;
+    if (chunk < kCutMinChunk) chunk = kCutMinChunk;
+    if (chunk >= tiles) return whole;
+    Cut c = {(int)chunk, 0, 0};
+    for (int b; (b = blocks_in_piece<SWEEP>((int)n, grp, (int)blocks, (int)chunk, c.pieces)) > 0; ++c.pieces) c.units += b;
+    return c;
+}
+
 template <int SWEEP>
 kvs_status launch_sweep(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale_log2,
-                        float *lse2, float *alpha, hipStream_t st)
+                        const float *lse2, float *result, float *part, const Cut &cut, hipStream_t st)
 {
     static DeviceOnce attr_once;
     const kvs_status ast = once_per_device(attr_once, [] {
@@ -353,20 +463,43 @@ kvs_status launch_sweep(const kvs_shape *shape, int64_t n, const void *q, const 
         return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_attn_colsum: hipFuncSetAttribute: %s", hipGetErrorString(e));
     });
     if (ast != KVS_OK) return ast;
-    const int grp = shape->n_q_heads / shape->n_kv_heads;
-    const int64_t n_fixed = SWEEP == 1 ? n * grp : n;
-    const int64_t blocks = (n_fixed + FIXED - 1) / FIXED;
-    hipLaunchKernelGGL(colsum_kernel<SWEEP>, dim3((unsigned)(blocks * shape->n_kv_heads)), dim3(NT), LDS_BYTES, st,
-                       (int)n, shape->n_q_heads, shape->n_kv_heads, (const uint16_t *)q, (const uint16_t *)k, scale_log2,
-                       lse2, alpha);
-    return check_launch(SWEEP == 1 ? "kvs_attn_colsum(row sums)" : "kvs_attn_colsum(column sums)");
+    const int grp = shape->n_q_heads / shape->n_kv_heads, hk = shape->n_kv_heads;
+    hipLaunchKernelGGL(colsum_kernel<SWEEP>, dim3((unsigned)(cut.units * (int64_t)hk)), dim3(NT), LDS_BYTES, st,
+                       (int)n, shape->n_q_heads, hk, (const uint16_t *)q, (const uint16_t *)k, scale_log2,
+                       lse2, cut.chunk > 0 ? part : result, cut.chunk);
+    const kvs_status stt = check_launch(SWEEP == 1 ? "kvs_attn_colsum(row sums)" : "kvs_attn_colsum(column sums)");
+    if (stt != KVS_OK || cut.chunk == 0) return stt;
+    const dim3 grid((unsigned)(((SWEEP == 1 ? n * grp : n) + 255) / 256), (unsigned)hk);
+    if (SWEEP == 1) hipLaunchKernelGGL(colsum_join_rows, grid, dim3(256), 0, st, (int)(n * grp), hk, grp, cut.chunk, part, result);
+    else hipLaunchKernelGGL(colsum_join_cols, grid, dim3(256), 0, st, (int)n, hk, grp, cut.chunk, part, result);
+    return check_launch("kvs_attn_colsum(join)");
+}
+
+bool on_matrix_cores(const kvs_shape *shape, int64_t n_tokens)
+{
+    // rows are addressed with 32-bit byte offsets and divided by the group size with a 24-bit trick
+    return shape->dtype == KVS_BF16 && shape->head_dim == D && n_tokens * shape->n_q_heads * (int64_t)ROW_B < ((int64_t)1 << 32) &&
+           n_tokens * (shape->n_q_heads / shape->n_kv_heads) < (1 << 24);
+}
+
+size_t row_bytes(const kvs_shape *shape, int64_t n_tokens) { return ((size_t)n_tokens * shape->n_q_heads * sizeof(float) + 255) / 256 * 256; }
+
+// the pieces of one sweep at a time
+size_t piece_bytes(const kvs_shape *shape, int64_t n_tokens)
+{
+    const Cut c1 = plan_cut<1>(shape, n_tokens), c2 = plan_cut<2>(shape, n_tokens);
+    const size_t b1 = c1.chunk > 0 ? (size_t)c1.pieces * n_tokens * shape->n_q_heads * sizeof(float) : 0;
+    const size_t b2 = c2.chunk > 0 ? (size_t)c2.pieces * n_tokens * shape->n_kv_heads * sizeof(float) : 0;
+    return b1 > b2 ? b1 : b2;
 }
 
 } // namespace
 
 size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
-    return (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
+    if (n_tokens <= 0 || shape->n_kv_heads <= 0 || shape->n_q_heads < shape->n_kv_heads || !on_matrix_cores(shape, n_tokens))
+        return (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
+    return row_bytes(shape, n_tokens) + piece_bytes(shape, n_tokens) + 256;
 }
 
 } // namespace kvs
@@ -384,19 +517,27 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     if (!q || !k || !alpha) return fail(KVS_EINVAL, "kvs_attn_colsum: NULL tensor pointer");
     if (!aligned16(q) || !aligned16(k)) return fail(KVS_EINVAL, "kvs_attn_colsum: Q/K pointers must be 16-byte aligned");
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return fail(KVS_EINVAL, "kvs_attn_colsum: workspace must be given, 256-byte aligned");
-    if (workspace_bytes < colsum_workspace_bytes(shape, n_tokens))
-        return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, colsum_workspace_bytes(shape, n_tokens));
+    // the rows' log-sum-exps have to fit; with less than the size asked for the sweeps run uncut
+    const size_t least = (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
+    if (workspace_bytes < least) return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, least);
     // the matrix-core kernel: bf16, head_dim 128, a positive scale (it folds the scale into an exp2
-    // argument after taking maxima), rows addressed with 32-bit byte offsets and divided by the group
-    // size with a 24-bit trick.  Everything else takes the plain vector kernels.
+    // argument after taking maxima).  Everything else takes the plain vector kernels.
     const bool mfma = shape->dtype == KVS_BF16 && shape->head_dim == D && scale > 0.f;
     if (!mfma) return launch_colsum_valu(shape, n_tokens, q, k, scale, (float *)workspace, alpha, (hipStream_t)stream);
-    if (n_tokens * shape->n_q_heads * (int64_t)ROW_B >= ((int64_t)1 << 32) || n_tokens * (shape->n_q_heads / shape->n_kv_heads) >= (1 << 24))
+    if (!on_matrix_cores(shape, n_tokens))
         return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d heads exceed the 4 GiB the kernel addresses", (long long)n_tokens, shape->n_q_heads);
     float *lse2 = (float *)workspace;
     const float scale_log2 = scale * 1.4426950408889634f;
     hipStream_t hs = (hipStream_t)stream;
-    st = launch_sweep<1>(shape, n_tokens, q, k, scale_log2, lse2, alpha, hs);
+    Cut c1 = plan_cut<1>(shape, n_tokens), c2 = plan_cut<2>(shape, n_tokens);
+    float *part = (float *)((char *)workspace + row_bytes(shape, n_tokens));
+    if (workspace_bytes < colsum_workspace_bytes(shape, n_tokens)) {
+        const int grp = shape->n_q_heads / shape->n_kv_heads;
+        c1 = Cut{0, 1, (int)((n_tokens * grp + FIXED - 1) / FIXED)};
+        c2 = Cut{0, 1, (int)((n_tokens + FIXED - 1) / FIXED)};
+        part = nullptr;
+    }
+    st = launch_sweep<1>(shape, n_tokens, q, k, scale_log2, nullptr, lse2, part, c1, hs);
     if (st != KVS_OK) return st;
-    return launch_sweep<2>(shape, n_tokens, q, k, scale_log2, lse2, alpha, hs);
+    return launch_sweep<2>(shape, n_tokens, q, k, scale_log2, lse2, alpha, part, c2, hs);
 }
