@@ -29,6 +29,8 @@
 // pulls through its L2 is then its block's rows of weights plus its block's hidden rows, and the cut is
 // chosen for the smallest block first (the launch is as long as the fullest XCD) and the smallest sum of
 // the two after that.
+//
+// Launches too small for that tile take a second kernel, project_few_kernel, below.
 #include "kvs_internal.h"
 
 #include <type_traits>
@@ -296,6 +298,301 @@ __global__ __launch_bounds__(PNT, 1) void project_qkv_kernel(
     }
 }
 
+// ---- few tokens ---------------------------------------------------------------------------------------
+// With 256 x 256 tiles a launch of a few hundred tokens leaves most of the chip idle and the others on one long
+// tile.  Here a workgroup owns 64 FBW features of one head (rotation pairs together) x 32 TB tokens, the pair chosen per
+// launch so that the tiles just fill the chip.  Tiles this small are bound by the global -> LDS path (1 KiB per ~23
+// clocks and compute unit) and the LDS port, not by the matrix cores, so what matters is that nothing waits:
+//   * eight waves, two per SIMD: wave (kg, half) multiplies the 16-wide slice kg of every contraction step of 64 for
+//     one half of the features, so every 16-byte operand feeds FBW or TB MFMAs whatever the tile's shape;
+//   * operands of step j+1 are fetched from LDS while step j multiplies; one barrier per step, which says that step
+//     j+1 has landed and that everybody has fetched step j, whose slot then takes step j + slots;
+//   * the four slices' sums meet in LDS at the end, 32 tokens at a time, where the rotation pairs sit in one thread
+//     and rows leave as whole segments.
+// What bounds it: one tile on an otherwise idle chip runs at the global -> LDS rate (128 x 160 tile, hidden 4096: 27 us;
+// 36 us before fetches and loads were dealt out between the MFMAs); with all units busy L2 takes over (41 us at 656
+// tokens, 550 MB in all).  Starting every tile at its own place in the contraction loses the shared L2 lines: 71 us.
+constexpr int FNT = 512;
+constexpr int FBK = 64;                        // contraction step; rows of 128 bytes in LDS
+constexpr int FROW_B = FBK * 2;
+constexpr int FLDS_MAX = 152 * 1024;
+
+// slots of the ring: what fits, at most 12 (a few tokens: the launch streams the weights, and bytes in flight are all)
+constexpr int few_slots(int fbw, int tb)
+{
+    const int stage = (64 * fbw + 32 * tb) * FROW_B, n = FLDS_MAX / stage;
+    return n < 12 ? n : 12;
+}
+constexpr int few_lds_bytes(int fbw, int tb)
+{
+    const int ring = few_slots(fbw, tb) * (64 * fbw + 32 * tb) * FROW_B, join = 4 * 32 * (64 * fbw + 4) * 4;
+    return ring > join ? ring : join;
+}
+
+template <int FBW, int TB>
+__global__ __launch_bounds__(FNT, 2) void project_few_kernel(
+    int n_q_heads, int n_kv_heads, int hidden, const uint16_t *__restrict__ x, int64_t n_tokens,
+    const int32_t *__restrict__ x_rows, const int32_t *__restrict__ sel_pos, int n_sel,
+    const uint16_t *__restrict__ w, const float *__restrict__ rope, int rope_positions,
+    uint16_t *__restrict__ q_out, uint16_t *__restrict__ k_out, uint16_t *__restrict__ v_out,
+    int tiles_m, int n_tiles, int per_xcd)
+{
+    constexpr int WROWS = 64 * FBW, TROWS = 32 * TB;
+    constexpr int STAGE_B = (WROWS + TROWS) * FROW_B, W_B = WROWS * FROW_B;
+    constexpr int SLOTS = few_slots(FBW, TB);
+    constexpr int NLOADS = (WROWS + TROWS) / 8;                 // 1 KiB instructions per stage, dealt to the eight waves
+    constexpr int PER_WAVE = (NLOADS + 7) / 8, SHORT_FROM = NLOADS % 8 == 0 ? 8 : NLOADS % 8;   // waves from here on issue one fewer
+    static_assert(SLOTS >= 3, "ring depth");
+    extern __shared__ __attribute__((aligned(16))) char plds[];
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, hf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kg = wave & 3, half = wave >> 2;
+    // an XCD takes a run of tiles, the token tile fastest: the workgroups that share weight rows share an L2
+    const int tile = (int)(blockIdx.x % PXCDS) * per_xcd + (int)(blockIdx.x / PXCDS);
+    if (tile >= n_tiles) return;                                // uniform
+    const int tile_n = tile / tiles_m, m0 = (tile % tiles_m) * TROWS;
+    const int head = FBW == 2 ? tile_n : tile_n >> 1, c0 = FBW == 2 ? 0 : 32 * (tile_n & 1);
+    const int nk = hidden / FBK;
+    const uint32_t row_bytes = (uint32_t)hidden * 2u;
+
+    // ---- staging: one instruction moves 8 rows of 128 bytes; instruction q of a stage is weight rows 8 q .. for
+    // 8 q < WROWS, token rows behind them; wave v issues q = v, v + 8, ...  Piece p of row r sits at position
+    // p ^ ((r >> 1) & 7): 16 lanes reading one piece of 16 rows then hit all 64 banks once.
+    uint32_t voff[PER_WAVE];
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+        const int r = 8 * (wave + 8 * i) + (lane >> 3);
+        const uint32_t piece = (uint32_t)((lane & 7) ^ ((r >> 1) & 7)) * 16u;
+        if (r < WROWS) {
+            // feature row r of the tile: FBW 2: channel r; FBW 1: channels c0 .. c0+31, then c0+64 .. c0+95
+            const int c = FBW == 2 ? r : c0 + (r & 31) + 64 * (r >> 5);
+            voff[i] = (uint32_t)(head * PD + c) * row_bytes + piece;
+        } else {
+            const int t = min(m0 + r - WROWS, n_sel - 1);       // rows past the end repeat the last token (never stored)
+            int64_t xr = x_rows ? (int64_t)x_rows[t] : (int64_t)t;
+            xr = min(max(xr, (int64_t)0), n_tokens - 1);        // memory safety; the caller guarantees the range
+            voff[i] = (uint32_t)xr * row_bytes + piece;
+        }
+    }
+    auto make_rsrc = [&](const uint16_t *base, uint64_t bytes) -> u32x4_t {
+        const uint64_t a = reinterpret_cast<uint64_t>(base);
+        u32x4_t r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
+        r.x = __builtin_amdgcn_readfirstlane(r.x);
+        r.y = __builtin_amdgcn_readfirstlane(r.y);
+        r.z = __builtin_amdgcn_readfirstlane(r.z);
+        return r;
+    };
+    const u32x4_t wrs = make_rsrc(w, (uint64_t)(n_q_heads + 2 * n_kv_heads) * PD * row_bytes);
+    const u32x4_t xrs = make_rsrc(x, (uint64_t)n_tokens * row_bytes);
+    const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)plds);
+    // the offsets above came through ordinary loads: none may be outstanding when the counted waits begin
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // load i of the wave's share of a stage; steps past the end repeat the last one (their slots are never read)
+    auto stage_one = [&](int step, int slot, int i) {
+        const uint32_t soff = __builtin_amdgcn_readfirstlane((uint32_t)min(step, nk - 1) * (uint32_t)FROW_B);
+        const int q = wave + 8 * i;
+        if (i < PER_WAVE - 1 || wave < SHORT_FROM) {            // uniform
+            const uint32_t dst = __builtin_amdgcn_readfirstlane(lds_base + (uint32_t)(slot * STAGE_B + q * 1024));
+            const u32x4_t &rs = i < WROWS / 64 ? wrs : xrs;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" :: "s"(dst), "v"(voff[i]), "s"(rs), "s"(soff));
+        }
+    };
+    auto stage = [&](int step, int slot) {
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) stage_one(step, slot, i);
+    };
+    // waits for this wave's own loads but the youngest `SLOTS - 2` stages', and for its LDS fetches; then the barrier
+    auto step_barrier = [&]() {
+        if (wave < SHORT_FROM) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((SLOTS - 2) * PER_WAVE) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"((SLOTS - 2) * (PER_WAVE - 1)) : "memory");
+    };
+    static_assert((SLOTS - 2) * PER_WAVE <= 63, "the wait's counter has 6 bits");
+
+    // ---- operands: lane (ln, hf) reads piece 2 kg + hf of row (block base + ln)
+    const uint32_t rd = (uint32_t)(ln * FROW_B + (((2 * kg + hf) ^ ((ln >> 1) & 7)) * 16));
+    struct Ops { u32x4_t a[FBW], b[TB]; };
+    auto fetch = [&](int slot, Ops &o) {
+        const char *base = plds + slot * STAGE_B + rd;
+#pragma unroll
+        for (int i = 0; i < FBW; ++i) o.a[i] = *reinterpret_cast<const u32x4_t *>(base + (FBW * half + i) * 32 * FROW_B);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) o.b[i] = *reinterpret_cast<const u32x4_t *>(base + W_B + i * 32 * FROW_B);
+    };
+    floatx16 acc[FBW][TB];
+#pragma unroll
+    for (int fb = 0; fb < FBW; ++fb)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[fb][tb][r] = 0.f;
+    auto multiply = [&](const Ops &o) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+            for (int fb = 0; fb < FBW; ++fb)
+                acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(o.a[fb]), as_frag(o.b[tb]), acc[fb][tb], 0, 0, 0);
+    };
+
+    // Stages 0 .. SLOTS-2 go out ahead; stage 0 has landed when the SLOTS-2 younger ones may be in flight.
+#pragma unroll
+    for (int s = 0; s < SLOTS - 1; ++s) stage(s, s);
+    step_barrier();
+    Ops o0, o1;
+    fetch(0, o0);
+    stage(SLOTS - 1, SLOTS - 1);
+    int slot = 0;                                   // of step j
+    auto next = [](int s) { return s + 1 == SLOTS ? 0 : s + 1; };
+    auto step = [&](int j, const Ops &cur, Ops &nxt) {
+        step_barrier();                             // step j+1 has landed; everybody has fetched step j
+        const int s1 = next(slot);
+        const char *base = plds + s1 * STAGE_B + rd;
+        // issue is in order: the step's fetches and loads are dealt out between its MFMAs and pinned there
+        constexpr int MM = FBW * TB, SIDE = FBW + TB + PER_WAVE;
+#pragma unroll
+        for (int m = 0; m < MM; ++m) {
+            const int tb = m / FBW, fb = m % FBW;
+            acc[fb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(cur.a[fb]), as_frag(cur.b[tb]), acc[fb][tb], 0, 0, 0);
+#pragma unroll
+            for (int o = m * SIDE / MM; o < (m + 1) * SIDE / MM; ++o) {
+                const int ld = (o + 1) * PER_WAVE / SIDE, is_ld = ld != o * PER_WAVE / SIDE, f = o - ld;
+                if (is_ld) stage_one(j + SLOTS, slot, ld - 1);
+                else if (f < FBW) nxt.a[f] = *reinterpret_cast<const u32x4_t *>(base + (FBW * half + f) * 32 * FROW_B);
+                else nxt.b[f - FBW] = *reinterpret_cast<const u32x4_t *>(base + W_B + (f - FBW) * 32 * FROW_B);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        slot = s1;
+    };
+    int j = 0;
+    for (; j + 2 <= nk; j += 2) {
+        step(j, o0, o1);
+        step(j + 1, o1, o0);
+    }
+    if (j < nk) multiply(o0);                       // odd number of steps
+    // nothing may still be on its way into LDS when it changes its use
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+
+    // ---- epilogue, 32 tokens at a time: [kg][token][feature] sums in LDS, 16 bytes of padding per row
+    constexpr int JROW = WROWS + 4;                 // floats
+    float *join = reinterpret_cast<float *>(plds);
+    uint16_t *dst;
+    int heads_of_dst, h_local;
+    if (head < n_q_heads) { dst = q_out; heads_of_dst = n_q_heads; h_local = head; }
+    else if (head < n_q_heads + n_kv_heads) { dst = k_out; heads_of_dst = n_kv_heads; h_local = head - n_q_heads; }
+    else { dst = v_out; heads_of_dst = n_kv_heads; h_local = head - n_q_heads - n_kv_heads; }
+    const bool turned = rope != nullptr && head < n_q_heads + n_kv_heads;
+    constexpr int PER_TOK = 8 * FBW;                // threads per token: four channels and their partners 64 on each
+    const int my_tok = tid / PER_TOK, my_c = 4 * (tid % PER_TOK);   // channel inside the tile's lower half
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        __syncthreads();
+#pragma unroll
+        for (int fb = 0; fb < FBW; ++fb)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                *reinterpret_cast<float4 *>(join + (kg * 32 + ln) * JROW + 32 * (FBW * half + fb) + 8 * r4 + 4 * hf) =
+                    make_float4(acc[fb][tb][4 * r4], acc[fb][tb][4 * r4 + 1], acc[fb][tb][4 * r4 + 2], acc[fb][tb][4 * r4 + 3]);
+        __syncthreads();
+        const int t = m0 + 32 * tb + my_tok;
+        if (my_tok < 32 && t < n_sel) {
+            float y1[4] = {0.f, 0.f, 0.f, 0.f}, y2[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float4 a = *reinterpret_cast<const float4 *>(join + (k * 32 + my_tok) * JROW + my_c);
+                const float4 b = *reinterpret_cast<const float4 *>(join + (k * 32 + my_tok) * JROW + 32 * FBW + my_c);
+                y1[0] += a.x; y1[1] += a.y; y1[2] += a.z; y1[3] += a.w;
+                y2[0] += b.x; y2[1] += b.y; y2[2] += b.z; y2[3] += b.w;
+            }
+            const int c = c0 + my_c;                // channel of the head, its partner is c + 64
+            if (turned) {
+                int p = sel_pos[t];
+                p = min(max(p, 0), rope_positions - 1);         // memory safety; the caller guarantees the range
+                const float4 *cs = reinterpret_cast<const float4 *>(rope + ((int64_t)p * (PD / 2) + c) * 2);
+                const float4 cs01 = cs[0], cs23 = cs[1];
+                const float co[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a = y1[i], b = y2[i];
+                    y1[i] = a * co[i] - b * sn[i];
+                    y2[i] = b * co[i] + a * sn[i];
+                }
+            }
+            uint16_t *row = dst + ((int64_t)t * heads_of_dst + h_local) * PD + c;
+            *reinterpret_cast<uint2 *>(row) = make_uint2(pack_bf16x2(y1[0], y1[1]), pack_bf16x2(y1[2], y1[3]));
+            *reinterpret_cast<uint2 *>(row + 64) = make_uint2(pack_bf16x2(y2[0], y2[1]), pack_bf16x2(y2[2], y2[3]));
+        }
+    }
+}
+
+} // namespace
+
+namespace {
+struct ProjectArgs {
+    const kvs_shape *shape;
+    int hidden;
+    const void *x;
+    int64_t n_tokens;
+    const int32_t *x_rows, *sel_pos;
+    int64_t n_sel;
+    const void *w;
+    const float *rope;
+    int64_t rope_positions;
+    void *q, *k, *v;
+};
+
+template <int FBW, int TB>
+kvs_status launch_few(const ProjectArgs &a, hipStream_t hs)
+{
+    constexpr int lds = few_lds_bytes(FBW, TB);
+    static DeviceOnce attr_once;
+    const kvs_status st = once_per_device(attr_once, [] {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&project_few_kernel<FBW, TB>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_project_qkv: hipFuncSetAttribute: %s", hipGetErrorString(e));
+    });
+    if (st != KVS_OK) return st;
+    const int64_t tiles_m = (a.n_sel + 32 * TB - 1) / (32 * TB);
+    const int64_t tiles = tiles_m * (a.shape->n_q_heads + 2 * a.shape->n_kv_heads) * (2 / FBW);
+    const int64_t per_xcd = (tiles + PXCDS - 1) / PXCDS;
+    hipLaunchKernelGGL((project_few_kernel<FBW, TB>), dim3((unsigned)(per_xcd * PXCDS)), dim3(FNT), lds, hs, a.shape->n_q_heads,
+                       a.shape->n_kv_heads, a.hidden, (const uint16_t *)a.x, a.n_tokens, a.x_rows, a.sel_pos, (int)a.n_sel,
+                       (const uint16_t *)a.w, a.rope, (int)a.rope_positions, (uint16_t *)a.q, (uint16_t *)a.k, (uint16_t *)a.v,
+                       (int)tiles_m, (int)tiles, (int)per_xcd);
+    return check_launch("kvs_project_qkv(few)");
+}
+
+// Which tile.  A launch takes rounds of one workgroup per compute unit, 32 units per XCD; a round costs what its tile
+// costs, measured in nanoseconds per 64 of the contraction and per tile (rounds that fill the chip).  The cheapest sum
+// is taken.  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16 tokens 72 -> 12 us, 96 tokens 73 -> 16,
+// 256 tokens 75 -> 22, 384 tokens 75 -> 27, 640 tokens 75 -> 37, 656 tokens 75 -> 41, 1280 tokens 82 -> 75; from some
+// 1500 tokens on (85 against 91) the large tiles fill the chip and win.
+struct FewTile {
+    int fbw, tb, step_ns, fixed_ns;
+    kvs_status (*launch)(const ProjectArgs &, hipStream_t);
+};
+constexpr int kLargeStepNs = 1100, kLargeFixedNs = 8000;        // the 256 x 256 kernel
+constexpr int kUnitsPerXcd = 32;
+const FewTile few_tiles[] = {
+    {1, 1, 150, 2500, launch_few<1, 1>}, {1, 2, 210, 2600, launch_few<1, 2>}, {2, 1, 235, 2600, launch_few<2, 1>},
+    {1, 3, 270, 2700, launch_few<1, 3>}, {2, 2, 300, 2800, launch_few<2, 2>}, {2, 3, 410, 3000, launch_few<2, 3>},
+    {2, 4, 510, 3300, launch_few<2, 4>}, {2, 5, 590, 3500, launch_few<2, 5>},
+};
+
+// NULL: the 256 x 256 kernel
+const FewTile *choose_few(const ProjectArgs &a)
+{
+    const int64_t heads = a.shape->n_q_heads + 2 * a.shape->n_kv_heads, steps = a.hidden / FBK;
+    auto rounds = [](int64_t tiles) { return ((tiles + PXCDS - 1) / PXCDS + kUnitsPerXcd - 1) / kUnitsPerXcd; };
+    const int64_t large = (a.n_sel + PBM - 1) / PBM * (heads * PD / PBN);
+    int64_t best = rounds(large) * (steps * kLargeStepNs + kLargeFixedNs);
+    const FewTile *pick = nullptr;
+    for (const FewTile &f : few_tiles) {
+        const int64_t tiles = (a.n_sel + 32 * f.tb - 1) / (32 * f.tb) * heads * (2 / f.fbw);
+        const int64_t cost = rounds(tiles) * (steps * f.step_ns + f.fixed_ns);
+        if (cost < best && tiles <= 0x7fffffff) { best = cost; pick = &f; }
+    }
+    return pick;
+}
 } // namespace
 } // namespace kvs
 
@@ -326,6 +623,8 @@ extern "C" kvs_status kvs_project_qkv(const kvs_shape *shape, int32_t hidden, co
         return fail(KVS_EUNSUPPORTED, "kvs_project_qkv: x or w of 4 GiB or more");
     if (n_sel > 0x7fffffff) return fail(KVS_EUNSUPPORTED, "kvs_project_qkv: too many tokens");
     if (rope && rope_positions * (int64_t)(PD * 4) >= ((int64_t)1 << 32)) return fail(KVS_EUNSUPPORTED, "kvs_project_qkv: rotary table of 4 GiB or more");
+    const ProjectArgs args = {shape, hidden, x, n_tokens, x_rows, sel_pos, n_sel, w_qkv, rope, rope_positions, q_out, k_out, v_out};
+    if (const FewTile *few = choose_few(args)) return few->launch(args, (hipStream_t)stream);
     static DeviceOnce attr_once;
     st = once_per_device(attr_once, [] {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&project_qkv_kernel),
