@@ -1,0 +1,70 @@
+"""kvs_first_order_impact (bf16) where its list of reused tokens and its pieces of rows have edges, against the formula in
+64-bit torch on the same H and log-sum-exp; with the full workspace, with the least one (no list, rows uncut) and with no mask."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_16525_amd import binding as B
+from paper_2503_16525_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(lay, h, lse, grp):
+    n = lay["q"].shape[0]
+    imp, slack = np.zeros((3, n)), np.zeros(n)
+    causal = torch.tril(torch.ones((n, n), dtype=torch.bool))
+    for head in range(lay["q"].shape[1]):
+        g = head // grp
+        q, kf, vf = lay["q"][:, head].double(), lay["k_fresh"][:, g].double(), lay["v_fresh"][:, g].double()
+        dk, dv = lay["k_cache"][:, g].double() - kf, lay["v_cache"][:, g].double() - vf
+        a = torch.where(causal, torch.exp(q @ kf.T - lse[:, head, None].double()), torch.zeros((), dtype=torch.float64))
+        t = q @ dk.T
+        x = vf[None] - h[:, head, None].double()                       # [row, token, channel]
+        imp[0] += (a.sum(0) * dv.abs().sum(-1)).numpy()
+        imp[1] += (a * t.abs() * x.abs().sum(-1)).sum(0).numpy()
+        imp[2] += (a * (dv[None] + t[..., None] * x).abs().sum(-1)).sum(0).numpy()
+        # t is the difference of two fp32 dot products, each 8 steps of 16 channels whose partial sums stay below
+        # sum |q| |k|: off by up to 2 * 8 * 2^-24 of that, whatever is left of t
+        kc = lay["k_cache"][:, g].double()
+        e = 8 * 2.0 ** -24 * (q.abs() @ kf.abs().T + q.abs() @ kc.abs().T)
+        slack += (a * e * x.abs().sum(-1)).sum(0).numpy()
+    return imp, (0.0 * slack, slack, slack)
+
+
+@pytest.mark.parametrize("n,reused_tokens,hq,hk,d", [
+    (1, 1, 4, 2, 128), (33, 0, 4, 2, 128), (64, 1, 7, 1, 128), (65, 63, 4, 4, 128), (129, 64, 4, 1, 128), (200, 65, 14, 2, 128),
+    (257, 257, 4, 2, 128), (300, 190, 3, 3, 64), (160, 128, 8, 2, 64)])
+def test_list_and_piece_edges(n, reused_tokens, hq, hk, d):
+    print(f"impact tiles: {n} tokens, {reused_tokens} reused, {hq}x{hk} heads, head_dim {d}", flush=True)
+    w = synth.scaled(synth.LLAMA, n, n_q_heads=hq, n_kv_heads=hk, head_dim=d, coverage=1.0)
+    lay = synth.make_layer(w)
+    picked = np.random.default_rng(n).permutation(n)[:reused_tokens]
+    mask = torch.zeros(n, dtype=torch.uint8)
+    mask[picked] = 1
+    q, k, v = lay["q"].double(), lay["k_fresh"].double(), lay["v_fresh"].double()
+    grp = hq // hk
+    s = torch.einsum("jhd,ihd->hji", q, k.repeat_interleave(grp, 1)).masked_fill(~torch.tril(torch.ones((n, n), dtype=torch.bool)), -np.inf)
+    lse = torch.logsumexp(s, -1).T.contiguous()
+    h = torch.einsum("hji,ihd->jhd", torch.softmax(s, -1), v.repeat_interleave(grp, 1)).to(torch.bfloat16).contiguous()
+    lse = lse.float()
+    ref, slack = reference(lay, h, lse, grp)
+    sh = B.shape_of(w)
+    full = B.kvs_workspace_size("first_order_impact", sh, 1, n)
+    least = 12 * hk * n + 256
+    dev = {x: lay[x].cuda() for x in ("q", "k_fresh", "v_fresh", "k_cache", "v_cache")}
+    for what, ws_bytes, m in (("list and pieces", full, mask), ("neither", least, mask), ("no mask", full, None)):
+        out = [torch.full((n,), float("nan"), device="cuda") for _ in range(3)]
+        ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device="cuda")        # NaN patterns: nothing unwritten may be read
+        B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(),
+                                 None if m is None else m.cuda(), 1.0, *out, ws)
+        cand = np.ones(n, bool) if m is None else m.numpy() != 0
+        for name, o, r, sl in zip(("value", "key", "both"), out, ref, slack):
+            got = o.cpu().numpy()
+            assert np.array_equal(np.isneginf(got), ~cand), (what, name)
+            # fp32: dot products of 128 terms (1e-6 of a logit), the hardware's exp, sums of positive terms
+            err = np.abs(got[cand] - r[cand])
+            assert np.all(err <= 2e-5 * np.abs(r[cand]) + 1e-6 + sl[cand]), f"{what}: {name}: {err.max()}"
+    with pytest.raises(B.KvsError):
+        B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(),
+                                 mask.cuda(), 1.0, *out, torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
