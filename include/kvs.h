@@ -208,7 +208,7 @@ KVS_API kvs_status kvs_scatter_kv(const kvs_shape *shape, int64_t n_rows,
  *         summation order.  With less, such launches keep whole key ranges.
  * bf16 inputs (head_dim 128, scale > 0) are contracted on the matrix cores with fp32 accumulation
  * and an fp32 softmax, the softmax weights entering the second product as bf16; every other case
- * takes an fp32 vector path.
+ * is computed in fp32 throughout, on the fp32 matrix instruction.
  */
 KVS_API kvs_status kvs_partial_attention(const kvs_shape *shape, int32_t batch,
                                  const int64_t *ctx_off, const int64_t *ctx_len,
@@ -261,7 +261,7 @@ KVS_API kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, int64
  * Cost: two passes of n_tokens^2 / 2 * head_dim * n_q_heads multiply-adds on the matrix cores.
  *
  * bf16 with head_dim 128 and a positive scale runs on the matrix cores (tensors below 4 GiB);
- * every other supported shape, fp32 included, takes a plain vector kernel that is only meant for
+ * every other supported shape, fp32 included, takes an fp32 kernel that is only meant for
  * small problems.  Q and K as for the other calls: [n_tokens, heads, head_dim], 16-byte aligned.
  *
  * q         [dev] [n_tokens, n_q_heads, head_dim]

@@ -1,6 +1,6 @@
 // Host-side pieces of the C ABI that are not tied to one kernel: error reporting, shape
 // validation, workspace sizing and the kvs_partial_attention entry point, which validates the
-// ragged batch description and dispatches to the matrix-core or the fp32 vector kernel.
+// ragged batch description and dispatches to the matrix-core or the fp32 kernel.
 #include "kvs_internal.h"
 #include "attention.h"
 
@@ -110,7 +110,7 @@ extern "C" kvs_status kvs_partial_attention(const kvs_shape *shape, int32_t batc
         return fail(KVS_EINVAL, "kvs_partial_attention: Q/K/V/out pointers must be 16-byte aligned");
     hipStream_t hs = (hipStream_t)stream;
     // the matrix-core kernel folds the scale into an exp2 argument and takes the row max before
-    // scaling, which needs scale > 0; anything else goes to the vector kernel
+    // scaling, which needs scale > 0; anything else goes to the fp32 kernel
     const bool mfma = attention_mfma_supports(shape) && scale > 0.f && scale < 3.0e38f;
     for (int32_t b0 = 0; b0 < batch; b0 += kAttnMaxReq) {
         const int nr = (batch - b0) < kAttnMaxReq ? (batch - b0) : kAttnMaxReq;
@@ -127,7 +127,7 @@ extern "C" kvs_status kvs_partial_attention(const kvs_shape *shape, int32_t batc
         const int64_t ns = cu_sel[b0 + nr] - cu_sel[b0];
         if (ns == 0) continue;
         st = mfma ? launch_attention_mfma(shape, bd, ns, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, workspace, workspace_bytes, hs)
-                  : launch_attention_valu(shape, bd, ns, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, hs);
+                  : launch_attention_f32(shape, bd, ns, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, hs);
         if (st != KVS_OK) return st;
     }
     return KVS_OK;

@@ -84,7 +84,7 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
                                   float scale, void *out, float *lse_out, void *workspace,
                                   const AttnSplitPlan &plan, hipStream_t st);
 
-kvs_status launch_attention_valu(const kvs_shape *shape, const AttnBatch &bd, int64_t n_sel,
+kvs_status launch_attention_f32(const kvs_shape *shape, const AttnBatch &bd, int64_t n_sel,
                                  const void *q_sel, const int32_t *sel_pos, const void *k_cache,
                                  const void *v_cache, float scale, void *out, float *lse_out,
                                  hipStream_t st);

@@ -521,9 +521,9 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     const size_t least = (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
     if (workspace_bytes < least) return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, least);
     // the matrix-core kernel: bf16, head_dim 128, a positive scale (it folds the scale into an exp2
-    // argument after taking maxima).  Everything else takes the plain vector kernels.
+    // argument after taking maxima).  Everything else takes the fp32 kernels.
     const bool mfma = shape->dtype == KVS_BF16 && shape->head_dim == D && scale > 0.f;
-    if (!mfma) return launch_colsum_valu(shape, n_tokens, q, k, scale, (float *)workspace, alpha, (hipStream_t)stream);
+    if (!mfma) return launch_colsum_f32(shape, n_tokens, q, k, scale, (float *)workspace, alpha, (hipStream_t)stream);
     if (!on_matrix_cores(shape, n_tokens))
         return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d heads exceed the 4 GiB the kernel addresses", (long long)n_tokens, shape->n_q_heads);
     float *lse2 = (float *)workspace;

@@ -1,0 +1,115 @@
+// kvs_attn_colsum in fp32 for the shapes the bf16 matrix-core kernel does not cover (fp32, head_dim 64, a scale that is not
+// positive): the same two sweeps (row log-sum-exps, then column sums of exp(score - lse); Alg. 1 steps 1-2) on the fp32
+// matrix instruction.  A workgroup owns 16 fixed rows of a KV head (query rows, flattened (token, head-in-group), in sweep
+// 1; keys in sweep 2); its eight waves deal the streamed 16-row tiles among themselves and read them straight from global
+// memory.  A lane's results belong to one fixed row, so the running sums are a lane's own and the loop has no cross-lane
+// traffic; the 32 shares of a fixed row meet in LDS, in a fixed order.
+//
+// Measured, fp32 512 tokens x 4 heads, head_dim 64: 57 -> 18 us for both sweeps (before: one wave per row on the vector
+// units, element by element).  Meant for small layers; nothing is staged or shared between workgroups.
+#include "f32_tiles.h"
+
+#include <math.h>
+
+namespace kvs {
+namespace {
+
+constexpr int kCfWaves = 8;
+constexpr int kCfThreads = kCfWaves * 64;
+constexpr int kCfRows = 16;
+
+// SWEEP 1: lse[g][row]; SWEEP 2: alpha[g][key].  Rows of a KV head's queries: row = token * grp + head-in-group.
+template <int SWEEP, int DTYPE, int D>
+__global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_heads, int n_kv_heads, const void *__restrict__ q,
+                                                                const void *__restrict__ k, float scale,
+                                                                const float *__restrict__ lse, float *__restrict__ result)
+{
+    __shared__ float m_s[kCfWaves * 4][kCfRows], z_s[kCfWaves * 4][kCfRows];
+    const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kk = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = n_q_heads / n_kv_heads;
+    const int g = blockIdx.x % n_kv_heads, blk = blockIdx.x / n_kv_heads;
+    const int n_qrows = n * grp, n_fixed = SWEEP == 1 ? n_qrows : n;
+    // heaviest first: the last query rows see the most keys, the first keys are seen by the most rows
+    const int fb = (SWEEP == 1 ? (n_fixed - 1) / kCfRows - blk : blk) * kCfRows;
+    auto q_row = [&](int r) { return ((int64_t)(r / grp) * n_q_heads + g * grp + r % grp) * D; };
+    auto k_row = [&](int i) { return ((int64_t)i * n_kv_heads + g) * D; };
+    const int fr = min(fb + m16, n_fixed - 1);
+    float fx[D / 4];
+    load_quarter<DTYPE, D>(SWEEP == 1 ? q : k, SWEEP == 1 ? q_row(fr) : k_row(fr), kk, fx);
+    const int fpos = SWEEP == 1 ? fr / grp : fr;       // position of the fixed row
+    const int last = min(fb + kCfRows, n_fixed) - 1;
+    const int t_begin = SWEEP == 1 ? 0 : fb * grp / kCfRows, t_end = SWEEP == 1 ? last / grp / kCfRows + 1 : (n_qrows + kCfRows - 1) / kCfRows;
+    const int n_stream = SWEEP == 1 ? n : n_qrows;
+    float m = -1.0e30f, z = 0.f;
+    for (int t = t_begin + wave; t < t_end; t += kCfWaves) {
+        float x[D / 4];
+        const int sr = min(t * kCfRows + m16, n_stream - 1);
+        load_quarter<DTYPE, D>(SWEEP == 1 ? k : q, SWEEP == 1 ? k_row(sr) : q_row(sr), kk, x);
+        float l4[4];
+        if (SWEEP == 2) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) l4[r] = lse[(int64_t)g * n_qrows + min(t * kCfRows + 4 * kk + r, n_stream - 1)];
+        }
+        const f32x4 s = dots<D>(x, fx);
+        float y[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = t * kCfRows + 4 * kk + r;
+            const bool sees = SWEEP == 1 ? row <= fpos : row < n_stream && row / grp >= fpos;
+            y[r] = sees ? s[r] * scale : -INFINITY;
+        }
+        if (SWEEP == 1) {
+            const float mn = fmaxf(m, fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
+            z *= expf(m - mn);
+            m = mn;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z += expf(y[r] - m);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z += expf(y[r] - l4[r]);
+        }
+    }
+    m_s[wave * 4 + kk][m16] = m;
+    z_s[wave * 4 + kk][m16] = z;
+    __syncthreads();
+    if (tid < kCfRows && fb + tid < n_fixed) {
+        float mt = -1.0e30f, zt = 0.f;
+        if (SWEEP == 1) {
+#pragma unroll
+            for (int w = 0; w < kCfWaves * 4; ++w) mt = fmaxf(mt, m_s[w][tid]);
+#pragma unroll
+            for (int w = 0; w < kCfWaves * 4; ++w) zt += z_s[w][tid] * expf(m_s[w][tid] - mt);
+            result[(int64_t)g * n_qrows + fb + tid] = mt + logf(zt);
+        } else {
+#pragma unroll
+            for (int w = 0; w < kCfWaves * 4; ++w) zt += z_s[w][tid];
+            result[(int64_t)g * n + fb + tid] = zt;
+        }
+    }
+}
+
+template <int DTYPE, int D>
+kvs_status launch_both(int n, int hq, int hk, const void *q, const void *k, float scale, float *lse, float *alpha, hipStream_t st)
+{
+    const int64_t rows = (int64_t)n * (hq / hk);
+    const dim3 block(kCfThreads), g1((unsigned)((rows + kCfRows - 1) / kCfRows * hk)), g2((unsigned)(((int64_t)n + kCfRows - 1) / kCfRows * hk));
+    hipLaunchKernelGGL((colsum_f32_kernel<1, DTYPE, D>), g1, block, 0, st, n, hq, hk, q, k, scale, (const float *)nullptr, lse);
+    hipLaunchKernelGGL((colsum_f32_kernel<2, DTYPE, D>), g2, block, 0, st, n, hq, hk, q, k, scale, (const float *)lse, alpha);
+    return check_launch("kvs_attn_colsum(f32)");
+}
+
+} // namespace
+
+kvs_status launch_colsum_f32(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale,
+                             float *lse, float *alpha, hipStream_t st)
+{
+    const int d = shape->head_dim, hq = shape->n_q_heads, hk = shape->n_kv_heads;
+    // quadratic work at a few percent of the bf16 matrix-core rate: refuse what would run for minutes
+    if (n > 65536) return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens are too many for the fp32 path (this shape has no bf16 matrix-core kernel)", (long long)n);
+    if (n * (int64_t)(hq / hk) > 0x7ffffff0) return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d query heads", (long long)n, hq);
+    if (shape->dtype == KVS_F32) return d == 64 ? launch_both<KVS_F32, 64>((int)n, hq, hk, q, k, scale, lse, alpha, st) : launch_both<KVS_F32, 128>((int)n, hq, hk, q, k, scale, lse, alpha, st);
+    return d == 64 ? launch_both<KVS_BF16, 64>((int)n, hq, hk, q, k, scale, lse, alpha, st) : launch_both<KVS_BF16, 128>((int)n, hq, hk, q, k, scale, lse, alpha, st);
+}
+
+} // namespace kvs

@@ -57,7 +57,7 @@ size_t decode_workspace_bytes(const kvs_shape *shape, int32_t batch, int64_t n_r
 size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t match_workspace_bytes(int64_t n_target, int64_t n_candidate);
-kvs_status launch_colsum_valu(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale,
+kvs_status launch_colsum_f32(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale,
                               float *lse, float *alpha, hipStream_t st);
 
 // ---- deviation scoring and top-k in one call (kvs_deviation_topk) ----------------------------------

@@ -1,0 +1,84 @@
+"""The fp32 attention and column-mass kernels (fp32, head_dim 64, scales that are not positive) at the edges of their 16-row
+tiles, of a wave's 64 keys and of the eight waves' 512, and the scoring kernel's small tiles, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2503_16525_amd import binding as B
+from paper_2503_16525_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [("f32", 4, 4, 64), ("f32", 6, 2, 128), ("bf16", 10, 2, 64), ("bf16", 3, 1, 128)]
+
+
+def layer(dtype, hq, hk, d, n):
+    return synth.scaled(synth.TINY, n, dtype=dtype, n_q_heads=hq, n_kv_heads=hk, head_dim=d, n_spans=0, span_mean=16.0, coverage=0.8)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+@pytest.mark.parametrize("n,k", [(1, 1), (16, 16), (17, 5), (64, 16), (65, 17), (512, 33), (513, 8), (1030, 48)])
+def test_attention(dtype, hq, hk, d, n, k):
+    print(f"fp32 attention: {dtype} {hq}x{hk} heads, head_dim {d}, {k} of {n} tokens", flush=True)
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    pos = np.sort(np.random.default_rng(n).permutation(n)[:k]).astype(np.int32)
+    pos[-1] = n - 1
+    q = lay["q"][torch.from_numpy(pos.astype(np.int64))].contiguous()
+    scale = -0.7 if d == 128 and dtype == "bf16" else 1.0
+    kc, vc = oracle._as_np(lay["k_cache"]), oracle._as_np(lay["v_cache"])
+    ref, lse_ref = oracle.partial_attention(q, pos, kc, vc, scale)
+    guard = 3
+    out = torch.full((k + guard, hq, d), 7.0, dtype=w.torch_dtype, device="cuda")
+    lse = torch.full((k + guard, hq), 7.0, device="cuda")
+    B.kvs_partial_attention(B.shape_of(w), [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), lay["k_cache"].cuda(),
+                            lay["v_cache"].cuda(), scale, out, lse)
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.all(got[k:] == 7.0) and bool((lse[k:] == 7.0).all()), "rows past the last one were written"
+    # fp32 products and sums of up to 1030 weights: 1e-5 of the values' size; a bf16 result adds its own rounding
+    tol = 1e-5 * (1.0 + np.abs(ref).max()) + (2.0 ** -8 * np.abs(ref) if dtype == "bf16" else 0.0)
+    assert np.all(np.abs(got[:k] - ref) <= tol), np.abs(got[:k] - ref).max()
+    np.testing.assert_allclose(lse[:k].cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 127, 129, 300])
+def test_column_mass(dtype, hq, hk, d, n):
+    print(f"fp32 column mass: {dtype} {hq}x{hk} heads, head_dim {d}, {n} tokens", flush=True)
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    scale = -0.7 if d == 128 and dtype == "bf16" else 1.0
+    _, ref = oracle.alpha_prefill(lay["q"], lay["k_fresh"], scale)
+    alpha = torch.full((hk + 1, n), 7.0, device="cuda")
+    ws = torch.empty(B.kvs_workspace_size("attn_colsum", B.shape_of(w), 1, n), dtype=torch.uint8, device="cuda")
+    B.kvs_attn_colsum(B.shape_of(w), n, lay["q"].cuda(), lay["k_fresh"].cuda(), scale, alpha, ws)
+    assert bool((alpha[hk] == 7.0).all())
+    np.testing.assert_allclose(alpha[:hk].cpu().numpy(), ref, rtol=1e-5, atol=1e-7)
+
+
+@pytest.mark.parametrize("dtype,hk,d", [("f32", 4, 64), ("f32", 64, 128), ("bf16", 5, 128), ("bf16", 33, 64)])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 40, 8191, 8192])
+@pytest.mark.parametrize("mode", [B.SCORE_V, B.SCORE_KV])
+def test_small_scoring_tiles(dtype, hk, d, n, mode):
+    if n > 1000 and hk > 5:
+        pytest.skip("large and covered by the smaller head counts")
+    print(f"scoring tiles: {dtype} {hk} heads, head_dim {d}, {n} tokens, mode {mode}", flush=True)
+    w = layer(dtype, hk, hk, d, n)
+    lay = synth.make_layer(w)
+    alpha = torch.rand((hk, n), generator=torch.Generator().manual_seed(n)) + 0.5
+    dk_ref, dv_ref, sc_ref = oracle.deviation(lay["v_fresh"], lay["v_cache"], lay["k_fresh"], lay["k_cache"], reused=lay["reused"],
+                                              alpha=alpha, mode=mode) if mode == B.SCORE_KV else oracle.deviation(
+                                                  lay["v_fresh"], lay["v_cache"], reused=lay["reused"], alpha=alpha)
+    g = {x: lay[x].cuda() for x in ("k_fresh", "v_fresh", "k_cache", "v_cache", "reused")}
+    dev_v, score = torch.full((hk, n), 7.0, device="cuda"), torch.full((n + 64,), 7.0, device="cuda")
+    dev_k = torch.full((hk, n), 7.0, device="cuda") if mode == B.SCORE_KV else None
+    B.kvs_deviation(B.shape_of(w), n, g["k_fresh"], g["v_fresh"], g["k_cache"], g["v_cache"], g["reused"], alpha.cuda(), mode, dev_k, dev_v, score)
+    sc = score.cpu().numpy()
+    assert np.all(sc[n:] == 7.0)
+    assert np.array_equal(np.isneginf(sc[:n]), np.isneginf(sc_ref))
+    fin = np.isfinite(sc_ref)
+    np.testing.assert_allclose(sc[:n][fin], sc_ref[fin], rtol=1e-5)          # fp32 sums of at most 128 terms, by head
+    np.testing.assert_allclose(dev_v.cpu().numpy(), dv_ref, rtol=1e-5)
+    if dev_k is not None:
+        np.testing.assert_allclose(dev_k.cpu().numpy(), dk_ref, rtol=1e-5)
