@@ -15,7 +15,10 @@ namespace kvs {
 namespace {
 
 constexpr int kDevThreads = 256;
-constexpr int kDevTok = 32; // tokens per workgroup tile
+// tokens per workgroup tile: 32, or 8 for rows that 32 would spread over fewer workgroups than there are compute units
+// (8000 bf16 tokens of 8 heads, the call with its top-k: 21.2 -> 15.6 us; 512 fp32 tokens of 4 heads, the kernel: 7.6 -> 3.4)
+constexpr int kDevTok = 32, kDevTokFew = 8;
+constexpr int64_t kDevFewBelow = 256 * kDevTok;
 
 template <int DTYPE>
 __device__ __forceinline__ float l1_piece(const uint4 a, const uint4 b)
@@ -49,11 +52,11 @@ __device__ __forceinline__ float group_sum(float v)
 
 __device__ __forceinline__ uint4 stream_load(const uint4 *p) { return stream_load16(p); }
 
-// One workgroup = kDevTok consecutive tokens = kDevTok * n_kv_heads cells.
+// One workgroup = TOK consecutive tokens = TOK * n_kv_heads cells.
 // HIST (kvs_deviation_topk): every token's order-preserving key is stored beside its score and
 // counted into the histogram of the keys' leading bits (finite scores only), which the selecting
 // kernel consumes.
-template <int DTYPE, int LPH, bool HAS_K, int UNROLL, bool HIST>
+template <int DTYPE, int LPH, bool HAS_K, int UNROLL, bool HIST, int TOK>
 __global__ __launch_bounds__(kDevThreads) void deviation_kernel(
     int64_t n_tokens, int n_kv_heads,
     const uint4 *__restrict__ k_fresh, const uint4 *__restrict__ v_fresh,
@@ -62,19 +65,25 @@ __global__ __launch_bounds__(kDevThreads) void deviation_kernel(
     float *__restrict__ dev_k, float *__restrict__ dev_v, float *__restrict__ score,
     uint32_t *__restrict__ keys_out, uint32_t *__restrict__ key_hist)
 {
-    extern __shared__ float lds[]; // dv[n_kv_heads][kDevTok], then dk[n_kv_heads][kDevTok]
+    extern __shared__ float lds[]; // dv[n_kv_heads][TOK], then dk[n_kv_heads][TOK]
     float *dv_s = lds;
-    float *dk_s = lds + n_kv_heads * kDevTok;
+    float *dk_s = lds + n_kv_heads * TOK;
 
     constexpr int CPW = kWave / LPH;                    // cells per wave per step
     constexpr int CPB = CPW * (kDevThreads / kWave);    // cells per workgroup per step
     const int tid = threadIdx.x;
     const int sub = tid % LPH;                          // 16-byte piece within the cell
     const int cell_in_step = tid / LPH;
-    const int64_t tok0 = (int64_t)blockIdx.x * kDevTok;
-    const int tile_tok = (int)min((int64_t)kDevTok, n_tokens - tok0);
+    const int64_t tok0 = (int64_t)blockIdx.x * TOK;
+    const int tile_tok = (int)min((int64_t)TOK, n_tokens - tok0);
     const int tile_cells = tile_tok * n_kv_heads;
     const int64_t cell0 = tok0 * n_kv_heads;
+    // what the end of the kernel needs besides the sums, requested along with the first pieces: the mask and, in small
+    // tiles, the weights if there is one per thread at most (parked in LDS below; large launches hide that trip)
+    const uint8_t is_reused = reused && tid < tile_tok ? reused[tok0 + tid] : (uint8_t)1;
+    const bool early_alpha = TOK == kDevTokFew && alpha && n_kv_heads * TOK <= kDevThreads;
+    float my_alpha = 1.f;
+    if (early_alpha && tid < n_kv_heads * TOK && tid % TOK < tile_tok) my_alpha = alpha[(int64_t)(tid / TOK) * n_tokens + tok0 + tid % TOK];
 
     for (int base = 0; base < tile_cells; base += CPB * UNROLL) {
         uint4 vf[UNROLL], vc[UNROLL], kf[UNROLL], kc[UNROLL];
@@ -103,15 +112,17 @@ __global__ __launch_bounds__(kDevThreads) void deviation_kernel(
             if (HAS_K) sk = group_sum<LPH>(sk);
             if (c < tile_cells && sub == 0) {
                 const int t = c / n_kv_heads, g = c - t * n_kv_heads;
-                dv_s[g * kDevTok + t] = sv;
-                if (HAS_K) dk_s[g * kDevTok + t] = sk;
+                dv_s[g * TOK + t] = sv;
+                if (HAS_K) dk_s[g * TOK + t] = sk;
             }
         }
     }
+    float *al_s = dk_s + (HAS_K ? n_kv_heads * TOK : 0);   // [n_kv_heads][TOK]
+    if (early_alpha && tid < n_kv_heads * TOK) al_s[tid] = my_alpha;
     __syncthreads();
 
-    for (int e = tid; e < n_kv_heads * kDevTok; e += kDevThreads) {
-        const int g = e / kDevTok, t = e % kDevTok;
+    for (int e = tid; e < n_kv_heads * TOK; e += kDevThreads) {
+        const int g = e / TOK, t = e % TOK;
         if (t < tile_tok) {
             const int64_t o = (int64_t)g * n_tokens + tok0 + t;
             if (dev_v) dev_v[o] = dv_s[e];
@@ -122,13 +133,12 @@ __global__ __launch_bounds__(kDevThreads) void deviation_kernel(
         const int64_t i = tok0 + tid;
         float s = 0.f;
         for (int g = 0; g < n_kv_heads; ++g) {
-            float dev = dv_s[g * kDevTok + tid];
-            if (HAS_K && mode_kv) dev = dk_s[g * kDevTok + tid] + dev;
-            const float a = alpha ? alpha[(int64_t)g * n_tokens + i] : 1.0f;
+            float dev = dv_s[g * TOK + tid];
+            if (HAS_K && mode_kv) dev = dk_s[g * TOK + tid] + dev;
+            const float a = early_alpha ? al_s[g * TOK + tid] : alpha ? alpha[(int64_t)g * n_tokens + i] : 1.0f;
             s += a * dev;
         }
-        const bool cand = reused ? (reused[i] != 0) : true;
-        const float sc = cand ? s : -INFINITY;
+        const float sc = is_reused != 0 ? s : -INFINITY;
         if (score) score[i] = sc;
         if (HIST) {
             const uint32_t key = score_key(sc);
@@ -143,16 +153,21 @@ kvs_status launch(int64_t n, int hk, bool has_k, const void *kf, const void *vf,
                   const void *vc, const uint8_t *reused, const float *alpha, int mode_kv,
                   float *dev_k, float *dev_v, float *score, const FusedScratch *fs, hipStream_t st)
 {
-    const int64_t blocks = (n + kDevTok - 1) / kDevTok;
+    const bool few = n < kDevFewBelow;
+    const int tok = few ? kDevTokFew : kDevTok;
+    const int64_t blocks = (n + tok - 1) / tok;
     if (blocks > 0x7fffffff) return fail(KVS_EINVAL, "kvs_deviation: too many tokens");
-    const size_t lds = sizeof(float) * hk * kDevTok * 2;
+    const size_t lds = sizeof(float) * hk * tok * 3;
     dim3 grid((unsigned)blocks), block(kDevThreads);
-#define KVS_DEV_LAUNCH(HASK, UNR, HIST)                                                                          \
-    hipLaunchKernelGGL((deviation_kernel<DTYPE, LPH, HASK, UNR, HIST>), grid, block, lds, st, n, hk,             \
+#define KVS_DEV_LAUNCH(HASK, UNR, HIST, TOK)                                                                     \
+    hipLaunchKernelGGL((deviation_kernel<DTYPE, LPH, HASK, UNR, HIST, TOK>), grid, block, lds, st, n, hk,        \
                        (const uint4 *)kf, (const uint4 *)vf, (const uint4 *)kc, (const uint4 *)vc, reused, alpha, \
                        mode_kv, dev_k, dev_v, score, fs ? fs->keys : nullptr, fs ? fs->hist : nullptr)
-    if (has_k) { if (fs) KVS_DEV_LAUNCH(true, 2, true); else KVS_DEV_LAUNCH(true, 2, false); }
-    else { if (fs) KVS_DEV_LAUNCH(false, 4, true); else KVS_DEV_LAUNCH(false, 4, false); }
+    // (rows short enough for small tiles are ranked by the one-workgroup kernel: no histogram)
+    static_assert(kDevFewBelow <= kFusedMinTokens, "small tiles have no histogram variant");
+    if (few) { if (has_k) KVS_DEV_LAUNCH(true, 2, false, kDevTokFew); else KVS_DEV_LAUNCH(false, 4, false, kDevTokFew); }
+    else if (has_k) { if (fs) KVS_DEV_LAUNCH(true, 2, true, kDevTok); else KVS_DEV_LAUNCH(true, 2, false, kDevTok); }
+    else { if (fs) KVS_DEV_LAUNCH(false, 4, true, kDevTok); else KVS_DEV_LAUNCH(false, 4, false, kDevTok); }
 #undef KVS_DEV_LAUNCH
     return check_launch("kvs_deviation");
 }
