@@ -24,6 +24,8 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTok = 64;          // tokens per workgroup in the logits kernel (= one wavefront in the partials step)
 constexpr int kMaxReq = kAttnMaxReq;
+constexpr int kSpreadBelow = 1024;    // tiles below which the scoring launch gives each four waves
+constexpr int kSpreadMaxHeads = 16;   // KV heads up to which a counting one does
 
 struct DecodeBatch {
     int64_t ctx_off[kMaxReq];
@@ -174,15 +176,22 @@ __global__ __launch_bounds__(kThreads) void decode_logits_kernel(
 // K goes from global memory straight into LDS (buffer loads with the LDS flag and the
 // non-temporal hint: the cache is read once; 1 KiB = four
 // 256-byte rows per instruction, 16-byte pieces XOR-swizzled by the row so that the operand reads
-// are conflict-free).  A workgroup is still one 64-token tile; wave w takes KV heads w, w+4, ..,
-// each as two units of 32 tokens that it stages and consumes by itself through its own two LDS
-// slots, so there is no barrier anywhere: a wave only waits for its own loads.
-// workgroups of the matrix-core logits launch at most: beyond that each takes several 64-token tiles (64-request
-// batch, 10.9k tiles: 335 us per check with 1024 workgroups against 344 us with one per tile; 512 and 2048: 340, 339)
-#ifndef KVS_DEC_PERSIST
-#define KVS_DEC_PERSIST 1024
-#endif
-constexpr int kMmaUnitBytes = 32 * 256;            // 32 tokens x 256 bytes
+// are conflict-free).  A unit is 32 tokens of one KV head; a workgroup takes a run of 32-token items for eight KV heads,
+// wave w the heads w and w+4, so the four waves together read whole stretches of the cache.  Every wave stages and
+// consumes its units by itself through two LDS slots of its own, so there is no barrier anywhere, and the loads of the
+// next units are on their way while one is multiplied.
+//
+// A bare stream through the same loads reads 64 MiB in 12 us and 1.25 GiB at 6.8 TB/s; what kept this kernel from it was
+// what came after a unit's product:
+//   * stores count where a wave waits for loads, so a unit's logits leave after the wait for the next unit, by exactly RU
+//     store instructions (lanes past the context store outside the buffer, which drops it), and the waits are counted for them;
+//   * the softmax statistics are each lane's own (running maximum and sum per head) and meet only where a run's request ends.
+// Measured, the logits launch: 64 requests / 629k rows 270 -> 252 us, 60 Yi-shaped requests (the whole check) 206 -> 172;
+// one 32k context 20 us either way, of which the bare stream takes 12.
+constexpr int kMmaTok = 32;                        // tokens per item
+constexpr int kMmaHeads = 8;                       // KV heads per workgroup
+constexpr int kMmaWgs = 512;                       // two workgroups of 64 KiB are resident per compute unit
+constexpr int kMmaUnitBytes = kMmaTok * 256;       // 32 tokens x 256 bytes
 constexpr int kMmaSlots = 2;
 constexpr int kMmaLds = (kThreads / 64) * kMmaSlots * kMmaUnitBytes;
 
@@ -204,241 +213,314 @@ __device__ __forceinline__ float half_sum(float v)
     return v + __shfl_xor(v, 16);
 }
 
-__global__ __launch_bounds__(kThreads) void decode_logits_mfma_kernel(
-    const DecodeBatch bd, int n_q_heads, int n_kv_heads, int64_t n_rows,
+// which workgroup of the launch has item `item`
+__host__ __device__ inline int mma_wg_of(int64_t item, int64_t n_items, int64_t wgs) { return (int)(((item + 1) * wgs - 1) / n_items); }
+
+// RU: result registers that hold heads of the group (4: up to 8 heads, 8: up to 16, 16: up to 32)
+template <int RU>
+__global__ __launch_bounds__(kThreads, 2) void decode_logits_mfma_kernel(
+    const DecodeBatch bd /* tile_begin counts kMmaTok-token items */, int n_q_heads, int n_kv_heads, int64_t n_rows,
     const uint16_t *__restrict__ q_new, const uint16_t *__restrict__ k_cache, float scale,
-    float *__restrict__ logits, float2 *__restrict__ partial /* [tile][n_q_heads] (max, sum exp) */, int n_tiles)
+    float *__restrict__ logits, float2 *__restrict__ partial /* [workgroup + request][n_q_heads] (max, sum exp) */, int n_items)
 {
     constexpr int D = 128, ROW_B = 256;
     extern __shared__ __attribute__((aligned(16))) char lds_mma[];
-    // a workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ...: nothing below synchronises the waves, and
-    // every wave leaves a tile with its own loads and LDS reads complete
-    for (int tile_id = blockIdx.x; tile_id < n_tiles; tile_id += gridDim.x) {
-    int b = 0;
-    while (b + 1 < bd.n_req && tile_id >= bd.tile_begin[b + 1]) ++b;
-    const int tile = tile_id - bd.tile_begin[b];
-    const int len = bd.ctx_len[b];
-    const int tok0 = tile * kTok;
-    const int tile_tok = min(kTok, len - tok0);
-    const int64_t row0 = bd.ctx_off[b] + tok0;
     const int grp = n_q_heads / n_kv_heads;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hf = lane >> 5, ln = lane & 31;
-    const uint16_t *qb = q_new + (int64_t)(bd.req0 + b) * n_q_heads * D;
+    const int first = (int)((int64_t)blockIdx.x * n_items / gridDim.x), last = (int)((int64_t)(blockIdx.x + 1) * n_items / gridDim.x);
+    const int head0 = (int)blockIdx.y * kMmaHeads + wave;       // this wave's KV heads: head0, head0 + 4
+    const int n_heads_w = head0 + 4 < n_kv_heads ? 2 : head0 < n_kv_heads ? 1 : 0;
+    const int n_units = (last - first) * n_heads_w;
+    if (n_units <= 0) return;
 
-    // the whole cache as one buffer (the host checks that it is below 4 GiB)
+    auto make_rsrc = [&](const void *base, uint32_t bytes) -> u32x4_t {
+        const uint64_t a = reinterpret_cast<uint64_t>(base);
+        u32x4_t r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+        r.x = __builtin_amdgcn_readfirstlane(r.x);
+        r.y = __builtin_amdgcn_readfirstlane(r.y);
+        r.z = __builtin_amdgcn_readfirstlane(r.z);
+        return r;
+    };
+    // the whole cache and all logits as one buffer each (the host checks that both are below 4 GiB)
     const uint32_t row_bytes = (uint32_t)n_kv_heads * ROW_B;
-    u32x4_t rs;
-    {
-        const uint64_t a = reinterpret_cast<uint64_t>(k_cache);
-        rs.x = __builtin_amdgcn_readfirstlane((uint32_t)a);
-        rs.y = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-        rs.z = __builtin_amdgcn_readfirstlane((uint32_t)n_rows * row_bytes);
-        rs.w = 0x00020000u;
-    }
+    const u32x4_t rs = make_rsrc(k_cache, (uint32_t)n_rows * row_bytes);
+    const u32x4_t lrs = make_rsrc(logits, (uint32_t)n_rows * (uint32_t)n_q_heads * 4u);
     char *const my_lds = lds_mma + wave * (kMmaSlots * kMmaUnitBytes);
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
         (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)my_lds);
+    // a place in the run: item, the wave's head index, the item's request
+    struct Cursor { int item, h, b; };
+    auto settle = [&](Cursor &c) { while (c.b + 1 < bd.n_req && c.item >= bd.tile_begin[c.b + 1]) ++c.b; };
+    auto advance = [&](Cursor &c) { if (++c.h == n_heads_w) { c.h = 0; ++c.item; settle(c); } };
     // staging: instruction j moves rows 4j .. 4j+3 of the unit; lane = (row in the four, position);
     // piece p of row r sits at position p ^ (r & 15)
     const int st_r = lane >> 4, st_p = lane & 15;
-    // This wave's KV heads are wave, wave + 4, ...; they are taken two at a time, and the four units
-    // of a pair go (head A, tokens 0-31), (head B, 0-31), (A, 32-63), (B, 32-63): with two units in
-    // flight per wave the four waves together are then reading all heads of the same 32 token rows,
-    // i.e. one contiguous stretch of the cache, instead of every other 256-byte chunk of it.
-    const int n_heads_w = (n_kv_heads - wave + 3) / 4;
-    const int n_units = 2 * n_heads_w;
-    // unit u of the wave -> (index of the head among the wave's heads, token half)
-    auto unit_head = [&](int u) { const int pair = u >> 2, k = u & 3; return (n_heads_w - 2 * pair >= 2) ? 2 * pair + (k & 1) : 2 * pair; };
-    auto unit_sub = [&](int u) { const int pair = u >> 2, k = u & 3; return (n_heads_w - 2 * pair >= 2) ? (k >> 1) : (k & 1); };
-    auto stage_unit = [&](int u) {
-        const int g = wave + 4 * unit_head(u), sub = unit_sub(u);
+    auto stage_unit = [&](const Cursor &c, int u) {
+        const int tok0 = (c.item - bd.tile_begin[c.b]) * kMmaTok;
+        const int tok_last = bd.ctx_len[c.b] - 1 - tok0;                    // rows past the context: its last row
+        const int64_t row0 = bd.ctx_off[c.b] + tok0;
         const uint32_t slot = lds_base + (uint32_t)((u & (kMmaSlots - 1)) * kMmaUnitBytes);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int r = 4 * j + st_r;
-            const int t = min(32 * sub + r, tile_tok - 1);          // rows past the context: its last row
-            const uint32_t voff = (uint32_t)(row0 + t) * row_bytes + (uint32_t)g * ROW_B + (uint32_t)((st_p ^ (r & 15)) * 16);
+            const uint32_t voff = (uint32_t)(row0 + min(r, tok_last)) * row_bytes + (uint32_t)(head0 + 4 * c.h) * ROW_B + (uint32_t)((st_p ^ (r & 15)) * 16);
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
                          :: "s"(__builtin_amdgcn_readfirstlane(slot + (uint32_t)(j * 1024))), "v"(voff), "s"(rs));
         }
     };
     // B operand: K row ln, pieces 2*ks + hf
     const uint32_t b_read_off = (uint32_t)(ln * ROW_B + ((hf ^ (ln & 15)) * 16));
-    const dec_floatx16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // A operands: query head g*grp + ln of the group, both heads kept for a whole request (rows past the group are zero)
+    dec_bf16x8 qa[2][D / 16];
+    auto load_q = [&](int b, int h) {
+        const uint16_t *qb = q_new + ((int64_t)(bd.req0 + b) * n_q_heads + (head0 + 4 * h) * grp + ln) * D + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            u32x4_t v = {0u, 0u, 0u, 0u};
+            if (ln < grp) v = *reinterpret_cast<const u32x4_t *>(qb + 16 * ks);
+            qa[h][ks] = __builtin_bit_cast(dec_bf16x8, v);
+        }
+    };
+    // register r of half-wave hf is query head 8*(r/4) + 4*hf + r%4 of the group, column = token
+    auto head_in_group = [&](int r) { return 8 * (r >> 2) + 4 * hf + (r & 3); };
+    float run_m[2][RU], run_z[2][RU];      // this lane's running maximum and sum of exp(logit - maximum)
+    auto reset = [&]() {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < RU; ++r) { run_m[h][r] = -1.0e30f; run_z[h][r] = 0.f; }
+    };
+    auto emit = [&](int b) {               // the run's share of request b
+        for (int h = 0; h < 2; ++h) {
+            if (h < n_heads_w) {
+#pragma unroll
+                for (int r = 0; r < RU; ++r) {
+                    const float m0 = h == 0 ? run_m[0][r] : run_m[1][r], z0 = h == 0 ? run_z[0][r] : run_z[1][r];
+                    const float m = half_max(m0), z = half_sum(z0 * __expf(m0 - m));
+                    const int hh = head_in_group(r);
+                    if (hh < grp && ln == 0) partial[(int64_t)((int)blockIdx.x + b) * n_q_heads + (head0 + 4 * h) * grp + hh] = make_float2(m, z);
+                }
+            }
+        }
+    };
+    // a finished unit's logits and where they go, stored after the wait for the next unit
+    float lg[RU];
+    uint32_t lg_off[RU];
+    auto flush = [&]() {
+#pragma unroll
+        for (int r = 0; r < RU; ++r) asm volatile("buffer_store_dword %0, %1, %2, 0 offen" :: "v"(lg[r]), "v"(lg_off[r]), "s"(lrs) : "memory");
+    };
 
-    if (n_units > 0) stage_unit(0);
-    if (n_units > 1) stage_unit(1);
-    for (int pair = 0; 2 * pair < n_heads_w; ++pair) {
-        const int heads_here = min(2, n_heads_w - 2 * pair);
-        // A operands: query head g*grp + ln of each head of the pair (rows past the group are zero)
-        dec_bf16x8 qa[2][D / 16];
+    Cursor ahead = {first, 0, 0}, cur;
+    settle(ahead);
+    cur = ahead;
+    load_q(cur.b, 0);
+    if (n_heads_w == 2) load_q(cur.b, 1);
+    int q_of = cur.b;
+    reset();
+    stage_unit(ahead, 0);
+    advance(ahead);
+    if (n_units > 1) { stage_unit(ahead, 1); advance(ahead); }
+    for (int u = 0; u < n_units; ++u) {
+        if (cur.b != q_of) {                            // another request: its queries, its own statistics
+            emit(q_of);
+            reset();
+            load_q(cur.b, 0);
+            if (n_heads_w == 2) load_q(cur.b, 1);
+            q_of = cur.b;
+        }
+        // younger than this unit's eight loads: from the third unit on the RU stores of the unit before last, and the next
+        // unit's eight loads (anything else only makes the wait longer)
+        if (u + 1 == n_units) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        else if (u < 2) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(8 + RU) : "memory");
+        if (u > 0) flush();
+        const char *slot = my_lds + (u & (kMmaSlots - 1)) * kMmaUnitBytes;
+        dec_floatx16 x = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int g = wave + 4 * (2 * pair + min(i, heads_here - 1));
+        for (int ks = 0; ks < D / 16; ++ks) {
+            const u32x4_t kb = *reinterpret_cast<const u32x4_t *>(slot + (b_read_off ^ (uint32_t)(32 * ks)));
+            if (cur.h == 0) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[0][ks], __builtin_bit_cast(dec_bf16x8, kb), x, 0, 0, 0);
+            else x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[1][ks], __builtin_bit_cast(dec_bf16x8, kb), x, 0, 0, 0);
+        }
+        // the slot is free once its reads have returned; refill it with the unit after next
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (u + kMmaSlots < n_units) { stage_unit(ahead, u + kMmaSlots); advance(ahead); }
+        const int tok = (cur.item - bd.tile_begin[cur.b]) * kMmaTok + ln;
+        const bool live = tok < bd.ctx_len[cur.b];
+        const uint32_t at = ((uint32_t)(bd.ctx_off[cur.b] + tok) + (uint32_t)((head0 + 4 * cur.h) * grp) * (uint32_t)n_rows) * 4u;
 #pragma unroll
-            for (int ks = 0; ks < D / 16; ++ks) {
-                u32x4_t v = {0u, 0u, 0u, 0u};
-                if (ln < grp) v = *reinterpret_cast<const u32x4_t *>(qb + (int64_t)(g * grp + ln) * D + 16 * ks + 8 * hf);
-                qa[i][ks] = __builtin_bit_cast(dec_bf16x8, v);
+        for (int r = 0; r < RU; ++r) {
+            const int hh = head_in_group(r);
+            lg[r] = x[r] * scale;
+            lg_off[r] = live && hh < grp ? at + (uint32_t)hh * (uint32_t)n_rows * 4u : 0xfffffffcu;      // outside: dropped
+            const float v = live ? lg[r] : -INFINITY;
+            if (cur.h == 0) {
+                const float m = fmaxf(run_m[0][r], v);
+                run_z[0][r] = run_z[0][r] * __expf(run_m[0][r] - m) + __expf(v - m);
+                run_m[0][r] = m;
+            } else {
+                const float m = fmaxf(run_m[1][r], v);
+                run_z[1][r] = run_z[1][r] * __expf(run_m[1][r] - m) + __expf(v - m);
+                run_m[1][r] = m;
             }
         }
-        dec_floatx16 x[2][2];      // [head of the pair][token half]
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k < 2 * heads_here) {
-                const int u = 4 * pair + k;
-                const int i = heads_here == 2 ? (k & 1) : 0, sub = heads_here == 2 ? (k >> 1) : (k & 1);
-                // this unit's eight loads are older than the next unit's eight
-                if (u + 1 < n_units) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                const char *slot = my_lds + (u & (kMmaSlots - 1)) * kMmaUnitBytes;
-                dec_floatx16 acc = zero;
-#pragma unroll
-                for (int ks = 0; ks < D / 16; ++ks) {
-                    const u32x4_t kb = *reinterpret_cast<const u32x4_t *>(slot + (b_read_off ^ (uint32_t)(32 * ks)));
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(i == 0 ? qa[0][ks] : qa[1][ks], __builtin_bit_cast(dec_bf16x8, kb), acc, 0, 0, 0);
-                }
-                if (i == 0) { if (sub == 0) x[0][0] = acc; else x[0][1] = acc; }
-                else { if (sub == 0) x[1][0] = acc; else x[1][1] = acc; }
-                // the slot is free once its reads have returned; refill it with the unit after next
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                if (u + kMmaSlots < n_units) stage_unit(u + kMmaSlots);
-            }
-        }
-        // register r of half-wave hf is query head 8*(r/4) + 4*hf + r%4 of the group, column = token
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            if (i < heads_here) {
-                const int g = wave + 4 * (2 * pair + i);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int hh = 8 * (r >> 2) + 4 * hf + (r & 3);
-                    if (hh < grp) {                                      // uniform per half-wave
-                        const int h = g * grp + hh;
-                        float v[2];
-#pragma unroll
-                        for (int sub = 0; sub < 2; ++sub) {
-                            const int t = 32 * sub + ln;
-                            v[sub] = x[i][sub][r] * scale;
-                            if (t < tile_tok) logits[(int64_t)h * n_rows + row0 + t] = v[sub];
-                            else v[sub] = -INFINITY;
-                        }
-                        const float m = half_max(fmaxf(v[0], v[1]));
-                        const float z = half_sum(__expf(v[0] - m) + __expf(v[1] - m));
-                        if (ln == 0) partial[(int64_t)tile_id * n_q_heads + h] = make_float2(m, z);
-                    }
-                }
-            }
-        }
+        advance(cur);
     }
-    }   // tiles of this workgroup
+    flush();
+    emit(q_of);
 }
 
 // ---- 2. softmax statistics per (request, head): merge the tile partials ------------------------------
 __global__ __launch_bounds__(kThreads) void decode_stats_kernel(
     const DecodeBatch bd, int n_q_heads, const float2 *__restrict__ partial,
-    float2 *__restrict__ stats /* [batch][n_q_heads] (max, sum) */)
+    float2 *__restrict__ stats /* [batch][n_q_heads] (max, sum) */, int mma_items, int mma_wgs /* 0: one partial per tile of `bd` */)
 {
-    __shared__ float red[kThreads / 64];
-    __shared__ float bc;
+    __shared__ float2 red[kThreads / 64];
     const int b = blockIdx.x / n_q_heads, h = blockIdx.x % n_q_heads;
-    const int t0 = bd.tile_begin[b], t1 = bd.tile_begin[b + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    float m = -INFINITY;
-    for (int t = t0 + tid; t < t1; t += kThreads) m = fmaxf(m, partial[(int64_t)t * n_q_heads + h].x);
-    m = wave_max(m);
-    if (lane == 0) red[wave] = m;
-    __syncthreads();
-    if (tid == 0) { float x = red[0]; for (int w = 1; w < kThreads / 64; ++w) x = fmaxf(x, red[w]); bc = x; }
-    __syncthreads();
-    m = bc;
-    float z = 0.f;
-    for (int t = t0 + tid; t < t1; t += kThreads) {
-        const float2 p = partial[(int64_t)t * n_q_heads + h];
-        z += p.y * expf(p.x - m);
+    int t0 = bd.tile_begin[b], t1 = bd.tile_begin[b + 1];
+    if (mma_wgs > 0 && t0 < t1) {              // the runs that touch the request, each a record of its own
+        t0 = mma_wg_of(t0, mma_items, mma_wgs) + b;
+        t1 = mma_wg_of(t1 - 1, mma_items, mma_wgs) + b + 1;
     }
-    z = wave_sum(z);
-    __syncthreads();
-    if (lane == 0) red[wave] = z;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // one pass over the partials, several in flight per thread; every thread keeps its own maximum
+    constexpr int UNROLL = 4;
+    float m = -INFINITY, z = 0.f;
+    for (int t = t0 + tid; t < t1; t += kThreads * UNROLL) {
+        float2 p[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const int at = t + u * kThreads;
+            p[u] = at < t1 ? partial[(int64_t)at * n_q_heads + h] : make_float2(-INFINITY, 0.f);
+        }
+        float mn = m;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) mn = fmaxf(mn, p[u].x);       // finite: p[0] is there
+        z *= expf(m - mn);
+        m = mn;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) z += p[u].y * expf(p[u].x - m);
+    }
+    const float mw = wave_max(m);
+    const float zw = wave_sum(m == -INFINITY ? 0.f : z * expf(m - mw));
+    if (lane == 0) red[wave] = make_float2(mw, zw);
     __syncthreads();
     if (tid == 0) {
-        float x = 0.f;
-        for (int w = 0; w < kThreads / 64; ++w) x += red[w];
-        stats[(int64_t)(bd.req0 + b) * n_q_heads + h] = make_float2(m, x);
+        float x = red[0].x, y = 0.f;
+        for (int w = 1; w < kThreads / 64; ++w) x = fmaxf(x, red[w].x);
+        for (int w = 0; w < kThreads / 64; ++w) y += red[w].y > 0.f ? red[w].y * expf(red[w].x - x) : 0.f;
+        stats[(int64_t)(bd.req0 + b) * n_q_heads + h] = make_float2(x, y);
     }
 }
 
 // ---- 3. scores ---------------------------------------------------------------------------------
-// One wave per kTok-token tile, lane = token: every load is 64 consecutive floats, there is no
-// LDS and no barrier, and the sum over the KV heads runs in head order.  GRP > 0: the group size
-// is a compile-time constant, so the loads of two KV heads are in flight together.
+// lane = token of a kTok-token tile, every load is 64 consecutive floats, loads of two KV heads in flight.  SPREAD (launches
+// of few tiles, and those that count keys): four waves per tile, wave w of them takes KV heads w, w+4, .. and leaves their
+// masses beside the deviations in LDS, and the first adds them in head order: one trip to memory instead of four on eight
+// heads.  Otherwise a wave per tile, no LDS (64-request batch: 25 us against 47 with four waves per tile).
+// GRP > 0: the group size is a compile-time constant.
 // HIST (one context whose top-k then runs from the histogram, as in kvs_deviation_topk): the token's
-// order-preserving key goes to keys_out[token index in the context] and is counted by its leading bits.
-template <int GRP, bool HIST>
-__global__ __launch_bounds__(kThreads) void decode_score_kernel(
+// order-preserving key goes to keys_out[token index in the context] and is counted by its leading bits, in SPREAD launches
+// first in LDS over a workgroup's four tiles: the counts of a launch fall on a few dozen addresses, which the memory side
+// adds to one after the other (one 32k context: 12.3 us with an atomic per wave and bin, 6.0 like this, 4.3 uncounted).
+constexpr int score_tiles(bool hist, bool spread) { return spread && !hist ? 1 : 4; }      // tiles per workgroup
+constexpr int score_threads(bool hist, bool spread) { return spread ? 256 * score_tiles(hist, spread) : 256; }
+template <int GRP, bool HIST, bool SPREAD>
+__global__ __launch_bounds__((score_threads(HIST, SPREAD))) void decode_score_kernel(
     const DecodeBatch bd, int n_tiles, int n_q_heads, int n_kv_heads, int64_t n_rows,
     const float *__restrict__ logits, const float2 *__restrict__ stats,
     const float *__restrict__ dev_v, const uint8_t *__restrict__ reused, float *__restrict__ score,
     uint32_t *__restrict__ keys_out, uint32_t *__restrict__ key_hist)
 {
     static_assert(kTok == 64, "one token per lane");
+    constexpr int WAVES = SPREAD ? 4 : 1;          // waves that share a tile
+    constexpr int TILES = score_tiles(HIST, SPREAD);
+    extern __shared__ float2 score_lds[];          // SPREAD: [TILES][n_kv_heads][kTok] (mass, deviation), then HIST: the counts
     const int lane = threadIdx.x & 63;
-    const int tile_id = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kThreads / 64) + (int)(threadIdx.x >> 6));
-    if (tile_id >= n_tiles) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile_here = wave / WAVES, g_first = wave % WAVES;
+    float2 *md_s = score_lds + tile_here * n_kv_heads * kTok;
+    uint32_t *count_s = reinterpret_cast<uint32_t *>(score_lds + TILES * n_kv_heads * kTok);
+    const int tile_id = min((int)blockIdx.x * TILES + tile_here, n_tiles - 1);
+    const bool mine = (int)blockIdx.x * TILES + tile_here < n_tiles;      // (a tile too many is computed and dropped)
+    if (HIST && SPREAD)
+        for (int x = threadIdx.x; x < kKeyHistBins; x += score_threads(HIST, SPREAD)) count_s[x] = 0u;
     int b = 0;
     while (b + 1 < bd.n_req && tile_id >= bd.tile_begin[b + 1]) ++b;
     const int tile = tile_id - bd.tile_begin[b];
     const int i = tile * kTok + lane;
-    const bool live = i < bd.ctx_len[b];
+    const bool live = mine && i < bd.ctx_len[b];
     const int64_t row = bd.ctx_off[b] + min(i, bd.ctx_len[b] - 1);
     const float2 *st = stats + (int64_t)(bd.req0 + b) * n_q_heads;
+    const bool cand = (!SPREAD || g_first == 0) && reused ? reused[row] != 0 : true;
     float s = 0.f;
+    auto take = [&](int g, float mass, float dev) {
+        if (SPREAD) md_s[g * kTok + lane] = make_float2(mass, dev);
+        else s += mass * dev;
+    };
     if constexpr (GRP > 0) {
         constexpr int GB = 2;                       // KV heads per batch of loads
-        for (int g0 = 0; g0 < n_kv_heads; g0 += GB) {
+        for (int g0 = g_first; g0 < n_kv_heads; g0 += GB * WAVES) {
             float lg[GB][GRP], dv[GB];
 #pragma unroll
             for (int j = 0; j < GB; ++j) {
-                const int g = min(g0 + j, n_kv_heads - 1);
+                const int g = min(g0 + j * WAVES, n_kv_heads - 1);
 #pragma unroll
                 for (int hh = 0; hh < GRP; ++hh) lg[j][hh] = logits[(int64_t)(g * GRP + hh) * n_rows + row];
                 dv[j] = dev_v[(int64_t)g * n_rows + row];
             }
 #pragma unroll
             for (int j = 0; j < GB; ++j) {
-                if (g0 + j < n_kv_heads) {
+                const int g = g0 + j * WAVES;
+                if (g < n_kv_heads) {
                     float mass = 0.f;
 #pragma unroll
                     for (int hh = 0; hh < GRP; ++hh) {
-                        const float2 ms = st[(g0 + j) * GRP + hh];
+                        const float2 ms = st[g * GRP + hh];
                         mass += __builtin_amdgcn_exp2f((lg[j][hh] - ms.x) * 1.4426950408889634f) * (1.0f / ms.y);
                     }
-                    s += mass * dv[j];
+                    take(g, mass, dv[j]);
                 }
             }
         }
     } else {
         const int grp = n_q_heads / n_kv_heads;
-        for (int g = 0; g < n_kv_heads; ++g) {
+        for (int g = g_first; g < n_kv_heads; g += WAVES) {
             float mass = 0.f;
             for (int hh = 0; hh < grp; ++hh) {
                 const int h = g * grp + hh;
                 const float2 ms = st[h];
                 mass += __builtin_amdgcn_exp2f((logits[(int64_t)h * n_rows + row] - ms.x) * 1.4426950408889634f) * (1.0f / ms.y);
             }
-            s += mass * dev_v[(int64_t)g * n_rows + row];
+            take(g, mass, dev_v[(int64_t)g * n_rows + row]);
         }
     }
-    if (live) {
-        const bool cand = reused ? reused[row] != 0 : true;
+    if (SPREAD) {
+        __syncthreads();
+        if (!HIST && g_first != 0) return;
+        for (int g = 0; g < n_kv_heads; ++g) {
+            const float2 md = md_s[g * kTok + lane];
+            s += md.x * md.y;
+        }
+    }
+    if (live && (!SPREAD || g_first == 0)) {
         const float sc = cand ? s : -INFINITY;
         score[row] = sc;
         if (HIST) {
             const uint32_t key = score_key(sc);
             keys_out[i] = key;
-            key_hist_count<true>(key_hist, key, sc != -INFINITY);
+            if (!SPREAD) key_hist_count<true>(key_hist, key, sc != -INFINITY);
+            else if (sc != -INFINITY) atomicAdd(&count_s[key >> kKeyHistShift], 1u);
+        }
+    }
+    if (HIST && SPREAD) {
+        __syncthreads();
+        for (int x = threadIdx.x; x < kKeyHistBins; x += score_threads(HIST, SPREAD)) {
+            const uint32_t c = count_s[x];
+            if (c) __hip_atomic_fetch_add(key_hist + key_hist_slot((uint32_t)x), c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -649,6 +731,11 @@ extern "C" kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, in
     float2 *partial = (float2 *)ws;
     ws += align_up(sizeof(float2) * ((size_t)n_rows / kTok + (size_t)batch + 1) * (size_t)hq, 256);
     float *attn_part = (float *)ws;
+    // The matrix-core logits launch leaves a record per workgroup and request it touches, at most one per 32-token item and
+    // one more per request.  They go where the attention output's shares go later (dead by then): a record per query head
+    // is 8 bytes, the shares of kAttTok tokens and of a request at least 256 each.
+    static_assert(kAttTok / kMmaTok * sizeof(float2) <= 64 * sizeof(float), "the records fit the shares' room");
+    float2 *const run_partial = (float2 *)ws;
     ws += align_up(sizeof(float) * ((size_t)n_rows / kAttTok + (size_t)batch + 1) * (size_t)hq * (size_t)d, 256);
     void *select_ws = ws;
     const int lph = (int)(d * elem_bytes(shape->dtype) / 16);
@@ -701,16 +788,36 @@ extern "C" kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, in
         // bf16 / head_dim 128: the matrix-core kernel, as long as 32-bit byte offsets reach the whole cache
         const bool mma = shape->dtype == KVS_BF16 && d == 128 && grp <= 32 && n_rows * (int64_t)hk * 256 < ((int64_t)1 << 32) &&
                          aligned16(q_new) && aligned16(k_cache);
+        DecodeBatch bd_item = bd_tok;        // the same requests in kMmaTok-token items
+        int mma_items = 0, mma_wgs = 0;
         if (mma) {
-            static DeviceOnce attr_once;
-            st = once_per_device(attr_once, [] {
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_logits_mfma_kernel),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kMmaLds);
-                return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_decode_check: hipFuncSetAttribute: %s", hipGetErrorString(e));
-            });
-            if (st != KVS_OK) return st;
-            hipLaunchKernelGGL(decode_logits_mfma_kernel, dim3((unsigned)(KVS_DEC_PERSIST > 0 && tiles_tok > KVS_DEC_PERSIST ? KVS_DEC_PERSIST : tiles_tok)), block, kMmaLds, hs, bd_tok, hq, hk, n_rows,
-                               (const uint16_t *)q_new, (const uint16_t *)k_cache, scale, logits, part_l, (int)tiles_tok);
+            int64_t items = 0;
+            for (int i = 0; i < kMaxReq; ++i) {
+                bd_item.tile_begin[i] = (int32_t)items;
+                items += ((int64_t)bd_tok.ctx_len[i] + kMmaTok - 1) / kMmaTok;
+            }
+            bd_item.tile_begin[kMaxReq] = (int32_t)items;
+            if (items > 0x7fffffffLL) return fail(KVS_EINVAL, "kvs_decode_check: too many tokens in one launch");
+            part_l = run_partial;
+            mma_items = (int)items;
+            mma_wgs = items < kMmaWgs ? (int)items : kMmaWgs;
+            const dim3 lgrid((unsigned)mma_wgs, (unsigned)((hk + kMmaHeads - 1) / kMmaHeads));
+#define KVS_DEC_MMA(RU)                                                                                                              \
+    do {                                                                                                                             \
+        static DeviceOnce attr_once;                                                                                                 \
+        st = once_per_device(attr_once, [] {                                                                                         \
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_logits_mfma_kernel<RU>),                 \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMmaLds);                           \
+            return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_decode_check: hipFuncSetAttribute: %s", hipGetErrorString(e));     \
+        });                                                                                                                          \
+        if (st != KVS_OK) return st;                                                                                                 \
+        hipLaunchKernelGGL(decode_logits_mfma_kernel<RU>, lgrid, block, kMmaLds, hs, bd_item, hq, hk, n_rows, (const uint16_t *)q_new, \
+                           (const uint16_t *)k_cache, scale, logits, part_l, (int)items);                                            \
+    } while (0)
+            if (grp <= 8) KVS_DEC_MMA(4);
+            else if (grp <= 16) KVS_DEC_MMA(8);
+            else KVS_DEC_MMA(16);
+#undef KVS_DEC_MMA
         }
         else if (shape->dtype == KVS_BF16 && lph == 16) KVS_DEC_CASE(KVS_BF16, 16);
         else if (shape->dtype == KVS_BF16 && lph == 8) KVS_DEC_CASE(KVS_BF16, 8);
@@ -720,17 +827,31 @@ extern "C" kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, in
 #undef KVS_DEC_CASE
 #undef KVS_DEC_LAUNCH
         if ((st = check_launch("kvs_decode_check(logits)")) != KVS_OK) return st;
-        hipLaunchKernelGGL(decode_stats_kernel, dim3((unsigned)(nr * hq)), block, 0, hs, bd_tok, hq, part_l, stats);
+        hipLaunchKernelGGL(decode_stats_kernel, dim3((unsigned)(nr * hq)), block, 0, hs, mma ? bd_item : bd_tok, hq, part_l, stats, mma_items, mma_wgs);
         if ((st = check_launch("kvs_decode_check(stats)")) != KVS_OK) return st;
-        const dim3 sgrid((unsigned)((tiles_tok + kThreads / 64 - 1) / (kThreads / 64)));
+        // (counting launches of many KV heads would need more LDS than a workgroup has)
+        const bool spread = from_hist ? hk <= kSpreadMaxHeads : tiles_tok < kSpreadBelow;
+#define KVS_DEC_SCORE_(G, H, S)                                                                                                   \
+    do {                                                                                                                          \
+        constexpr int per = score_tiles(H, S);                                                                                    \
+        const size_t slds = S ? sizeof(float2) * per * (size_t)hk * kTok + (H ? sizeof(uint32_t) * kKeyHistBins : 0) : 0;         \
+        if (S && H) {                                                                                                             \
+            static DeviceOnce attr_once;                                                                                          \
+            st = once_per_device(attr_once, [] {                                                                                  \
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&decode_score_kernel<G, H, S>),           \
+                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)(sizeof(float2) * per * kSpreadMaxHeads * kTok + sizeof(uint32_t) * kKeyHistBins)); \
+                return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_decode_check: hipFuncSetAttribute: %s", hipGetErrorString(e)); \
+            });                                                                                                                   \
+            if (st != KVS_OK) return st;                                                                                          \
+        }                                                                                                                         \
+        hipLaunchKernelGGL((decode_score_kernel<G, H, S>), dim3((unsigned)((tiles_tok + per - 1) / per)), dim3(score_threads(H, S)), slds, hs, \
+                           bd_tok, (int)tiles_tok, hq, hk, n_rows, logits, stats, dev_v, reused, score,                           \
+                           H ? fs.keys : (uint32_t *)nullptr, H ? fs.hist : (uint32_t *)nullptr);                                 \
+    } while (0)
 #define KVS_DEC_SCORE(G)                                                                                                          \
     do {                                                                                                                          \
-        if (from_hist)                                                                                                            \
-            hipLaunchKernelGGL((decode_score_kernel<G, true>), sgrid, block, 0, hs, bd_tok, (int)tiles_tok, hq, hk, n_rows, logits, \
-                               stats, dev_v, reused, score, fs.keys, fs.hist);                                                    \
-        else                                                                                                                      \
-            hipLaunchKernelGGL((decode_score_kernel<G, false>), sgrid, block, 0, hs, bd_tok, (int)tiles_tok, hq, hk, n_rows, logits, \
-                               stats, dev_v, reused, score, (uint32_t *)nullptr, (uint32_t *)nullptr);                            \
+        if (from_hist) { if (spread) KVS_DEC_SCORE_(G, true, true); else KVS_DEC_SCORE_(G, true, false); }                        \
+        else { if (spread) KVS_DEC_SCORE_(G, false, true); else KVS_DEC_SCORE_(G, false, false); }                                \
     } while (0)
         if (grp == 1) KVS_DEC_SCORE(1);
         else if (grp == 2) KVS_DEC_SCORE(2);
@@ -739,6 +860,7 @@ extern "C" kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, in
         else if (grp == 8) KVS_DEC_SCORE(8);
         else KVS_DEC_SCORE(0);
 #undef KVS_DEC_SCORE
+#undef KVS_DEC_SCORE_
         if ((st = check_launch("kvs_decode_check(score)")) != KVS_OK) return st;
         if (attn_out) {
             DecodeBatch bd_att = bd_tok;   // the same requests in kAttTok-token tiles

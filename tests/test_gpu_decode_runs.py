@@ -1,0 +1,63 @@
+"""kvs_decode_check's matrix-core logits launch where its runs of 32-token items have edges: contexts around an item, around
+a 64-token tile, empty ones, runs that span several requests, more items than workgroups, head counts that leave waves
+without a head or need a second block of heads, group sizes on both sides of the result registers' steps; against the
+oracle.  Scores 1e-5 relative (fp32 logits of exact bf16 products, fp32 softmax), index lists checked as a valid top-k."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from attn_check import check_topk_band
+from paper_2503_16525_amd import binding as B
+from paper_2503_16525_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 0, 33, 63, 64, 65, 0, 95, 96, 97, 128, 300]
+CASES = [
+    ("edges-4x8", 32, 8, EDGES),
+    ("one-kv-head", 8, 1, EDGES),
+    ("three-kv-heads-g3", 9, 3, EDGES),
+    ("five-kv-heads", 10, 5, EDGES),
+    ("nine-kv-heads", 18, 9, EDGES),
+    ("sixteen-kv-heads", 16, 16, EDGES),
+    ("group-9", 18, 2, EDGES),
+    ("group-16", 16, 1, EDGES),
+    ("group-17", 34, 2, EDGES),
+    ("group-32", 32, 1, EDGES),
+    ("70-requests", 8, 4, [7 + 13 * i for i in range(70)]),
+    ("more-items-than-workgroups", 16, 4, [9000, 33, 12000]),
+    ("one-context-with-key-counts", 32, 8, [16500]),
+    ("one-context-17-heads-with-key-counts", 34, 17, [12400]),
+]
+
+
+@pytest.mark.parametrize("name,hq,hk,lens", CASES, ids=[c[0] for c in CASES])
+def test_runs(name, hq, hk, lens):
+    print(f"decode runs: {name}", flush=True)
+    d, slack = 128, 3
+    rng = torch.Generator().manual_seed(len(name))
+    off = np.cumsum([0] + [n + slack for n in lens[:-1]])
+    rows = int(off[-1]) + lens[-1] + slack
+    q = (torch.randn((len(lens), hq, d), generator=rng) / d ** 0.5).to(torch.bfloat16)
+    k = torch.randn((rows, hk, d), generator=rng).to(torch.bfloat16)
+    dev_v = torch.rand((hk, rows), generator=rng) + 0.1
+    reused = (torch.rand(rows, generator=rng) < 0.9).to(torch.uint8)
+    k_req = [min(n, max(0, int(reused[o:o + n].sum()) // 10)) for o, n in zip(off, lens)]
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("decode_check", sh, len(lens), rows),), 255, dtype=torch.uint8, device="cuda")
+    idx = torch.full((sum(k_req) + 8,), -7, dtype=torch.int32, device="cuda")
+    score = torch.full((rows,), 7.0, device="cuda")
+    for _ in range(2):                    # the second call finds the workspace as the first left it
+        B.kvs_decode_check(sh, rows, off, lens, q.cuda(), k.cuda(), None, dev_v.cuda(), reused.cuda(), 1.0, k_req, idx, score, None, ws)
+        _, ref, _ = oracle.decode_check(q, k, dev_v, reused, 1.0, off, lens, k_req)
+        got, got_idx, at = score.cpu().numpy(), idx.cpu().numpy(), 0
+        assert np.all(got_idx[sum(k_req):] == -7)
+        for o, n, kr in zip(off, lens, k_req):
+            g, r = got[o:o + n], ref[o:o + n]
+            assert np.array_equal(np.isneginf(g), np.isneginf(r))
+            fin = np.isfinite(r)
+            np.testing.assert_allclose(g[fin], r[fin], rtol=1e-5)
+            assert np.all(got[o + n:o + n + slack] == 7.0), "rows outside the contexts were written"
+            check_topk_band(got_idx[at:at + kr], r, kr)
+            at += kr
