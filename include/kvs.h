@@ -268,9 +268,8 @@ KVS_API kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, int64
  * k         [dev] [n_tokens, n_kv_heads, head_dim] (the fresh keys)
  * alpha     [dev] fp32[n_kv_heads, n_tokens], written
  * workspace [dev] kvs_workspace_size("attn_colsum", shape, 1, n_tokens, 0) bytes, 256-byte
- *           aligned, required; contents on return are unspecified.  It holds every row's log-sum-exp
- *           (4 n_tokens n_q_heads + 256 bytes: less is refused) and the pieces into which short sweeps, and
- *           sweeps of uneven blocks, are cut; with the log-sum-exps' room alone the sweeps run uncut, slower
+ *           aligned, required; contents on return are unspecified.  It holds every row's log-sum-exp and the
+ *           results of the pieces into which short sweeps, and sweeps of uneven blocks, are cut
  */
 KVS_API kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, const void *q, const void *k,
                            float scale, float *alpha,
@@ -297,9 +296,6 @@ KVS_API kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, con
  * reused   [dev] uint8[n_tokens] or NULL (every token is rated)
  * impact_* [dev] fp32[n_tokens], each may be NULL
  * workspace [dev] kvs_workspace_size("first_order_impact", shape, 1, n_tokens, 0) bytes, 256-byte aligned
- *          (bf16: with 12 n_tokens n_kv_heads + 256 bytes only, the least that is accepted, rows are not cut into
- *          pieces and tokens that are not reused are rated too before they are masked: slower, the same results
- *          up to the order of the sums)
  * All arithmetic is fp32 on exactly widened inputs in a fixed order (bit-reproducible); up to 2^20 tokens.
  */
 KVS_API kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_tokens, const void *q,

@@ -517,9 +517,8 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     if (!q || !k || !alpha) return fail(KVS_EINVAL, "kvs_attn_colsum: NULL tensor pointer");
     if (!aligned16(q) || !aligned16(k)) return fail(KVS_EINVAL, "kvs_attn_colsum: Q/K pointers must be 16-byte aligned");
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return fail(KVS_EINVAL, "kvs_attn_colsum: workspace must be given, 256-byte aligned");
-    // the rows' log-sum-exps have to fit; with less than the size asked for the sweeps run uncut
-    const size_t least = (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
-    if (workspace_bytes < least) return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, least);
+    if (workspace_bytes < colsum_workspace_bytes(shape, n_tokens))
+        return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, colsum_workspace_bytes(shape, n_tokens));
     // the matrix-core kernel: bf16, head_dim 128, a positive scale (it folds the scale into an exp2
     // argument after taking maxima).  Everything else takes the fp32 kernels.
     const bool mfma = shape->dtype == KVS_BF16 && shape->head_dim == D && scale > 0.f;
@@ -529,14 +528,8 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     float *lse2 = (float *)workspace;
     const float scale_log2 = scale * 1.4426950408889634f;
     hipStream_t hs = (hipStream_t)stream;
-    Cut c1 = plan_cut<1>(shape, n_tokens), c2 = plan_cut<2>(shape, n_tokens);
+    const Cut c1 = plan_cut<1>(shape, n_tokens), c2 = plan_cut<2>(shape, n_tokens);
     float *part = (float *)((char *)workspace + row_bytes(shape, n_tokens));
-    if (workspace_bytes < colsum_workspace_bytes(shape, n_tokens)) {
-        const int grp = shape->n_q_heads / shape->n_kv_heads;
-        c1 = Cut{0, 1, (int)((n_tokens * grp + FIXED - 1) / FIXED)};
-        c2 = Cut{0, 1, (int)((n_tokens + FIXED - 1) / FIXED)};
-        part = nullptr;
-    }
     st = launch_sweep<1>(shape, n_tokens, q, k, scale_log2, nullptr, lse2, part, c1, hs);
     if (st != KVS_OK) return st;
     return launch_sweep<2>(shape, n_tokens, q, k, scale_log2, lse2, alpha, part, c2, hs);

@@ -106,7 +106,7 @@ kvs_status launch_colsum_f32(const kvs_shape *shape, int64_t n, const void *q, c
 {
     const int d = shape->head_dim, hq = shape->n_q_heads, hk = shape->n_kv_heads;
     // quadratic work at a few percent of the bf16 matrix-core rate: refuse what would run for minutes
-    if (n > 65536) return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens are too many for the fp32 path (this shape has no bf16 matrix-core kernel)", (long long)n);
+    if (n > 65536) return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens are too many for the vector path (this shape has no matrix-core kernel)", (long long)n);
     if (n * (int64_t)(hq / hk) > 0x7ffffff0) return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d query heads", (long long)n, hq);
     if (shape->dtype == KVS_F32) return d == 64 ? launch_both<KVS_F32, 64>((int)n, hq, hk, q, k, scale, lse, alpha, st) : launch_both<KVS_F32, 128>((int)n, hq, hk, q, k, scale, lse, alpha, st);
     return d == 64 ? launch_both<KVS_BF16, 64>((int)n, hq, hk, q, k, scale, lse, alpha, st) : launch_both<KVS_BF16, 128>((int)n, hq, hk, q, k, scale, lse, alpha, st);

@@ -442,7 +442,7 @@ size_t impact_part_bytes(const kvs_shape *shape, int64_t n, int pieces) { return
 
 size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
-    if (n_tokens <= 0 || shape->dtype != KVS_BF16) return impact_part_bytes(shape, n_tokens, 1) + 256;
+    if (n_tokens <= 0 || shape->n_kv_heads <= 0 || shape->dtype != KVS_BF16) return impact_part_bytes(shape, n_tokens, 1) + 256;
     // the pieces' sums, then the list of reused tokens and its length
     return impact_part_bytes(shape, n_tokens, impact_pieces(shape, n_tokens)) + sizeof(int32_t) * ((size_t)n_tokens + 1) + 256;
 }
@@ -466,20 +466,16 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
     if (!q || !k_fresh || !v_fresh || !k_cache || !v_cache || !h_fresh || !lse) return fail(KVS_EINVAL, "kvs_first_order_impact: NULL tensor pointer");
     if (!(isfinite(scale))) return fail(KVS_EINVAL, "kvs_first_order_impact: scale is not finite");
     if (shape->n_kv_heads > 65535) return fail(KVS_EUNSUPPORTED, "kvs_first_order_impact: too many kv heads");
-    // the sums of uncut rows have to fit; with less than the size asked for the rows are not cut and every token is rated
-    const size_t least = impact_part_bytes(shape, n_tokens, 1) + 256;
-    if (!workspace || workspace_bytes < least) return fail(KVS_EWORKSPACE, "kvs_first_order_impact: workspace %zu < %zu bytes", workspace_bytes, least);
+    const size_t need = impact_workspace_bytes(shape, n_tokens);
+    if (!workspace || workspace_bytes < need) return fail(KVS_EWORKSPACE, "kvs_first_order_impact: workspace %zu < %zu bytes", workspace_bytes, need);
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return fail(KVS_EINVAL, "kvs_first_order_impact: workspace must be 256-byte aligned");
     hipStream_t hs = (hipStream_t)stream;
     const int n = (int)n_tokens, hk = shape->n_kv_heads;
     float *part = (float *)workspace;
     int pieces = 1;
     if (shape->dtype == KVS_BF16) {
-        int32_t *list = nullptr;
-        if (workspace_bytes >= impact_workspace_bytes(shape, n_tokens)) {
-            pieces = impact_pieces(shape, n_tokens);
-            if (reused) list = (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces));
-        }
+        pieces = impact_pieces(shape, n_tokens);
+        int32_t *list = reused ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
         int32_t *count = list ? list + n : nullptr;
         if (list) {
             hipLaunchKernelGGL(impact_list_kernel, dim3(1), dim3(kListThreads), 0, hs, n, reused, list, count);

@@ -1,5 +1,4 @@
-"""kvs_attn_colsum with its sweeps cut into pieces, against the oracle and against the uncut sweeps that a smaller
-workspace gives.  Lengths sit at the edges of tiles (32), blocks (256) and pieces; group sizes that do and do not
+"""kvs_attn_colsum with its sweeps cut into pieces, against the oracle.  Lengths sit at the edges of tiles (32), blocks (256) and pieces; group sizes that do and do not
 divide a tile."""
 import numpy as np
 import pytest
@@ -22,22 +21,19 @@ def colsum(w, q, k, ws_bytes):
 
 @pytest.mark.parametrize("hq,hk", [(28, 4), (32, 8), (8, 1), (3, 3)])
 @pytest.mark.parametrize("n", [127, 128, 129, 160, 255, 257, 512, 1031])
-def test_pieces_against_the_oracle_and_the_uncut_sweeps(hq, hk, n):
+def test_pieces_against_the_oracle(hq, hk, n):
     print(f"column mass in pieces: {hq}x{hk} heads, {n} tokens", flush=True)
     w = synth.scaled(synth.LLAMA, n, n_q_heads=hq, n_kv_heads=hk, span_mean=64.0)
     lay = synth.make_layer(w)
     q, k = lay["q"], lay["k_fresh"]
     _, ref = oracle.alpha_prefill(q, k, 1.0)
-    least = 4 * n * hq + 256
     full = B.kvs_workspace_size("attn_colsum", B.shape_of(w), 1, n)
-    assert full >= least
-    cut, uncut = colsum(w, q, k, full), colsum(w, q, k, least)
+    cut = colsum(w, q, k, full)
     # fp32 logits of exact bf16 products (1e-6 of a logit of at most ~8), exp2 and log2 to an ulp: some 1e-6 in all
     np.testing.assert_allclose(cut, ref, rtol=2e-5, atol=1e-7)
-    np.testing.assert_allclose(uncut, ref, rtol=2e-5, atol=1e-7)
     np.testing.assert_array_equal(cut, colsum(w, q, k, full))     # no atomics: the same bits again
     with pytest.raises(B.KvsError):
-        colsum(w, q, k, least - 1)
+        colsum(w, q, k, full - 1)
 
 
 def test_a_late_outlier_in_a_later_piece():

