@@ -328,7 +328,7 @@ KVS_API kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_toke
  * workspace         [dev] kvs_workspace_size("match_tokens", NULL, 1, n_target, n_candidate) bytes,
  *                   256-byte aligned (not needed when a sequence is shorter than the window)
  * Up to 2^26 tokens per sequence.  Integer work: the outputs are exact and do not depend on the
- * order in which the device's atomics arrive.  Six launches, no host synchronisation.  Cost grows
+ * order in which the device's atomics arrive.  Five launches, no host synchronisation.  Cost grows
  * with the matched tokens, except for degenerate inputs (one token repeated throughout both
  * sequences makes every pair of windows a candidate: n_target x n_candidate steps).
  * Several earlier requests are matched in one call by concatenating them into one candidate with a token id

@@ -8,9 +8,9 @@
 // its partner is j + p - i; and the output lists the pairs by (j, i, p).  That statement is what
 // runs here, in parallel:
 //
-//   1. match_hash_kernel    Eq. (7) for every window of both sequences, each from its own w tokens
-//                           (Horner; nothing rolls, so no carried state between threads); clears the
-//                           tables.
+//   1. match_hash_kernel    Eq. (7) for every window of both sequences by doubling: the hash of 2^(k+1) tokens is
+//                           that of the first 2^k times b^(2^k) plus that of the next 2^k, so a window costs some
+//                           log2(w) modular products (short windows: token by token); clears the tables.
 //   2. match_insert_kernel  a chained hash table over the target's window hashes (one atomic
 //                           exchange per window; the order inside a chain does not matter below).
 //   3. match_seed_kernel    a lane per candidate window walks its chain.  A pair (i, j) whose
@@ -20,25 +20,24 @@
 //                           positions per trip, and claims the positions it reaches with a 64-bit
 //                           atomic minimum on (j, i).  A stretch of R equal tokens costs R atomics
 //                           instead of the scan's R^2 / 2 comparisons.
-//   4. match_mark_kernel    partner of every target position; counts the maximal stretches of
-//                           positions with the same (j, i) per block of 1024 positions.
-//   5. match_segments_kernel  numbers the stretches in position order (start, end, key).
-//   6. match_order_kernel   a wavefront per stretch adds up the lengths of the stretches that come
+//   4. match_mark_kernel    partner of every target position; the maximal stretches of positions with the
+//                           same (j, i), cut at blocks of 1024 positions, are numbered as they come.
+//   5. match_order_kernel   a wavefront per stretch adds up the lengths of the stretches that come
 //                           before it in (j, i, start) order and writes its pairs there: the lists
-//                           come out in the scan's order of discovery.
+//                           come out in the scan's order of discovery, whatever numbers they had.
 //
 // Cost: reading both sequences a few times plus one atomic per matched position; the stretches are
-// few (tens to hundreds for a prompt assembled from earlier requests), so step 6's all-pairs count
+// few (tens to hundreds for a prompt assembled from earlier requests), so step 5's all-pairs count
 // is small.  Worst cases are bounded, not fast: sequences of one repeated token make every pair of
 // windows an equal-hash pair (n_target x n_candidate chain steps), and a target whose matched
-// positions alternate makes n_target / 2 stretches (step 6 is quadratic in them).
+// positions alternate makes n_target / 2 stretches (step 5 is quadratic in them).
 #include "kvs_internal.h"
 
 namespace kvs {
 namespace {
 
 constexpr int kMatchThreads = 256;
-constexpr int kMatchChunk = 1024;          // target positions per workgroup in steps 4 and 5
+constexpr int kMatchChunk = 1024;          // target positions per workgroup in step 4
 constexpr uint64_t kNoMatch = ~0ull;
 
 struct MatchWs {
@@ -47,7 +46,6 @@ struct MatchWs {
     int32_t *head;         // [table]       first target window of each slot's chain, -1: none
     int32_t *next;         // [n_target]    next target window of the same slot
     uint64_t *best;        // [n_target]    smallest (j << 32 | i) that reaches the position
-    uint32_t *chunk_count; // [chunks]      stretches that start in each block of kMatchChunk positions
     int32_t *seg_start;    // [n_target]    stretch s covers positions seg_start[s] .. seg_end[s]-1
     int32_t *seg_end;
     uint64_t *seg_key;     // [n_target]
@@ -65,16 +63,15 @@ inline int table_bits(int64_t windows)
 
 inline size_t carve(MatchWs *ws, char *base, int64_t n_t, int64_t n_c, int bits)
 {
-    const int64_t chunks = (n_t + kMatchChunk - 1) / kMatchChunk;
     int64_t off = 0;
     auto take = [&](int64_t bytes) { char *p = base ? base + off : nullptr; off += round256(bytes); return p; };
     char *best = take(8 * n_t), *seg_key = take(8 * n_t);
     char *ht = take(4 * n_t), *hc = take(4 * n_c), *head = take(4 * ((int64_t)1 << bits)), *next = take(4 * n_t);
-    char *cc = take(4 * chunks), *ss = take(4 * n_t), *se = take(4 * n_t), *ct = take(256);
+    char *ss = take(4 * n_t), *se = take(4 * n_t), *ct = take(256);
     if (ws) {
         ws->best = (uint64_t *)best; ws->seg_key = (uint64_t *)seg_key;
         ws->ht = (uint32_t *)ht; ws->hc = (uint32_t *)hc; ws->head = (int32_t *)head; ws->next = (int32_t *)next;
-        ws->chunk_count = (uint32_t *)cc; ws->seg_start = (int32_t *)ss; ws->seg_end = (int32_t *)se; ws->counters = (uint32_t *)ct;
+        ws->seg_start = (int32_t *)ss; ws->seg_end = (int32_t *)se; ws->counters = (uint32_t *)ct;
     }
     return (size_t)off;
 }
@@ -101,31 +98,70 @@ __device__ __forceinline__ uint32_t window_hash(Tokens tok, int64_t i, int w, ui
 }
 __device__ __forceinline__ uint32_t slot_of(uint32_t h, int bits) { return (h * 2654435761u) >> (32 - bits); }
 
-// Windows up to this long are hashed out of LDS: a workgroup's 256 windows overlap in all but 255
-// tokens, and a Horner chain over global memory would pay one memory latency per token.
+// Windows up to kHashLdsWindow tokens are hashed out of LDS (a workgroup's 256 windows overlap in all but 255 tokens): by
+// doubling, or token by token where that is as short as the doubling's barriers (whole call, 32768 tokens, token by token
+// against doubling: window 16 23.9 and 24.5 us, 24 the same, 32 25.3 and 24.6, 64 29.8 and 25.8).
 constexpr int kHashLdsWindow = 768;
+constexpr int kHashOneByOne = 16;
+constexpr int kHashPerThread = 4;
+static_assert(kMatchThreads + kHashLdsWindow - 1 <= kHashPerThread * kMatchThreads, "positions of a tile per thread");
 
 // hashes of the windows that start at base .. base+255 (those below n_windows) of one sequence
 __device__ __forceinline__ void hash_block(const int32_t *__restrict__ tok, int64_t n, int64_t n_windows, int64_t base, int w, uint32_t b,
-                                           const Modulus &md, int32_t *tile, uint32_t *__restrict__ out)
+                                           const Modulus &md, uint32_t *tile, uint32_t *__restrict__ out)
 {
-    const int64_t i = base + threadIdx.x;
-    if (w <= kHashLdsWindow) {
-        const int64_t span = min((int64_t)kMatchThreads + w - 1, n - base);
-        __syncthreads();                                   // the tile's previous readers are done
-        for (int64_t x = threadIdx.x; x < span; x += kMatchThreads) tile[x] = tok[base + x];
-        __syncthreads();
-        if (i < n_windows) out[i] = window_hash(tile, (int64_t)threadIdx.x, w, b, md);
-    } else if (i < n_windows) {
-        out[i] = window_hash(tok, i, w, b, md);
+    const int tid = threadIdx.x;
+    const int64_t i = base + tid;
+    if (w > kHashLdsWindow) {
+        if (i < n_windows) out[i] = window_hash(tok, i, w, b, md);
+        return;
     }
+    if (w <= kHashOneByOne) {
+        const int64_t sp = min((int64_t)kMatchThreads + w - 1, n - base);
+        for (int64_t x = tid; x < sp; x += kMatchThreads) tile[x] = (uint32_t)tok[base + x];
+        __syncthreads();
+        if (i < n_windows) out[i] = window_hash(tile, (int64_t)tid, w, b, md);
+        return;
+    }
+    const int span = (int)min((int64_t)kMatchThreads + w - 1, n - base);
+    for (int x = tid; x < span; x += kMatchThreads) tile[x] = (uint32_t)reduce((uint64_t)(uint32_t)tok[base + x], md);
+    __syncthreads();
+    // tile[x] = hash of the 2^k tokens from x on; h = hash of the first `len` tokens of this thread's window, len the
+    // bits of w below bit k
+    uint64_t pw = reduce((uint64_t)b, md);              // b^(2^k)
+    uint32_t h = 0;
+    int len = 0;
+    for (int k = 0;; ++k) {                              // uniform
+        if ((w >> k) & 1) {
+            const int at = min(tid + len, span - 1);     // (a window past the end is not stored)
+            h = len == 0 ? tile[min(tid, span - 1)] : (uint32_t)reduce((uint64_t)h * pw + tile[at], md);
+            len += 1 << k;
+        }
+        if ((w >> (k + 1)) == 0) break;
+        uint32_t next[kHashPerThread];
+        const int reach = span - (2 << k);               // last position with 2^(k+1) tokens ahead of it
+#pragma unroll
+        for (int c = 0; c < kHashPerThread; ++c) {
+            const int x = tid + c * kMatchThreads;
+            if (x <= reach) next[c] = (uint32_t)reduce((uint64_t)tile[x] * pw + tile[x + (1 << k)], md);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kHashPerThread; ++c) {
+            const int x = tid + c * kMatchThreads;
+            if (x <= reach) tile[x] = next[c];
+        }
+        __syncthreads();
+        pw = reduce(pw * pw, md);
+    }
+    if (i < n_windows) out[i] = h;
 }
 
 __global__ __launch_bounds__(kMatchThreads) void match_hash_kernel(
     const int32_t *__restrict__ target, int64_t n_t, const int32_t *__restrict__ cand, int64_t n_c,
     int w, uint32_t b, Modulus md, int bits, MatchWs ws)
 {
-    __shared__ int32_t tile[kMatchThreads + kHashLdsWindow];
+    __shared__ uint32_t tile[kMatchThreads + kHashLdsWindow];
     const int64_t tid = (int64_t)blockIdx.x * kMatchThreads + threadIdx.x, nth = (int64_t)gridDim.x * kMatchThreads;
     const int64_t wt = n_t - w + 1, wc = n_c - w + 1, table = (int64_t)1 << bits;
     for (int64_t i = tid; i < n_t; i += nth) ws.best[i] = kNoMatch;
@@ -216,7 +252,7 @@ __global__ __launch_bounds__(kMatchThreads) void match_seed_kernel(
     }
 }
 
-// flags of the four consecutive positions a thread owns in steps 4 and 5
+// flags of the four consecutive positions a thread owns in step 4; stretches are cut at the edges of a chunk
 struct Flags {
     uint64_t key[4];
     bool start[4], end[4];
@@ -232,20 +268,20 @@ __device__ __forceinline__ Flags read_flags(const uint64_t *__restrict__ best, i
     for (int u = 0; u < 4; ++u) {
         f.key[u] = k[u];
         const bool matched = k[u] != kNoMatch;          // positions past the end read as unmatched
-        f.start[u] = matched && (u == 0 ? before : k[u - 1]) != k[u];
-        f.end[u] = matched && k[u + 1] != k[u];
+        f.start[u] = matched && ((u == 0 ? before : k[u - 1]) != k[u] || (p0 + u) % kMatchChunk == 0);
+        f.end[u] = matched && (k[u + 1] != k[u] || (p0 + u + 1) % kMatchChunk == 0);
     }
     return f;
 }
 
-__global__ __launch_bounds__(kMatchThreads) void match_mark_kernel(int64_t n_t, int32_t *__restrict__ match_cand, MatchWs ws)
+__global__ __launch_bounds__(kMatchThreads) void match_mark_kernel(int64_t n_t, int32_t *__restrict__ match_cand, int lists, MatchWs ws)
 {
-    __shared__ uint32_t tot[2];
-    if (threadIdx.x < 2) tot[threadIdx.x] = 0u;
-    __syncthreads();
+    __shared__ uint32_t wave_starts[kMatchThreads / kWave], wave_matched[kMatchThreads / kWave];
+    __shared__ uint32_t base_sh;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int64_t p0 = (int64_t)blockIdx.x * kMatchChunk + 4 * threadIdx.x;
     const Flags f = read_flags(ws.best, p0, n_t);
-    uint32_t starts = 0, matched = 0;
+    uint32_t mine = 0, matched = 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         if (p0 + u < n_t) {
@@ -253,51 +289,29 @@ __global__ __launch_bounds__(kMatchThreads) void match_mark_kernel(int64_t n_t, 
             const int32_t j = (int32_t)(f.key[u] >> 32), i = (int32_t)(uint32_t)f.key[u];
             match_cand[p0 + u] = mt ? j + (int32_t)(p0 + u - i) : -1;
             matched += mt ? 1u : 0u;
-            starts += f.start[u] ? 1u : 0u;
+            mine += f.start[u] ? 1u : 0u;
         }
     }
-    // workgroup totals: wavefront sums, then one LDS atomic per wavefront
-    for (int o = 32; o > 0; o >>= 1) { starts += __shfl_xor(starts, o); matched += __shfl_xor(matched, o); }
-    if ((threadIdx.x & (kWave - 1)) == 0) { atomicAdd(&tot[0], starts); atomicAdd(&tot[1], matched); }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ws.chunk_count[blockIdx.x] = tot[0];
-        if (tot[1]) atomicAdd(&ws.counters[0], tot[1]);
-    }
-}
-
-__global__ __launch_bounds__(kMatchThreads) void match_segments_kernel(int64_t n_t, MatchWs ws)
-{
-    __shared__ uint32_t wave_tot[kMatchThreads / kWave];
-    __shared__ uint32_t base_sh;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    // stretches that start in the blocks before this one
-    uint32_t before = 0;
-    for (int64_t c = threadIdx.x; c < (int64_t)blockIdx.x; c += kMatchThreads) before += ws.chunk_count[c];
-    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
-    if (lane == 0) wave_tot[wave] = before;
-    __syncthreads();
-    if (threadIdx.x == 0) base_sh = wave_tot[0] + wave_tot[1] + wave_tot[2] + wave_tot[3];
-    __syncthreads();
-    const uint32_t base = base_sh;
-    __syncthreads();
-    const int64_t p0 = (int64_t)blockIdx.x * kMatchChunk + 4 * threadIdx.x;
-    const Flags f = read_flags(ws.best, p0, n_t);
-    uint32_t mine = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) mine += f.start[u] ? 1u : 0u;
-    // exclusive scan over the workgroup in thread order
+    // numbers for the chunk's stretches: any run of free ones (the order below goes by key and position)
     uint32_t incl = mine;
     for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t up = __shfl_up(incl, o);
         if (lane >= o) incl += up;
     }
-    if (lane == kWave - 1) wave_tot[wave] = incl;
+    for (int o = 32; o > 0; o >>= 1) matched += __shfl_xor(matched, o);
+    if (lane == kWave - 1) { wave_starts[wave] = incl; wave_matched[wave] = matched; }
     __syncthreads();
-    uint32_t run = base + incl - mine;
-    for (int v = 0; v < wave; ++v) run += wave_tot[v];
-    // run = stretches that start before this thread's first position; a position's stretch is the
-    // last one that started at or before it
+    if (threadIdx.x == 0) {
+        uint32_t starts = 0, total = 0;
+        for (int v = 0; v < kMatchThreads / kWave; ++v) { starts += wave_starts[v]; total += wave_matched[v]; }
+        if (total) atomicAdd(&ws.counters[0], total);
+        base_sh = lists && starts ? atomicAdd(&ws.counters[1], starts) : 0u;
+    }
+    if (!lists) return;                                  // uniform
+    __syncthreads();
+    uint32_t run = base_sh + incl - mine;
+    for (int v = 0; v < wave; ++v) run += wave_starts[v];
+    // run = number of the next stretch that starts; a position's stretch is the last one that started at or before it
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         if (f.start[u]) {
@@ -307,7 +321,6 @@ __global__ __launch_bounds__(kMatchThreads) void match_segments_kernel(int64_t n
         }
         if (f.end[u]) ws.seg_end[run - 1] = (int32_t)(p0 + u + 1);
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kMatchThreads - 1) ws.counters[1] = run;
 }
 
 __global__ __launch_bounds__(kMatchThreads) void match_order_kernel(int32_t *__restrict__ target_matches, int32_t *__restrict__ cand_matches,
@@ -389,9 +402,8 @@ extern "C" kvs_status kvs_match_tokens(const int32_t *target, int64_t n_target, 
     hipLaunchKernelGGL(match_seed_kernel, dim3((unsigned)((wc + kMatchThreads - 1) / kMatchThreads)), dim3(kMatchThreads), 0, hs,
                        target, n_target, candidate, n_candidate, (int)window, bits, ws);
     const unsigned chunks = (unsigned)((n_target + kMatchChunk - 1) / kMatchChunk);
-    hipLaunchKernelGGL(match_mark_kernel, dim3(chunks), dim3(kMatchThreads), 0, hs, n_target, match_cand, ws);
     const bool lists = target_matches || candidate_matches;
-    if (lists) hipLaunchKernelGGL(match_segments_kernel, dim3(chunks), dim3(kMatchThreads), 0, hs, n_target, ws);
+    hipLaunchKernelGGL(match_mark_kernel, dim3(chunks), dim3(kMatchThreads), 0, hs, n_target, match_cand, (int)lists, ws);
     hipLaunchKernelGGL(match_order_kernel, dim3(lists ? 256u : 1u), dim3(kMatchThreads), 0, hs, target_matches, candidate_matches, n_matches, ws);
     return check_launch("kvs_match_tokens");
 }
