@@ -71,6 +71,7 @@ constexpr int K_RING = AHEAD <= 4 ? 4 : 8;   // tiles, >= AHEAD; see the slot ar
 constexpr int V_RING = 8;                    // >= AHEAD + 2
 static_assert(K_RING >= AHEAD && V_RING >= AHEAD + 2, "ring depth");
 constexpr int LDS_BYTES = (K_RING + V_RING) * TILE_B;
+constexpr int64_t kAttnLeaveSpread = 64;   // whole-range launches let waves leave from this mean spread of a row tile on (key tiles; 33: 4 % slower, 77: 3 % faster)
 constexpr float kRefShift = 60.0f;      // base-2 offset of the fixed softmax reference above the first tile's maximum
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -212,7 +213,8 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
 // workspace and the merge kernel combines them.  The pieces are absolute key ranges, the same for
 // every row tile, and the list runs through them range by range: the workgroups that are resident
 // together read the same stretch of K and V, which then stays in L2.
-template <bool WANT_LSE, bool SPLIT>
+// LEAVE: a wave whose own positions end before the workgroup's leaves the arithmetic there and only stages.
+template <bool WANT_LSE, bool SPLIT, bool LEAVE>
 __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const AttnTiles td, int n_q_heads, int n_kv_heads, int total_tiles,
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
@@ -659,6 +661,12 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         // may sit in different loops.
         const int j_unmasked = (pmin + 1) / BN;     // tiles 0 .. j_unmasked-1: every key <= pmin
         const int j_inside = ctx_len / BN;          // tiles 0 .. j_inside-1 need no row clamp
+        // Past the wave's own last position every key is masked: with LEAVE the wave then only stages and keeps the
+        // barriers until the others are done.  Rows of a workgroup are up to 64 tokens of a sparse selection: at the 2 % of
+        // a decode batch the first wave's positions end 75 key tiles before the last one's, and the workgroup is as slow
+        // as its slowest wave.  64 requests 1566 -> 1500 us, pieces of 2 to 10 % 1 to 2 % faster; where a tile's tokens are
+        // close together the wave's two ways out cost more than they save (15 % of 32768 tokens 997 -> 1006 us).
+        const int w_hi = LEAVE ? min(t_hi, __builtin_amdgcn_readfirstlane(pmax) / BN + 1) : t_hi;
         if (t_lo + 3 <= t_hi && t_lo + AHEAD + 3 <= j_inside) {
             // the first step has no earlier tile to multiply: scores of the second tile, softmax of the first
             u32x4_t p_a[NB][2], p_b[NB][2];
@@ -675,7 +683,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
                 fast_step(std::false_type{}, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
             }
             // the tiles around the wave's own positions, same pipeline with the causal compare
-            for (; jt + 1 < t_hi && jt + AHEAD + 1 < j_inside; jt += 2) {
+            for (; (LEAVE ? jt < w_hi && jt + 1 < t_hi : jt + 1 < t_hi) && jt + AHEAD + 1 < j_inside; jt += 2) {
                 fast_step(std::true_type{}, jt, s_nxt, s_cur, p_a, p_b, ka, va);
                 fast_step(std::true_type{}, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
             }
@@ -684,7 +692,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             for (int nb = 0; nb < NB; ++nb) s_cur[nb] = s_nxt[nb];
         }
         // general loop; s_cur = scores of tile jt
-        for (; jt < t_hi; ++jt) {
+        for (; jt < w_hi; ++jt) {
             // scores of the next tile first (past the last tile the slot holds stale data and the
             // result is discarded)
             qk(jt + 1, s_nxt);
@@ -695,6 +703,13 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             if (jt + AHEAD < t_hi) stage_tile(jt + AHEAD);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) s_cur[nb] = s_nxt[nb];
+        }
+        // the other waves' tiles: this wave's share of the staging, and the barriers.  Tile jt+2 has to have landed at the
+        // barrier of step jt; the last tile sent before it is jt+AHEAD-1, if there is one.
+        for (; LEAVE && jt < t_hi; ++jt) {
+            if (jt + AHEAD - 1 < t_hi) KVS_ATTN_BARRIER(KVS_ATTN_IN_FLIGHT);
+            else KVS_ATTN_BARRIER(0);
+            if (jt + AHEAD < t_hi) stage_tile(jt + AHEAD);
         }
         // nothing may still be on its way into LDS when the rings are reused or the workgroup ends
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -867,7 +882,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     }
 }
 
-template <bool WANT_LSE, bool SPLIT>
+template <bool WANT_LSE, bool SPLIT, bool LEAVE>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
                       float scale_log2, void *out, float *lse_out, int n_splits, const int4 *split_plan,
@@ -875,12 +890,12 @@ kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const A
 {
     static DeviceOnce attr_once;
     const kvs_status ast = once_per_device(attr_once, [lds_bytes] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT, LEAVE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_partial_attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
     });
     if (ast != KVS_OK) return ast;
-    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
+    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT, LEAVE>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
                        shape->n_kv_heads, tiles, (const uint16_t *)q_sel, sel_pos, (const uint16_t *)k_cache,
                        (const uint16_t *)v_cache, scale_log2, (uint16_t *)out, lse_out, n_splits, split_plan, piece_list,
                        part_o, part_ml, share_units);
@@ -957,10 +972,19 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     if (n_splits <= 1 || !workspace) {
         const int share_units = share_units_for(shape, tiles);
         const dim3 grid((unsigned)((share_units > 0 ? share_units : tiles) * shape->n_kv_heads));
-        return lse_out ? launch_one<true, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
-                                                 scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
-                       : launch_one<false, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
-                                                  scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units);
+        // key tiles that the tokens of a row tile are spread over, on average
+        int64_t ctx = 0, sel = 0;
+        for (int i = 0; i < bd.n_req; ++i) {
+            const int64_t n = bd.cu_sel[i + 1] - bd.cu_sel[i];
+            if (n > 0) { ctx += bd.ctx_len[i]; sel += n; }
+        }
+        const int grp = shape->n_q_heads / shape->n_kv_heads;
+        const bool leave = ctx * ROWS >= sel * grp * (int64_t)(BN * kAttnLeaveSpread);
+#define KVS_ATTN_WHOLE(LSE, LV) launch_one<LSE, false, LV>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
+                                                          scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
+        if (lse_out) return leave ? KVS_ATTN_WHOLE(true, true) : KVS_ATTN_WHOLE(true, false);
+        return leave ? KVS_ATTN_WHOLE(false, true) : KVS_ATTN_WHOLE(false, false);
+#undef KVS_ATTN_WHOLE
     }
     if (tiles > PLAN_MAX_TILES) return fail(KVS_EINVAL, "kvs_partial_attention: split launch with %lld row tiles", (long long)tiles);
     // workspace: the pieces' accumulators, their (reference, sums) records, the plan, the piece list.  Pieces are
@@ -981,9 +1005,9 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));
-    stt = lse_out ? launch_one<true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+    stt = lse_out ? launch_one<true, true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                            scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0)
-                  : launch_one<false, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+                  : launch_one<false, true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                             scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0);
     if (stt != KVS_OK) return stt;
     return launch_attention_merge(n_rows_total, n_splits, (const float *)workspace, ml_base,
