@@ -266,7 +266,7 @@ KVS_API kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, int64
  * k         [dev] [n_tokens, n_kv_heads, head_dim] (the fresh keys)
  * alpha     [dev] fp32[n_kv_heads, n_tokens], written
  * workspace [dev] kvs_workspace_size("attn_colsum", shape, 1, n_tokens, 0) bytes, 256-byte
- *           aligned, required; contents on return are unspecified.  It holds every row's log-sum-exp and the
+ *           aligned, required; contents on return are unspecified.  It holds every row's softmax statistics and the
  *           results of the pieces into which short sweeps, and sweeps of uneven blocks, are cut
  */
 KVS_API kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, const void *q, const void *k,

@@ -498,8 +498,9 @@ size_t piece_bytes(const kvs_shape *shape, int64_t n_tokens)
 size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
     if (n_tokens <= 0 || shape->n_kv_heads <= 0 || shape->n_q_heads < shape->n_kv_heads || !on_matrix_cores(shape, n_tokens))
-        return (size_t)n_tokens * shape->n_q_heads * sizeof(float) + 256;
-    return row_bytes(shape, n_tokens) + piece_bytes(shape, n_tokens) + 256;
+        return (size_t)n_tokens * shape->n_q_heads * 2 * sizeof(float) + 256;
+    const size_t rows = row_bytes(shape, n_tokens), pieces = piece_bytes(shape, n_tokens);
+    return rows + (pieces > rows ? pieces : rows) + 256;           // (a scale that is not positive takes the fp32 kernels: two floats a row)
 }
 
 } // namespace kvs
@@ -522,7 +523,7 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     // the matrix-core kernel: bf16, head_dim 128, a positive scale (it folds the scale into an exp2
     // argument after taking maxima).  Everything else takes the fp32 kernels.
     const bool mfma = shape->dtype == KVS_BF16 && shape->head_dim == D && scale > 0.f;
-    if (!mfma) return launch_colsum_f32(shape, n_tokens, q, k, scale, (float *)workspace, alpha, (hipStream_t)stream);
+    if (!mfma) return launch_colsum_f32(shape, n_tokens, q, k, scale, workspace, alpha, (hipStream_t)stream);
     if (!on_matrix_cores(shape, n_tokens))
         return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d heads exceed the 4 GiB the kernel addresses", (long long)n_tokens, shape->n_q_heads);
     float *lse2 = (float *)workspace;

@@ -58,7 +58,7 @@ size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t match_workspace_bytes(int64_t n_target, int64_t n_candidate);
 kvs_status launch_colsum_f32(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale,
-                              float *lse, float *alpha, hipStream_t st);
+                              void *row_stats, float *alpha, hipStream_t st);
 
 // ---- deviation scoring and top-k in one call (kvs_deviation_topk) ----------------------------------
 // The scoring kernel leaves, beside the scores, every token's order-preserving key and a histogram
