@@ -384,16 +384,16 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
     red[(3 * 8 + wave) * kTileCols + lane] = dv_l1;
     __syncthreads();
     if (wave == 0 && col_ok) {
-        float sa = 0.f, sk = 0.f, skv = 0.f, l1 = 0.f;
+        double sa = 0., sk = 0., skv = 0., l1 = 0.;          // (a few additions: rounded once, where the share is stored)
         for (int w = 0; w < 8; ++w) {
             if (w % CG == 0) sa += red[(0 * 8 + w) * kTileCols + lane];
             sk += red[(1 * 8 + w) * kTileCols + lane];
             skv += red[(2 * 8 + w) * kTileCols + lane];
             if (w < CG) l1 += red[(3 * 8 + w) * kTileCols + lane];
         }
-        part[o] = sa * l1;                // value direction: (sum of A over rows and heads of the group) * |dV|_1
-        part[o + stride] = sk;
-        part[o + 2 * stride] = skv;
+        part[o] = (float)(sa * l1);       // value direction: (sum of A over rows and heads of the group) * |dV|_1
+        part[o + stride] = (float)sk;
+        part[o + 2 * stride] = (float)skv;
     }
 }
 
@@ -405,18 +405,18 @@ __global__ void impact_reduce_kernel(int n, int n_kv_heads, int pieces, const fl
     if (i >= n) return;
     const bool cand = reused ? reused[i] != 0 : true;
     const int64_t stride = (int64_t)n_kv_heads * n;
-    float s[3] = {0.f, 0.f, 0.f};
+    double s[3] = {0., 0., 0.};
     if (cand)
         for (int g = 0; g < n_kv_heads; ++g)
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
-                float x = 0.f;
+                double x = 0.;
                 for (int p = 0; p < pieces; ++p) x += part[(3 * p + t) * stride + (int64_t)g * n + i];
                 s[t] += x;
             }
-    if (impact_v) impact_v[i] = cand ? s[0] : -INFINITY;
-    if (impact_k) impact_k[i] = cand ? s[1] : -INFINITY;
-    if (impact_kv) impact_kv[i] = cand ? s[2] : -INFINITY;
+    if (impact_v) impact_v[i] = cand ? (float)s[0] : -INFINITY;
+    if (impact_k) impact_k[i] = cand ? (float)s[1] : -INFINITY;
+    if (impact_kv) impact_kv[i] = cand ? (float)s[2] : -INFINITY;
 }
 
 template <int D>
