@@ -19,8 +19,8 @@
 //   * the dot products are the one part that is a contraction: q . K_fresh and q . K_cache (exact bf16 operands; their
 //     difference is q . dK) run on the matrix cores, 32 rows x 64 tokens at a time, and leave (a, t) per pair in LDS;
 //   * the rows are cut into pieces so that the triangle of (row, token) pairs spreads evenly over the chip.
-// Measured, Qwen-shaped 8192 tokens (80 % reused): 18.7 -> 10.5 to 11.2 ms by box, over 90 % of what four instructions per (pair, channel) take at
-// the unpacked fp32 rate; 1500 Llama-shaped tokens 1.23 -> 0.72 ms.  One 256-register workgroup per compute unit instead of two
+// Measured, Qwen-shaped 8192 tokens (80 % reused): 18.7 -> 9.8 to 10.4 ms by box, over 94 % of what four instructions per (pair, channel) take at
+// the unpacked fp32 rate; 1963 Llama-shaped tokens 2.04 -> 0.81 ms, 526 Qwen-shaped 549 -> 78 us.  One 256-register workgroup per compute unit instead of two
 // of 128: 14.6 ms (nothing runs beside the matrix-core step and the barriers).
 //
 // fp32 (impact_kernel): one workgroup owns 32 tokens (columns) of one KV head: their K, dK, V, dV rows sit in LDS,
@@ -397,26 +397,33 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
     }
 }
 
-// adds the pieces and the KV heads; what is not rated is -inf (and was never written)
-__global__ void impact_reduce_kernel(int n, int n_kv_heads, int pieces, const float *__restrict__ part, const uint8_t *__restrict__ reused,
-                                     float *__restrict__ impact_v, float *__restrict__ impact_k, float *__restrict__ impact_kv)
+// adds the pieces and the KV heads; what is not rated is -inf (and was never written).  A workgroup takes one of the three
+// results for 64 tokens, its eight waves the pieces in turn: a thread that adds all 3 x 32 x 4 shares of a token by itself is a
+// chain of loads (8192 tokens: 124 us, 5 like this; the whole call at 526 tokens: 167 -> 78).
+constexpr int kReduceWaves = 8;
+__global__ __launch_bounds__(kReduceWaves * 64) void impact_reduce_kernel(
+    int n, int n_kv_heads, int pieces, const float *__restrict__ part, const uint8_t *__restrict__ reused,
+    float *__restrict__ impact_v, float *__restrict__ impact_k, float *__restrict__ impact_kv)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const bool cand = reused ? reused[i] != 0 : true;
-    const int64_t stride = (int64_t)n_kv_heads * n;
-    double s[3] = {0., 0., 0.};
+    __shared__ double share[kReduceWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t = blockIdx.y;
+    float *out = t == 0 ? impact_v : t == 1 ? impact_k : impact_kv;
+    if (!out) return;                                        // uniform
+    const int i = blockIdx.x * 64 + lane;
+    const bool cand = i < n && (reused ? reused[i] != 0 : true);
+    double s = 0.;
     if (cand)
-        for (int g = 0; g < n_kv_heads; ++g)
-#pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                double x = 0.;
-                for (int p = 0; p < pieces; ++p) x += part[(3 * p + t) * stride + (int64_t)g * n + i];
-                s[t] += x;
-            }
-    if (impact_v) impact_v[i] = cand ? (float)s[0] : -INFINITY;
-    if (impact_k) impact_k[i] = cand ? (float)s[1] : -INFINITY;
-    if (impact_kv) impact_kv[i] = cand ? (float)s[2] : -INFINITY;
+        for (int p = wave; p < pieces; p += kReduceWaves) {
+            const float *from = part + (int64_t)(3 * p + t) * n_kv_heads * n + i;
+#pragma unroll 4
+            for (int g = 0; g < n_kv_heads; ++g) s += from[(int64_t)g * n];
+        }
+    share[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && i < n) {
+        for (int w = 1; w < kReduceWaves; ++w) s += share[w][lane];
+        out[i] = cand ? (float)s : -INFINITY;
+    }
 }
 
 template <int D>
@@ -519,7 +526,7 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
 #undef KVS_IMP
     }
     if ((st = check_launch("kvs_first_order_impact")) != KVS_OK) return st;
-    hipLaunchKernelGGL(impact_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, n, hk, pieces, part, reused,
+    hipLaunchKernelGGL(impact_reduce_kernel, dim3((unsigned)((n + 63) / 64), 3), dim3(kReduceWaves * 64), 0, hs, n, hk, pieces, part, reused,
                        impact_v, impact_k, impact_kv);
     return check_launch("kvs_first_order_impact(reduce)");
 }
