@@ -53,18 +53,27 @@ kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *par
 
 // What the host fixes for a split launch of the 256-row kernel: piece slots per row tile (1: no
 // cutting, nothing else is read), the longest context in key tiles, and the small pieces at the
-// bottom of the context (n_small of small_chunk key tiles).  Launches too small to fill the chip cut the key
-// range; the size of the large pieces is chosen on the device, from the positions, so that the pieces just
-// fill whole rounds of the compute units.  Pieces are started from the top of the context down, range by range.
-// (Launches that fill the chip keep whole key ranges also where K and V outgrow the last-level cache: fixed pieces
-// walked in step, and their merge, cost more than the caches they keep warm.  131072 Yi-shaped tokens, 12452 selected:
-// 12.6 ms in pieces of 8192 keys, 11.4 ms whole; 2 to 12 % over contexts of 50000 to 131072 and 2300 to 15200 selected.)
+// bottom of the context (n_small of small_chunk key tiles).  Two cases cut the key range:
+//   * launches too small to fill the chip: the size of the large pieces is chosen on the device,
+//     from the positions, so that the pieces just fill whole rounds of the compute units;
+//   * launches whose K and V no longer fit the last-level cache (kAttnRangeMajorBytes; the 131k
+//     context): chunk > 0 fixes the piece size so that one key range of one KV head fits an L2.
+//     Workgroups of a KV head that start at different times otherwise sweep K/V at different
+//     places and every one of them streams from HBM on its own (measured: 16 % of the matrix
+//     peak at 131k against 45 % at 32k, where K and V stay cached), and a workgroup that meets a
+//     logit 111 above its first tile's repeats a piece instead of its whole sweep.  (131072
+//     Yi-shaped tokens, 12452 selected, pieces against whole ranges: 12.8 and 11.7 ms where no row
+//     repeats, 13.1 and 27.2 with 200 keys of 40 times the size in mid-context.)
+// Pieces are started from the top of the context down, range by range.
 struct AttnSplitPlan {
     int n_splits;
     int ctx_tiles;
     int small_chunk;
     int n_small;
+    int chunk;          // 0: chosen on the device
 };
+constexpr int64_t kAttnRangeMajorBytes = (int64_t)192 << 20;   // K + V of a launch above which key ranges are walked in step
+constexpr int kAttnRangeChunk = 256;       // key tiles per piece then: 8192 keys = 4 MiB of K and V per KV head
 constexpr int kAttnPlanMaxTiles = 2048;    // row tiles a planned launch may have
 // the device-side plan and the list of piece ids (16 bits each, kAttnSplitMax per row tile), after
 // the pieces in the workspace

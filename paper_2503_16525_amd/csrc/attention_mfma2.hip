@@ -793,7 +793,7 @@ constexpr int PLAN_MAX_ROUNDS = 4;
 __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const AttnTiles td, int grp, int n_kv_heads, int total_tiles, const int32_t *__restrict__ sel_pos,
     int s_max, int ctx_tiles, int small_chunk, int n_small, float round_fill, float piece_overhead,
-    int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
+    int forced_chunk, int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
 {
     __shared__ int len[PLAN_MAX_TILES];       // key tiles of each row tile
     __shared__ int first_fit[PLAN_MAX_ROUNDS];
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const int c_max = max(c_min, ctx_tiles - bottom);
     const int step = (c_max - c_min + PLAN_NT - 1) / PLAN_NT;
     const int c = c_min + tid * step;
-    const bool tries = c <= c_max && (step > 0 || tid == 0);
+    const bool tries = forced_chunk <= 0 && c <= c_max && (step > 0 || tid == 0);   // a fixed chunk needs no search
     int pieces = 0x7fffffff;
     if (tries) {
         const float rc = 1.0f / (float)c;
@@ -841,6 +841,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
             const float time = (float)(r + 1) * ((float)first_fit[r] + piece_overhead);
             if (time < best_t) { best_t = time; best_c = first_fit[r]; }
         }
+        if (forced_chunk > 0) best_c = min(max(forced_chunk, c_min), c_max);
         chosen = make_int4(n_small + (ctx_tiles - bottom + best_c - 1) / best_c, best_c, small_chunk, n_small);
         *plan = chosen;
     }
@@ -931,16 +932,23 @@ int share_units_for(const kvs_shape *shape, int64_t tiles)
 
 AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, size_t workspace_bytes)
 {
-    const AttnSplitPlan whole = {1, 0, 0, 0};
+    const AttnSplitPlan whole = {1, 0, 0, 0, 0};
     const int grp = shape->n_q_heads / shape->n_kv_heads;
-    int64_t tiles = 0, max_ctx = 0;
+    int64_t tiles = 0, max_ctx = 0, kv_bytes = 0;
     for (int i = 0; i < bd.n_req; ++i) {
         tiles += ((bd.cu_sel[i + 1] - bd.cu_sel[i]) * grp + ROWS - 1) / ROWS;
         max_ctx = bd.ctx_len[i] > max_ctx ? bd.ctx_len[i] : max_ctx;
+        // (what has to stay cached is one request's K and V: requests do not share keys)
+        if (bd.cu_sel[i + 1] > bd.cu_sel[i]) {
+            const int64_t b = bd.ctx_len[i] * (int64_t)shape->n_kv_heads * ROW_B * 2;
+            kv_bytes = b > kv_bytes ? b : kv_bytes;
+        }
     }
     const int64_t wgs = tiles * shape->n_kv_heads;
     if (wgs <= 0 || tiles > kAttnPlanMaxTiles) return whole;
-    if (wgs >= kAttnSplitBelowWgs) return whole;
+    const bool small_launch = wgs < kAttnSplitBelowWgs;
+    const bool range_major = !small_launch && kv_bytes > kAttnRangeMajorBytes;
+    if (!small_launch && !range_major) return whole;
     const int64_t ctx_tiles = (max_ctx + BN - 1) / BN;
     const int64_t n_rows_total = (bd.cu_sel[bd.n_req] - bd.cu_sel[0]) * shape->n_q_heads;
     int64_t s_max = kAttnSplitMax;
@@ -950,11 +958,19 @@ AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, 
     const int64_t by_ws = (int64_t)((workspace_bytes - kAttnPlanBytes) / (kAttnPartBytesPerSlot * (size_t)(n_rows_total > 0 ? n_rows_total : 1)));
     if (s_max > by_ws) s_max = by_ws;
     if (s_max < 2) return whole;
+    if (range_major) {
+        // as small a piece as the slots allow, down to the one whose K and V fit an L2
+        int64_t chunk = (ctx_tiles + s_max - 1) / s_max;
+        if (chunk < kAttnRangeChunk) chunk = kAttnRangeChunk;
+        const int64_t n = (ctx_tiles + chunk - 1) / chunk;
+        if (n < 2) return whole;
+        return AttnSplitPlan{(int)n, (int)ctx_tiles, 0, 0, (int)chunk};
+    }
     // Small pieces at the bottom of the context (every row tile has them, and they start last)
     // fill the gaps the large ones leave; they pay off once the large pieces can be several times
     // their size.
     const bool taper = s_max >= 6 && ctx_tiles >= 8 * kAttnSmallChunk;
-    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, kAttnSmallChunk, taper ? kAttnSmallPieces : 0};
+    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, kAttnSmallChunk, taper ? kAttnSmallPieces : 0, 0};
 }
 
 kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, const void *q_sel,
@@ -998,10 +1014,10 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     int4 *split_plan = (int4 *)(ml_base + n_rows_total * n_splits);
     uint16_t *piece_list = (uint16_t *)(split_plan + 1);
     float round_fill = kAttnRoundFill, piece_overhead = kAttnPieceOverhead;
-    int small_chunk = plan.small_chunk, n_small = plan.n_small;
+    int forced_chunk = plan.chunk, small_chunk = plan.small_chunk, n_small = plan.n_small;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(PLAN_NT), 0, st, td, shape->n_q_heads / shape->n_kv_heads,
                        shape->n_kv_heads, (int)tiles, sel_pos, n_splits, plan.ctx_tiles, small_chunk, n_small, round_fill,
-                       piece_overhead, split_plan, piece_list);
+                       piece_overhead, forced_chunk, split_plan, piece_list);
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));

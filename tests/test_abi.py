@@ -151,6 +151,16 @@ def test_attn_colsum_argument_errors(lib):
     assert b"vector path" in lib.kvs_last_error()
 
 
+def test_attention_workspace_beyond_the_last_level_cache(lib):
+    """One request whose K and V pass 192 MiB is given room for 16 pieces of every output row's key range (528 bytes each);
+    a request below it, or a batch of the same rows, only for launches that leave the chip idle."""
+    sh = _shape(hq=32, hk=4)                                  # 2 KiB of K and V a token: 98304 tokens are 192 MiB
+    pieces = 528 * 16 * 32 * 12452
+    size = lambda batch, n: B.kvs_workspace_size("partial_attention", sh, batch, n, 12452)
+    assert size(1, 131072) >= pieces and size(1, 98305) >= pieces
+    assert size(1, 98304) < pieces and size(2, 131072) < pieces
+
+
 def test_deviation_topk_argument_errors(lib):
     sh = _shape()
 
