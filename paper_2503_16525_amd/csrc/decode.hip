@@ -405,13 +405,15 @@ __global__ __launch_bounds__(kThreads) void decode_stats_kernel(
         for (int u = 0; u < UNROLL; ++u) z += p[u].y * expf(p[u].x - m);
     }
     const float mw = wave_max(m);
-    const float zw = wave_sum(m == -INFINITY ? 0.f : z * expf(m - mw));
+    // only threads and waves without a record are left out: a NaN sum (a NaN in K or q) has to reach the result
+    const float zw = wave_sum(t0 + tid < t1 ? z * expf(m - mw) : 0.f);
     if (lane == 0) red[wave] = make_float2(mw, zw);
     __syncthreads();
     if (tid == 0) {
         float x = red[0].x, y = 0.f;
         for (int w = 1; w < kThreads / 64; ++w) x = fmaxf(x, red[w].x);
-        for (int w = 0; w < kThreads / 64; ++w) y += red[w].y > 0.f ? red[w].y * expf(red[w].x - x) : 0.f;
+        for (int w = 0; w < kThreads / 64; ++w)
+            if (t0 + w * 64 < t1) y += red[w].y * expf(red[w].x - x);
         stats[(int64_t)(bd.req0 + b) * n_q_heads + h] = make_float2(x, y);
     }
 }

@@ -61,3 +61,44 @@ def test_runs(name, hq, hk, lens):
             assert np.all(got[o + n:o + n + slack] == 7.0), "rows outside the contexts were written"
             check_topk_band(got_idx[at:at + kr], r, kr)
             at += kr
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 64)])
+@pytest.mark.parametrize("lens,bad", [([300, 40, 900], 0), ([40, 9000, 300], 1), ([16500], 0)], ids=["short", "many-records", "key-counts"])
+def test_a_nan_in_k_reaches_every_score_of_its_request(dtype, d, lens, bad):
+    """The softmax over a context that holds a NaN is NaN: no score of that request may look valid, and the other
+    requests' may not change."""
+    print(f"decode NaN: {dtype}, head_dim {d}, contexts {lens}", flush=True)
+    hq, hk = 8, 2
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = torch.Generator().manual_seed(d + len(lens))
+    off = np.cumsum([0] + lens[:-1]).tolist()
+    rows = sum(lens)
+    q = (torch.randn((len(lens), hq, d), generator=rng) / d ** 0.5).to(t).cuda()
+    k, v = (torch.randn((rows, hk, d), generator=rng).to(t).cuda() for _ in range(2))
+    dev_v = (torch.rand((hk, rows), generator=rng) + 0.1).cuda()
+    reused = (torch.rand(rows, generator=rng) < 0.9).to(torch.uint8).cuda()
+    k_req = [n // 20 for n in lens]
+    sh = B.make_shape(hq, hk, d, B.BF16 if dtype == "bf16" else B.F32)
+    ws = torch.empty(B.kvs_workspace_size("decode_check", sh, len(lens), rows), dtype=torch.uint8, device="cuda")
+    idx = torch.empty(sum(k_req), dtype=torch.int32, device="cuda")
+
+    def check(keys):
+        score, out = torch.zeros(rows, device="cuda"), torch.zeros_like(q)
+        B.kvs_decode_check(sh, rows, off, lens, q, keys, v, dev_v, reused, 1.0, k_req, idx, score, out, ws)
+        return score.cpu().numpy(), out.float().cpu().numpy()
+    clean, clean_out = check(k)
+    assert np.all(np.isfinite(clean_out))
+    for at in (0, lens[bad] // 2, lens[bad] - 1):
+        hurt = k.clone()
+        hurt[off[bad] + at, 1, 5] = float("nan")
+        got, out = check(hurt)
+        for r, (o, n) in enumerate(zip(off, lens)):
+            g, c = got[o:o + n], clean[o:o + n]
+            if r != bad:
+                np.testing.assert_array_equal(g, c)
+                np.testing.assert_array_equal(out[r], clean_out[r])
+            else:
+                assert np.all(np.isnan(g[np.isfinite(c)])) and np.all(np.isneginf(g[np.isneginf(c)]))
+                np.testing.assert_array_equal(out[r, :hq // 2], clean_out[r, :hq // 2])      # the other KV head's
+                assert np.all(np.isnan(out[r, hq // 2:]))
