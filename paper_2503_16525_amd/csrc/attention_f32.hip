@@ -59,9 +59,10 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const int pos = min(max(sel_pos[s_glob], 0), ctx_len - 1);       // memory safety; the caller guarantees the range
     float qv[D / 4];
     load_quarter<DTYPE, D>(q_sel, (s_glob * n_q_heads + head) * (int64_t)D, kk, qv);
-    int pmax = pos;
+    int pmin = pos, pmax = pos;
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) pmax = max(pmax, __shfl_xor(pmax, o));
+    for (int o = 1; o < 16; o <<= 1) { pmin = min(pmin, __shfl_xor(pmin, o)); pmax = max(pmax, __shfl_xor(pmax, o)); }
+    pmin = __builtin_amdgcn_readfirstlane(pmin);
     pmax = __builtin_amdgcn_readfirstlane(pmax);
 
     f32x4 acc[DB];
@@ -71,10 +72,27 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     for (int k0 = wave * kF32Keys; k0 <= pmax; k0 += kF32Waves * kF32Keys) {
         f32x4 s[4];
         float mx = -INFINITY;
+        // tile t's Inf and NaN values, which its products leave out: to the rows that see their keys (rare and slow)
+        auto add_odd_values = [&](int t) {
+#pragma unroll 1
+            for (int kq = 0; kq < 4; ++kq) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int key = k0 + 16 * t + 4 * kq + r;
+                    const float p = __shfl(s[t][r], 16 * kq + m16);
+                    const int64_t vrow = ((ctx_off + min(key, pmax)) * n_kv_heads + g) * (int64_t)D + 4 * kk;
+#pragma unroll
+                    for (int c = 0; c < D / 4; ++c) {              // acc[c / 4][c % 4] is channel 16 (c / 4) + 4 kk + c % 4
+                        const float v = load_elem<DTYPE>(v_cache, vrow + 16 * (c >> 2) + (c & 3));
+                        if (key <= pos && !(fabsf(v) < INFINITY)) acc[c >> 2][c & 3] += p * v;
+                    }
+                }
+            }
+        };
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             float kv[D / 4];
-            const int key = min(k0 + 16 * t + m16, ctx_len - 1);
+            const int key = min(k0 + 16 * t + m16, pmax);          // (nothing past the last row's position is read)
             load_quarter<DTYPE, D>(k_cache, ((ctx_off + key) * n_kv_heads + g) * (int64_t)D, kk, kv);
             s[t] = dots<D>(kv, qv);
 #pragma unroll
@@ -96,14 +114,23 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) { s[t][r] = expf(s[t][r] - m_new); l_run += s[t][r]; }
             // instruction r contracts over keys 4 kk + r of the tile, kk = 0 .. 3
+            const bool all_seen = k0 + 16 * t + 15 <= pmin;        // uniform: every row sees every key of the tile
+            bool odd = false;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int key = min(k0 + 16 * t + 4 * kk + r, ctx_len - 1);
+                const int key = min(k0 + 16 * t + 4 * kk + r, pmax);
                 const int64_t vrow = ((ctx_off + key) * n_kv_heads + g) * (int64_t)D + m16;
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
-                    acc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(load_elem<DTYPE>(v_cache, vrow + 16 * db), s[t][r], acc[db], 0, 0, 0);
+                for (int db = 0; db < DB; ++db) {
+                    float v = load_elem<DTYPE>(v_cache, vrow + 16 * db);
+                    // a weight of 0 does not hide an Inf or NaN from a row that does not see the key
+                    const bool keep = all_seen || fabsf(v) < INFINITY;
+                    odd |= !keep;
+                    v = keep ? v : 0.f;
+                    acc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, s[t][r], acc[db], 0, 0, 0);
+                }
             }
+            if (!all_seen && __any(odd)) add_odd_values(t);
         }
     }
     l_run += __shfl_xor(l_run, 16);

@@ -43,6 +43,46 @@ def test_attention(dtype, hq, hk, d, n, k):
 
 
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+@pytest.mark.parametrize("at", [0, 15, 16, 50, 130, 400])
+def test_attention_hides_what_a_row_does_not_see(dtype, hq, hk, d, at):
+    """An Inf or NaN in K or V reaches the rows whose position is at or past it, and no other: bit for bit."""
+    print(f"fp32 attention, Inf and NaN at token {at}: {dtype} {hq}x{hk} heads, head_dim {d}", flush=True)
+    n, grp = 600, hq // hk
+    pos = np.array([0, 3, 14, 15, 16, 17, 49, 50, 51, 129, 130, 131, 200, 399, 400, 401], np.int32)
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    q = lay["q"][torch.from_numpy(pos.astype(np.int64))].contiguous().cuda()
+    scale = -0.7 if d == 128 and dtype == "bf16" else 1.0
+
+    def run(k, v):
+        out, lse = torch.full((len(pos), hq, d), 7.0, dtype=w.torch_dtype, device="cuda"), torch.full((len(pos), hq), 7.0, device="cuda")
+        B.kvs_partial_attention(B.shape_of(w), [0], [n], [0, len(pos)], q, torch.from_numpy(pos).cuda(), k, v, scale, out, lse)
+        return out.float().cpu().numpy(), lse.cpu().numpy()
+    k, v = lay["k_cache"].cuda(), lay["v_cache"].cuda()
+    clean, lse_clean = run(k, v)
+    assert np.all(np.isfinite(clean))
+    # rows of the cache that nothing selected reaches yet
+    k1, v1 = k.clone(), v.clone()
+    k1[402:], v1[402:] = float("nan"), float("inf")
+    out, lse = run(k1, v1)
+    np.testing.assert_array_equal(out, clean)
+    np.testing.assert_array_equal(lse, lse_clean)
+    # single values of one token: the last KV head's channels 5 and 7
+    v1 = v.clone()
+    v1[at, hk - 1, 5], v1[at, hk - 1, 7] = float("inf"), float("nan")
+    want, sees = clean.copy(), pos >= at
+    want[sees, (hk - 1) * grp:, 5], want[sees, (hk - 1) * grp:, 7] = np.inf, np.nan
+    np.testing.assert_array_equal(run(k, v1)[0], want)
+    k1 = k.clone()
+    k1[at, 0, 3] = float("nan")
+    want, lse_want = clean.copy(), lse_clean.copy()
+    want[sees, :grp], lse_want[sees, :grp] = np.nan, np.nan
+    out, lse = run(k1, v)
+    np.testing.assert_array_equal(out, want)
+    np.testing.assert_array_equal(lse, lse_want)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 127, 129, 300])
 def test_column_mass(dtype, hq, hk, d, n):
     print(f"fp32 column mass: {dtype} {hq}x{hk} heads, head_dim {d}, {n} tokens", flush=True)
