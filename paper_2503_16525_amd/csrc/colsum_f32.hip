@@ -55,11 +55,12 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
         }
         const f32x4 s = dots<D>(x, fx);
         float y[4];
+        bool sees[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int row = t * kCfRows + 4 * kk + r;
-            const bool sees = SWEEP == 1 ? row <= fpos : row < n_stream && row / grp >= fpos;
-            y[r] = sees ? s[r] * scale : -INFINITY;
+            sees[r] = SWEEP == 1 ? row <= fpos : row < n_stream && row / grp >= fpos;
+            y[r] = sees[r] ? s[r] * scale : -INFINITY;
         }
         if (SWEEP == 1) {
             const float mn = fmaxf(m, fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
@@ -69,7 +70,10 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
             for (int r = 0; r < 4; ++r) z += expf(y[r] - m);
         } else {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) z = fmaf(expf(y[r] - st4[r].x), st4[r].y, z);
+            for (int r = 0; r < 4; ++r) {
+                const float zr = fmaf(expf(y[r] - st4[r].x), st4[r].y, z);
+                z = sees[r] ? zr : z;              // a row that does not see the key adds nothing, whatever its statistics are
+            }
         }
     }
     m_s[wave * 4 + kk][m16] = m;

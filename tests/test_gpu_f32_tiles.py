@@ -97,6 +97,34 @@ def test_column_mass(dtype, hq, hk, d, n):
     np.testing.assert_allclose(alpha[:hk].cpu().numpy(), ref, rtol=1e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+@pytest.mark.parametrize("row", [0, 7, 15, 16, 100, 255])
+def test_column_mass_hides_rows_that_do_not_see_a_key(dtype, hq, hk, d, row):
+    """A query row with a NaN or an Inf spoils the mass of the keys that it sees, and of no other: bit for bit."""
+    print(f"fp32 column mass, odd query row {row}: {dtype} {hq}x{hk} heads, head_dim {d}", flush=True)
+    n = 256
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    scale = -0.7 if d == 128 and dtype == "bf16" else 1.0
+    k = lay["k_fresh"].cuda()
+
+    def run(q):
+        alpha = torch.full((hk, n), 7.0, device="cuda")
+        ws = torch.empty(B.kvs_workspace_size("attn_colsum", B.shape_of(w), 1, n), dtype=torch.uint8, device="cuda")
+        B.kvs_attn_colsum(B.shape_of(w), n, q, k, scale, alpha, ws)
+        return alpha.cpu().numpy()
+    q = lay["q"].cuda()
+    clean = run(q)
+    assert np.all(np.isfinite(clean))
+    for odd in ("nan", "inf"):
+        q1 = q.clone()
+        q1[row, 0, 2] = float(odd)
+        got = run(q1)
+        assert np.all(np.isnan(got[0, :row + 1]))          # inf - inf or inf * 0 in its softmax
+        np.testing.assert_array_equal(got[0, row + 1:], clean[0, row + 1:])
+        np.testing.assert_array_equal(got[1:], clean[1:])
+
+
 @pytest.mark.parametrize("dtype,hk,d", [("f32", 4, 64), ("f32", 64, 128), ("bf16", 5, 128), ("bf16", 33, 64)])
 @pytest.mark.parametrize("n", [1, 7, 8, 9, 40, 8191, 8192])
 @pytest.mark.parametrize("mode", [B.SCORE_V, B.SCORE_KV])
