@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     f32x4 acc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -1.0e30f, l_run = 0.f;               // l_run: this lane's keys only
+    float m_run = kLowest, l_run = 0.f;               // l_run: this lane's keys only
     for (int k0 = wave * kF32Keys; k0 <= pmax; k0 += kF32Waves * kF32Keys) {
         f32x4 s[4];
         float mx = -INFINITY;

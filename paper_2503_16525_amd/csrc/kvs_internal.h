@@ -22,6 +22,9 @@ inline size_t elem_bytes(int32_t dtype) { return dtype == KVS_F32 ? 4 : 2; }
 // Validates a kvs_shape for the kernels that exist; on failure the status says why.
 kvs_status check_shape(const kvs_shape *s);
 
+// Where a running maximum starts when exp(first - maximum) must be 0 and not exp(-inf + inf): below every finite score.
+constexpr float kLowest = -3.402823466e38f;
+
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // One-time set-up per device (kernel attributes, device queries).  The HIP runtime keeps function

@@ -98,6 +98,25 @@ def test_column_mass(dtype, hq, hk, d, n):
 
 
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+def test_attention_of_scores_far_below_zero(dtype, hq, hk, d):
+    """All scores below -1e34: a row gives the largest, which only one token has, a weight of 1."""
+    print(f"fp32 attention, scores below -1e34: {dtype} {hq}x{hk} heads, head_dim {d}", flush=True)
+    n, t = 70, torch.float32 if dtype == "f32" else torch.bfloat16
+    pos = np.array([0, 1, 40, 69], np.int32)
+    q = torch.full((4, hq, d), 2.0 ** 55, dtype=t)
+    k = torch.full((n, hk, d), -2.0 ** 55, dtype=t)
+    v = torch.randn((n, hk, d), generator=torch.Generator().manual_seed(d)).to(t)
+    k[1] *= 0.5                                   # token 1 is the only one with weight for the rows that see it
+    sh = B.make_shape(hq, hk, d, B.F32 if dtype == "f32" else B.BF16)
+    out, lse = torch.full((4, hq, d), 7.0, dtype=t, device="cuda"), torch.full((4, hq), 7.0, device="cuda")
+    scale = 1.0 if d == 64 or dtype == "f32" else -1.0
+    B.kvs_partial_attention(sh, [0], [n], [0, 4], q.cuda(), torch.from_numpy(pos).cuda(), k.cuda() * (1.0 if scale > 0 else -1.0), v.cuda(), scale, out, lse)
+    want = v[[0, 1, 1, 1]].repeat_interleave(hq // hk, 1)
+    assert torch.equal(out.cpu(), want)
+    np.testing.assert_allclose(lse[:, 0].cpu().numpy(), -(2.0 ** 110) * d * np.array([1.0, 0.5, 0.5, 0.5]), rtol=1e-6)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
 @pytest.mark.parametrize("row", [0, 7, 15, 16, 100, 255])
 def test_column_mass_hides_rows_that_do_not_see_a_key(dtype, hq, hk, d, row):
     """A query row with a NaN or an Inf spoils the mass of the keys that it sees, and of no other: bit for bit."""
