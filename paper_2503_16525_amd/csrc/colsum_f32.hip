@@ -43,7 +43,7 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
     const int last = min(fb + kCfRows, n_fixed) - 1;
     const int t_begin = SWEEP == 1 ? 0 : fb * grp / kCfRows, t_end = SWEEP == 1 ? last / grp / kCfRows + 1 : (n_qrows + kCfRows - 1) / kCfRows;
     const int n_stream = SWEEP == 1 ? n : n_qrows;
-    float m = -1.0e30f, z = 0.f;
+    float m = kLowest, z = 0.f;
     for (int t = t_begin + wave; t < t_end; t += kCfWaves) {
         float x[D / 4];
         const int sr = min(t * kCfRows + m16, n_stream - 1);
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
     z_s[wave * 4 + kk][m16] = z;
     __syncthreads();
     if (tid < kCfRows && fb + tid < n_fixed) {
-        float mt = -1.0e30f, zt = 0.f;
+        float mt = kLowest, zt = 0.f;
         if (SWEEP == 1) {
 #pragma unroll
             for (int w = 0; w < kCfWaves * 4; ++w) mt = fmaxf(mt, m_s[w][tid]);

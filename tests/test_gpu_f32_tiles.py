@@ -117,6 +117,23 @@ def test_attention_of_scores_far_below_zero(dtype, hq, hk, d):
 
 
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+def test_column_mass_of_scores_far_below_zero(dtype, hq, hk, d):
+    """All scores below -1e34: every row that sees token 1 gives it all of its weight."""
+    print(f"fp32 column mass, scores below -1e34: {dtype} {hq}x{hk} heads, head_dim {d}", flush=True)
+    n, t = 70, torch.float32 if dtype == "f32" else torch.bfloat16
+    scale = 1.0 if d == 64 or dtype == "f32" else -1.0
+    q, k = torch.full((n, hq, d), 2.0 ** 55, dtype=t), torch.full((n, hk, d), -scale * 2.0 ** 55, dtype=t)
+    k[1] *= 0.5
+    sh = B.make_shape(hq, hk, d, B.F32 if dtype == "f32" else B.BF16)
+    alpha = torch.full((hk, n), 7.0, device="cuda")
+    ws = torch.empty(B.kvs_workspace_size("attn_colsum", sh, 1, n), dtype=torch.uint8, device="cuda")
+    B.kvs_attn_colsum(sh, n, q.cuda(), k.cuda(), scale, alpha, ws)
+    want = np.zeros((hk, n), np.float32)
+    want[:, 0], want[:, 1] = hq // hk, (hq // hk) * (n - 1)
+    np.testing.assert_array_equal(alpha.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
 @pytest.mark.parametrize("row", [0, 7, 15, 16, 100, 255])
 def test_column_mass_hides_rows_that_do_not_see_a_key(dtype, hq, hk, d, row):
     """A query row with a NaN or an Inf spoils the mass of the keys that it sees, and of no other: bit for bit."""
