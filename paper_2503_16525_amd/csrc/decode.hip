@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_logits_mfma_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int r = 0; r < RU; ++r) { run_m[h][r] = -1.0e30f; run_z[h][r] = 0.f; }
+            for (int r = 0; r < RU; ++r) { run_m[h][r] = kLowest; run_z[h][r] = 0.f; }
     };
     auto emit = [&](int b) {               // the run's share of request b
         for (int h = 0; h < 2; ++h) {

@@ -102,3 +102,25 @@ def test_a_nan_in_k_reaches_every_score_of_its_request(dtype, d, lens, bad):
                 assert np.all(np.isnan(g[np.isfinite(c)])) and np.all(np.isneginf(g[np.isneginf(c)]))
                 np.testing.assert_array_equal(out[r, :hq // 2], clean_out[r, :hq // 2])      # the other KV head's
                 assert np.all(np.isnan(out[r, hq // 2:]))
+
+
+@pytest.mark.parametrize("hq,hk", [(8, 2), (16, 1), (32, 1)])
+def test_scores_of_logits_far_below_zero(hq, hk):
+    """All logits below -1e34: the request's second token is the only one with weight."""
+    print(f"decode, logits below -1e34: {hq}x{hk} heads", flush=True)
+    lens, d = [300, 1, 40], 128
+    off, rows = [0, 300, 301], 341
+    q = torch.full((3, hq, d), 2.0 ** 55, dtype=torch.bfloat16, device="cuda")
+    k = torch.full((rows, hk, d), -2.0 ** 55, dtype=torch.bfloat16, device="cuda")
+    want = np.zeros(rows, np.float32)
+    for o, n in zip(off, lens):
+        top = o + min(1, n - 1)
+        k[top] *= 0.5
+        want[top] = 0.25 * hq
+    dev_v = torch.full((hk, rows), 0.25, device="cuda")
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("decode_check", sh, 3, rows), dtype=torch.uint8, device="cuda")
+    idx, score = torch.full((3,), -7, dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda")
+    B.kvs_decode_check(sh, rows, off, lens, q, k, None, dev_v, None, 1.0, [1, 1, 1], idx, score, None, ws)
+    np.testing.assert_array_equal(score.cpu().numpy(), want)
+    assert idx.tolist() == [1, 0, 1]
