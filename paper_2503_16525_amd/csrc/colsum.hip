@@ -484,23 +484,31 @@ bool on_matrix_cores(const kvs_shape *shape, int64_t n_tokens)
 
 size_t row_bytes(const kvs_shape *shape, int64_t n_tokens) { return ((size_t)n_tokens * shape->n_q_heads * sizeof(float) + 255) / 256 * 256; }
 
-// the pieces of one sweep at a time
+// The most that the pieces of one sweep take at a time, in a form that grows with n_tokens (the pieces themselves do not:
+// their number jumps where plan_cut rounds, and a large sweep 1 is not cut), so that a workspace for the longest prompt serves
+// the shorter ones.  With e = n_tokens * n_q_heads results per piece of sweep 1 (sweep 2: no more pieces times results), t
+// its tiles and w = plan_cut's work, w >= t * e / 512: a chunk c gives at most t / c + 1 pieces, and c is at least 4, at
+// least 4/5 of w / 3072, and at least 4/5 of w / 512 unless it is 16.
 size_t piece_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
-    const Cut c1 = plan_cut<1>(shape, n_tokens), c2 = plan_cut<2>(shape, n_tokens);
-    const size_t b1 = c1.chunk > 0 ? (size_t)c1.pieces * n_tokens * shape->n_q_heads * sizeof(float) : 0;
-    const size_t b2 = c2.chunk > 0 ? (size_t)c2.pieces * n_tokens * shape->n_kv_heads * sizeof(float) : 0;
-    return b1 > b2 ? b1 : b2;
+    static_assert(kCutMinChunk == 4 && kCutRoundChunk == 16 && kCutSmallUnits == 512 && kCutUnits == 3072, "the bounds below");
+    const int64_t e = n_tokens * shape->n_q_heads, steps = (n_tokens < (1 << 20) ? n_tokens : 1 << 20) * e;   // (from there on by_units is the least)
+    const int64_t by_least = steps / 128 + 2 * e;
+    const int64_t sixteen = steps / 512, by_small = (sixteen > 640 * 512 ? sixteen : 640 * 512) + 2 * e;
+    const int64_t by_units = 3840 * 512 + 2 * e;
+    const int64_t most = by_least < by_small ? by_least : by_small;
+    return sizeof(float) * (size_t)(most < by_units ? most : by_units);
 }
 
 } // namespace
 
 size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
-    if (n_tokens <= 0 || shape->n_kv_heads <= 0 || shape->n_q_heads < shape->n_kv_heads || !on_matrix_cores(shape, n_tokens))
-        return (size_t)n_tokens * shape->n_q_heads * 2 * sizeof(float) + 256;
-    const size_t rows = row_bytes(shape, n_tokens), pieces = piece_bytes(shape, n_tokens);
-    return rows + (pieces > rows ? pieces : rows) + 256;           // (a scale that is not positive takes the fp32 kernels: two floats a row)
+    if (n_tokens <= 0) return 256;
+    const size_t rows = row_bytes(shape, n_tokens);
+    // (fp32 kernels: two floats a row; they also take a scale that is not positive)
+    const size_t pieces = shape->dtype == KVS_BF16 && shape->head_dim == D ? piece_bytes(shape, n_tokens) : 0;
+    return rows + (pieces > rows ? pieces : rows) + 256;
 }
 
 } // namespace kvs

@@ -151,6 +151,18 @@ def test_attn_colsum_argument_errors(lib):
     assert b"vector path" in lib.kvs_last_error()
 
 
+SIZED = [(28, 4, 128), (32, 8, 128), (8, 1, 128), (3, 3, 64), (64, 64, 128)]
+
+
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+@pytest.mark.parametrize("hq,hk,d", SIZED)
+@pytest.mark.parametrize("call", ["attn_colsum"])
+def test_a_workspace_for_a_long_prompt_serves_the_shorter_ones(call, hq, hk, d, dtype):
+    sh = _shape(hq=hq, hk=hk, d=d, dt=dtype)
+    sizes = [B.kvs_workspace_size(call, sh, 1, n) for n in [*range(0, 9000), *range(9000, 70000, 61), 1 << 20]]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_attention_workspace_beyond_the_last_level_cache(lib):
     """One request whose K and V pass 192 MiB is given room for 16 pieces of every output row's key range (528 bytes each);
     a request below it, or a batch of the same rows, only for launches that leave the chip idle."""
