@@ -450,8 +450,16 @@ size_t impact_part_bytes(const kvs_shape *shape, int64_t n, int pieces) { return
 size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
     if (n_tokens <= 0 || shape->n_kv_heads <= 0 || shape->dtype != KVS_BF16) return impact_part_bytes(shape, n_tokens, 1) + 256;
-    // the pieces' sums, then the list of reused tokens and its length
-    return impact_part_bytes(shape, n_tokens, impact_pieces(shape, n_tokens)) + sizeof(int32_t) * ((size_t)n_tokens + 1) + 256;
+    // The pieces' sums, then the list of reused tokens and its length.  The pieces are counted by a bound that grows with the
+    // tokens, so that a workspace for the longest prompt serves the shorter ones: no more than their limits allow, and no
+    // more than kImpUnits strips' worth of sums, unless it is one.
+    int64_t most = n_tokens / kImpMinRows;
+    if (most > kImpMaxPieces) most = kImpMaxPieces;
+    if (most < 1) most = 1;
+    size_t part = impact_part_bytes(shape, n_tokens, (int)most);
+    const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * kTileCols;
+    if (part > strips) part = strips > one ? strips : one;
+    return part + sizeof(int32_t) * ((size_t)n_tokens + 1) + 256;
 }
 
 } // namespace kvs
