@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
     auto token = [&](int c) { const int l = min(l0 + c, n_cols - 1); return list ? list[l] : l; };
     const int i = token(lane);
     const bool col_ok = l0 + lane < n_cols;
-    const int i0 = __builtin_amdgcn_readfirstlane(i);
+    const int i0 = __builtin_amdgcn_readfirstlane(i), i_last = __builtin_amdgcn_readlane(i, min(kTileCols, n_cols - l0) - 1);
     // rows j of this piece that the first (lowest) token can be seen by
     const int j0 = max(i0, piece * rows_per_piece), j1 = min(n, (piece + 1) * rows_per_piece);
     const int64_t stride = (int64_t)n_kv_heads * n, o = 3 * stride * piece + (int64_t)g * n + i;
@@ -348,6 +348,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
         }
         __syncthreads();
         // |key term|_1 = a |t| sum_c |v_c - h_c| and |both|_1 = a sum_c |dv_c + t (v_c - h_c)|
+        // (a pair that is none, a row before its token or past the end, adds nothing even where its norm is Inf or NaN)
+        const bool all_pairs = j0 + (int)(p0 / (uint32_t)grp) >= i_last && p0 + kTileRows <= n_pairs;     // uniform
         float blk_a = 0.f, blk_k = 0.f, blk_kv = 0.f;
 #pragma unroll 1
         for (int rr = 0; rr < RPW; ++rr) {
@@ -367,8 +369,10 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
                 }
             }
             blk_a += w.x;
-            blk_k = fmaf(w.x * fabsf(w.y), nk[0] + nk[1], blk_k);
-            blk_kv = fmaf(w.x, nkv[0] + nkv[1], blk_kv);
+            const float to_k = fmaf(w.x * fabsf(w.y), nk[0] + nk[1], blk_k), to_kv = fmaf(w.x, nkv[0] + nkv[1], blk_kv);
+            const bool pair = all_pairs || rowJ[r] >= i;
+            blk_k = pair ? to_k : blk_k;
+            blk_kv = pair ? to_kv : blk_kv;
         }
         add_carried(sum_a, carry_a, blk_a);
         add_carried(sum_k, carry_k, blk_k);

@@ -67,3 +67,45 @@ def test_list_and_piece_edges(n, reused_tokens, hq, hk, d):
     with pytest.raises(B.KvsError):
         B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(),
                                  mask.cuda(), 1.0, *out, torch.empty(full - 1, dtype=torch.uint8, device="cuda"))
+
+
+def small_layer(n, hq, hk, d):
+    """The inputs of a call on the device, exact H and log-sum-exp among them."""
+    lay = synth.make_layer(synth.scaled(synth.LLAMA, n, n_q_heads=hq, n_kv_heads=hk, head_dim=d, coverage=1.0))
+    q, k, v = lay["q"].double(), lay["k_fresh"].double().repeat_interleave(hq // hk, 1), lay["v_fresh"].double().repeat_interleave(hq // hk, 1)
+    s = torch.einsum("jhd,ihd->hji", q, k).masked_fill(~torch.tril(torch.ones((n, n), dtype=torch.bool)), -np.inf)
+    g = {x: lay[x].cuda() for x in ("q", "k_fresh", "v_fresh", "k_cache", "v_cache")}
+    g["h"] = torch.einsum("hji,ihd->jhd", torch.softmax(s, -1), v).to(torch.bfloat16).contiguous().cuda()
+    g["lse"] = torch.logsumexp(s, -1).T.contiguous().float().cuda()
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("first_order_impact", sh, 1, n), dtype=torch.uint8, device="cuda")
+
+    def impact(reused=None, **changed):
+        a = dict(g, **changed)
+        out = [torch.full((n,), 7.0, device="cuda") for _ in range(3)]
+        B.kvs_first_order_impact(sh, n, a["q"], a["k_fresh"], a["v_fresh"], a["k_cache"], a["v_cache"], a["h"], a["lse"], reused, 1.0, *out, ws)
+        return [o.cpu().numpy() for o in out]
+    return g, impact
+
+
+@pytest.mark.parametrize("hq,hk,d", [(4, 2, 128), (3, 3, 64)])
+@pytest.mark.parametrize("share", [1.0, 0.3, 0.02])
+def test_a_row_adds_nothing_to_tokens_that_it_does_not_see(hq, hk, d, share):
+    """An Inf or NaN in a row's H, Q or log-sum-exp reaches the tokens up to the row, and no other: bit for bit."""
+    print(f"impact, odd rows: {hq}x{hk} heads, head_dim {d}, {share} reused", flush=True)
+    n = 300
+    g, impact = small_layer(n, hq, hk, d)
+    mask = (torch.rand(n, generator=torch.Generator().manual_seed(3)) < share).to(torch.uint8)
+    mask[[0, 150, 299]] = 1
+    cand = mask.numpy() != 0
+    mask = mask.cuda()
+    clean = impact(mask)
+    for row in (0, 31, 150, 298):
+        for what, at, reaches in (("h", (row, 1, 5), (False, True, True)), ("q", (row, 1, 5), (True, True, True)), ("lse", (row, 1), (True, True, True))):
+            x = g[what].clone()
+            x[at] = float("nan")
+            for name, a, b, r in zip(("value", "key", "both"), impact(mask, **{what: x}), clean, reaches):
+                want = b.copy()
+                if r:
+                    want[:row + 1][cand[:row + 1]] = np.nan
+                np.testing.assert_array_equal(a, want, err_msg=f"{what} of row {row}: {name}")
