@@ -211,11 +211,11 @@ constexpr int kTileCh = 32;                                  // channels a wave 
 template <int D>
 constexpr int tile_lds_bytes() { return 2 * kTileCols * D * 2 + kTileRows * D * (2 + 4) + kTileRows * kTileCols * 8 + 2 * kTileRows * 4; }
 
-// sum += x, the rounding error carried along (a lane adds tens of thousands of rows)
+// sum += x, the rounding error carried along (a lane adds tens of thousands of rows); an infinite sum stays infinite
 __device__ __forceinline__ void add_carried(float &sum, float &carry, float x)
 {
     const float y = x - carry, t = sum + y;
-    carry = (t - sum) - y;
+    carry = fabsf(t) < INFINITY ? (t - sum) - y : 0.f;
     sum = t;
 }
 
@@ -395,7 +395,8 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
             skv += red[(2 * 8 + w) * kTileCols + lane];
             if (w < CG) l1 += red[(3 * 8 + w) * kTileCols + lane];
         }
-        part[o] = (float)(sa * l1);       // value direction: (sum of A over rows and heads of the group) * |dV|_1
+        // value direction: (sum of A over rows and heads of the group) * |dV|_1, nothing from a piece that does not see the token
+        part[o] = sa == 0. ? 0.f : (float)(sa * l1);
         part[o + stride] = (float)sk;
         part[o + 2 * stride] = (float)skv;
     }

@@ -109,3 +109,18 @@ def test_a_row_adds_nothing_to_tokens_that_it_does_not_see(hq, hk, d, share):
                 if r:
                     want[:row + 1][cand[:row + 1]] = np.nan
                 np.testing.assert_array_equal(a, want, err_msg=f"{what} of row {row}: {name}")
+
+
+@pytest.mark.parametrize("hq,hk,d", [(4, 2, 128), (3, 3, 64)])
+def test_an_infinite_movement_stays_infinite(hq, hk, d):
+    print(f"impact, infinite movement: {hq}x{hk} heads, head_dim {d}", flush=True)
+    n = 200
+    g, impact = small_layer(n, hq, hk, d)
+    clean = impact()
+    for i in (0, 1, 64, 100, 199):
+        v = g["v_cache"].clone()
+        v[i, 0, 3] = float("inf")
+        for name, a, b, moved in zip(("value", "key", "both"), impact(v_cache=v), clean, (np.inf, clean[1][i], np.inf)):
+            want = b.copy()
+            want[i] = moved
+            np.testing.assert_array_equal(a, want, err_msg=name)
