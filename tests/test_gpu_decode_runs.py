@@ -27,6 +27,7 @@ CASES = [
     ("group-32", 32, 1, EDGES),
     ("70-requests", 8, 4, [7 + 13 * i for i in range(70)]),
     ("more-items-than-workgroups", 16, 4, [9000, 33, 12000]),
+    ("more-items-than-workgroups-of-a-head-block", 24, 12, [9000, 33, 700]),
     ("one-context-with-key-counts", 32, 8, [16500]),
     ("one-context-17-heads-with-key-counts", 34, 17, [12400]),
 ]
