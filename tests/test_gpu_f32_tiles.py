@@ -18,7 +18,7 @@ def layer(dtype, hq, hk, d, n):
 
 
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
-@pytest.mark.parametrize("n,k", [(1, 1), (16, 16), (17, 5), (64, 16), (65, 17), (512, 33), (513, 8), (1030, 48)])
+@pytest.mark.parametrize("n,k", [(1, 1), (16, 16), (17, 5), (64, 16), (65, 17), (128, 128), (129, 40), (512, 33), (513, 8), (1030, 48)])
 def test_attention(dtype, hq, hk, d, n, k):
     print(f"fp32 attention: {dtype} {hq}x{hk} heads, head_dim {d}, {k} of {n} tokens", flush=True)
     w = layer(dtype, hq, hk, d, n)
