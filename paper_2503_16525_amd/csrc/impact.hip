@@ -438,15 +438,27 @@ constexpr size_t impact_lds_bytes()
 }
 
 // Pieces of the rows (bf16): 64 tokens of a KV head see up to n rows, and the launch is a triangle of such strips;
-// some 16384 workgroups, half of them with rows, even it out over 512 resident ones.  At least 16 rows each.
-constexpr int kImpUnits = 16384, kImpMaxPieces = 32, kImpMinRows = 16;
-int impact_pieces(const kvs_shape *shape, int64_t n)
+// some 16384 workgroups, half of them with rows, even it out over 512 resident ones.  A piece is a whole number of blocks of
+// kTileRows (row, head in group) pairs, as nearly as its rows allow: a block costs the same however few of its pairs there are
+// (256 tokens of 64 heads in groups of one, pieces of 16 rows: 134 us, 77 like this; 16 Qwen-shaped tokens, one piece of 3.5 blocks: 41, 14).
+constexpr int kImpUnits = 16384, kImpMaxPieces = 32;
+struct ImpactPieces {
+    int n, rows;            // pieces, rows of each
+};
+int64_t impact_most_pieces(const kvs_shape *shape, int64_t n)
 {
-    const int64_t strips = (n + kTileCols - 1) / kTileCols * shape->n_kv_heads;
+    const int64_t blocks = (n * (shape->n_q_heads / shape->n_kv_heads) + kTileRows - 1) / kTileRows;
+    return blocks < 1 ? 1 : blocks < kImpMaxPieces ? blocks : kImpMaxPieces;
+}
+ImpactPieces impact_pieces(const kvs_shape *shape, int64_t n)
+{
+    const int64_t strips = (n + kTileCols - 1) / kTileCols * shape->n_kv_heads, grp = shape->n_q_heads / shape->n_kv_heads;
     int64_t p = kImpUnits / strips;
-    if (p > kImpMaxPieces) p = kImpMaxPieces;
-    if (p > n / kImpMinRows) p = n / kImpMinRows;
-    return p < 1 ? 1 : (int)p;
+    if (p > impact_most_pieces(shape, n)) p = impact_most_pieces(shape, n);
+    if (p < 1) p = 1;
+    int64_t rows = (n + p - 1) / p;
+    rows = (rows * grp + kTileRows - 1) / kTileRows * kTileRows / grp;
+    return {(int)((n + rows - 1) / rows), (int)rows};
 }
 size_t impact_part_bytes(const kvs_shape *shape, int64_t n, int pieces) { return sizeof(float) * 3 * (size_t)pieces * (size_t)shape->n_kv_heads * (size_t)n; }
 
@@ -458,9 +470,7 @@ size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
     // The pieces' sums, then the list of reused tokens and its length.  The pieces are counted by a bound that grows with the
     // tokens, so that a workspace for the longest prompt serves the shorter ones: no more than their limits allow, and no
     // more than kImpUnits strips' worth of sums, unless it is one.
-    int64_t most = n_tokens / kImpMinRows;
-    if (most > kImpMaxPieces) most = kImpMaxPieces;
-    if (most < 1) most = 1;
+    const int64_t most = impact_most_pieces(shape, n_tokens);
     size_t part = impact_part_bytes(shape, n_tokens, (int)most);
     const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * kTileCols;
     if (part > strips) part = strips > one ? strips : one;
@@ -494,15 +504,16 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
     float *part = (float *)workspace;
     int pieces = 1;
     if (shape->dtype == KVS_BF16) {
-        pieces = impact_pieces(shape, n_tokens);
-        int32_t *list = reused ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
+        const ImpactPieces cut = impact_pieces(shape, n_tokens);
+        pieces = cut.n;
+        // (one strip of tokens is no shorter for a list: all are computed, and those not reused dropped at the end)
+        int32_t *list = reused && n > kTileCols ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
         int32_t *count = list ? list + n : nullptr;
         if (list) {
             hipLaunchKernelGGL(impact_list_kernel, dim3(1), dim3(kListThreads), 0, hs, n, reused, list, count);
             if ((st = check_launch("kvs_first_order_impact(list)")) != KVS_OK) return st;
         }
         const dim3 grid((unsigned)((n + kTileCols - 1) / kTileCols), (unsigned)hk, (unsigned)pieces);
-        const int rows = (n + pieces - 1) / pieces;
 #define KVS_IMP(DD)                                                                                                       \
     do {                                                                                                                  \
         static DeviceOnce once;                                                                                           \
@@ -512,7 +523,7 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
             return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_first_order_impact: hipFuncSetAttribute: %s", hipGetErrorString(e)); \
         });                                                                                                               \
         if (st != KVS_OK) return st;                                                                                      \
-        hipLaunchKernelGGL(impact_tiles_kernel<DD>, grid, dim3(kTileThreads), tile_lds_bytes<DD>(), hs, n, shape->n_q_heads, hk, rows, \
+        hipLaunchKernelGGL(impact_tiles_kernel<DD>, grid, dim3(kTileThreads), tile_lds_bytes<DD>(), hs, n, shape->n_q_heads, hk, cut.rows, \
                            (const uint16_t *)q, (const uint16_t *)k_fresh, (const uint16_t *)v_fresh, (const uint16_t *)k_cache, \
                            (const uint16_t *)v_cache, (const uint16_t *)h_fresh, lse, scale, list, count, part);          \
     } while (0)

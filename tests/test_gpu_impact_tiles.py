@@ -34,7 +34,7 @@ def reference(lay, h, lse, grp):
 
 @pytest.mark.parametrize("n,reused_tokens,hq,hk,d", [
     (1, 1, 4, 2, 128), (33, 0, 4, 2, 128), (64, 1, 7, 1, 128), (65, 63, 4, 4, 128), (129, 64, 4, 1, 128), (200, 65, 14, 2, 128),
-    (257, 257, 4, 2, 128), (300, 190, 3, 3, 64), (160, 128, 8, 2, 64)])
+    (257, 257, 4, 2, 128), (300, 190, 3, 3, 64), (160, 128, 8, 2, 64), (9, 5, 40, 1, 128), (64, 30, 3, 3, 64), (65, 40, 7, 1, 64), (481, 200, 2, 2, 64)])
 def test_list_and_piece_edges(n, reused_tokens, hq, hk, d):
     print(f"impact tiles: {n} tokens, {reused_tokens} reused, {hq}x{hk} heads, head_dim {d}", flush=True)
     w = synth.scaled(synth.LLAMA, n, n_q_heads=hq, n_kv_heads=hk, head_dim=d, coverage=1.0)
