@@ -563,14 +563,19 @@ kvs_status launch_few(const ProjectArgs &a, hipStream_t hs)
 
 // Which tile.  A launch takes rounds of one workgroup per compute unit, 32 units per XCD; a round costs what its tile
 // costs, measured in nanoseconds per 64 of the contraction and per tile (rounds that fill the chip).  The cheapest sum
-// is taken.  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16 tokens 72 -> 12 us, 96 tokens 73 -> 16,
-// 256 tokens 75 -> 22, 384 tokens 75 -> 27, 640 tokens 75 -> 37, 656 tokens 75 -> 41, 1280 tokens 82 -> 75; from some
-// 1500 tokens on (85 against 91) the large tiles fill the chip and win.
+// is taken, against the 256 x 256 tiles with what rounds after the first cost besides: a workgroup that follows another
+// starts cold, and with more rounds than one every XCD streams the selected rows through its L2 again (without the two, 4 to 44 %
+// slower than the large tiles at 2300 to 6600 tokens of 8 to 24 heads and at hidden 512).  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16
+// tokens 72 -> 12 us, 96 tokens 73 -> 16, 256 tokens 75 -> 22, 384 tokens 75 -> 27, 640 tokens 75 -> 37, 656 tokens 75 -> 41,
+// 1280 tokens 82 -> 75; the large tiles from 1281 on (78.4 us; the small ones 4 % less up to 1400, 22 % more at 1700), and the
+// small ones once more where a third of another large round is empty: 2561 to 2688 tokens 177 -> 153 us.
 struct FewTile {
     int fbw, tb, step_ns, fixed_ns;
     kvs_status (*launch)(const ProjectArgs &, hipStream_t);
 };
 constexpr int kLargeStepNs = 1100, kLargeFixedNs = 8000;        // the 256 x 256 kernel
+constexpr int kLargeRoundNs = 5000, kFewRoundNs = 4000;         // a round after the first, besides
+constexpr int kFewBytesPerNs = 10000;                           // selected rows, if there is one
 constexpr int kUnitsPerXcd = 32;
 const FewTile few_tiles[] = {
     {1, 1, 150, 2500, launch_few<1, 1>}, {1, 2, 210, 2600, launch_few<1, 2>}, {2, 1, 235, 2600, launch_few<2, 1>},
@@ -584,14 +589,15 @@ const FewTile *choose_few(const ProjectArgs &a)
     const int64_t heads = a.shape->n_q_heads + 2 * a.shape->n_kv_heads, steps = a.hidden / FBK;
     auto rounds = [](int64_t tiles) { return ((tiles + PXCDS - 1) / PXCDS + kUnitsPerXcd - 1) / kUnitsPerXcd; };
     const int64_t large = (a.n_sel + PBM - 1) / PBM * (heads * PD / PBN);
-    int64_t best = rounds(large) * (steps * kLargeStepNs + kLargeFixedNs);
+    int64_t best = INT64_MAX, n = 0;
     const FewTile *pick = nullptr;
     for (const FewTile &f : few_tiles) {
         const int64_t tiles = (a.n_sel + 32 * f.tb - 1) / (32 * f.tb) * heads * (2 / f.fbw);
         const int64_t cost = rounds(tiles) * (steps * f.step_ns + f.fixed_ns);
-        if (cost < best && tiles <= 0x7fffffff) { best = cost; pick = &f; }
+        if (cost < best && tiles <= 0x7fffffff) { best = cost; n = rounds(tiles); pick = &f; }
     }
-    return pick;
+    if (n > 1) best += (n - 1) * kFewRoundNs + a.n_sel * a.hidden * 2 / kFewBytesPerNs;
+    return best < rounds(large) * (steps * kLargeStepNs + kLargeFixedNs + kLargeRoundNs) - kLargeRoundNs ? pick : nullptr;
 }
 } // namespace
 } // namespace kvs

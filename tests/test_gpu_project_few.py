@@ -45,6 +45,22 @@ def test_other_heads_and_a_longer_contraction(n_sel):
     check(6, 1, 640, n_sel, True, True)
 
 
+@pytest.mark.parametrize("hq,hk,hidden,n_sel", [(32, 8, 1024, 1000), (32, 8, 4096, 2561), (32, 8, 4096, 2688), (32, 8, 4096, 2689), (6, 2, 1024, 4096), (6, 2, 1024, 5000)])
+def test_around_the_rounds(hq, hk, hidden, n_sel):
+    """Small tiles of several rounds, and the large tiles on the other side of the rule."""
+    print(f"project: {hq}x{hk} heads, hidden {hidden}, {n_sel} tokens", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n_sel)
+    x = torch.randn((n_sel + 9, hidden), generator=gen, device="cuda").to(torch.bfloat16)
+    w = (torch.randn(((hq + 2 * hk) * 128, hidden), generator=gen, device="cuda") / hidden ** 0.5).to(torch.bfloat16)
+    rows = torch.randperm(n_sel + 9, generator=gen, device="cuda")[:n_sel].to(torch.int32)
+    outs = [torch.full((n_sel + 64, h, 128), 7.0, dtype=torch.bfloat16, device="cuda") for h in (hq, hk, hk)]
+    B.kvs_project_qkv(B.make_shape(hq, hk, 128, B.BF16), x, rows, None, n_sel, w, None, *outs)
+    ref = (x[rows.long()].double() @ w.double().T).view(n_sel, -1, 128)
+    for o, r in zip(outs, torch.split(ref, [hq, hk, hk], 1)):
+        assert bool((o[n_sel:] == 7.0).all())
+        assert bool(((o[:n_sel].double() - r).abs() <= 2.0 ** -8 * r.abs() + 2e-4).all())
+
+
 def test_large_tile_with_a_ragged_end():
     print("project: 2817 tokens, hidden 1024", flush=True)
     check(32, 8, 1024, 2817, True, True)
