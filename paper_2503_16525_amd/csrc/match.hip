@@ -323,6 +323,42 @@ __global__ __launch_bounds__(kMatchThreads) void match_mark_kernel(int64_t n_t, 
     }
 }
 
+// stretches s0, s0 + step, .. (PER of them): each entry of the table is read once for all
+template <int PER>
+__device__ __forceinline__ void order_stretches(int64_t s0, int64_t step, int64_t n_seg, int32_t *__restrict__ target_matches,
+                                                int32_t *__restrict__ cand_matches, const MatchWs &ws, int lane)
+{
+    uint64_t key[PER];
+    int32_t start[PER], len[PER];
+    uint32_t offset[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t s = s0 + u * step;
+        const bool has = u == 0 || s < n_seg;                // uniform
+        key[u] = has ? ws.seg_key[s] : 0;                    // (key 0 and start 0: nothing comes before)
+        start[u] = has ? ws.seg_start[s] : 0;
+        len[u] = has ? ws.seg_end[s] - start[u] : 0;
+        offset[u] = 0;
+    }
+    for (int64_t o = lane; o < n_seg; o += kWave) {
+        const uint64_t ko = ws.seg_key[o];
+        const int32_t so = ws.seg_start[o];
+        const uint32_t n = (uint32_t)(ws.seg_end[o] - so);
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (ko < key[u] || (ko == key[u] && so < start[u])) offset[u] += n;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        for (int x = 32; x > 0; x >>= 1) offset[u] += __shfl_xor(offset[u], x);
+        const int32_t j = (int32_t)(key[u] >> 32), i = (int32_t)(uint32_t)key[u];
+        for (int32_t t = lane; t < len[u]; t += kWave) {
+            if (target_matches) target_matches[offset[u] + t] = start[u] + t;
+            if (cand_matches) cand_matches[offset[u] + t] = j + (start[u] + t - i);
+        }
+    }
+}
+
 __global__ __launch_bounds__(kMatchThreads) void match_order_kernel(int32_t *__restrict__ target_matches, int32_t *__restrict__ cand_matches,
                                                                     int64_t *__restrict__ n_matches, MatchWs ws)
 {
@@ -331,21 +367,12 @@ __global__ __launch_bounds__(kMatchThreads) void match_order_kernel(int32_t *__r
     if (wave == 0 && lane == 0 && n_matches) *n_matches = (int64_t)ws.counters[0];
     if (!target_matches && !cand_matches) return;
     const int64_t n_seg = ws.counters[1];
-    for (int64_t s = wave; s < n_seg; s += n_waves) {
-        const uint64_t key = ws.seg_key[s];
-        const int32_t start = ws.seg_start[s], len = ws.seg_end[s] - start;
-        uint32_t offset = 0;
-        for (int64_t o = lane; o < n_seg; o += kWave) {
-            const uint64_t ko = ws.seg_key[o];
-            const int32_t so = ws.seg_start[o];
-            if (ko < key || (ko == key && so < start)) offset += (uint32_t)(ws.seg_end[o] - so);
-        }
-        for (int x = 32; x > 0; x >>= 1) offset += __shfl_xor(offset, x);
-        const int32_t j = (int32_t)(key >> 32), i = (int32_t)(uint32_t)key;
-        for (int32_t t = lane; t < len; t += kWave) {
-            if (target_matches) target_matches[offset + t] = start + t;
-            if (cand_matches) cand_matches[offset + t] = j + (start + t - i);
-        }
+    // one stretch a wave as long as there are waves (131072 tokens in 6900 stretches, the whole call: 226 us with one
+    // at a time, 117 with four)
+    if (n_seg <= n_waves) {
+        if (wave < n_seg) order_stretches<1>(wave, n_waves, n_seg, target_matches, cand_matches, ws, lane);
+    } else {
+        for (int64_t s0 = wave; s0 < n_seg; s0 += 4 * n_waves) order_stretches<4>(s0, n_waves, n_seg, target_matches, cand_matches, ws, lane);
     }
 }
 

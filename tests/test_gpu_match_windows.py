@@ -33,3 +33,13 @@ def test_stretches_across_blocks(n):
     c[::7] = 10 ** 7                    # every seventh token differs: stretches of six
     check(t, c, 3)
     check(t, np.concatenate([t[n // 2:], t[:n // 2]]), 16)
+
+
+@pytest.mark.parametrize("stretches", [1023, 1024, 1025, 4097])
+def test_more_stretches_than_waves(stretches):
+    """Stretches of three tokens, each from a place of its own in the candidate: none joins the next."""
+    print(f"match: {stretches} stretches", flush=True)
+    rng = np.random.default_rng(stretches)
+    c = np.arange(3 * stretches)
+    t = c.reshape(stretches, 3)[rng.permutation(stretches)].reshape(-1)
+    assert check(t, c, 3) == 3 * stretches
