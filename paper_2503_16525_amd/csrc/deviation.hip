@@ -132,12 +132,17 @@ __global__ __launch_bounds__(kDevThreads) void deviation_kernel(
     if ((score || HIST) && tid < tile_tok) {
         const int64_t i = tok0 + tid;
         float s = 0.f;
-        for (int g = 0; g < n_kv_heads; ++g) {
-            float dev = dv_s[g * TOK + tid];
-            if (HAS_K && mode_kv) dev = dk_s[g * TOK + tid] + dev;
-            const float a = early_alpha ? al_s[g * TOK + tid] : alpha ? alpha[(int64_t)g * n_tokens + i] : 1.0f;
-            s += a * dev;
-        }
+        auto add_heads = [&](auto weight) {
+            for (int g = 0; g < n_kv_heads; ++g) {
+                float dev = dv_s[g * TOK + tid];
+                if (HAS_K && mode_kv) dev = dk_s[g * TOK + tid] + dev;
+                s += weight(g) * dev;
+            }
+        };
+        // (a loop of its own for each: one that chooses inside does not have its loads in flight together)
+        if (early_alpha) add_heads([&](int g) { return al_s[g * TOK + tid]; });
+        else if (alpha) add_heads([&](int g) { return alpha[(int64_t)g * n_tokens + i]; });
+        else add_heads([](int) { return 1.0f; });
         const float sc = is_reused != 0 ? s : -INFINITY;
         if (score) score[i] = sc;
         if (HIST) {
