@@ -563,7 +563,7 @@ kvs_status launch_few(const ProjectArgs &a, hipStream_t hs)
 
 // Which tile.  A launch takes rounds of one workgroup per compute unit, 32 units per XCD; a round costs what its tile
 // costs, measured in nanoseconds per 64 of the contraction and per tile (rounds that fill the chip).  The cheapest sum
-// is taken, against the 256 x 256 tiles with what rounds after the first cost besides: a workgroup that follows another
+// is taken, against the 256 x 256 tiles with what rounds after the first cost it besides: a workgroup that follows another
 // starts cold, and with more rounds than one every XCD streams the selected rows through its L2 again (without the two, 4 to 44 %
 // slower than the large tiles at 2300 to 6600 tokens of 8 to 24 heads and at hidden 512).  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16
 // tokens 72 -> 12 us, 96 tokens 73 -> 16, 256 tokens 75 -> 22, 384 tokens 75 -> 27, 640 tokens 75 -> 37, 656 tokens 75 -> 41,
@@ -574,8 +574,7 @@ struct FewTile {
     kvs_status (*launch)(const ProjectArgs &, hipStream_t);
 };
 constexpr int kLargeStepNs = 1100, kLargeFixedNs = 8000;        // the 256 x 256 kernel
-constexpr int kLargeRoundNs = 5000, kFewRoundNs = 4000;         // a round after the first, besides
-constexpr int kFewBytesPerNs = 10000;                           // selected rows, if there is one
+constexpr int kFewRoundNs = 2000, kFewBytesPerNs = 5000;        // a round after the first, and the selected rows if there is one
 constexpr int kUnitsPerXcd = 32;
 const FewTile few_tiles[] = {
     {1, 1, 150, 2500, launch_few<1, 1>}, {1, 2, 210, 2600, launch_few<1, 2>}, {2, 1, 235, 2600, launch_few<2, 1>},
@@ -597,7 +596,7 @@ const FewTile *choose_few(const ProjectArgs &a)
         if (cost < best && tiles <= 0x7fffffff) { best = cost; n = rounds(tiles); pick = &f; }
     }
     if (n > 1) best += (n - 1) * kFewRoundNs + a.n_sel * a.hidden * 2 / kFewBytesPerNs;
-    return best < rounds(large) * (steps * kLargeStepNs + kLargeFixedNs + kLargeRoundNs) - kLargeRoundNs ? pick : nullptr;
+    return best < rounds(large) * (steps * kLargeStepNs + kLargeFixedNs) ? pick : nullptr;
 }
 } // namespace
 } // namespace kvs
