@@ -156,7 +156,7 @@ SIZED = [(28, 4, 128), (32, 8, 128), (8, 1, 128), (3, 3, 64), (64, 64, 128)]
 
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
 @pytest.mark.parametrize("hq,hk,d", SIZED)
-@pytest.mark.parametrize("call", ["attn_colsum", "first_order_impact"])
+@pytest.mark.parametrize("call", ["attn_colsum", "first_order_impact", "decode_check", "select_topk"])
 def test_a_workspace_for_a_long_prompt_serves_the_shorter_ones(call, hq, hk, d, dtype):
     sh = _shape(hq=hq, hk=hk, d=d, dt=dtype)
     sizes = [B.kvs_workspace_size(call, sh, 1, n) for n in [*range(0, 9000), *range(9000, 70000, 61), 1 << 20]]
