@@ -378,7 +378,7 @@ KVS_API kvs_status kvs_project_qkv(const kvs_shape *shape, int32_t hidden, const
  * returns 0).  n_rows_total is the total number of score / cache rows the call will see (match_tokens: the
  * target's tokens), n_sel_total the total number of selected tokens (partial_attention) or the candidate's
  * tokens (match_tokens, which ignores shape: it may be NULL there).  The answer is an upper bound valid for any split of the
- * totals over `batch` requests.
+ * totals over `batch` requests, and does not shrink as the totals grow.
  */
 KVS_API size_t kvs_workspace_size(const char *call, const kvs_shape *shape, int32_t batch,
                           int64_t n_rows_total, int64_t n_sel_total);

@@ -14,14 +14,15 @@
 // absolute sum, fma(t, v - h, dv), its absolute sum, with a = A[h,j,i] and t = scale * (q . dK) entering once per pair --
 // so the kernel is built to issue little else:
 //   * only reused tokens are rated: a list of them is made first, and a workgroup takes 64 consecutive entries;
-//   * a lane is one token; a wave holds 32 channels of its 64 tokens' V and dV in registers for the whole sweep, and the
+//   * a lane is one token; a wave holds 32 channels of its 64 tokens' V and dV for the whole sweep, and the
 //     eight waves are (channel group, share of the rows), so a row's H is one broadcast 16-byte LDS read per four channels;
 //   * the dot products are the one part that is a contraction: q . K_fresh and q . K_cache (exact bf16 operands; their
 //     difference is q . dK) run on the matrix cores, 32 rows x 64 tokens at a time, and leave (a, t) per pair in LDS;
 //   * the rows are cut into pieces so that the triangle of (row, token) pairs spreads evenly over the chip.
-// Measured, Qwen-shaped 8192 tokens (80 % reused): 18.7 -> 9.8 to 10.4 ms by box, over 94 % of what four instructions per (pair, channel) take at
-// the unpacked fp32 rate; 1963 Llama-shaped tokens 2.04 -> 0.81 ms, 526 Qwen-shaped 549 -> 78 us.  One 256-register workgroup per compute unit instead of two
-// of 128: 14.6 ms (nothing runs beside the matrix-core step and the barriers).
+// Measured, Qwen-shaped 8192 tokens (80 % reused): 18.7 -> 9.8 to 10.4 ms by box, 92 to 94 % of what four instructions per (pair, channel) take at
+// the unpacked fp32 rate (the matrix-core step's operands push 68 bytes a lane of V and dV into scratch); 1963 Llama-shaped tokens
+// 2.04 -> 0.78 ms, 526 Qwen-shaped 549 -> 78 us.  One 256-register workgroup per compute unit instead of two of 128: 14.6 ms (nothing
+// runs beside the matrix-core step and the barriers).
 //
 // fp32 (impact_kernel): one workgroup owns 32 tokens (columns) of one KV head: their K, dK, V, dV rows sit in LDS,
 // channel-major so that the 32 column lanes of a wave hit 32 banks.  Rows stream past in blocks of 64 flattened (query

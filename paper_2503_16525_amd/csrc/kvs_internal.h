@@ -109,10 +109,10 @@ constexpr uint32_t kKeyNegInf = 0x007fffffu;
 // Integer counts: the histogram does not depend on the order in which the atomics land.
 // PER_BIN: one atomic per distinct bin of the wavefront instead of one per lane.  The scores of neighbouring
 // tokens fall into a dozen bins or so and the memory side executes atomics to one address one after the
-// other; measured, the grouping takes the decode scoring launch from 15.5 to ~10 us (a wave there has 64
-// tokens and nothing else to do), but makes kvs_deviation_topk 1.7 us slower: its scoring workgroups stream
-// V and their 32-token epilogue is short, so a serial loop over bins at the end of every workgroup costs
-// more than the atomics it saves (2.7 us for the per-lane add).
+// other; measured, the grouping takes a scoring launch of the decode check with a wave per tile from 15.5 to ~10 us
+// (contexts of more than 16 KV heads; with fewer it counts in LDS first and does not come here), but makes
+// kvs_deviation_topk 1.7 us slower: its scoring workgroups stream V and their 32-token epilogue is short, so a serial loop
+// over bins at the end of every workgroup costs more than the atomics it saves (2.7 us for the per-lane add).
 template <bool PER_BIN>
 __device__ __forceinline__ void key_hist_count(uint32_t *__restrict__ key_hist, uint32_t key, bool counted)
 {
