@@ -71,7 +71,6 @@ constexpr int K_RING = AHEAD <= 4 ? 4 : 8;   // tiles, >= AHEAD; see the slot ar
 constexpr int V_RING = 8;                    // >= AHEAD + 2
 static_assert(K_RING >= AHEAD && V_RING >= AHEAD + 2, "ring depth");
 constexpr int LDS_BYTES = (K_RING + V_RING) * TILE_B;
-constexpr int64_t kAttnLeaveSpread = 64;   // whole-range launches let waves leave from this mean spread of a row tile on (key tiles; 33: 4 % slower, 77: 3 % faster)
 constexpr float kRefShift = 60.0f;      // base-2 offset of the fixed softmax reference above the first tile's maximum
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8, v); }
 
@@ -213,8 +212,7 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
 // workspace and the merge kernel combines them.  The pieces are absolute key ranges, the same for
 // every row tile, and the list runs through them range by range: the workgroups that are resident
 // together read the same stretch of K and V, which then stays in L2.
-// LEAVE: a wave whose own positions end before the workgroup's leaves the arithmetic there and only stages.
-template <bool WANT_LSE, bool SPLIT, bool LEAVE>
+template <bool WANT_LSE, bool SPLIT>
 __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const AttnTiles td, int n_q_heads, int n_kv_heads, int total_tiles,
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
@@ -260,6 +258,10 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const int row0 = tile * ROWS - ((td.tile_begin[b + 1] - td.tile_begin[b]) * ROWS - n_rows);
     const int ctx_len = td.ctx_len[b];
     const int64_t ctx_off = td.ctx_off[b];
+    // First row of the wave's block nb, of the tile's eight blocks of 32 rows in ascending order of position.  A wave has one
+    // of the four lower blocks and its counterpart among the upper ones: what a lower block's early end saves falls to
+    // every wave alike, where with two neighbouring blocks a wave the workgroup is as slow as the last wave.
+    auto block_row = [&](int nb) { return 32 * (nb == 0 ? wave : 2 * NWAVES - 1 - wave); };
 
     // the plan: (pieces per row tile in use, key tiles per large piece, per small piece, small pieces)
     int4 plan = make_int4(1, 0, 0, 0);
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         if (split >= plan.x) {   // a piece slot the plan does not use: mark it empty for the merge
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const int rq = row0 + wave * WROWS + nb * 32 + ln;
+                const int rq = row0 + block_row(nb) + ln;
                 const int t_sel = rq / grp, hh = rq - t_sel * grp;
                 if (rq >= 0 && hf == 0)
                     part_ml[((sel0 + t_sel) * n_q_heads + g * grp + hh) * (int64_t)n_splits + split] = make_float4(-1.0e30f, 0.f, 0.f, 0.f);
@@ -281,10 +283,10 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     bool row_ok[NB];
     int pos[NB];
     int64_t row_idx[NB];
-    int pmin = 0x7fffffff, pmax = 0;
+    int lo_pos[NB], hi_pos[NB];   // lowest and highest position of each block (a block of padding rows only: nothing to see)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-        const int rq = row0 + wave * WROWS + nb * 32 + ln;
+        const int rq = row0 + block_row(nb) + ln;
         row_ok[nb] = rq >= 0;
         const int rqc = max(rq, 0);
         const int t_sel = rqc / grp, hh = rqc - t_sel * grp;
@@ -293,14 +295,15 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         p = min(max(p, 0), ctx_len - 1);             // memory safety; the caller guarantees the range
         pos[nb] = p;
         row_idx[nb] = s_glob * n_q_heads + g * grp + hh;
-        pmin = min(pmin, p);
-        pmax = max(pmax, p);
-    }
+        lo_pos[nb] = p;
+        hi_pos[nb] = row_ok[nb] ? p : -1;
 #pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-        pmin = min(pmin, __shfl_xor(pmin, o));
-        pmax = max(pmax, __shfl_xor(pmax, o));
+        for (int o = 1; o < 32; o <<= 1) {
+            lo_pos[nb] = min(lo_pos[nb], __shfl_xor(lo_pos[nb], o));
+            hi_pos[nb] = max(hi_pos[nb], __shfl_xor(hi_pos[nb], o));
+        }
     }
+    const int pmin = min(lo_pos[0], lo_pos[1]), pmax = max(max(hi_pos[0], hi_pos[1]), 0);
     if (lane == 0) wg_max_pos[wave] = pmax;
 
     // ---- Q as the B operand: Q[query ln][16*ks + 8*hf + j] ----------------------------------------
@@ -543,10 +546,11 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     int key_lim[NB];   // a key of the tile is visible to the lane's query nb iff its (half-wave-relative) index <= this
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) key_lim[nb] = pos[nb] - 8 * hf;
-    auto fast_step = [&](auto masked, int jt, const floatx16 (&s_in)[NB], floatx16 (&s_out)[NB],
+    auto fast_step = [&](auto masked, auto live, int jt, const floatx16 (&s_in)[NB], floatx16 (&s_out)[NB],
                          const u32x4_t (&p_in)[NB][2], u32x4_t (&p_out)[NB][2],
                          u32x4_t &ka, u32x4_t &va) {
-        constexpr bool MASKED = decltype(masked)::value;
+        constexpr int MASKED = decltype(masked)::value, FIRST = decltype(live)::value;   // block nb: bit nb; blocks FIRST .. NB-1 are worked on
+        constexpr int PER = FIRST == 0 ? 4 : 2;                                          // scores per slice
         const uint32_t ks = k_slot(jt + 1), vs = v_slot(jt - 1), ks_next = k_slot(jt + 2), vs_next = v_slot(jt);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -562,30 +566,25 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
                 ka_n = read_k(ks_next, 0);
                 va_n = read_vt(vs_next, 0, 0);
             }
-            const int nbs = i >> 2, r0 = 4 * (i & 3), a = i >> 2, db = i & 3;
-            s_out[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka), qreg[0][i], i == 0 ? zero : s_out[0], 0, 0, 0);
-            float x0 = fmaf(s_in[nbs][r0 + 0], scale_log2, -m_ref[nbs]);
-            float x1 = fmaf(s_in[nbs][r0 + 1], scale_log2, -m_ref[nbs]);
-            float x2 = fmaf(s_in[nbs][r0 + 2], scale_log2, -m_ref[nbs]);
-            float x3 = fmaf(s_in[nbs][r0 + 3], scale_log2, -m_ref[nbs]);
-            if (MASKED) {   // entry r of the lane is key jt*BN + 16*(r>>3) + 8*hf + (r&7)
+            const int nbs = FIRST == 0 ? i >> 2 : 1, r0 = PER * (FIRST == 0 ? i & 3 : i), a = i >> 2, db = i & 3;
+            if (FIRST == 0) s_out[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka), qreg[0][i], i == 0 ? zero : s_out[0], 0, 0, 0);
+            float x[PER], e[PER];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) x[u] = fmaf(s_in[nbs][r0 + u], scale_log2, -m_ref[nbs]);
+            if (MASKED >> nbs & 1) {   // entry r of the lane is key jt*BN + 16*(r>>3) + 8*hf + (r&7)
                 const int k0 = jt * BN + 16 * (r0 >> 3) + (r0 & 7);
-                x0 = k0 + 0 > key_lim[nbs] ? -INFINITY : x0;
-                x1 = k0 + 1 > key_lim[nbs] ? -INFINITY : x1;
-                x2 = k0 + 2 > key_lim[nbs] ? -INFINITY : x2;
-                x3 = k0 + 3 > key_lim[nbs] ? -INFINITY : x3;
+#pragma unroll
+                for (int u = 0; u < PER; ++u) x[u] = k0 + u > key_lim[nbs] ? -INFINITY : x[u];
             }
             s_out[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka), qreg[1][i], i == 0 ? zero : s_out[1], 0, 0, 0);
-            const float e0 = __builtin_amdgcn_exp2f(x0);
-            const float e1 = __builtin_amdgcn_exp2f(x1);
-            const float e2 = __builtin_amdgcn_exp2f(x2);
-            const float e3 = __builtin_amdgcn_exp2f(x3);
-            o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va), as_bf16x8(p_in[0][a]), o_acc[db][0], 0, 0, 0);
-            const uint32_t w0 = pack2(e0, e1), w1 = pack2(e2, e3);
-            p_out[nbs][r0 >> 3][(r0 & 7) >> 1] = w0;
-            p_out[nbs][r0 >> 3][((r0 & 7) >> 1) + 1] = w1;
-            l_run[nbs] = add_rounded_pair(w1, add_rounded_pair(w0, l_run[nbs]));
-            if (WANT_LSE) l_exact[nbs] += (e0 + e1) + (e2 + e3);
+#pragma unroll
+            for (int u = 0; u < PER; ++u) e[u] = __builtin_amdgcn_exp2f(x[u]);
+            if (FIRST == 0) o_acc[db][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va), as_bf16x8(p_in[0][a]), o_acc[db][0], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < PER; u += 2) p_out[nbs][r0 >> 3][((r0 & 7) + u) >> 1] = pack2(e[u], e[u + 1]);
+#pragma unroll
+            for (int u = 0; u < PER; u += 2) l_run[nbs] = add_rounded_pair(p_out[nbs][r0 >> 3][((r0 & 7) + u) >> 1], l_run[nbs]);
+            if (WANT_LSE) l_exact[nbs] += FIRST == 0 ? (e[0] + e[1]) + (e[PER - 2] + e[PER - 1]) : e[0] + e[1];
             o_acc[db][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(va), as_bf16x8(p_in[1][a]), o_acc[db][1], 0, 0, 0);
             ka = ka_n;
             va = va_n;
@@ -593,6 +592,12 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             if (i >= 4) stage_part(jt + AHEAD, i - 4);
         }
     };
+    using Both = std::integral_constant<int, 0>;   // `live`: both blocks, or the upper one only
+    using Upper = std::integral_constant<int, 1>;
+    using Mask0 = std::integral_constant<int, 0>;  // `masked`: no block, the lower one, the upper one, both
+    using MaskLower = std::integral_constant<int, 1>;
+    using MaskUpper = std::integral_constant<int, 2>;
+    using MaskBoth = std::integral_constant<int, 3>;
 
     // ---- passes -------------------------------------------------------------------------------------------
     // Pass 0 takes each row's exponent reference from its first tile (every row sees key 0) and
@@ -659,14 +664,15 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         // wave leaves it at its own point and finishes in the general loop below: both send the same
         // tile's loads in the same step and hit one barrier per step, so the waves of a workgroup
         // may sit in different loops.
-        const int j_unmasked = (pmin + 1) / BN;     // tiles 0 .. j_unmasked-1: every key <= pmin
+        const int j_unmasked = __builtin_amdgcn_readfirstlane(pmin + 1) / BN;     // tiles 0 .. j_unmasked-1: every key <= pmin
         const int j_inside = ctx_len / BN;          // tiles 0 .. j_inside-1 need no row clamp
-        // Past the wave's own last position every key is masked: with LEAVE the wave then only stages and keeps the
-        // barriers until the others are done.  Rows of a workgroup are up to 64 tokens of a sparse selection: at the 2 % of
-        // a decode batch the first wave's positions end 75 key tiles before the last one's, and the workgroup is as slow
-        // as its slowest wave.  64 requests 1566 -> 1500 us, pieces of 2 to 10 % 1 to 2 % faster; where a tile's tokens are
-        // close together the wave's two ways out cost more than they save (15 % of 32768 tokens 997 -> 1006 us).
-        const int w_hi = LEAVE ? min(t_hi, __builtin_amdgcn_readfirstlane(pmax) / BN + 1) : t_hi;
+        // Past a block's own last position every key is masked.  A wave goes on with its upper block alone where the lower one
+        // has ended (half the MFMAs and softmax of a step, all of its LDS reads: about 0.7 of its time), and past the upper
+        // one's end it only stages and keeps the barriers until the others are done.  The rows of a tile are up to 64
+        // tokens of a sparse selection: at the 2 % of a decode batch its blocks end 12 key tiles apart.  Against waves of two
+        // neighbouring blocks: 64 requests of 2 % 1522 -> 1431 us, of 4 % 2612 -> 2460, 46 of 2.8 % 183 -> 172, 15 % of
+        // 32768 tokens 1017 -> 997, 30 % 2047 -> 2017, pieces of 5 % 418 -> 420.
+        const int w_hi = min(t_hi, __builtin_amdgcn_readfirstlane(pmax) / BN + 1);
         if (t_lo + 3 <= t_hi && t_lo + AHEAD + 3 <= j_inside) {
             // the first step has no earlier tile to multiply: scores of the second tile, softmax of the first
             u32x4_t p_a[NB][2], p_b[NB][2];
@@ -677,16 +683,23 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             // K of the third tile, V of the first
             u32x4_t ka = read_k(k_slot(t_lo + 2), 0);
             u32x4_t va = read_vt(v_slot(t_lo), 0, 0);
+            jt = t_lo + 1;
             // two steps per trip so that the score and weight buffers swap roles without copies
-            for (jt = t_lo + 1; jt + 1 < min(j_unmasked, t_hi) && jt + AHEAD + 1 < j_inside; jt += 2) {
-                fast_step(std::false_type{}, jt, s_nxt, s_cur, p_a, p_b, ka, va);
-                fast_step(std::false_type{}, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
-            }
-            // the tiles around the wave's own positions, same pipeline with the causal compare
-            for (; (LEAVE ? jt < w_hi && jt + 1 < t_hi : jt + 1 < t_hi) && jt + AHEAD + 1 < j_inside; jt += 2) {
-                fast_step(std::true_type{}, jt, s_nxt, s_cur, p_a, p_b, ka, va);
-                fast_step(std::true_type{}, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
-            }
+            auto sweep = [&](auto masked, auto live, int stop) {
+                for (; jt < stop && jt + 1 < t_hi && jt + AHEAD + 1 < j_inside; jt += 2) {
+                    fast_step(masked, live, jt, s_nxt, s_cur, p_a, p_b, ka, va);
+                    fast_step(masked, live, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
+                }
+            };
+            sweep(Mask0{}, Both{}, j_unmasked - 1);
+            // the tiles around the blocks' own positions, same pipeline with the causal compare
+            // (the weights of tile jt-1 enter the step of tile jt: past the lower block's last tile they are zero)
+            const int j_both = min(w_hi, __builtin_amdgcn_readfirstlane(hi_pos[0] + BN) / BN + 1);
+            const int j_upper = __builtin_amdgcn_readfirstlane(lo_pos[1] + 1) / BN - 1;     // tiles 0 .. j_upper: every key <= lo_pos[1]
+            sweep(MaskLower{}, Both{}, min(j_both, j_upper));
+            sweep(MaskBoth{}, Both{}, j_both);
+            sweep(Mask0{}, Upper{}, min(w_hi, j_upper));
+            sweep(MaskUpper{}, Upper{}, w_hi);
             pv_product(jt - 1, p_a);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) s_cur[nb] = s_nxt[nb];
@@ -706,7 +719,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         }
         // the other waves' tiles: this wave's share of the staging, and the barriers.  Tile jt+2 has to have landed at the
         // barrier of step jt; the last tile sent before it is jt+AHEAD-1, if there is one.
-        for (; LEAVE && jt < t_hi; ++jt) {
+        for (; jt < t_hi; ++jt) {
             if (jt + AHEAD - 1 < t_hi) KVS_ATTN_BARRIER(KVS_ATTN_IN_FLIGHT);
             else KVS_ATTN_BARRIER(0);
             if (jt + AHEAD < t_hi) stage_tile(jt + AHEAD);
@@ -883,7 +896,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     }
 }
 
-template <bool WANT_LSE, bool SPLIT, bool LEAVE>
+template <bool WANT_LSE, bool SPLIT>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
                       float scale_log2, void *out, float *lse_out, int n_splits, const int4 *split_plan,
@@ -891,12 +904,12 @@ kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const A
 {
     static DeviceOnce attr_once;
     const kvs_status ast = once_per_device(attr_once, [lds_bytes] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT, LEAVE>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_partial_attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
     });
     if (ast != KVS_OK) return ast;
-    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT, LEAVE>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
+    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
                        shape->n_kv_heads, tiles, (const uint16_t *)q_sel, sel_pos, (const uint16_t *)k_cache,
                        (const uint16_t *)v_cache, scale_log2, (uint16_t *)out, lse_out, n_splits, split_plan, piece_list,
                        part_o, part_ml, share_units);
@@ -988,18 +1001,9 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     if (n_splits <= 1 || !workspace) {
         const int share_units = share_units_for(shape, tiles);
         const dim3 grid((unsigned)((share_units > 0 ? share_units : tiles) * shape->n_kv_heads));
-        // key tiles that the tokens of a row tile are spread over, on average
-        int64_t ctx = 0, sel = 0;
-        for (int i = 0; i < bd.n_req; ++i) {
-            const int64_t n = bd.cu_sel[i + 1] - bd.cu_sel[i];
-            if (n > 0) { ctx += bd.ctx_len[i]; sel += n; }
-        }
-        const int grp = shape->n_q_heads / shape->n_kv_heads;
-        const bool leave = ctx * ROWS >= sel * grp * (int64_t)(BN * kAttnLeaveSpread);
-#define KVS_ATTN_WHOLE(LSE, LV) launch_one<LSE, false, LV>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
-                                                          scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
-        if (lse_out) return leave ? KVS_ATTN_WHOLE(true, true) : KVS_ATTN_WHOLE(true, false);
-        return leave ? KVS_ATTN_WHOLE(false, true) : KVS_ATTN_WHOLE(false, false);
+#define KVS_ATTN_WHOLE(LSE) launch_one<LSE, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
+                                                  scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
+        return lse_out ? KVS_ATTN_WHOLE(true) : KVS_ATTN_WHOLE(false);
 #undef KVS_ATTN_WHOLE
     }
     if (tiles > PLAN_MAX_TILES) return fail(KVS_EINVAL, "kvs_partial_attention: split launch with %lld row tiles", (long long)tiles);
@@ -1021,9 +1025,9 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));
-    stt = lse_out ? launch_one<true, true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+    stt = lse_out ? launch_one<true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                            scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0)
-                  : launch_one<false, true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+                  : launch_one<false, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                             scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0);
     if (stt != KVS_OK) return stt;
     return launch_attention_merge(n_rows_total, n_splits, (const float *)workspace, ml_base,
