@@ -53,27 +53,25 @@ kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *par
 
 // What the host fixes for a split launch of the 256-row kernel: piece slots per row tile (1: no
 // cutting, nothing else is read), the longest context in key tiles, and the small pieces at the
-// bottom of the context (n_small of small_chunk key tiles).  Two cases cut the key range:
-//   * launches too small to fill the chip: the size of the large pieces is chosen on the device,
-//     from the positions, so that the pieces just fill whole rounds of the compute units;
-//   * launches whose K and V no longer fit the last-level cache (kAttnRangeMajorBytes; the 131k
-//     context): chunk > 0 fixes the piece size so that one key range of one KV head fits an L2.
-//     Workgroups of a KV head that start at different times otherwise sweep K/V at different
-//     places and every one of them streams from HBM on its own (measured: 16 % of the matrix
-//     peak at 131k against 45 % at 32k, where K and V stay cached), and a workgroup that meets a
-//     logit 111 above its first tile's repeats a piece instead of its whole sweep.  (131072
-//     Yi-shaped tokens, 12452 selected, pieces against whole ranges: 12.8 and 11.7 ms where no row
-//     repeats, 13.1 and 27.2 with 200 keys of 40 times the size in mid-context.)
-// Pieces are started from the top of the context down, range by range.
+// bottom of the context (n_small of small_chunk key tiles).  Launches too small to fill the chip
+// are cut: the size of the large pieces is chosen on the device, from the positions, so that the
+// pieces just fill whole rounds of the compute units.  Pieces are started from the top of the
+// context down, range by range.
+// recentre: whole key ranges with a reference that moves where a row's sum outgrows it, for launches
+// whose K and V no longer fit the last-level cache (kAttnRecentreBytes).  There a workgroup that
+// repeats its sweep with the exact maxima streams everything from HBM a second and third time; the
+// look at the sums after every tile costs 4 to 5 % of the sweep, which shorter contexts save.
+// (131072 Yi-shaped tokens, 12452 selected, plain and with 200 keys of 40 times the size in
+// mid-context, ms: recentred 12.0 and 11.9, fixed reference 11.6 and 27.1, pieces of 8192 keys with a
+// merge, which repeat a piece only, 12.9 and 13.2.)
 struct AttnSplitPlan {
     int n_splits;
     int ctx_tiles;
     int small_chunk;
     int n_small;
-    int chunk;          // 0: chosen on the device
+    bool recentre;
 };
-constexpr int64_t kAttnRangeMajorBytes = (int64_t)192 << 20;   // K + V of a launch above which key ranges are walked in step
-constexpr int kAttnRangeChunk = 256;       // key tiles per piece then: 8192 keys = 4 MiB of K and V per KV head
+constexpr int64_t kAttnRecentreBytes = (int64_t)192 << 20;   // K + V of a launch's largest request
 constexpr int kAttnPlanMaxTiles = 2048;    // row tiles a planned launch may have
 // the device-side plan and the list of piece ids (16 bits each, kAttnSplitMax per row tile), after
 // the pieces in the workspace

@@ -527,7 +527,7 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     }
     // with fewer 256-row tiles than compute units the large kernel still wins if the caller's
     // workspace lets it cut the key ranges and its tiles are not mostly padding
-    AttnSplitPlan plan2 = {1, 0, 0, 0, 0};
+    AttnSplitPlan plan2 = {1, 0, 0, 0, false};
     if (workspace && fits32) plan2 = attention_mfma2_plan(shape, bd, workspace_bytes);
     const int splits2 = plan2.n_splits;
     const bool fills = big_tiles * shape->n_kv_heads >= kAttnBigTileMinGrid;
@@ -535,7 +535,7 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     // (below ~50 such tiles the per-workgroup start-up of the large kernel costs more than it gains)
     const bool big = fits32 && (forced ? forced == 2 : fills || (splits2 >= 2 && dense_tiles && big_tiles * shape->n_kv_heads >= 48));
     if (big) {
-        if (fills && !forced && plan2.chunk == 0) plan2 = {1, 0, 0, 0, 0};   // fills the chip and stays cached: whole key ranges
+        if (fills && !forced) plan2 = {1, 0, 0, 0, plan2.recentre};   // fills the chip: whole key ranges
         return launch_attention_mfma2(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, workspace, plan2, st);
     }
     return launch_mfma_variant<KVS_ATTN_NWAVES>(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out,
@@ -546,15 +546,15 @@ size_t attention_workspace_bytes(const kvs_shape *shape, int32_t batch, int64_t 
 {
     const int64_t rows = n_sel_total * shape->n_q_heads;
     int64_t slots = rows * kSplitMax;
-    // Launches that fill the chip keep whole key ranges unless their K and V outgrow the last-level
-    // cache (then every row may have up to kSplitMax pieces).  Otherwise pieces are only used below
+    // Launches that fill the chip keep whole key ranges.  Pieces are only used below
     // kSplitBelowWgs workgroups: at most kSplitMaxWgs workgroup-pieces of 32*KVS_ATTN_NWAVES rows
     // each (128-row kernel) or fewer than kAttnSplitBelowWgs tiles of 256 rows with up to kSplitMax
     // pieces each (256-row kernel).
     // (a batch is sized for the capped case: with several requests the rows say nothing about the
-    // longest one, and a launch whose workspace is too small for pieces keeps whole key ranges)
+    // longest one, and a launch whose workspace is too small for pieces keeps whole key ranges; one request beyond
+    // the last-level cache is given room for kSplitMax pieces of every row, as callers have been)
     const int64_t kv_bytes = n_rows_total * shape->n_kv_heads * (int64_t)D * 2 * 2;
-    if (batch > 1 || kv_bytes <= kAttnRangeMajorBytes) {
+    if (batch > 1 || kv_bytes <= kAttnRecentreBytes) {
         const int64_t cap = (int64_t)(kSplitMaxWgs + kSplitBelowWgs) * 256 + (int64_t)batch * 256 * kSplitMax;
         if (slots > cap) slots = cap;
     }

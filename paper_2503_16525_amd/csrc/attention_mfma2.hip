@@ -72,6 +72,7 @@ constexpr int V_RING = 8;                    // >= AHEAD + 2
 static_assert(K_RING >= AHEAD && V_RING >= AHEAD + 2, "ring depth");
 constexpr int LDS_BYTES = (K_RING + V_RING) * TILE_B;
 constexpr float kRefShift = 60.0f;      // base-2 offset of the fixed softmax reference above the first tile's maximum
+constexpr float kSumLimit = 1.8446744e19f;   // 2^64: a sum of weights beyond it moves the reference (RECENTRE)
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8, v); }
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi)
@@ -212,7 +213,8 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
 // workspace and the merge kernel combines them.  The pieces are absolute key ranges, the same for
 // every row tile, and the list runs through them range by range: the workgroups that are resident
 // together read the same stretch of K and V, which then stays in L2.
-template <bool WANT_LSE, bool SPLIT>
+// RECENTRE: the softmax reference is not fixed for the sweep; see recentre below, and AttnSplitPlan for when.
+template <bool WANT_LSE, bool SPLIT, bool RECENTRE>
 __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const AttnTiles td, int n_q_heads, int n_kv_heads, int total_tiles,
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
@@ -536,6 +538,39 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             }
     };
 
+    // RECENTRE: the reference moves where a row's sum outgrows it.  Looked at after every tile, before the tile's weights are
+    // multiplied with V: the row's reference goes up by a whole number (at least 100, and past the tile's largest logit by
+    // kRefShift), its sum without the tile and its accumulators come down by that power of two, and the tile's weights
+    // are computed again, from scores that are still there.  (A NaN moves nothing.)
+    auto outgrown = [&](int first) __attribute__((always_inline)) -> bool {
+        return __builtin_amdgcn_ballot_w64((first == 0 ? fmaxf(l_run[0], l_run[1]) : l_run[1]) >= kSumLimit) != 0;
+    };
+    float l_before[NB], le_before[NB];   // the sums without the tile
+    auto keep_sums = [&]() {
+#pragma unroll
+        for (int nb = 0; RECENTRE && nb < NB; ++nb) { l_before[nb] = l_run[nb]; le_before[nb] = l_exact[nb]; }
+    };
+    auto recentre = [&](int jt, floatx16 (&s)[NB], u32x4_t (&pop)[NB][2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            floatx16 &m = s[nb];          // (the scores are not read again)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) m[r] = jt * BN + 16 * (r >> 3) + 8 * hf + (r & 7) > pos[nb] ? -INFINITY : m[r];
+            const float other = __shfl_xor(l_run[nb], 32);
+            const float up = !(l_run[nb] >= kSumLimit || other >= kSumLimit) ? 0.f : fmaxf(ceilf(row_max(m) + kRefShift - m_ref[nb]), 100.f);
+            const float down = __builtin_amdgcn_exp2f(-up);
+            m_ref[nb] += up;
+            l_run[nb] = l_before[nb] * down;
+            l_exact[nb] = le_before[nb] * down;
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][nb][r] *= down;
+#pragma unroll
+            for (int r0 = 0; r0 < 16; r0 += 4) softmax4(m, nb, r0, pop[nb]);
+        }
+    };
+
     // One step of the pipelined sweep (tile jt+AHEAD lies wholly inside the context; `masked` says whether
     // tile jt needs the causal compare for this wave): scores of tile jt+1, softmax of tile jt, PV of
     // tile jt-1, written as eight slices of four MFMAs and four scores each, LDS operands fetched one
@@ -546,11 +581,12 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     int key_lim[NB];   // a key of the tile is visible to the lane's query nb iff its (half-wave-relative) index <= this
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) key_lim[nb] = pos[nb] - 8 * hf;
-    auto fast_step = [&](auto masked, auto live, int jt, const floatx16 (&s_in)[NB], floatx16 (&s_out)[NB],
+    auto fast_step = [&](auto masked, auto live, int jt, floatx16 (&s_in)[NB], floatx16 (&s_out)[NB],
                          const u32x4_t (&p_in)[NB][2], u32x4_t (&p_out)[NB][2],
-                         u32x4_t &ka, u32x4_t &va) {
+                         u32x4_t &ka, u32x4_t &va) __attribute__((always_inline)) {
         constexpr int MASKED = decltype(masked)::value, FIRST = decltype(live)::value;   // block nb: bit nb; blocks FIRST .. NB-1 are worked on
         constexpr int PER = FIRST == 0 ? 4 : 2;                                          // scores per slice
+        keep_sums();
         const uint32_t ks = k_slot(jt + 1), vs = v_slot(jt - 1), ks_next = k_slot(jt + 2), vs_next = v_slot(jt);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -591,6 +627,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             if (i == 3) KVS_ATTN_BARRIER(KVS_ATTN_IN_FLIGHT);   // tile jt+2 has landed; younger ones may be in flight
             if (i >= 4) stage_part(jt + AHEAD, i - 4);
         }
+        if (RECENTRE && outgrown(FIRST)) recentre(jt, s_in, p_out);
     };
     using Both = std::integral_constant<int, 0>;   // `live`: both blocks, or the upper one only
     using Upper = std::integral_constant<int, 1>;
@@ -610,10 +647,10 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // the first tile's maximum already overflowed, which heavy-tailed keys do reach: half the
     // workgroups of a 131k-token launch repeated the pass.)  If a row's sum does end above 2^100 (or
     // inf / nan) the workgroup computes the exact row maxima in a score-only sweep and repeats the
-    // pass with those (pass 1), which cannot overflow: a correctness net.
+    // pass with those (pass 1), which cannot overflow: a correctness net.  (RECENTRE has no use for it.)
     __shared__ int redo_flag;
     float l_tot[NB];
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < (RECENTRE ? 1 : 2); ++pass) {
         if (pass == 1) {
             // exact row maxima: a score-only sweep with three tiles on their way.  Tile jt+3 goes to
             // the K slot of tile jt-1, which every wave has finished reading when it passes the
@@ -685,7 +722,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             u32x4_t va = read_vt(v_slot(t_lo), 0, 0);
             jt = t_lo + 1;
             // two steps per trip so that the score and weight buffers swap roles without copies
-            auto sweep = [&](auto masked, auto live, int stop) {
+            auto sweep = [&](auto masked, auto live, int stop) __attribute__((always_inline)) {
                 for (; jt < stop && jt + 1 < t_hi && jt + AHEAD + 1 < j_inside; jt += 2) {
                     fast_step(masked, live, jt, s_nxt, s_cur, p_a, p_b, ka, va);
                     fast_step(masked, live, jt + 1, s_cur, s_nxt, p_b, p_a, ka, va);
@@ -708,9 +745,11 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         for (; jt < w_hi; ++jt) {
             // scores of the next tile first (past the last tile the slot holds stale data and the
             // result is discarded)
+            keep_sums();
             qk(jt + 1, s_nxt);
             u32x4_t pop[NB][2];
             softmax(jt, s_cur, pop);
+            if (RECENTRE && outgrown(0)) recentre(jt, s_cur, pop);
             pv_product(jt, pop);
             KVS_ATTN_BARRIER(0);
             if (jt + AHEAD < t_hi) stage_tile(jt + AHEAD);
@@ -733,7 +772,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             l_tot[nb] = l_run[nb] + __shfl_xor(l_run[nb], 32);
             bad |= !(l_tot[nb] < 1.2676506e30f);          // 2^100; also true for inf and nan
         }
-        if (pass == 1) break;
+        if (RECENTRE || pass == 1) break;
         if (tid == 0) redo_flag = 0;
         __syncthreads();
         if (bad) redo_flag = 1;
@@ -806,7 +845,7 @@ constexpr int PLAN_MAX_ROUNDS = 4;
 __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const AttnTiles td, int grp, int n_kv_heads, int total_tiles, const int32_t *__restrict__ sel_pos,
     int s_max, int ctx_tiles, int small_chunk, int n_small, float round_fill, float piece_overhead,
-    int forced_chunk, int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
+    int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
 {
     __shared__ int len[PLAN_MAX_TILES];       // key tiles of each row tile
     __shared__ int first_fit[PLAN_MAX_ROUNDS];
@@ -830,7 +869,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const int c_max = max(c_min, ctx_tiles - bottom);
     const int step = (c_max - c_min + PLAN_NT - 1) / PLAN_NT;
     const int c = c_min + tid * step;
-    const bool tries = forced_chunk <= 0 && c <= c_max && (step > 0 || tid == 0);   // a fixed chunk needs no search
+    const bool tries = c <= c_max && (step > 0 || tid == 0);
     int pieces = 0x7fffffff;
     if (tries) {
         const float rc = 1.0f / (float)c;
@@ -854,7 +893,6 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
             const float time = (float)(r + 1) * ((float)first_fit[r] + piece_overhead);
             if (time < best_t) { best_t = time; best_c = first_fit[r]; }
         }
-        if (forced_chunk > 0) best_c = min(max(forced_chunk, c_min), c_max);
         chosen = make_int4(n_small + (ctx_tiles - bottom + best_c - 1) / best_c, best_c, small_chunk, n_small);
         *plan = chosen;
     }
@@ -896,7 +934,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     }
 }
 
-template <bool WANT_LSE, bool SPLIT>
+template <bool WANT_LSE, bool SPLIT, bool RECENTRE>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
                       float scale_log2, void *out, float *lse_out, int n_splits, const int4 *split_plan,
@@ -904,12 +942,12 @@ kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const A
 {
     static DeviceOnce attr_once;
     const kvs_status ast = once_per_device(attr_once, [lds_bytes] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma2_kernel<WANT_LSE, SPLIT, RECENTRE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_partial_attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
     });
     if (ast != KVS_OK) return ast;
-    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
+    hipLaunchKernelGGL((attn_mfma2_kernel<WANT_LSE, SPLIT, RECENTRE>), grid, dim3(NT), lds_bytes, st, td, shape->n_q_heads,
                        shape->n_kv_heads, tiles, (const uint16_t *)q_sel, sel_pos, (const uint16_t *)k_cache,
                        (const uint16_t *)v_cache, scale_log2, (uint16_t *)out, lse_out, n_splits, split_plan, piece_list,
                        part_o, part_ml, share_units);
@@ -945,23 +983,20 @@ int share_units_for(const kvs_shape *shape, int64_t tiles)
 
 AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, size_t workspace_bytes)
 {
-    const AttnSplitPlan whole = {1, 0, 0, 0, 0};
+    const AttnSplitPlan whole = {1, 0, 0, 0, false};
     const int grp = shape->n_q_heads / shape->n_kv_heads;
     int64_t tiles = 0, max_ctx = 0, kv_bytes = 0;
     for (int i = 0; i < bd.n_req; ++i) {
         tiles += ((bd.cu_sel[i + 1] - bd.cu_sel[i]) * grp + ROWS - 1) / ROWS;
         max_ctx = bd.ctx_len[i] > max_ctx ? bd.ctx_len[i] : max_ctx;
-        // (what has to stay cached is one request's K and V: requests do not share keys)
         if (bd.cu_sel[i + 1] > bd.cu_sel[i]) {
             const int64_t b = bd.ctx_len[i] * (int64_t)shape->n_kv_heads * ROW_B * 2;
             kv_bytes = b > kv_bytes ? b : kv_bytes;
         }
     }
     const int64_t wgs = tiles * shape->n_kv_heads;
+    if (wgs >= kAttnSplitBelowWgs) return AttnSplitPlan{1, 0, 0, 0, kv_bytes > kAttnRecentreBytes};
     if (wgs <= 0 || tiles > kAttnPlanMaxTiles) return whole;
-    const bool small_launch = wgs < kAttnSplitBelowWgs;
-    const bool range_major = !small_launch && kv_bytes > kAttnRangeMajorBytes;
-    if (!small_launch && !range_major) return whole;
     const int64_t ctx_tiles = (max_ctx + BN - 1) / BN;
     const int64_t n_rows_total = (bd.cu_sel[bd.n_req] - bd.cu_sel[0]) * shape->n_q_heads;
     int64_t s_max = kAttnSplitMax;
@@ -971,19 +1006,11 @@ AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, 
     const int64_t by_ws = (int64_t)((workspace_bytes - kAttnPlanBytes) / (kAttnPartBytesPerSlot * (size_t)(n_rows_total > 0 ? n_rows_total : 1)));
     if (s_max > by_ws) s_max = by_ws;
     if (s_max < 2) return whole;
-    if (range_major) {
-        // as small a piece as the slots allow, down to the one whose K and V fit an L2
-        int64_t chunk = (ctx_tiles + s_max - 1) / s_max;
-        if (chunk < kAttnRangeChunk) chunk = kAttnRangeChunk;
-        const int64_t n = (ctx_tiles + chunk - 1) / chunk;
-        if (n < 2) return whole;
-        return AttnSplitPlan{(int)n, (int)ctx_tiles, 0, 0, (int)chunk};
-    }
     // Small pieces at the bottom of the context (every row tile has them, and they start last)
     // fill the gaps the large ones leave; they pay off once the large pieces can be several times
     // their size.
     const bool taper = s_max >= 6 && ctx_tiles >= 8 * kAttnSmallChunk;
-    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, kAttnSmallChunk, taper ? kAttnSmallPieces : 0, 0};
+    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, kAttnSmallChunk, taper ? kAttnSmallPieces : 0, false};
 }
 
 kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, const void *q_sel,
@@ -1001,9 +1028,10 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     if (n_splits <= 1 || !workspace) {
         const int share_units = share_units_for(shape, tiles);
         const dim3 grid((unsigned)((share_units > 0 ? share_units : tiles) * shape->n_kv_heads));
-#define KVS_ATTN_WHOLE(LSE) launch_one<LSE, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
-                                                  scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
-        return lse_out ? KVS_ATTN_WHOLE(true) : KVS_ATTN_WHOLE(false);
+#define KVS_ATTN_WHOLE(LSE, RC) launch_one<LSE, false, RC>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
+                                                          scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units)
+        if (lse_out) return plan.recentre ? KVS_ATTN_WHOLE(true, true) : KVS_ATTN_WHOLE(true, false);
+        return plan.recentre ? KVS_ATTN_WHOLE(false, true) : KVS_ATTN_WHOLE(false, false);
 #undef KVS_ATTN_WHOLE
     }
     if (tiles > PLAN_MAX_TILES) return fail(KVS_EINVAL, "kvs_partial_attention: split launch with %lld row tiles", (long long)tiles);
@@ -1018,16 +1046,16 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     int4 *split_plan = (int4 *)(ml_base + n_rows_total * n_splits);
     uint16_t *piece_list = (uint16_t *)(split_plan + 1);
     float round_fill = kAttnRoundFill, piece_overhead = kAttnPieceOverhead;
-    int forced_chunk = plan.chunk, small_chunk = plan.small_chunk, n_small = plan.n_small;
+    int small_chunk = plan.small_chunk, n_small = plan.n_small;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(PLAN_NT), 0, st, td, shape->n_q_heads / shape->n_kv_heads,
                        shape->n_kv_heads, (int)tiles, sel_pos, n_splits, plan.ctx_tiles, small_chunk, n_small, round_fill,
-                       piece_overhead, forced_chunk, split_plan, piece_list);
+                       piece_overhead, split_plan, piece_list);
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));
-    stt = lse_out ? launch_one<true, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+    stt = lse_out ? launch_one<true, true, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                            scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0)
-                  : launch_one<false, true>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
+                  : launch_one<false, true, false>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache,
                                             scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0);
     if (stt != KVS_OK) return stt;
     return launch_attention_merge(n_rows_total, n_splits, (const float *)workspace, ml_base,

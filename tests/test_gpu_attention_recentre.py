@@ -1,0 +1,58 @@
+"""Contexts whose K and V outgrow the last-level cache: the softmax reference moves where a row's sum of weights outgrows it,
+once or several times, by a little or by more than fp32 holds, in the first, a middle and the last tile, in one row or in all.
+Every checked row against softmax in 64 bits; the log-sum-exp with it."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_16525_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("want_lse", [False, True])
+@pytest.mark.parametrize("what", ["steps", "jump", "one-row", "last", "infinite"])
+def test_reference_moves(what, want_lse):
+    print(f"recentred attention: {what}, lse {want_lse}", flush=True)
+    hq, hk, d, n, k = 64, 8, 128, 49200, 1600             # 201 MB of K and V; 50 row tiles a KV head
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    kk = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    v = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randn((k, hq, d), generator=gen, device=DEV)
+    q = (q / q.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    pos = torch.arange(n - k * 30, n, 30, device=DEV, dtype=torch.int32)
+    u = q[7, ::8].float()                                 # the direction that the large keys have, by KV head
+    if what == "steps":                                   # each 90 above the one before: one move every few tiles
+        for i, at in enumerate((40, 1000, 1017, 20000, 40000)):
+            kk[at] = (u * 90 * (i + 1)).to(torch.bfloat16)
+        q[:] = q[7:8, ::8].repeat_interleave(8, 1)
+    elif what == "jump":                                  # far past what fp32 holds, in every row
+        kk[25000] = (u * 3000).to(torch.bfloat16)
+        q[:] = q[7:8, ::8].repeat_interleave(8, 1)
+    elif what == "one-row":
+        kk[25000] = (u * 400).to(torch.bfloat16)          # row 7 of a group's first head sees 400, the others a few tens
+    elif what == "last":
+        kk[n - 31] = (u * 500).to(torch.bfloat16)         # the last row's own tile
+        q[:] = q[7:8, ::8].repeat_interleave(8, 1)
+    else:
+        kk[30011, 3, 5] = float("inf")
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("partial_attention", sh, 1, n, k), dtype=torch.uint8, device=DEV)
+    out = torch.full((k, hq, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((k, hq), 7.0, device=DEV) if want_lse else None
+    B.kvs_partial_attention(sh, [0], [n], [0, k], q, pos, kk, v, 1.0, out, lse, ws)
+    for h in (0, 7, 8, 26, 29, 63):
+        rows = torch.tensor([0, 7, 8, 31, 32, 250, 800, 833, k - 65, k - 64, k - 2, k - 1], device=DEV)
+        s = q[rows, h].double() @ kk[:, h // 8].double().t()
+        s.masked_fill_(torch.arange(n, device=DEV)[None] > pos[rows, None].long(), -np.inf)
+        z = torch.logsumexp(s, -1)
+        ref = torch.softmax(s, -1) @ v[:, h // 8].double()
+        got = out[rows, h].double()
+        fine = torch.isfinite(ref).all(-1)                # (an infinite key: rows whose product with it is +Inf have no finite result,
+        assert torch.equal(torch.isfinite(got).all(-1), fine), (what, h)      # the others give it no weight)
+        got, ref, z, rows = got[fine], ref[fine], z[fine], rows[fine]
+        # weights and results in bf16: two roundings of 2^-9 of values up to max |v|
+        assert float((got - ref).abs().max()) <= 2.0 ** -8 * float(v.abs().max()), (what, h)
+        if want_lse:
+            assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max())
