@@ -33,6 +33,7 @@ FLAGS = [
 # registers and copies the scores out one by one
 EXTRA_FLAGS = {
     "attention_mfma2.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "impact.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

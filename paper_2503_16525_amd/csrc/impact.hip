@@ -10,19 +10,20 @@
 // a contraction for the matrix cores (only the two dot products per pair are).  It is a diagnostic
 // for check layers, not a step of the hot path.
 //
-// bf16 (impact_tiles_kernel).  Per (row, token, channel) there are four vector instructions that nothing saves -- v - h, its
-// absolute sum, fma(t, v - h, dv), its absolute sum, with a = A[h,j,i] and t = scale * (q . dK) entering once per pair --
-// so the kernel is built to issue little else:
-//   * only reused tokens are rated: a list of them is made first, and a workgroup takes 64 consecutive entries;
-//   * a lane is one token; a wave holds 32 channels of its 64 tokens' V and dV for the whole sweep, and the
-//     eight waves are (channel group, share of the rows), so a row's H is one broadcast 16-byte LDS read per four channels;
-//   * the dot products are the one part that is a contraction: q . K_fresh and q . K_cache (exact bf16 operands; their
-//     difference is q . dK) run on the matrix cores, 32 rows x 64 tokens at a time, and leave (a, t) per pair in LDS;
+// bf16 (impact_tiles_kernel).  Per (row, token, channel) there are a subtraction, v - h, its absolute sum, fma(t, v - h, dv)
+// and its absolute sum, with a = A[h,j,i] and t = scale * (q . dK) entering once per pair.  The subtraction is a product: over a
+// tile of rows x tokens v - h = [-h, 1] . [1, v], a contraction of two that bf16 operands enter exactly.  So the matrix cores make
+// it beside the vector units, which are left with three instructions per term and bound the kernel:
+//   * only reused tokens are rated: a list of them is made first, and a workgroup takes 32 consecutive entries, whose K, V and dV
+//     it keeps in LDS;
+//   * a wave takes 32 flattened (row, head) pairs at a time, alone (no barrier in the sweep): q . K_fresh and q . K_cache (exact bf16
+//     operands; their difference is q . dK) on the matrix cores, then channel by channel one 32x32x8 MFMA for the differences
+//     and 48 vector instructions on its 16 results a lane.  The row's H is an operand as it lies in memory, four channels at
+//     a time; the other operand picks one of them (-1 in its slot, zeros beside it).  The fp32 instruction of the same
+//     shape takes twice the matrix time and gained nothing (9.9 ms: vector work does not run beside all of it);
 //   * the rows are cut into pieces so that the triangle of (row, token) pairs spreads evenly over the chip.
-// Measured, Qwen-shaped 8192 tokens (80 % reused): 18.7 -> 9.8 to 10.4 ms by box, 92 to 94 % of what four instructions per (pair, channel) take at
-// the unpacked fp32 rate (the matrix-core step's operands push 68 bytes a lane of V and dV into scratch); 1963 Llama-shaped tokens
-// 2.04 -> 0.78 ms, 526 Qwen-shaped 549 -> 78 us.  One 256-register workgroup per compute unit instead of two of 128: 14.6 ms (nothing
-// runs beside the matrix-core step and the barriers).
+// Measured against four vector instructions a term (lanes are tokens, a wave 32 channels, H through LDS, barriers): Qwen-shaped 8192
+// tokens (80 % reused) 10.2 -> 7.5 ms, 7300 Llama-shaped 8.8 -> 7.2, 1963 0.77 -> 0.68, 526 Qwen-shaped 68 -> 58 us, 256 Yi-shaped 41 -> 33.
 //
 // fp32 (impact_kernel): one workgroup owns 32 tokens (columns) of one KV head: their K, dK, V, dV rows sit in LDS,
 // channel-major so that the 32 column lanes of a wave hit 32 banks.  Rows stream past in blocks of 64 flattened (query
@@ -203,14 +204,19 @@ __global__ __launch_bounds__(kListThreads) void impact_list_kernel(int n, const 
     if (tid == kListThreads - 1) *count = at;
 }
 
-// ---- bf16: 64 tokens of the list x one piece of the rows ----------------------------------------------------------
+// ---- bf16: 32 tokens of the list x one piece of the rows ----------------------------------------------------------
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 imp_bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float imp_floatx16;
-constexpr int kTileCols = 64, kTileRows = 32, kTileThreads = 512;
-constexpr int kTileCh = 32;                                  // channels a wave holds
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short imp_s16x4;
+constexpr int kTileCols = 32, kTileRows = 32, kTileThreads = 256, kTileWaves = kTileThreads / kWave;
 
+// a token's row in LDS is an odd number of 16-byte pieces: the reads of eight lanes meet no bank twice
 template <int D>
-constexpr int tile_lds_bytes() { return 2 * kTileCols * D * 2 + kTileRows * D * (2 + 4) + kTileRows * kTileCols * 8 + 2 * kTileRows * 4; }
+constexpr int tile_ld_v() { return D + 2; }
+template <int D>
+constexpr int tile_ld_dv() { return D + 4; }
+template <int D>
+constexpr int tile_lds_bytes() { return 2 * kTileCols * D * 2 + kTileCols * (tile_ld_v<D>() * 8 + tile_ld_dv<D>() * 4) + D * 8; }
 
 // sum += x, the rounding error carried along (a lane adds tens of thousands of rows); an infinite sum stays infinite
 __device__ __forceinline__ void add_carried(float &sum, float &carry, float x)
@@ -221,7 +227,7 @@ __device__ __forceinline__ void add_carried(float &sum, float &carry, float x)
 }
 
 template <int D>
-__global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
+__global__ __launch_bounds__(kTileThreads, 2) void impact_tiles_kernel(
     int n, int n_q_heads, int n_kv_heads, int rows_per_piece,
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_fresh, const uint16_t *__restrict__ v_fresh,
     const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
@@ -230,33 +236,30 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
     float *__restrict__ part /* [pieces][3][n_kv_heads][n]: value, key, both */)
 {
     constexpr int PIECES = D / 8;                            // 16-byte pieces of a bf16 row
-    constexpr int CG = D / kTileCh, RS = 8 / CG, RPW = kTileRows / RS;     // channel groups, row shares, rows per wave
+    constexpr int LDV = tile_ld_v<D>(), LDD = tile_ld_dv<D>();
     extern __shared__ __attribute__((aligned(16))) char ilds[];
-    uint16_t *colKf = reinterpret_cast<uint16_t *>(ilds);    // [64][D], pieces XOR-swizzled by the row
+    uint64_t *colV = reinterpret_cast<uint64_t *>(ilds);     // [32][LDV]: channel c in 16-bit slot c & 3, zeros beside it
+    uint64_t *minus = colV + kTileCols * LDV;                // [D]: -1 likewise
+    float *colDV = reinterpret_cast<float *>(minus + D);     // [32][LDD]
+    uint16_t *colKf = reinterpret_cast<uint16_t *>(colDV + kTileCols * LDD);            // [32][D], pieces XOR-swizzled by the row
     uint16_t *colKc = colKf + kTileCols * D;
-    uint16_t *rowQ = colKc + kTileCols * D;                  // [32][D], likewise
-    float *rowH = reinterpret_cast<float *>(rowQ + kTileRows * D);         // [32][D]
-    float2 *at = reinterpret_cast<float2 *>(rowH + kTileRows * D);         // [32][64] (a, t)
-    float *rowL = reinterpret_cast<float *>(at + kTileRows * kTileCols);   // [32] lse
-    int *rowJ = reinterpret_cast<int *>(rowL + kTileRows);                 // [32] query row
 
     const int tid = threadIdx.x, lane = tid & 63, ln = tid & 31, hf = (tid >> 5) & 1;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cg = wave % CG, rs = wave / CG;
     const int g = blockIdx.y, piece = blockIdx.z;
     const int grp = n_q_heads / n_kv_heads;
     const int n_cols = list ? *count : n;
     const int l0 = blockIdx.x * kTileCols;
     if (l0 >= n_cols) return;                                // uniform; these columns are nobody's
     auto token = [&](int c) { const int l = min(l0 + c, n_cols - 1); return list ? list[l] : l; };
-    const int i = token(lane);
-    const bool col_ok = l0 + lane < n_cols;
+    const int i = token(ln);
+    const bool col_ok = l0 + ln < n_cols;
     const int i0 = __builtin_amdgcn_readfirstlane(i), i_last = __builtin_amdgcn_readlane(i, min(kTileCols, n_cols - l0) - 1);
     // rows j of this piece that the first (lowest) token can be seen by
     const int j0 = max(i0, piece * rows_per_piece), j1 = min(n, (piece + 1) * rows_per_piece);
     const int64_t stride = (int64_t)n_kv_heads * n, o = 3 * stride * piece + (int64_t)g * n + i;
     if (j0 >= j1) {
-        if (wave == 0 && col_ok) { part[o] = 0.f; part[o + stride] = 0.f; part[o + 2 * stride] = 0.f; }
+        if (tid < kTileCols && col_ok) { part[o] = 0.f; part[o + stride] = 0.f; part[o + 2 * stride] = 0.f; }
         return;
     }
     for (int e = tid; e < kTileCols * PIECES; e += kTileThreads) {
@@ -265,137 +268,148 @@ __global__ __launch_bounds__(kTileThreads, 4) void impact_tiles_kernel(
         const int dst = t * D + 8 * (pc ^ (t & (PIECES - 1)));
         *reinterpret_cast<uint4 *>(colKf + dst) = *reinterpret_cast<const uint4 *>(k_fresh + from);
         *reinterpret_cast<uint4 *>(colKc + dst) = *reinterpret_cast<const uint4 *>(k_cache + from);
-    }
-    float v[kTileCh], dv[kTileCh], dv_l1 = 0.f;
-#pragma unroll
-    for (int c8 = 0; c8 < kTileCh / 8; ++c8) {
-        const int64_t from = ((int64_t)i * n_kv_heads + g) * D + kTileCh * cg + 8 * c8;
         const uint4 f = *reinterpret_cast<const uint4 *>(v_fresh + from), x = *reinterpret_cast<const uint4 *>(v_cache + from);
         const uint32_t fw[4] = {f.x, f.y, f.z, f.w}, xw[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            v[8 * c8 + 2 * u] = bf16_lo(fw[u]);
-            v[8 * c8 + 2 * u + 1] = bf16_hi(fw[u]);
-            dv[8 * c8 + 2 * u] = bf16_lo(xw[u]) - bf16_lo(fw[u]);
-            dv[8 * c8 + 2 * u + 1] = bf16_hi(xw[u]) - bf16_hi(fw[u]);
+            const float v0 = bf16_lo(fw[u]), v1 = bf16_hi(fw[u]);
+            *reinterpret_cast<ulonglong2 *>(colV + t * LDV + 8 * pc + 2 * u) = make_ulonglong2((uint64_t)(fw[u] & 0xffffu) << (u & 1 ? 32 : 0),
+                                                                                            (uint64_t)(fw[u] & 0xffff0000u) << (u & 1 ? 32 : 0));
+            *reinterpret_cast<float2 *>(colDV + t * LDD + 8 * pc + 2 * u) = make_float2(bf16_lo(xw[u]) - v0, bf16_hi(xw[u]) - v1);
         }
     }
-#pragma unroll
-    for (int c = 0; c < kTileCh; ++c) dv_l1 += fabsf(dv[c]);
+    for (int e = tid; e < D; e += kTileThreads) minus[e] = (uint64_t)0xbf80u << (16 * (e & 3));
+    __syncthreads();
 
-    // a block's rows (one 16-byte piece of H and of Q per thread) are fetched while the block before is worked on
+    // v - h of one channel, 32 rows x 32 tokens, is a product over the lower half-wave's four slots of the contraction (four channels
+    // of the row's H with -1 in one of them) and the upper one's (ones with the token's V in the same slot)
+    const uint64_t *b_from = hf ? colV + ln * LDV : minus;
+    const float *dv_from = colDV + ln * LDD;
     const uint32_t n_pairs = (uint32_t)(j1 - j0) * (uint32_t)grp;          // flattened (row, head in group)
-    const bool stages = tid < kTileRows * PIECES;
-    const int st_pc = tid % PIECES, st_r = tid / PIECES;
-    uint4 h_next = make_uint4(0, 0, 0, 0), q_next = make_uint4(0, 0, 0, 0);
-    float l_next = 0.f;
-    int j_next = -1;
-    auto fetch = [&](uint32_t p0) {
-        if (stages) {
-            const uint32_t p = min(p0 + (uint32_t)st_r, n_pairs - 1), jr = p / (uint32_t)grp;
-            const int64_t from = ((int64_t)(j0 + (int)jr) * n_q_heads + g * grp + (int)(p - jr * (uint32_t)grp)) * D + 8 * st_pc;
-            h_next = *reinterpret_cast<const uint4 *>(h_fresh + from);
-            q_next = *reinterpret_cast<const uint4 *>(q + from);
-        }
-        if (tid < kTileRows) {
-            const uint32_t p = min(p0 + (uint32_t)tid, n_pairs - 1), jr = p / (uint32_t)grp;
-            l_next = lse[(int64_t)(j0 + (int)jr) * n_q_heads + g * grp + (int)(p - jr * (uint32_t)grp)];
-            j_next = p0 + (uint32_t)tid < n_pairs ? j0 + (int)jr : -1;     // -1: past the end, contributes nothing
-        }
-    };
-    // the token of this lane's column in the matrix-core step below (waves 0 and 1), out of reach if there is none
-    const int my_token = __shfl((int)col_ok, (32 * wave + ln) & 63) ? __shfl(i, (32 * wave + ln) & 63) : 0x7fffffff;
+    const int my_token = col_ok ? i : 0x7fffffff;            // out of reach if the column has none
     float sum_a = 0.f, sum_k = 0.f, sum_kv = 0.f, carry_a = 0.f, carry_k = 0.f, carry_kv = 0.f;
-    fetch(0);
-    for (uint32_t p0 = 0; p0 < n_pairs; p0 += kTileRows) {
-        __syncthreads();                                     // the block before has been consumed
-        if (stages) {
-            float *dst = rowH + st_r * D + 8 * st_pc;
-            *reinterpret_cast<float4 *>(dst) = make_float4(bf16_lo(h_next.x), bf16_hi(h_next.x), bf16_lo(h_next.y), bf16_hi(h_next.y));
-            *reinterpret_cast<float4 *>(dst + 4) = make_float4(bf16_lo(h_next.z), bf16_hi(h_next.z), bf16_lo(h_next.w), bf16_hi(h_next.w));
-            *reinterpret_cast<uint4 *>(rowQ + st_r * D + 8 * (st_pc ^ (st_r & (PIECES - 1)))) = q_next;
+    for (uint32_t p0 = (uint32_t)(wave * kTileRows); p0 < n_pairs; p0 += kTileWaves * kTileRows) {
+        const uint32_t p = min(p0 + (uint32_t)ln, n_pairs - 1), jr = p / (uint32_t)grp;
+        const int64_t row = (int64_t)(j0 + (int)jr) * n_q_heads + g * grp + (int)(p - jr * (uint32_t)grp);
+        const float row_lse = lse[row];
+        const int row_j = p0 + (uint32_t)ln < n_pairs ? j0 + (int)jr : -1;                // -1: past the end, contributes nothing
+        const uint4 *q_from = reinterpret_cast<const uint4 *>(q + row * D) + hf, *h_from = reinterpret_cast<const uint4 *>(h_fresh + row * D);
+        uint4 qa[D / 16], h[PIECES];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) qa[ks] = q_from[2 * ks];
+#pragma unroll
+        for (int c8 = 0; c8 < PIECES; ++c8) {
+            h[c8] = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+            if (hf == 0) h[c8] = h_from[c8];
         }
-        if (tid < kTileRows) { rowL[tid] = l_next; rowJ[tid] = j_next; }
-        __syncthreads();
-        if (p0 + kTileRows < n_pairs) fetch(p0 + kTileRows);
-        if (wave < 2) {
-            // 32 rows x tokens 32 wave .. 32 wave + 31; entry e of a lane is row 8 (e >> 2) + 4 hf + (e & 3), token 32 wave + ln
-            imp_floatx16 sf, sc;
+        // 32 rows x 32 tokens; entry e of a lane is row 8 (e >> 2) + 4 hf + (e & 3), token ln
+        imp_floatx16 sf, sc;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) { sf[e] = 0.f; sc[e] = 0.f; }
-            const int t = 32 * wave + ln;
-#pragma unroll 2
-            for (int ks = 0; ks < D / 16; ++ks) {            // (unrolled further, its operands push V and dV out of the registers)
-                const int pc = 2 * ks + hf;
-                const imp_bf16x8 qa = *reinterpret_cast<const imp_bf16x8 *>(rowQ + ln * D + 8 * (pc ^ (ln & (PIECES - 1))));
-                const imp_bf16x8 kf = *reinterpret_cast<const imp_bf16x8 *>(colKf + t * D + 8 * (pc ^ (t & (PIECES - 1))));
-                const imp_bf16x8 kc = *reinterpret_cast<const imp_bf16x8 *>(colKc + t * D + 8 * (pc ^ (t & (PIECES - 1))));
-                sf = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kf, sf, 0, 0, 0);
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kc, sc, 0, 0, 0);
-            }
+        for (int e = 0; e < 16; ++e) { sf[e] = 0.f; sc[e] = 0.f; }
 #pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {                 // rows 8 e4 + 4 hf .. + 3
-                const float4 l4 = *reinterpret_cast<const float4 *>(rowL + 8 * e4 + 4 * hf);
-                const int4 j4 = *reinterpret_cast<const int4 *>(rowJ + 8 * e4 + 4 * hf);
-                const float le[4] = {l4.x, l4.y, l4.z, l4.w};
-                const int je[4] = {j4.x, j4.y, j4.z, j4.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float a = __expf(scale * sf[4 * e4 + u] - le[u]);
-                    // causal: row j sees token i; rows past the end carry -1, tokens past the list see none
-                    at[(8 * e4 + 4 * hf + u) * kTileCols + t] = make_float2(je[u] >= my_token ? a : 0.f, scale * (sc[4 * e4 + u] - sf[4 * e4 + u]));
-                }
-            }
+        for (int ks = 0; ks < D / 16; ++ks) {
+            const int at = ln * D + 8 * ((2 * ks + hf) ^ (ln & (PIECES - 1)));
+            const imp_bf16x8 qv = __builtin_bit_cast(imp_bf16x8, qa[ks]);
+            sf = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, *reinterpret_cast<const imp_bf16x8 *>(colKf + at), sf, 0, 0, 0);
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qv, *reinterpret_cast<const imp_bf16x8 *>(colKc + at), sc, 0, 0, 0);
         }
-        __syncthreads();
+        float a[16], t[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = 8 * (e >> 2) + 4 * hf + (e & 3);
+            a[e] = __expf(scale * sf[e] - __shfl(row_lse, r));
+            a[e] = __shfl(row_j, r) >= my_token ? a[e] : 0.f;      // causal: row j sees token i
+            t[e] = scale * (sc[e] - sf[e]);
+        }
         // |key term|_1 = a |t| sum_c |v_c - h_c| and |both|_1 = a sum_c |dv_c + t (v_c - h_c)|
+        imp_floatx16 nk, nkv;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { nk[e] = 0.f; nkv[e] = 0.f; }
+        const imp_floatx16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto row_h = [&](int c) -> imp_s16x4 {               // the A operand: channels c & ~3 .. + 3
+            const uint4 w = h[c >> 3];
+            return __builtin_bit_cast(imp_s16x4, c & 4 ? (uint64_t)w.w << 32 | w.z : (uint64_t)w.y << 32 | w.x);
+        };
+        ulonglong2 b01 = *reinterpret_cast<const ulonglong2 *>(b_from), b23 = *reinterpret_cast<const ulonglong2 *>(b_from + 2);
+        float4 dv = *reinterpret_cast<const float4 *>(dv_from);
+        imp_floatx16 x = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(row_h(0), __builtin_bit_cast(imp_s16x4, (uint64_t)b01.x), zero, 0, 0, 0);
+#pragma unroll
+        for (int c4 = 0; c4 < D / 4; ++c4) {
+            const int next = c4 + 1 < D / 4 ? c4 + 1 : c4;
+            const ulonglong2 b01_next = *reinterpret_cast<const ulonglong2 *>(b_from + 4 * next), b23_next = *reinterpret_cast<const ulonglong2 *>(b_from + 4 * next + 2);
+            const float4 dv_next = *reinterpret_cast<const float4 *>(dv_from + 4 * next);
+            const uint64_t be[4] = {b01.y, b23.x, b23.y, b01_next.x};
+            const float dve[4] = {dv.x, dv.y, dv.z, dv.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                // the next channel's differences run beside this channel's vector work; nk and nkv pass through the empty statement,
+                // which keeps the compiler from drawing the MFMAs of all channels together
+                imp_floatx16 x_next = x;
+                if (4 * c4 + u + 1 < D) {
+                    x_next = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(row_h(4 * c4 + u + 1), __builtin_bit_cast(imp_s16x4, be[u]), zero, 0, 0, 0);
+                    asm volatile("" : "+v"(nk), "+v"(nkv));
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    nk[e] += fabsf(x[e]);
+                    nkv[e] += fabsf(fmaf(t[e], x[e], dve[u]));
+                }
+                x = x_next;
+            }
+            b01 = b01_next;
+            b23 = b23_next;
+            dv = dv_next;
+        }
+        // a slot's zero times an infinite or NaN H is a NaN in its three neighbours: then channel by channel
+        float any = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) any += nk[e];
+        if (__builtin_amdgcn_ballot_w64(any != any) != 0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint16_t *h_row = h_fresh + __shfl((long long)row, 8 * (e >> 2) + 4 * hf + (e & 3)) * D;
+                float k1 = 0.f, kv1 = 0.f;
+#pragma unroll 1
+                for (int c = 0; c < D; ++c) {
+                    const float d = __uint_as_float((uint32_t)(colV[ln * LDV + c] >> (16 * (c & 3))) << 16) - __uint_as_float((uint32_t)h_row[c] << 16);
+                    k1 += fabsf(d);
+                    kv1 += fabsf(fmaf(t[e], d, colDV[ln * LDD + c]));
+                }
+                nk[e] = k1;
+                nkv[e] = kv1;
+            }
+        }
         // (a pair that is none, a row before its token or past the end, adds nothing even where its norm is Inf or NaN)
         const bool all_pairs = j0 + (int)(p0 / (uint32_t)grp) >= i_last && p0 + kTileRows <= n_pairs;     // uniform
-        float blk_a = 0.f, blk_k = 0.f, blk_kv = 0.f;
-#pragma unroll 1
-        for (int rr = 0; rr < RPW; ++rr) {
-            const int r = rs * RPW + rr;
-            const float2 w = at[r * kTileCols + lane];
-            const float4 *h = reinterpret_cast<const float4 *>(rowH + r * D + kTileCh * cg);      // the same for every lane
-            float nk[2] = {0.f, 0.f}, nkv[2] = {0.f, 0.f};
+        float blk_a[4] = {0.f, 0.f, 0.f, 0.f}, blk_k[4] = {0.f, 0.f, 0.f, 0.f}, blk_kv[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c4 = 0; c4 < kTileCh / 4; ++c4) {
-                const float4 hv = h[c4];
-                const float he[4] = {hv.x, hv.y, hv.z, hv.w};
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float d = v[4 * c4 + u] - he[u];
-                    nk[u & 1] += fabsf(d);
-                    nkv[u & 1] += fabsf(fmaf(w.y, d, dv[4 * c4 + u]));
-                }
-            }
-            blk_a += w.x;
-            const float to_k = fmaf(w.x * fabsf(w.y), nk[0] + nk[1], blk_k), to_kv = fmaf(w.x, nkv[0] + nkv[1], blk_kv);
-            const bool pair = all_pairs || rowJ[r] >= i;
-            blk_k = pair ? to_k : blk_k;
-            blk_kv = pair ? to_kv : blk_kv;
+        for (int e = 0; e < 16; ++e) {
+            const bool pair = all_pairs || __shfl(row_j, 8 * (e >> 2) + 4 * hf + (e & 3)) >= my_token;
+            blk_a[e & 3] += a[e];
+            const float to_k = fmaf(a[e] * fabsf(t[e]), nk[e], blk_k[e & 3]), to_kv = fmaf(a[e], nkv[e], blk_kv[e & 3]);
+            blk_k[e & 3] = pair ? to_k : blk_k[e & 3];
+            blk_kv[e & 3] = pair ? to_kv : blk_kv[e & 3];
         }
-        add_carried(sum_a, carry_a, blk_a);
-        add_carried(sum_k, carry_k, blk_k);
-        add_carried(sum_kv, carry_kv, blk_kv);
+        add_carried(sum_a, carry_a, (blk_a[0] + blk_a[1]) + (blk_a[2] + blk_a[3]));
+        add_carried(sum_k, carry_k, (blk_k[0] + blk_k[1]) + (blk_k[2] + blk_k[3]));
+        add_carried(sum_kv, carry_kv, (blk_kv[0] + blk_kv[1]) + (blk_kv[2] + blk_kv[3]));
     }
-    // ---- the eight waves' shares, added in wave order; a column's A and |dV|_1 come once per row share / channel group ----
+    // ---- the shares of the waves and half-waves, added in their order ----
     __syncthreads();
-    float *red = rowH;                                       // [4][8][64]
-    static_assert(4 * 8 * kTileCols * 4 <= kTileRows * D * 4 + kTileRows * kTileCols * 8, "fits rowH and at");
-    red[(0 * 8 + wave) * kTileCols + lane] = sum_a;
-    red[(1 * 8 + wave) * kTileCols + lane] = sum_k;
-    red[(2 * 8 + wave) * kTileCols + lane] = sum_kv;
-    red[(3 * 8 + wave) * kTileCols + lane] = dv_l1;
+    float *red = reinterpret_cast<float *>(colKf);           // [3][4][64]
+    static_assert(3 * kTileWaves * 64 * 4 <= 2 * kTileCols * 64 * 2, "fits the smaller K tiles");
+    red[(0 * kTileWaves + wave) * 64 + lane] = sum_a;
+    red[(1 * kTileWaves + wave) * 64 + lane] = sum_k;
+    red[(2 * kTileWaves + wave) * 64 + lane] = sum_kv;
     __syncthreads();
-    if (wave == 0 && col_ok) {
+    if (tid < kTileCols && col_ok) {
         double sa = 0., sk = 0., skv = 0., l1 = 0.;          // (a few additions: rounded once, where the share is stored)
-        for (int w = 0; w < 8; ++w) {
-            if (w % CG == 0) sa += red[(0 * 8 + w) * kTileCols + lane];
-            sk += red[(1 * 8 + w) * kTileCols + lane];
-            skv += red[(2 * 8 + w) * kTileCols + lane];
-            if (w < CG) l1 += red[(3 * 8 + w) * kTileCols + lane];
+        for (int w = 0; w < 2 * kTileWaves; ++w) {
+            sa += red[0 * kTileWaves * 64 + 32 * w + ln];
+            sk += red[1 * kTileWaves * 64 + 32 * w + ln];
+            skv += red[2 * kTileWaves * 64 + 32 * w + ln];
         }
+        for (int c = 0; c < D; ++c) l1 += fabsf(colDV[ln * LDD + c]);
         // value direction: (sum of A over rows and heads of the group) * |dV|_1, nothing from a piece that does not see the token
         part[o] = sa == 0. ? 0.f : (float)(sa * l1);
         part[o + stride] = (float)sk;
@@ -438,11 +452,11 @@ constexpr size_t impact_lds_bytes()
     return sizeof(float) * (4 * D * kImpCols + 2 * kImpBlock * D + 2 * kImpBlock + 3 * kImpRowLanes * kImpCols);
 }
 
-// Pieces of the rows (bf16): 64 tokens of a KV head see up to n rows, and the launch is a triangle of such strips;
-// some 16384 workgroups, half of them with rows, even it out over 512 resident ones.  A piece is a whole number of blocks of
-// kTileRows (row, head in group) pairs, as nearly as its rows allow: a block costs the same however few of its pairs there are
-// (256 tokens of 64 heads in groups of one, pieces of 16 rows: 134 us, 77 like this; 16 Qwen-shaped tokens, one piece of 3.5 blocks: 41, 14).
-constexpr int kImpUnits = 16384, kImpMaxPieces = 32;
+// Pieces of the rows (bf16): 32 tokens of a KV head see up to n rows, and the launch is a triangle of such strips;
+// some 16384 workgroups, half of them with rows, even it out over 512 resident ones (8192 Qwen-shaped tokens 7.54 ms, with 8192
+// workgroups 7.62, 4096 8.00).  A piece is a whole number of rounds of the four waves, 128 (row, head in group) pairs, as nearly as its
+// rows allow: a round costs the same however few of its pairs there are (256 Yi-shaped tokens, pieces of 64 pairs: 52 us, 33 like this).
+constexpr int kImpUnits = 16384, kImpMaxPieces = 32, kImpRound = kTileRows * kTileWaves;
 struct ImpactPieces {
     int n, rows;            // pieces, rows of each
 };
@@ -458,7 +472,7 @@ ImpactPieces impact_pieces(const kvs_shape *shape, int64_t n)
     if (p > impact_most_pieces(shape, n)) p = impact_most_pieces(shape, n);
     if (p < 1) p = 1;
     int64_t rows = (n + p - 1) / p;
-    rows = (rows * grp + kTileRows - 1) / kTileRows * kTileRows / grp;
+    rows = (rows * grp + kImpRound - 1) / kImpRound * kImpRound / grp;
     return {(int)((n + rows - 1) / rows), (int)rows};
 }
 size_t impact_part_bytes(const kvs_shape *shape, int64_t n, int pieces) { return sizeof(float) * 3 * (size_t)pieces * (size_t)shape->n_kv_heads * (size_t)n; }
@@ -473,7 +487,7 @@ size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
     // more than kImpUnits strips' worth of sums, unless it is one.
     const int64_t most = impact_most_pieces(shape, n_tokens);
     size_t part = impact_part_bytes(shape, n_tokens, (int)most);
-    const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * kTileCols;
+    const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * 64;
     if (part > strips) part = strips > one ? strips : one;
     return part + sizeof(int32_t) * ((size_t)n_tokens + 1) + 256;
 }
@@ -508,7 +522,7 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
         const ImpactPieces cut = impact_pieces(shape, n_tokens);
         pieces = cut.n;
         // (one strip of tokens is no shorter for a list: all are computed, and those not reused dropped at the end)
-        int32_t *list = reused && n > kTileCols ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
+        int32_t *list = reused && n > 64 ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
         int32_t *count = list ? list + n : nullptr;
         if (list) {
             hipLaunchKernelGGL(impact_list_kernel, dim3(1), dim3(kListThreads), 0, hs, n, reused, list, count);

@@ -124,3 +124,30 @@ def test_an_infinite_movement_stays_infinite(hq, hk, d):
             want = b.copy()
             want[i] = moved
             np.testing.assert_array_equal(a, want, err_msg=name)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("hq,hk,d", [(4, 2, 128), (3, 3, 64)])
+def test_an_odd_output_row_reaches_only_its_own_sums(hq, hk, d, value):
+    """One infinite or NaN element of H: every token that its row sees has an infinite or NaN key term and sum, the later ones
+    what they have without it."""
+    n, row = 150, 77
+    print(f"impact: H with {value} at row {row}, {hq}x{hk} heads, head_dim {d}", flush=True)
+    lay = synth.make_layer(synth.scaled(synth.LLAMA, n, n_q_heads=hq, n_kv_heads=hk, head_dim=d, coverage=1.0))
+    dev = {x: lay[x].cuda() for x in ("q", "k_fresh", "v_fresh", "k_cache", "v_cache")}
+    gen = torch.Generator().manual_seed(n)
+    h, lse = (torch.randn((n, hq, d), generator=gen) / 4).to(torch.bfloat16), torch.full((n, hq), 3.0)
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("first_order_impact", sh, 1, n), dtype=torch.uint8, device="cuda")
+    res = []
+    for odd in (False, True):
+        if odd:
+            h[row, 1, 5] = value
+        out = [torch.zeros(n, device="cuda") for _ in range(3)]
+        B.kvs_first_order_impact(sh, n, dev["q"], dev["k_fresh"], dev["v_fresh"], dev["k_cache"], dev["v_cache"], h.cuda(), lse.cuda(), None, 1.0, *out, ws)
+        res.append([o.cpu().numpy() for o in out])
+    np.testing.assert_array_equal(res[1][0], res[0][0])
+    for x, y in zip(res[1][1:], res[0][1:]):
+        assert np.all(np.isnan(x[: row + 1]) if np.isnan(value) else x[: row + 1] == np.inf)
+        # the same fp32 sums of d terms with their last additions in another order at most
+        np.testing.assert_allclose(x[row + 1:], y[row + 1:], rtol=d * 2.0 ** -24)
