@@ -2,8 +2,9 @@
 // positive): the same two sweeps (row statistics, then column sums of the weights; Alg. 1 steps 1-2) on the fp32
 // matrix instruction.  A workgroup owns 16 fixed rows of a KV head (query rows, flattened (token, head-in-group), in sweep
 // 1; keys in sweep 2); its eight waves deal the streamed 16-row tiles among themselves and read them straight from global
-// memory.  A lane's results belong to one fixed row, so the running sums are a lane's own and the loop has no cross-lane
-// traffic; the 32 shares of a fixed row meet in LDS, in a fixed order.
+// memory, the next tile while one is worked on.  A lane's results belong to one fixed row, so the running sums are a lane's own and
+// the loop has no cross-lane traffic; the 32 shares of a fixed row meet in LDS, one a lane, in a fixed tree (one thread a row: the
+// five calls on the 512-token layer 43.2 us, 41.7 like this, and twice the rms error of alpha: 9.9e-8 against 4.3e-8).
 //
 // Measured, fp32 512 tokens x 4 heads, head_dim 64: 57 -> 18 us for both sweeps (before: one wave per row on the vector
 // units, element by element).  Meant for small layers; nothing is staged or shared between workgroups.
@@ -26,7 +27,7 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
                                                                 const void *__restrict__ k, float scale,
                                                                 const float2 *__restrict__ row_stats, float2 *__restrict__ stats, float *__restrict__ alpha)
 {
-    __shared__ float m_s[kCfWaves * 4][kCfRows], z_s[kCfWaves * 4][kCfRows];
+    __shared__ float m_s[kCfWaves * 4][kCfRows + 1], z_s[kCfWaves * 4][kCfRows + 1];
     const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = n_q_heads / n_kv_heads;
@@ -44,15 +45,26 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
     const int t_begin = SWEEP == 1 ? 0 : fb * grp / kCfRows, t_end = SWEEP == 1 ? last / grp / kCfRows + 1 : (n_qrows + kCfRows - 1) / kCfRows;
     const int n_stream = SWEEP == 1 ? n : n_qrows;
     float m = kLowest, z = 0.f;
-    for (int t = t_begin + wave; t < t_end; t += kCfWaves) {
-        float x[D / 4];
+    // the next tile's rows are on their way while a tile is worked on (past the last tile the last row again, never used)
+    float x_next[D / 4];
+    float2 st_next[4];
+    auto fetch = [&](int t) {
         const int sr = min(t * kCfRows + m16, n_stream - 1);
-        load_quarter<DTYPE, D>(SWEEP == 1 ? k : q, SWEEP == 1 ? k_row(sr) : q_row(sr), kk, x);
-        float2 st4[4];
+        load_quarter<DTYPE, D>(SWEEP == 1 ? k : q, SWEEP == 1 ? k_row(sr) : q_row(sr), kk, x_next);
         if (SWEEP == 2) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) st4[r] = row_stats[(int64_t)g * n_qrows + min(t * kCfRows + 4 * kk + r, n_stream - 1)];
+            for (int r = 0; r < 4; ++r) st_next[r] = row_stats[(int64_t)g * n_qrows + min(t * kCfRows + 4 * kk + r, n_stream - 1)];
         }
+    };
+    fetch(t_begin + wave);
+    for (int t = t_begin + wave; t < t_end; t += kCfWaves) {
+        float x[D / 4];
+        float2 st4[4];
+#pragma unroll
+        for (int c = 0; c < D / 4; ++c) x[c] = x_next[c];
+#pragma unroll
+        for (int r = 0; SWEEP == 2 && r < 4; ++r) st4[r] = st_next[r];
+        fetch(t + kCfWaves);
         const f32x4 s = dots<D>(x, fx);
         float y[4];
         bool sees[4];
@@ -79,19 +91,21 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
     m_s[wave * 4 + kk][m16] = m;
     z_s[wave * 4 + kk][m16] = z;
     __syncthreads();
-    if (tid < kCfRows && fb + tid < n_fixed) {
-        float mt = kLowest, zt = 0.f;
-        if (SWEEP == 1) {
+    // 32 lanes a row, their shares added in a fixed tree
+    static_assert(kCfWaves * 4 == 32 && kCfThreads == 32 * kCfRows, "one share a lane");
+    const int share = tid & 31, row = tid >> 5;
+    float zt = z_s[share][row], mt = m_s[share][row];
+    if (SWEEP == 1) {
+        const float mine = mt;
 #pragma unroll
-            for (int w = 0; w < kCfWaves * 4; ++w) mt = fmaxf(mt, m_s[w][tid]);
+        for (int o = 16; o >= 1; o >>= 1) mt = fmaxf(mt, __shfl_xor(mt, o));
+        zt *= expf(mine - mt);
+    }
 #pragma unroll
-            for (int w = 0; w < kCfWaves * 4; ++w) zt += z_s[w][tid] * expf(m_s[w][tid] - mt);
-            stats[(int64_t)g * n_qrows + fb + tid] = make_float2(mt, 1.0f / zt);
-        } else {
-#pragma unroll
-            for (int w = 0; w < kCfWaves * 4; ++w) zt += z_s[w][tid];
-            alpha[(int64_t)g * n + fb + tid] = zt;
-        }
+    for (int o = 16; o >= 1; o >>= 1) zt += __shfl_xor(zt, o);
+    if (share == 0 && fb + row < n_fixed) {
+        if (SWEEP == 1) stats[(int64_t)g * n_qrows + fb + row] = make_float2(mt, 1.0f / zt);
+        else alpha[(int64_t)g * n + fb + row] = zt;
     }
 }
 
