@@ -310,7 +310,7 @@ __global__ __launch_bounds__(PNT, 1) void project_qkv_kernel(
 //   * the four slices' sums meet in LDS at the end, 32 tokens at a time, where the rotation pairs sit in one thread
 //     and rows leave as whole segments.
 // What bounds it: one tile on an otherwise idle chip runs at the global -> LDS rate (128 x 160 tile, hidden 4096: 27 us;
-// 36 us before fetches and loads were dealt out between the MFMAs).  With all units busy (41 us at 656 tokens) no unit is
+// 36 us before fetches and loads were dealt out between the MFMAs).  With all units busy (39 us at 656 tokens) no unit is
 // saturated: matrix cores busy 38 % of the launch, L2 at 13 TB/s with 81 % hits, LDS port 18 %; the waves wait 37 % of their
 // time.  Starting every tile at its own place in the contraction loses the shared L2 lines: 71 us.
 constexpr int FNT = 512;
@@ -326,7 +326,7 @@ constexpr int few_slots(int fbw, int tb)
 }
 constexpr int few_lds_bytes(int fbw, int tb)
 {
-    const int ring = few_slots(fbw, tb) * (64 * fbw + 32 * tb) * FROW_B, join = 4 * 32 * (64 * fbw + 4) * 4;
+    const int ring = few_slots(fbw, tb) * (64 * fbw + 32 * tb) * FROW_B, join = (tb > 1 ? 2 : 1) * 4 * 32 * (64 * fbw + 4) * 4;
     return ring > join ? ring : join;
 }
 
@@ -386,6 +386,18 @@ __global__ __launch_bounds__(FNT, 2) void project_few_kernel(
     const u32x4_t wrs = make_rsrc(w, (uint64_t)(n_q_heads + 2 * n_kv_heads) * PD * row_bytes);
     const u32x4_t xrs = make_rsrc(x, (uint64_t)n_tokens * row_bytes);
     const uint32_t lds_base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)plds);
+    // the epilogue's thread: four channels of a token and their partners 64 on, PER_TOK threads per token; its tokens' positions
+    constexpr int PER_TOK = 8 * FBW;
+    const int my_tok = tid / PER_TOK, my_c = 4 * (tid % PER_TOK);   // channel inside the tile's lower half
+    const bool turned = rope != nullptr && head < n_q_heads + n_kv_heads;
+    int my_pos[TB];
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) my_pos[tb] = turned ? sel_pos[min(m0 + 32 * tb + my_tok, n_sel - 1)] : 0;
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+        my_pos[tb] = min(max(my_pos[tb], 0), rope_positions - 1);   // memory safety; the caller guarantees the range
+        asm volatile("" : "+v"(my_pos[tb]));
+    }
     // the offsets above came through ordinary loads: none may be outstanding when the counted waits begin
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // load i of the wave's share of a stage; steps past the end repeat the last one (their slots are never read)
@@ -473,20 +485,30 @@ __global__ __launch_bounds__(FNT, 2) void project_few_kernel(
     // nothing may still be on its way into LDS when it changes its use
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
 
-    // ---- epilogue, 32 tokens at a time: [kg][token][feature] sums in LDS, 16 bytes of padding per row
+    // ---- epilogue, 32 tokens at a time: [kg][token][feature] sums in LDS, 16 bytes of padding per row.  The positions were read
+    // before the sweep, the rotary rows of all token blocks are asked for before the first one is joined, and the blocks alternate
+    // between two places in LDS, one barrier each: block by block, two dependent round trips and two barriers each cost 16 tokens
+    // of 4096 11.8 -> 11.3 us, 96 tokens 16.1 -> 15.1, 384 27.5 -> 26.2, 656 41.2 -> 39.4; the rotation is now as good as free (39.0 without).
     constexpr int JROW = WROWS + 4;                 // floats
-    float *join = reinterpret_cast<float *>(plds);
+    const int c = c0 + my_c;                        // channel of the head, its partner is c + 64
+    float4 cs[TB][2];
+    if (turned) {
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+            const float4 *row = reinterpret_cast<const float4 *>(rope + ((int64_t)my_pos[tb] * (PD / 2) + c) * 2);
+            cs[tb][0] = row[0];
+            cs[tb][1] = row[1];
+        }
+    }
     uint16_t *dst;
     int heads_of_dst, h_local;
     if (head < n_q_heads) { dst = q_out; heads_of_dst = n_q_heads; h_local = head; }
     else if (head < n_q_heads + n_kv_heads) { dst = k_out; heads_of_dst = n_kv_heads; h_local = head - n_q_heads; }
     else { dst = v_out; heads_of_dst = n_kv_heads; h_local = head - n_q_heads - n_kv_heads; }
-    const bool turned = rope != nullptr && head < n_q_heads + n_kv_heads;
-    constexpr int PER_TOK = 8 * FBW;                // threads per token: four channels and their partners 64 on each
-    const int my_tok = tid / PER_TOK, my_c = 4 * (tid % PER_TOK);   // channel inside the tile's lower half
+    __syncthreads();
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-        __syncthreads();
+        float *join = reinterpret_cast<float *>(plds) + (tb & 1) * (4 * 32 * JROW);
 #pragma unroll
         for (int fb = 0; fb < FBW; ++fb)
 #pragma unroll
@@ -504,12 +526,8 @@ __global__ __launch_bounds__(FNT, 2) void project_few_kernel(
                 y1[0] += a.x; y1[1] += a.y; y1[2] += a.z; y1[3] += a.w;
                 y2[0] += b.x; y2[1] += b.y; y2[2] += b.z; y2[3] += b.w;
             }
-            const int c = c0 + my_c;                // channel of the head, its partner is c + 64
             if (turned) {
-                int p = sel_pos[t];
-                p = min(max(p, 0), rope_positions - 1);         // memory safety; the caller guarantees the range
-                const float4 *cs = reinterpret_cast<const float4 *>(rope + ((int64_t)p * (PD / 2) + c) * 2);
-                const float4 cs01 = cs[0], cs23 = cs[1];
+                const float4 cs01 = cs[tb][0], cs23 = cs[tb][1];
                 const float co[4] = {cs01.x, cs01.z, cs23.x, cs23.z}, sn[4] = {cs01.y, cs01.w, cs23.y, cs23.w};
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -567,9 +585,9 @@ kvs_status launch_few(const ProjectArgs &a, hipStream_t hs)
 // is taken, against the 256 x 256 tiles with what rounds after the first cost it besides: a workgroup that follows another
 // starts cold, and with more rounds than one every XCD streams the selected rows through its L2 again (without the two, 4 to 44 %
 // slower than the large tiles at 2300 to 6600 tokens of 8 to 24 heads and at hidden 512).  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16
-// tokens 72 -> 12 us, 96 tokens 73 -> 16, 256 tokens 75 -> 22, 384 tokens 75 -> 27, 640 tokens 75 -> 37, 656 tokens 75 -> 41,
-// 1280 tokens 82 -> 75; the large tiles from 1281 on (78.4 us; the small ones 4 % less up to 1400, 22 % more at 1700), and the
-// small ones once more where the large ones would start a second round for a handful: 2561 to 2688 tokens 177 -> 153 us.
+// tokens 72 -> 11 us, 96 tokens 73 -> 15, 256 tokens 75 -> 21, 384 tokens 75 -> 26, 640 tokens 75 -> 35, 656 tokens 75 -> 39,
+// 1280 tokens 82 -> 69; the large tiles from 1281 on (78.4 us; the small ones 4 % less up to 1400, 22 % more at 1700), and the
+// small ones once more where the large ones would start a second round for a handful: 2561 to 2688 tokens 177 -> 143 us.
 struct FewTile {
     int fbw, tb, step_ns, fixed_ns;
     kvs_status (*launch)(const ProjectArgs &, hipStream_t);
