@@ -1,7 +1,8 @@
 // kvs_select_topk: exact top-k of each row of a ragged fp32 score matrix (Alg. 1 step 4),
 // order (score descending, index ascending), indices emitted in ascending order.
 //
-// One workgroup of 1024 lanes (16 waves) owns a row; wave w owns the w-th contiguous sixteenth of
+// Rows of up to 768 entries take one wave each (select_wave_kernel); otherwise one workgroup of 1024 lanes (16 waves) owns
+// a row; wave w owns the w-th contiguous sixteenth of
 // it, so everything that depends on element order is wave-local except 16 totals.  Scores are
 // mapped to order-preserving unsigned keys held in registers (rows up to 49152 entries) or re-read
 // from L2 (longer rows).  The key T of the k-th entry is found by an MSB-first radix select with
@@ -242,6 +243,107 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float *__rest
             base_sel += __popcll(m_gt);
             base_eq += __popcll(m_eq);
         });
+    }
+}
+
+// ---- short rows ----------------------------------------------------------------------------------------
+// A row of up to KPT * 64 entries is one wave's: a lane holds KPT of its keys and nothing crosses waves, so there are no
+// barriers and no histograms to clear.  T is found bit by bit from the top: the largest value that at least k keys reach;
+// as soon as exactly k keys reach it they are the answer (after about log2(len) bits).  Bits that all finite scores share are
+// skipped.  What bounds it is the chain of compares, count and sum over the lanes per bit, KPT times as long in its first
+// link; the workgroup of 16 waves above pays a dozen barriers instead, whatever the length.
+template <bool LARGEST>
+__device__ __forceinline__ uint32_t wave_extreme(uint32_t v)
+{
+    auto with = [](uint32_t a, uint32_t b) { return LARGEST ? max(a, b) : min(a, b); };
+    constexpr int none = LARGEST ? 0 : -1;
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x111, 0xf, 0xf, false));   // as in wave_incl_scan
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x112, 0xf, 0xf, false));
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x114, 0xf, 0xf, false));
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x118, 0xf, 0xf, false));
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x142, 0xa, 0xf, false));
+    v = with(v, (uint32_t)__builtin_amdgcn_update_dpp(none, (int)v, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+template <int KPT>
+__global__ __launch_bounds__(kWave) void select_wave_kernel(const float *__restrict__ scores, int32_t *__restrict__ idx_out,
+                                                            const SelectRows rows)
+{
+    const int r = blockIdx.x;
+    const int len = rows.len[r], k = rows.k[r];
+    if (k <= 0 || len <= 0) return;
+    const float *__restrict__ row = scores + rows.begin[r];
+    int32_t *__restrict__ out = idx_out + rows.out_off[r];
+    const uint32_t lane = threadIdx.x;
+    uint32_t keys[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        const uint32_t e = j * kWave + lane;
+        const uint32_t key = score_key(row[min(e, (uint32_t)len - 1)]);
+        keys[j] = e < (uint32_t)len ? key : 0u;          // no element: below every real key, as above
+    }
+    auto reaching = [&](uint32_t t) {                    // keys that are >= t
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) n += keys[j] >= t ? 1 : 0;
+        return __builtin_amdgcn_readlane(wave_incl_scan(n), kWave - 1);
+    };
+    constexpr int kTieCheck = 11;                        // steps after which rows without equal scores have mostly ended
+    constexpr uint32_t kFirstFinite = 0x00800000u;       // one above the key of -inf
+    uint32_t T = 0, hi = 0, lo = 0xffffffffu;
+    int reach = KPT * kWave, bit = 31;                   // reach: keys that are >= T
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        hi = max(hi, keys[j]);
+        lo = keys[j] >= kFirstFinite ? min(lo, keys[j]) : lo;
+    }
+    hi = wave_extreme<true>(hi);
+    lo = wave_extreme<false>(lo);
+    if (lo <= hi) {                                      // there are finite scores: the bits above shared are common to them
+        const int shared = hi == lo ? -1 : 31 - __clz((int)(hi ^ lo));
+        const uint32_t prefix = shared < 31 ? hi >> (shared + 1) << (shared + 1) : 0u;
+        const int finite = reaching(kFirstFinite);
+        if (prefix >= kFirstFinite && finite >= k) { T = prefix; reach = finite; bit = shared; }
+    }
+    for (int steps = 0; bit >= 0 && reach != k; --bit) {
+        const uint32_t t = T | 1u << bit;
+        const int n = reaching(t);
+        if (n >= k) { T = t; reach = n; }
+        if (++steps == kTieCheck && reach != k) {        // equal scores?  Is the least that reaches T the k-th already?
+            lo = 0xffffffffu;
+#pragma unroll
+            for (int j = 0; j < KPT; ++j) lo = keys[j] >= T ? min(lo, keys[j]) : lo;
+            lo = wave_extreme<false>(lo);
+            if (lo != 0xffffffffu && reaching(lo + 1) < k) { T = lo; break; }
+        }
+    }
+    uint32_t base = 0;
+    if (reach == k && T > 0u) {                          // no tie is cut
+#pragma unroll
+        for (int j = 0; j < KPT; ++j) {
+            const bool sel = keys[j] >= T;
+            const uint64_t m = __ballot(sel);
+            if (sel) out[base + lanes_below(m)] = (int32_t)(j * kWave + lane);
+            base += __popcll(m);
+        }
+        return;
+    }
+    int above = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) above += __popcll(__ballot(keys[j] > T));
+    const uint32_t quota = (uint32_t)(k - above);        // entries equal to T that are taken, in index order
+    if (T == 0u) T = 1u;                                 // only reachable with NaN scores: never select padding
+    uint32_t base_eq = 0;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+        const bool is_gt = keys[j] > T, is_eq = keys[j] == T;
+        const uint64_t m_gt = __ballot(is_gt), m_eq = __ballot(is_eq);
+        const uint32_t gt_before = base + lanes_below(m_gt), eq_before = base_eq + lanes_below(m_eq);
+        if (is_gt) out[gt_before + min(eq_before, quota)] = (int32_t)(j * kWave + lane);
+        else if (is_eq && eq_before < quota) out[gt_before + eq_before] = (int32_t)(j * kWave + lane);
+        base += __popcll(m_gt);
+        base_eq += __popcll(m_eq);
     }
 }
 
@@ -875,7 +977,13 @@ kvs_status launch_select(const float *scores, int32_t n_rows, const int64_t *beg
         }
         if (max_len == 0) continue;
         dim3 grid(nr), block(kSelThreads);
-        if (max_len <= 4 * kSelThreads) hipLaunchKernelGGL(select_kernel<4>, grid, block, 0, hs, scores, idx_out, rows);
+        // A wave per row up to 768 entries, the first of each pair: 64 entries 6.8 -> 3.8 us, 300 6.8 -> 4.5, 512 6.8 -> 4.8 (a tie
+        // cut: 7.3 -> 5.0), 700 6.8 -> 4.8, 64 rows of 512 7.2 -> 5.8; at 1024 6.8 and 6.4, 64 rows of them 7.2 both; at 1500 6.8 and 8.7.
+        const dim3 wave(kWave);
+        if (max_len <= 4 * kWave) hipLaunchKernelGGL(select_wave_kernel<4>, grid, wave, 0, hs, scores, idx_out, rows);
+        else if (max_len <= 8 * kWave) hipLaunchKernelGGL(select_wave_kernel<8>, grid, wave, 0, hs, scores, idx_out, rows);
+        else if (max_len <= 12 * kWave) hipLaunchKernelGGL(select_wave_kernel<12>, grid, wave, 0, hs, scores, idx_out, rows);
+        else if (max_len <= 4 * kSelThreads) hipLaunchKernelGGL(select_kernel<4>, grid, block, 0, hs, scores, idx_out, rows);
         else if (max_len <= 8 * kSelThreads) hipLaunchKernelGGL(select_kernel<8>, grid, block, 0, hs, scores, idx_out, rows);
         else if (max_len <= 16 * kSelThreads) hipLaunchKernelGGL(select_kernel<16>, grid, block, 0, hs, scores, idx_out, rows);
         else if (max_len <= 32 * kSelThreads) hipLaunchKernelGGL(select_kernel<32>, grid, block, 0, hs, scores, idx_out, rows);
