@@ -73,6 +73,8 @@ static_assert(K_RING >= AHEAD && V_RING >= AHEAD + 2, "ring depth");
 constexpr int LDS_BYTES = (K_RING + V_RING) * TILE_B;
 constexpr float kRefShift = 60.0f;      // base-2 offset of the fixed softmax reference above the first tile's maximum
 constexpr float kSumLimit = 1.8446744e19f;   // 2^64: a sum of weights beyond it moves the reference (RECENTRE)
+constexpr float kFarRef = 65536.0f;          // references below it move by `up` to within 2^-8, and fp32 products up to it are that good
+constexpr float kLeastSum = 5.421011e-20f;   // 2^-64: less than any row's sum whose references stayed within kFarRef
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4_t v) { return __builtin_bit_cast(bf16x8, v); }
 
 __device__ __forceinline__ uint32_t pack2(float lo, float hi)
@@ -239,8 +241,11 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     if (listed) plan_shares(td, n_q_heads / n_kv_heads, total_tiles, sel_pos, share_units, wg,
                             reinterpret_cast<char *>(lds), my_tiles, &n_my_tiles);
     const int it_begin = listed ? 0 : wg, it_end = listed ? n_my_tiles : wg + 1;
-    for (int it = it_begin; it < it_end; ++it) {
-    if (it != it_begin) __syncthreads();   // every wave has left the previous tile: rings and tables are free
+    bool again = false;                    // RECENTRE: the same tile once more, with its rows' exact maxima
+    for (int it = it_begin; it < it_end; it += RECENTRE && again ? 0 : 1) {
+    if (it != it_begin || (RECENTRE && again)) __syncthreads();   // every wave has left the previous tile: rings and tables are free
+    const int first_pass = RECENTRE && again ? 1 : 0;
+    again = false;
     const int rest = it;
     // split launches walk the list of pieces the plan kernel wrote: the pieces that have keys first,
     // from the top of the context down, then the empty ones (which only mark their slot)
@@ -307,6 +312,8 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     }
     const int pmin = min(lo_pos[0], lo_pos[1]), pmax = max(max(hi_pos[0], hi_pos[1]), 0);
     if (lane == 0) wg_max_pos[wave] = pmax;
+    __shared__ int redo_flag;
+    if (RECENTRE && tid == 0) redo_flag = 0;
 
     // ---- Q as the B operand: Q[query ln][16*ks + 8*hf + j] ----------------------------------------
     bf16x8 qreg[NB][D / 16];
@@ -541,7 +548,8 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // RECENTRE: the reference moves where a row's sum outgrows it.  Looked at after every tile, before the tile's weights are
     // multiplied with V: the row's reference goes up by a whole number (at least 100, and past the tile's largest logit by
     // kRefShift), its sum without the tile and its accumulators come down by that power of two, and the tile's weights
-    // are computed again, from scores that are still there.  (A NaN moves nothing.)
+    // are computed again, from scores that are still there.  (A NaN moves nothing.)  References beyond kFarRef are not to be
+    // trusted: adding `up` to them, or to one that far off, loses what it adds.  Their workgroups end in the exact maxima's pass.
     auto outgrown = [&](int first) __attribute__((always_inline)) -> bool {
         return __builtin_amdgcn_ballot_w64((first == 0 ? fmaxf(l_run[0], l_run[1]) : l_run[1]) >= kSumLimit) != 0;
     };
@@ -647,10 +655,12 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // the first tile's maximum already overflowed, which heavy-tailed keys do reach: half the
     // workgroups of a 131k-token launch repeated the pass.)  If a row's sum does end above 2^100 (or
     // inf / nan) the workgroup computes the exact row maxima in a score-only sweep and repeats the
-    // pass with those (pass 1), which cannot overflow: a correctness net.  (RECENTRE has no use for it.)
-    __shared__ int redo_flag;
+    // pass with those (pass 1), which cannot overflow: a correctness net.  RECENTRE needs it for rows with logits beyond
+    // kFarRef only (and infinite or NaN ones); its pass 1 goes back to the start of the tile and takes the general loop (with both
+    // passes in one loop around the pipelined sweep, 131072 Yi-shaped tokens, 12452 selected: 12.13 ms against 11.67; like this as
+    // fast as without a net).
     float l_tot[NB];
-    for (int pass = 0; pass < (RECENTRE ? 1 : 2); ++pass) {
+    for (int pass = first_pass; pass < 2; ++pass) {
         if (pass == 1) {
             // exact row maxima: a score-only sweep with three tiles on their way.  Tile jt+3 goes to
             // the K slot of tile jt-1, which every wave has finished reading when it passes the
@@ -688,6 +698,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             // its weights at exp2(-inf) = 0 instead of NaN (the merge drops pieces with zero sum)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) m_ref[nb] = fmaxf(row_max(s_cur[nb]), -1.0e30f) + kRefShift;
+            if (RECENTRE && fmaxf(fabsf(m_ref[0]), fabsf(m_ref[1])) > kFarRef) redo_flag = 1;
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) { l_run[nb] = 0.f; l_exact[nb] = 0.f; }
@@ -710,7 +721,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         // neighbouring blocks: 64 requests of 2 % 1522 -> 1431 us, of 4 % 2612 -> 2460, 46 of 2.8 % 183 -> 172, 15 % of
         // 32768 tokens 1017 -> 997, 30 % 2047 -> 2017, pieces of 5 % 418 -> 420.
         const int w_hi = min(t_hi, __builtin_amdgcn_readfirstlane(pmax) / BN + 1);
-        if (t_lo + 3 <= t_hi && t_lo + AHEAD + 3 <= j_inside) {
+        if ((!RECENTRE || pass == 0) && t_lo + 3 <= t_hi && t_lo + AHEAD + 3 <= j_inside) {
             // the first step has no earlier tile to multiply: scores of the second tile, softmax of the first
             u32x4_t p_a[NB][2], p_b[NB][2];
             qk(t_lo + 1, s_nxt);
@@ -749,7 +760,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             qk(jt + 1, s_nxt);
             u32x4_t pop[NB][2];
             softmax(jt, s_cur, pop);
-            if (RECENTRE && outgrown(0)) recentre(jt, s_cur, pop);
+            if (RECENTRE && pass == 0 && outgrown(0)) recentre(jt, s_cur, pop);
             pv_product(jt, pop);
             KVS_ATTN_BARRIER(0);
             if (jt + AHEAD < t_hi) stage_tile(jt + AHEAD);
@@ -771,14 +782,17 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         for (int nb = 0; nb < NB; ++nb) {
             l_tot[nb] = l_run[nb] + __shfl_xor(l_run[nb], 32);
             bad |= !(l_tot[nb] < 1.2676506e30f);          // 2^100; also true for inf and nan
+            if (RECENTRE) bad |= !(l_tot[nb] >= kLeastSum) || m_ref[nb] > kFarRef;
         }
-        if (RECENTRE || pass == 1) break;
-        if (tid == 0) redo_flag = 0;
+        if (pass == 1) break;
+        if (!RECENTRE && tid == 0) redo_flag = 0;
         __syncthreads();
         if (bad) redo_flag = 1;
         __syncthreads();
-        if (redo_flag == 0) break;
+        if (RECENTRE) again = __builtin_amdgcn_readfirstlane(redo_flag) != 0;
+        if (RECENTRE || redo_flag == 0) break;
     }
+    if (RECENTRE && again) continue;
 
     // ---- epilogue: normalise, convert, store ----------------------------------------------------------
 #pragma unroll

@@ -56,3 +56,45 @@ def test_reference_moves(what, want_lse):
         assert float((got - ref).abs().max()) <= 2.0 ** -8 * float(v.abs().max()), (what, h)
         if want_lse:
             assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max())
+
+
+@pytest.mark.parametrize("want_lse", [False, True])
+@pytest.mark.parametrize("first", [-np.inf, -1e12, -4e9, -1e6])
+def test_a_first_tile_far_below_the_rest(first, want_lse):
+    """The first 32 keys give every row logits of `first`; the next tile has one of 150 for half of the heads, whose other logits are
+    around 0, while all of the other half's lie around -250.  Neither half may overflow or vanish."""
+    print(f"recentred attention: first tile at {first}, lse {want_lse}", flush=True)
+    hq, hk, d, n, k = 64, 8, 128, 49200, 1600
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    kk = torch.randn((n, hk, d), generator=gen, device=DEV)
+    v = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    u, w = torch.zeros(d, device=DEV), torch.zeros(d, device=DEV)
+    u[:60], w[60:120] = 60 ** -0.5, 60 ** -0.5
+    q = torch.empty((k, hq, d), device=DEV)
+    q[:, 0::2], q[:, 1::2] = u, w
+    q[:, :, 127] = -0.125
+    kk[:, :, 127] = 0
+    kk -= 250 * w
+    kk[40] += 150 * u
+    kk[:32] = 0
+    if np.isinf(first):
+        kk[:32, :, 127] = np.inf
+    else:
+        kk[:32] = first * (u + w)
+    kk, q = kk.to(torch.bfloat16), q.to(torch.bfloat16)
+    pos = torch.arange(n - k * 30, n, 30, device=DEV, dtype=torch.int32)
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("partial_attention", sh, 1, n, k), dtype=torch.uint8, device=DEV)
+    out = torch.full((k, hq, d), 7.0, dtype=torch.bfloat16, device=DEV)
+    lse = torch.full((k, hq), 7.0, device=DEV) if want_lse else None
+    B.kvs_partial_attention(sh, [0], [n], [0, k], q, pos, kk, v, 1.0, out, lse, ws)
+    rows = torch.tensor([0, 7, 8, 31, 32, 250, 800, 833, k - 65, k - 64, k - 2, k - 1], device=DEV)
+    for h in (0, 1, 30, 31, 63):
+        s = q[rows, h].double() @ kk[:, h // 8].double().t()
+        s.masked_fill_(torch.arange(n, device=DEV)[None] > pos[rows, None].long(), -np.inf)
+        ref = torch.softmax(s, -1) @ v[:, h // 8].double()
+        # weights and results in bf16, as above
+        assert float((out[rows, h].double() - ref).abs().max()) <= 2.0 ** -8 * float(v.abs().max()), h
+        if want_lse:
+            z = torch.logsumexp(s, -1)
+            assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max()), h
