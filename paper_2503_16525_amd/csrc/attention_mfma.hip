@@ -528,7 +528,7 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     // with fewer 256-row tiles than compute units the large kernel still wins if the caller's
     // workspace lets it cut the key ranges and its tiles are not mostly padding
     AttnSplitPlan plan2 = {1, 0, 0, 0, false};
-    if (workspace && fits32) plan2 = attention_mfma2_plan(shape, bd, workspace_bytes);
+    if (fits32) plan2 = attention_mfma2_plan(shape, bd, workspace ? workspace_bytes : 0);
     const int splits2 = plan2.n_splits;
     const bool fills = big_tiles * shape->n_kv_heads >= kAttnBigTileMinGrid;
     const bool dense_tiles = rows * 10 >= big_tiles * 256 * 6;

@@ -98,3 +98,25 @@ def test_a_first_tile_far_below_the_rest(first, want_lse):
         if want_lse:
             z = torch.logsumexp(s, -1)
             assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max()), h
+
+
+def test_a_workspace_changes_nothing():
+    """These launches keep whole key ranges and use no workspace: the bits are the same without one, where references move too."""
+    print("recentred attention: without a workspace", flush=True)
+    hq, hk, d, n, k = 64, 8, 128, 49200, 1600
+    gen = torch.Generator(device=DEV).manual_seed(6)
+    kk = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    v = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randn((k, hq, d), generator=gen, device=DEV)
+    q = (q / q.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    kk[24000:24200] *= 60                                 # logits to both sides, a few hundred at most
+    pos = torch.arange(n - k * 30, n, 30, device=DEV, dtype=torch.int32)
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("partial_attention", sh, 1, n, k), dtype=torch.uint8, device=DEV)
+    res = []
+    for workspace in (ws, None):
+        out, lse = torch.full((k, hq, d), 7.0, dtype=torch.bfloat16, device=DEV), torch.full((k, hq), 7.0, device=DEV)
+        B.kvs_partial_attention(sh, [0], [n], [0, k], q, pos, kk, v, 1.0, out, lse, workspace)
+        res.append((out, lse))
+    assert torch.isfinite(res[0][0]).all()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
