@@ -551,13 +551,13 @@ size_t attention_workspace_bytes(const kvs_shape *shape, int32_t batch, int64_t 
     // each (128-row kernel) or fewer than kAttnSplitBelowWgs tiles of 256 rows with up to kSplitMax
     // pieces each (256-row kernel).
     // (a batch is sized for the capped case: with several requests the rows say nothing about the
-    // longest one, and a launch whose workspace is too small for pieces keeps whole key ranges; one request beyond
-    // the last-level cache is given room for kSplitMax pieces of every row, as callers have been)
+    // longest one, and a launch whose workspace is too small for pieces keeps whole key ranges.  One request beyond
+    // the last-level cache is given room for kSplitMax pieces of every row that such a launch can have, below
+    // kAttnBigTileMinGrid tiles of 256: 131072 Yi-shaped tokens, 1600 selected, 1.64 ms against 1.80 with the capped size)
     const int64_t kv_bytes = n_rows_total * shape->n_kv_heads * (int64_t)D * 2 * 2;
-    if (batch > 1 || kv_bytes <= kAttnRecentreBytes) {
-        const int64_t cap = (int64_t)(kSplitMaxWgs + kSplitBelowWgs) * 256 + (int64_t)batch * 256 * kSplitMax;
-        if (slots > cap) slots = cap;
-    }
+    int64_t cap = (int64_t)(kSplitMaxWgs + kSplitBelowWgs) * 256 + (int64_t)batch * 256 * kSplitMax;
+    if (batch <= 1 && kv_bytes > kAttnRecentreBytes) cap = (int64_t)kAttnBigTileMinGrid * 256 * kSplitMax;
+    if (slots > cap) slots = cap;
     return (size_t)slots * kPartBytesPerSlot + kAttnPlanBytes + 256;
 }
 

@@ -164,13 +164,15 @@ def test_a_workspace_for_a_long_prompt_serves_the_shorter_ones(call, hq, hk, d, 
 
 
 def test_attention_workspace_beyond_the_last_level_cache(lib):
-    """One request whose K and V pass 192 MiB is given room for 16 pieces of every output row's key range (528 bytes each);
-    a request below it, or a batch of the same rows, only for launches that leave the chip idle."""
+    """One request whose K and V pass 192 MiB is given room for 16 pieces (528 bytes each) of every output row's key range, up to
+    the 65536 rows above which a launch keeps whole key ranges; a request below it, or a batch of the same rows, only for launches
+    that leave the chip idle."""
     sh = _shape(hq=32, hk=4)                                  # 2 KiB of K and V a token: 98304 tokens are 192 MiB
-    pieces = 528 * 16 * 32 * 12452
-    size = lambda batch, n: B.kvs_workspace_size("partial_attention", sh, batch, n, 12452)
-    assert size(1, 131072) >= pieces and size(1, 98305) >= pieces
-    assert size(1, 98304) < pieces and size(2, 131072) < pieces
+    size = lambda batch, n, sel: B.kvs_workspace_size("partial_attention", sh, batch, n, sel)
+    pieces = 528 * 16 * 32 * 2048
+    assert size(1, 131072, 2048) >= pieces and size(1, 98305, 2048) >= pieces
+    assert size(1, 98304, 2048) < pieces and size(2, 131072, 2048) < pieces
+    assert size(1, 131072, 131072) == size(1, 131072, 12452) == size(1, 131072, 2048) < 560e6
 
 
 def test_deviation_topk_argument_errors(lib):
