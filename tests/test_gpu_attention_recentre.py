@@ -120,3 +120,29 @@ def test_a_workspace_changes_nothing():
         res.append((out, lse))
     assert torch.isfinite(res[0][0]).all()
     assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+
+
+def test_the_log_sum_exp_of_a_long_context():
+    """One chain of sums over 131072 keys would show in the log-sum-exp.  What remains is its own rounding: log2 of the sum, around -46,
+    is rounded to 2^-18 and the result in base 2, around 17, to 2^-19 (each an error of 0.29 units, 7.6e-7 and 3.8e-7 in natural
+    units), the result in natural units to 2^-20 (2.8e-7): 8.9e-7 together."""
+    print("recentred attention: log-sum-exp of 131072 keys", flush=True)
+    hq, hk, d, n, k = 32, 4, 128, 131072, 3072
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    kk = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    v = torch.randn((n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    q = (torch.randn((k, hq, d), generator=gen, device=DEV) / d ** 0.5).to(torch.bfloat16)
+    pos = torch.arange(n - k * 4, n, 4, device=DEV, dtype=torch.int32)
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    ws = torch.empty(B.kvs_workspace_size("partial_attention", sh, 1, n, k), dtype=torch.uint8, device=DEV)
+    out, lse = torch.empty((k, hq, d), dtype=torch.bfloat16, device=DEV), torch.full((k, hq), 7.0, device=DEV)
+    B.kvs_partial_attention(sh, [0], [n], [0, k], q, pos, kk, v, 1.0, out, lse, ws)
+    rows = torch.arange(5, k, 37, device=DEV)
+    err = []
+    for h in range(0, hq, 3):
+        s = q[rows, h].double() @ kk[:, h // 8].double().t()
+        s.masked_fill_(torch.arange(n, device=DEV)[None] > pos[rows, None].long(), -np.inf)
+        err.append(lse[rows, h].double() - torch.logsumexp(s, -1))
+    std = float(torch.cat(err).std())
+    print(f"log-sum-exps off by {std:.2e}", flush=True)
+    assert std < 1e-6
