@@ -487,7 +487,7 @@ size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
     // more than kImpUnits strips' worth of sums, unless it is one.
     const int64_t most = impact_most_pieces(shape, n_tokens);
     size_t part = impact_part_bytes(shape, n_tokens, (int)most);
-    const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * 64;
+    const size_t one = impact_part_bytes(shape, n_tokens, 1), strips = sizeof(float) * 3 * (size_t)kImpUnits * kTileCols;
     if (part > strips) part = strips > one ? strips : one;
     return part + sizeof(int32_t) * ((size_t)n_tokens + 1) + 256;
 }

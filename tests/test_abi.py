@@ -175,6 +175,14 @@ def test_attention_workspace_beyond_the_last_level_cache(lib):
     assert size(1, 131072, 131072) == size(1, 131072, 12452) == size(1, 131072, 2048) < 560e6
 
 
+def test_impact_workspace_holds_the_pieces_and_no_more():
+    """Three sums for each token of at most 16384 strips of 32, and the list of tokens: what long prompts are cut into."""
+    sh = _shape(hq=28, hk=4)
+    for n in (8192, 32768, 65536):
+        size = B.kvs_workspace_size("first_order_impact", sh, 1, n)
+        assert 12 * 4 * n <= size <= max(12 * 4 * n, 12 * 16384 * 32) + 4 * (n + 1) + 256
+
+
 def test_deviation_topk_argument_errors(lib):
     sh = _shape()
 
