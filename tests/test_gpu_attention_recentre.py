@@ -1,5 +1,5 @@
 """Contexts whose K and V outgrow the last-level cache: the softmax reference moves where a row's sum of weights outgrows it,
-once or several times, by a little or by more than fp32 holds, in the first, a middle and the last tile, in one row or in all.
+once or several times, by a little or by more than fp32 holds, in an early, a middle and the last tile, in one row or in all.
 Every checked row against softmax in 64 bits; the log-sum-exp with it."""
 import numpy as np
 import pytest
@@ -56,6 +56,46 @@ def test_reference_moves(what, want_lse):
         assert float((got - ref).abs().max()) <= 2.0 ** -8 * float(v.abs().max()), (what, h)
         if want_lse:
             assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max())
+
+
+@pytest.mark.parametrize("order", ["ascending", "descending", "shuffled"])
+def test_reference_moves_among_a_tiles_own_positions(order):
+    """Large keys inside the band of positions of a row tile of 32 tokens: inside a lower block of four tokens, between the lower
+    and the upper blocks, inside the first upper block and inside the last.  There a wave compares with its positions, or goes on
+    with its upper block alone, while the lower one's scores and weights are stale.  Every token of those tiles: the keys
+    that it sees count, the others do not.  A short request rides along."""
+    print(f"recentred attention: keys among the positions, {order}", flush=True)
+    hq, hk, d, n, n2, k, k2 = 64, 8, 128, 49200, 900, 1600, 40
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    kk = torch.randn((n2 + n, hk, d), generator=gen, device=DEV)
+    v = torch.randn((n2 + n, hk, d), generator=gen, device=DEV).to(torch.bfloat16)
+    u = torch.randn(d, generator=gen, device=DEV)
+    u = (u / u.norm()).to(torch.bfloat16)
+    q = u.expand(k2 + k, hq, d).contiguous()
+    pos = torch.arange(n - k * 30, n, 30, device=DEV, dtype=torch.int32)
+    at = [int(pos[32 * tile + token]) + past for tile in (1, 24, 49) for token, past in ((2, 5), (15, 10), (18, 7), (29, 3))]
+    for i, key in enumerate(at):
+        kk[n2 + key] = 100 * (i + 1) * u.float()
+    kk[300], kk[700] = 150 * u.float(), 300 * u.float()
+    kk = kk.to(torch.bfloat16)
+    pos2 = torch.arange(n2 - k2 * 20, n2, 20, device=DEV, dtype=torch.int32)
+    if order != "ascending":
+        turn = torch.arange(31, -1, -1, device=DEV) if order == "descending" else torch.randperm(32, generator=gen, device=DEV)
+        pos = pos.view(-1, 32)[:, turn].reshape(-1)       # within each row tile
+        pos2 = pos2.flip(0)
+    sel_pos = torch.cat([pos2, pos]).contiguous()
+    sh = B.make_shape(hq, hk, d, B.BF16)
+    out, lse = torch.full((k2 + k, hq, d), 7.0, dtype=torch.bfloat16, device=DEV), torch.full((k2 + k, hq), 7.0, device=DEV)
+    B.kvs_partial_attention(sh, [0, n2], [n2, n], [0, k2, k2 + k], q, sel_pos, kk, v, 1.0, out, lse)
+    tiles = torch.cat([torch.arange(32 * t, 32 * t + 32, device=DEV) for t in (0, 1, 2, 24, 25, 49)])
+    for h in (0, 29, 63):
+        for first, length, rows in ((0, n2, torch.arange(k2, device=DEV)), (n2, n, k2 + tiles)):
+            s = q[rows, h].double() @ kk[first : first + length, h // 8].double().t()
+            s.masked_fill_(torch.arange(length, device=DEV)[None] > sel_pos[rows, None].long(), -np.inf)
+            ref, z = torch.softmax(s, -1) @ v[first : first + length, h // 8].double(), torch.logsumexp(s, -1)
+            # weights and results in bf16, as above
+            assert float((out[rows, h].double() - ref).abs().max()) <= 2.0 ** -8 * float(v.abs().max()), (h, length)
+            assert float((lse[rows, h].double() - z).abs().max()) <= 2e-3 + 1e-6 * float(z.abs().max()), (h, length)
 
 
 @pytest.mark.parametrize("want_lse", [False, True])
