@@ -58,12 +58,14 @@ kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *par
 // pieces just fill whole rounds of the compute units.  Pieces are started from the top of the
 // context down, range by range.
 // recentre: whole key ranges with a reference that moves where a row's sum outgrows it, for launches
-// whose K and V no longer fit the last-level cache (kAttnRecentreBytes).  There a workgroup that
-// repeats its sweep with the exact maxima streams everything from HBM a second and third time; the
-// look at the sums after every tile costs 4 to 5 % of the sweep, which shorter contexts save.
-// (131072 Yi-shaped tokens, 12452 selected, plain and with 200 keys of 40 times the size in
-// mid-context, ms: recentred 12.0 and 11.9, fixed reference 11.6 and 27.1, pieces of 8192 keys with a
-// merge, which repeat a piece only, 12.9 and 13.2.)
+// whose K and V no longer fit the last-level cache (kAttnRecentreBytes).  The look at the sums after
+// every tile costs 2 to 5 % of the sweep at any length, and spares the workgroups that meet a logit 111 above
+// their first tile's two more sweeps: fixed -> moving, ms, plain and with 200 keys of 40 times the size in
+// mid-context: 32768 tokens of 32:8 heads, 15 % selected, 1.13 -> 1.16 and 2.83 -> 1.17; 98304 of 32:4, 10 %,
+// 6.81 -> 7.08 and 15.7 -> 7.0; 131072 11.9 -> 12.3 and 26.6 -> 11.9; 131072 of 32:8, 5 %, 6.17 -> 6.52 and
+// 15.7 -> 6.5.  So the line is no crossing point.  It lies where such launches used to be cut into pieces of 8192
+// keys with a merge, which repeated a piece only (131072 tokens 12.9 and 13.2): beyond it large keys never cost
+// more sweeps, and shorter contexts, most of whose launches meet none, keep the plain speed.
 struct AttnSplitPlan {
     int n_splits;
     int ctx_tiles;

@@ -266,8 +266,9 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const int ctx_len = td.ctx_len[b];
     const int64_t ctx_off = td.ctx_off[b];
     // First row of the wave's block nb, of the tile's eight blocks of 32 rows in ascending order of position.  A wave has one
-    // of the four lower blocks and its counterpart among the upper ones: what a lower block's early end saves falls to
-    // every wave alike, where with two neighbouring blocks a wave the workgroup is as slow as the last wave.
+    // of the four lower blocks and its counterpart among the upper ones.  The waves meet in every step, so a step is as long
+    // as the slowest wave's: it shortens where the last lower block (block 3) has ended and every wave works on one block.  With two
+    // neighbouring blocks a wave it would where block 6 has, which is three blocks later.
     auto block_row = [&](int nb) { return 32 * (nb == 0 ? wave : 2 * NWAVES - 1 - wave); };
 
     // the plan: (pieces per row tile in use, key tiles per large piece, per small piece, small pieces)
@@ -726,8 +727,8 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         const int j_unmasked = __builtin_amdgcn_readfirstlane(pmin + 1) / BN;     // tiles 0 .. j_unmasked-1: every key <= pmin
         const int j_inside = ctx_len / BN;          // tiles 0 .. j_inside-1 need no row clamp
         // Past a block's own last position every key is masked.  A wave goes on with its upper block alone where the lower one
-        // has ended (half the MFMAs and softmax of a step, all of its LDS reads: about 0.7 of its time), and past the upper
-        // one's end it only stages and keeps the barriers until the others are done.  The rows of a tile are up to 64
+        // has ended (half the MFMAs and softmax of a step, all of its LDS reads: about 0.7 of its time once all four do), and past the
+        // upper one's end it only stages and keeps the barriers until the others are done.  The rows of a tile are up to 64
         // tokens of a sparse selection: at the 2 % of a decode batch its blocks end 12 key tiles apart.  Against waves of two
         // neighbouring blocks: 64 requests of 2 % 1522 -> 1431 us, of 4 % 2612 -> 2460, 46 of 2.8 % 183 -> 172, 15 % of
         // 32768 tokens 1017 -> 997, 30 % 2047 -> 2017, pieces of 5 % 418 -> 420.

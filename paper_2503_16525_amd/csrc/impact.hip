@@ -6,9 +6,9 @@
 // for the value term alone (which is Eq. (3): column mass times |dV|_1), the key term alone, and
 // both together.  The paper drops the key term "to reduce computational overhead": unlike the value
 // term it does not separate into (something of i) x (something of j) -- every (row, token) pair
-// needs its own L1 norm over the channels -- so this is N^2/2 * H_q * d work on the vector units, not
-// a contraction for the matrix cores (only the two dot products per pair are).  It is a diagnostic
-// for check layers, not a step of the hot path.
+// needs its own L1 norm over the channels -- so this is N^2/2 * H_q * d work on the vector units; only the
+// two dot products per pair and, for bf16, the differences inside the norm are contractions for the matrix
+// cores.  It is a diagnostic for check layers, not a step of the hot path.
 //
 // bf16 (impact_tiles_kernel).  Per (row, token, channel) there are a subtraction, v - h, its absolute sum, fma(t, v - h, dv)
 // and its absolute sum, with a = A[h,j,i] and t = scale * (q . dK) entering once per pair.  The subtraction is a product: over a
@@ -43,7 +43,7 @@ constexpr int kImpCols = 32;                 // tokens per workgroup
 constexpr int kImpRowLanes = 16;
 constexpr int kImpThreads = kImpCols * kImpRowLanes;    // 512
 constexpr int kImpPairs = 4;                 // (row, head) pairs a thread handles at a time: a column value read from LDS serves all of them
-constexpr int kImpBlock = kImpRowLanes * kImpPairs;      // 32 pairs staged per block
+constexpr int kImpBlock = kImpRowLanes * kImpPairs;      // 64 pairs staged per block
 
 // grid: (column tiles, heaviest first) x kv heads
 template <int D>
@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kTileThreads, 2) void impact_tiles_kernel(
             a[e] = __shfl(row_j, r) >= my_token ? a[e] : 0.f;      // causal: row j sees token i
             t[e] = scale * (sc[e] - sf[e]);
         }
-        // |key term|_1 = a |t| sum_c |v_c - h_c| and |both|_1 = a sum_c |dv_c + t (v_c - h_c)|
+        // |key term|_1 = a |t| sum_c |v_c - h_c| and |both|_1 = a sum_c |dv_c + t (v_c - h_c)|, each one fp32 chain over the channels
         imp_floatx16 nk, nkv;
 #pragma unroll
         for (int e = 0; e < 16; ++e) { nk[e] = 0.f; nkv[e] = 0.f; }
@@ -521,8 +521,9 @@ extern "C" kvs_status kvs_first_order_impact(const kvs_shape *shape, int64_t n_t
     if (shape->dtype == KVS_BF16) {
         const ImpactPieces cut = impact_pieces(shape, n_tokens);
         pieces = cut.n;
-        // (one strip of tokens is no shorter for a list: all are computed, and those not reused dropped at the end)
-        int32_t *list = reused && n > 64 ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
+        // (up to two strips of tokens are computed whole, and those not reused dropped at the end: the launch that makes the list
+        // costs more than a strip; 33 to 64 tokens of 28:4, 32:8 and 8:8 heads, 20 to 80 % reused: 24 us, with a list 27)
+        int32_t *list = reused && n > 2 * kTileCols ? (int32_t *)((char *)workspace + impact_part_bytes(shape, n_tokens, pieces)) : nullptr;
         int32_t *count = list ? list + n : nullptr;
         if (list) {
             hipLaunchKernelGGL(impact_list_kernel, dim3(1), dim3(kListThreads), 0, hs, n, reused, list, count);

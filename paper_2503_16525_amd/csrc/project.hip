@@ -310,8 +310,8 @@ __global__ __launch_bounds__(PNT, 1) void project_qkv_kernel(
 //   * the four slices' sums meet in LDS at the end, 32 tokens at a time, where the rotation pairs sit in one thread
 //     and rows leave as whole segments.
 // What bounds it: one tile on an otherwise idle chip runs at the global -> LDS rate (128 x 160 tile, hidden 4096: 27 us;
-// 36 us before fetches and loads were dealt out between the MFMAs).  With all units busy (39 us at 656 tokens) no unit is
-// saturated: matrix cores busy 38 % of the launch, L2 at 13 TB/s with 81 % hits, LDS port 18 %; the waves wait 37 % of their
+// 36 us before fetches and loads were dealt out between the MFMAs).  With all units busy (39 us at 656 tokens, 470 ns a step and 8 us
+// besides) no unit is saturated: matrix cores busy 38 % of the launch, L2 at 13 TB/s with 81 % hits, LDS port 18 %; the waves wait 37 % of their
 // time.  Starting every tile at its own place in the contraction loses the shared L2 lines: 71 us.
 constexpr int FNT = 512;
 constexpr int FBK = 64;                        // contraction step; rows of 128 bytes in LDS
@@ -585,9 +585,12 @@ kvs_status launch_few(const ProjectArgs &a, hipStream_t hs)
 // is taken, against the 256 x 256 tiles with what rounds after the first cost it besides: a workgroup that follows another
 // starts cold, and with more rounds than one every XCD streams the selected rows through its L2 again (without the two, 4 to 44 %
 // slower than the large tiles at 2300 to 6600 tokens of 8 to 24 heads and at hidden 512).  Llama-shaped layer, hidden 4096, 256 x 256 tiles -> the choice: 16
-// tokens 72 -> 11 us, 96 tokens 73 -> 15, 256 tokens 75 -> 21, 384 tokens 75 -> 26, 640 tokens 75 -> 35, 656 tokens 75 -> 39,
-// 1280 tokens 82 -> 69; the large tiles from 1281 on (78.4 us; the small ones 4 % less up to 1400, 22 % more at 1700), and the
-// small ones once more where the large ones would start a second round for a handful: 2561 to 2688 tokens 177 -> 143 us.
+// tokens 72 -> 12 us, 96 tokens 73 -> 16, 256 tokens 76 -> 22, 384 tokens 74 -> 26, 640 tokens 76 -> 34, 656 tokens 76 -> 39,
+// 1280 tokens 78 -> 65; the large tiles from 1281 on, and the small ones once more where the large ones would start a second
+// round for a handful: 2561 to 2688 tokens 175 -> 144 us.  The costs are from before the small tiles' epilogue lost 3 to 6 %, and
+// the line is early by that: small against large tiles 71 and 78 us at 1281 tokens, 72 and 78.5 at 1400, 76 and 78.6 at 1500, 77 and
+// 82 at 1600, 96 and 84 at 1700 (hidden 1024: 28 and 31 at 1281, 30 and 32 at 1600; 3584 on 28:4 heads: 66 and 71 at 1800, 72 and
+// 80 at 2100, where the large tiles are taken as well).
 struct FewTile {
     int fbw, tb, step_ns, fixed_ns;
     kvs_status (*launch)(const ProjectArgs &, hipStream_t);
