@@ -1,8 +1,8 @@
 """The attention tolerance, in one place for every GPU test.
 
-fp32 path: 1e-4 absolute (the spec bar).
+fp32 path: 1e-4 absolute.
 
-bf16 path: the spec bar is 2e-2 absolute.  It is asserted as it stands on every output
+bf16 path: the bar is 2e-2 absolute.  It is asserted as it stands on every output
 element whose attended magnitude  mag = sum_i a_i |v_i|  (the oracle's attention applied to |V|)
 is at most 4: there the bf16 storage of the output (half a unit in the last place, at most
 2^-9 |o| <= 2^-9 mag < 8e-3) cannot be what decides.  Above that magnitude the output's own bf16

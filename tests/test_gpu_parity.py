@@ -2,7 +2,7 @@
 on the same seeded inputs.  Sizes here are ones the oracle finishes in seconds but that span
 several tiles and a ragged tail; full-size cases live in test_gpu_fullsize.py.
 
-Tolerances (the spec bars): index sets bit-exact on identical fp32 scores; deviation and
+Tolerances: index sets bit-exact on identical fp32 scores; deviation and
 scores 1e-5 relative; attention 2e-2 absolute for bf16, 1e-4 for fp32.
 """
 import math
