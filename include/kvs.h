@@ -258,7 +258,8 @@ KVS_API kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, int64
  * i.e. the alpha that kvs_deviation takes.  Every row of A sums to 1, so sum_i alpha[g, i] =
  * n_tokens * n_q_heads / n_kv_heads.  The score matrix is never stored: one sweep leaves each
  * row's log-sum-exp in the workspace, a second one sums exp(score - lse) down the columns.
- * Cost: two passes of n_tokens^2 / 2 * head_dim * n_q_heads multiply-adds on the matrix cores.
+ * Cost: two passes of n_tokens^2 / 2 * head_dim * n_q_heads multiply-adds on the matrix cores
+ * (fp32 layers of up to 2048 tokens, with the workspace asked for: one).
  *
  * bf16 with head_dim 128 and a positive scale runs on the matrix cores (tensors below 4 GiB);
  * every other supported shape, fp32 included, takes an fp32 kernel that is only meant for
@@ -269,7 +270,8 @@ KVS_API kvs_status kvs_decode_check(const kvs_shape *shape, int32_t batch, int64
  * alpha     [dev] fp32[n_kv_heads, n_tokens], written
  * workspace [dev] kvs_workspace_size("attn_colsum", shape, 1, n_tokens, 0) bytes, 256-byte
  *           aligned, required; contents on return are unspecified.  It holds every row's softmax statistics and the
- *           results of the pieces into which short sweeps, and sweeps of uneven blocks, are cut
+ *           results of the pieces into which short sweeps, and sweeps of uneven blocks, are cut (short fp32 layers also
+ *           run, in two passes, with 8 * n_tokens * n_q_heads bytes rounded up to 512, and 256)
  */
 KVS_API kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, const void *q, const void *k,
                            float scale, float *alpha,

@@ -502,13 +502,21 @@ size_t piece_bytes(const kvs_shape *shape, int64_t n_tokens)
 
 } // namespace
 
-size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
+// what every call needs; fp32 layers take more if they are given it (one sweep instead of two)
+static size_t colsum_least_bytes(const kvs_shape *shape, int64_t n_tokens)
 {
-    if (n_tokens <= 0) return 256;
     const size_t rows = row_bytes(shape, n_tokens);
     // (fp32 kernels: two floats a row; they also take a scale that is not positive)
     const size_t pieces = shape->dtype == KVS_BF16 && shape->head_dim == D ? piece_bytes(shape, n_tokens) : 0;
     return rows + (pieces > rows ? pieces : rows) + 256;
+}
+
+size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens)
+{
+    if (n_tokens <= 0) return 256;
+    const size_t least = colsum_least_bytes(shape, n_tokens);
+    const size_t one_sweep = shape->dtype == KVS_BF16 && shape->head_dim == D ? 0 : colsum_f32_workspace_bytes(shape, n_tokens);
+    return one_sweep > least ? one_sweep : least;
 }
 
 } // namespace kvs
@@ -526,12 +534,12 @@ extern "C" kvs_status kvs_attn_colsum(const kvs_shape *shape, int64_t n_tokens, 
     if (!q || !k || !alpha) return fail(KVS_EINVAL, "kvs_attn_colsum: NULL tensor pointer");
     if (!aligned16(q) || !aligned16(k)) return fail(KVS_EINVAL, "kvs_attn_colsum: Q/K pointers must be 16-byte aligned");
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return fail(KVS_EINVAL, "kvs_attn_colsum: workspace must be given, 256-byte aligned");
-    if (workspace_bytes < colsum_workspace_bytes(shape, n_tokens))
-        return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, colsum_workspace_bytes(shape, n_tokens));
+    if (workspace_bytes < colsum_least_bytes(shape, n_tokens))
+        return fail(KVS_EWORKSPACE, "kvs_attn_colsum: workspace of %zu bytes, %zu needed", workspace_bytes, colsum_least_bytes(shape, n_tokens));
     // the matrix-core kernel: bf16, head_dim 128, a positive scale (it folds the scale into an exp2
     // argument after taking maxima).  Everything else takes the fp32 kernels.
     const bool mfma = shape->dtype == KVS_BF16 && shape->head_dim == D && scale > 0.f;
-    if (!mfma) return launch_colsum_f32(shape, n_tokens, q, k, scale, workspace, alpha, (hipStream_t)stream);
+    if (!mfma) return launch_colsum_f32(shape, n_tokens, q, k, scale, workspace, workspace_bytes, alpha, (hipStream_t)stream);
     if (!on_matrix_cores(shape, n_tokens))
         return fail(KVS_EUNSUPPORTED, "kvs_attn_colsum: %lld tokens x %d heads exceed the 4 GiB the kernel addresses", (long long)n_tokens, shape->n_q_heads);
     float *lse2 = (float *)workspace;

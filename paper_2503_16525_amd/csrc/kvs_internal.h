@@ -61,7 +61,8 @@ size_t colsum_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t impact_workspace_bytes(const kvs_shape *shape, int64_t n_tokens);
 size_t match_workspace_bytes(int64_t n_target, int64_t n_candidate);
 kvs_status launch_colsum_f32(const kvs_shape *shape, int64_t n, const void *q, const void *k, float scale,
-                              void *row_stats, float *alpha, hipStream_t st);
+                             void *workspace, size_t workspace_bytes, float *alpha, hipStream_t st);
+size_t colsum_f32_workspace_bytes(const kvs_shape *shape, int64_t n);   // for one sweep instead of two
 
 // ---- deviation scoring and top-k in one call (kvs_deviation_topk) ----------------------------------
 // The scoring kernel leaves, beside the scores, every token's order-preserving key and a histogram
@@ -158,6 +159,15 @@ __device__ __forceinline__ float row16_sum(float v)
     return v;
 }
 
+__device__ __forceinline__ float row16_max(float v)
+{
+    v = fmaxf(v, dpp_f32<0x128>(v));
+    v = fmaxf(v, dpp_f32<0x124>(v));
+    v = fmaxf(v, dpp_f32<0x122>(v));
+    v = fmaxf(v, dpp_f32<0x121>(v));
+    return v;
+}
+
 __device__ __forceinline__ float wave_sum(float v)
 {
     v = row16_sum(v);
@@ -168,10 +178,7 @@ __device__ __forceinline__ float wave_sum(float v)
 
 __device__ __forceinline__ float wave_max(float v)
 {
-    v = fmaxf(v, dpp_f32<0x128>(v));
-    v = fmaxf(v, dpp_f32<0x124>(v));
-    v = fmaxf(v, dpp_f32<0x122>(v));
-    v = fmaxf(v, dpp_f32<0x121>(v));
+    v = row16_max(v);
     v = fmaxf(v, __shfl_xor(v, 16));
     v = fmaxf(v, __shfl_xor(v, 32));
     return v;
