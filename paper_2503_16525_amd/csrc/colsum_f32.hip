@@ -120,10 +120,17 @@ __global__ __launch_bounds__(kCfThreads) void colsum_f32_kernel(int n, int n_q_h
 // one key, whose sum is its own and its three neighbours'.
 // Measured, fp32 layers of 4 heads, head_dim 64, the five calls of a layer with this one among them: 512 tokens 38.6 -> 34.3 us, 1024
 // 58.5 -> 50.7, 2048 95.6 -> 70.0; below 300 tokens the host is what they wait for.
+// The keys come through LDS (Rows16): 512 tokens 34.7 -> 32.7 us, the kernel 9.1 -> 6.9; 2048 tokens 70.0 -> 65.4.
+// A wave's tiles that are on their way together: all four of a short layer where they have room, else two, for two workgroups a unit.
+template <int DTYPE, int D>
+constexpr int tiles_in_flight(int max_tiles) { return max_tiles <= 4 && Rows16<DTYPE, D>::BYTES <= 4096 ? 4 : 2; }
 template <int DTYPE, int D, int MAXT>
 __global__ __launch_bounds__(kCfThreads, 2) void colsum_f32_rows_kernel(int n, int n_q_heads, int n_kv_heads, const void *__restrict__ q,
                                                                         const void *__restrict__ k, float scale, float *__restrict__ part)
 {
+    using Rows = Rows16<DTYPE, D>;
+    constexpr int FETCH = tiles_in_flight<DTYPE, D>(MAXT);
+    extern __shared__ __attribute__((aligned(16))) char rows_s[];  // the query rows, then FETCH tiles of keys a wave
     __shared__ __attribute__((aligned(16))) float m_s[kCfWaves][kCfRows], z_s[kCfWaves][kCfRows];
     const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -132,29 +139,46 @@ __global__ __launch_bounds__(kCfThreads, 2) void colsum_f32_rows_kernel(int n, i
     const int n_qrows = n * grp, row_tiles = (n_qrows + kCfRows - 1) / kCfRows, tile = row_tiles - 1 - blk;   // most keys first
     const int fb = tile * kCfRows;
     const int last = (min(fb + kCfRows, n_qrows) - 1) / grp;       // position of the last row
-    const int fr = min(fb + m16, n_qrows - 1);
-    float fx[D / 4];
-    load_quarter<DTYPE, D>(q, ((int64_t)(fr / grp) * n_q_heads + g * grp + fr % grp) * D, kk, fx);
+    char *const mine = rows_s + Rows::BYTES * (1 + FETCH * wave);
+    // (past the last row's position keys are clamped and not used)
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int i = 0; i < FETCH; ++i) {
+            const int k0 = (wave + (i0 + i) * kCfWaves) * kCfRows;
+            if (k0 > last) continue;                               // uniform
+#pragma unroll
+            for (int l = 0; l < Rows::LOADS; ++l)
+                Rows::load(k, [&](int r) { return ((int64_t)min(k0 + r, last) * n_kv_heads + g) * D; }, mine + i * Rows::BYTES, l, lane);
+        }
+    };
+    if (wave < Rows::LOADS)
+        Rows::load(q, [&](int r) { const int fr = min(fb + r, n_qrows - 1); return ((int64_t)(fr / grp) * n_q_heads + g * grp + fr % grp) * D; },
+                   rows_s, wave, lane);
+    fetch(0);
     int pos[4];                                                    // of this lane's rows (-1: no row)
 #pragma unroll
     for (int r = 0; r < 4; ++r) pos[r] = fb + 4 * kk + r < n_qrows ? (fb + 4 * kk + r) / grp : -1;
     float s[MAXT][4], m[4], z[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) { m[r] = kLowest; z[r] = 0.f; }
-    // four tiles' keys on their way at a time (past the last row's position they are clamped and not used)
-    constexpr int FETCH = 4;
+    __syncthreads();
+    float fx[D / 4];
+    Rows::read(rows_s, m16, kk, fx);
 #pragma unroll
     for (int i0 = 0; i0 < MAXT; i0 += FETCH) {
         if ((wave + i0 * kCfWaves) * kCfRows > last) continue;     // uniform
-        float x[FETCH][D / 4];
-#pragma unroll
-        for (int i = 0; i < FETCH; ++i)
-            load_quarter<DTYPE, D>(k, ((int64_t)min((wave + (i0 + i) * kCfWaves) * kCfRows + m16, last) * n_kv_heads + g) * D, kk, x[i]);
+        if (i0 > 0) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // what lay there has been read
+            fetch(i0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
 #pragma unroll
         for (int i = 0; i < FETCH; ++i) {
             const int key = (wave + (i0 + i) * kCfWaves) * kCfRows + m16;
             if (key - m16 > last) continue;
-            const f32x4 y = dots<D>(fx, x[i]);
+            float x[D / 4];
+            Rows::read(mine + i * Rows::BYTES, m16, kk, x);
+            const f32x4 y = dots<D>(fx, x);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 s[i0 + i][r] = key <= pos[r] ? y[r] * scale : -INFINITY;
@@ -227,14 +251,32 @@ __global__ __launch_bounds__(kCjKeys * kCjChains) void colsum_f32_join(int n, in
     alpha[(int64_t)g * n + key] = (float)sum;
 }
 
+template <int DTYPE, int D, int MAXT>
+kvs_status launch_rows(dim3 grid, int n, int hq, int hk, const void *q, const void *k, float scale, float *part, hipStream_t st)
+{
+    using Rows = Rows16<DTYPE, D>;
+    constexpr int lds_bytes = Rows::BYTES * (1 + tiles_in_flight<DTYPE, D>(MAXT) * kCfWaves);
+    static_assert(Rows::LOADS <= kCfWaves, "a wave loads one share of the query rows");
+    static DeviceOnce attr_once;
+    const kvs_status ast = once_per_device(attr_once, [] {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&colsum_f32_rows_kernel<DTYPE, D, MAXT>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_attn_colsum: hipFuncSetAttribute: %s", hipGetErrorString(e));
+    });
+    if (ast != KVS_OK) return ast;
+    hipLaunchKernelGGL((colsum_f32_rows_kernel<DTYPE, D, MAXT>), grid, dim3(kCfThreads), lds_bytes, st, n, hq, hk, q, k, scale, part);
+    return check_launch("kvs_attn_colsum(f32 rows)");
+}
+
 template <int DTYPE, int D>
 kvs_status launch_one_sweep(int n, int hq, int hk, const void *q, const void *k, float scale, float *part, float *alpha, hipStream_t st)
 {
     const int grp = hq / hk, row_tiles = (n * grp + kCfRows - 1) / kCfRows;
-    const dim3 grid((unsigned)(row_tiles * hk)), block(kCfThreads);
+    const dim3 grid((unsigned)(row_tiles * hk));
     constexpr int kFew = 4, kMost = kCfOneSweepTokens / (kCfRows * kCfWaves);
-    if (n <= kFew * kCfRows * kCfWaves) hipLaunchKernelGGL((colsum_f32_rows_kernel<DTYPE, D, kFew>), grid, block, 0, st, n, hq, hk, q, k, scale, part);
-    else hipLaunchKernelGGL((colsum_f32_rows_kernel<DTYPE, D, kMost>), grid, block, 0, st, n, hq, hk, q, k, scale, part);
+    kvs_status stt = n <= kFew * kCfRows * kCfWaves ? launch_rows<DTYPE, D, kFew>(grid, n, hq, hk, q, k, scale, part, st)
+                                                    : launch_rows<DTYPE, D, kMost>(grid, n, hq, hk, q, k, scale, part, st);
+    if (stt != KVS_OK) return stt;
     hipLaunchKernelGGL(colsum_f32_join, dim3((unsigned)((n + kCjKeys - 1) / kCjKeys), (unsigned)hk), dim3(kCjKeys * kCjChains), 0, st, n, grp, row_tiles,
                        (const float *)part, alpha);
     return check_launch("kvs_attn_colsum(f32)");

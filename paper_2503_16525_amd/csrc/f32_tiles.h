@@ -35,6 +35,38 @@ __device__ __forceinline__ void load_quarter(const void *__restrict__ base, int6
     }
 }
 
+// Sixteen rows on their way to such operands through LDS.  Taken straight from memory a lane's 16 bytes lie a row away from its
+// neighbours' and every load is 64 separate requests (16 KB a wave, 8 waves: 3.4 us on one compute unit); here consecutive lanes load
+// consecutive bytes, 1 KB an instruction.  Row r's 16-byte piece p lies at place p ^ swizzle(r), which spreads the 16 rows
+// that are read at one piece over all banks.
+template <int DTYPE, int D>
+struct Rows16 {
+    static constexpr int ROW_B = D * (DTYPE == KVS_F32 ? 4 : 2), PIECES = ROW_B / 16, BYTES = 16 * ROW_B, LOADS = BYTES / 1024, ROWS_A_LOAD = 1024 / ROW_B;
+    static __device__ __forceinline__ int swizzle(int r) { return PIECES >= 16 ? r : r >> 1; }
+    // a wave's load `i` of LOADS into the 16 rows at `lds`; row(r) is row r's first element in `base`
+    template <class Row>
+    static __device__ __forceinline__ void load(const void *__restrict__ base, Row row, char *lds, int i, int lane)
+    {
+        const int r = i * ROWS_A_LOAD + lane / PIECES, piece = (lane % PIECES) ^ swizzle(r);
+        const char *src = reinterpret_cast<const char *>(base) + row(r) * (ROW_B / D) + piece * 16;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)(lds + i * 1024), 16, 0, 0);
+    }
+    // the kk-th quarter of row m's channels, widened
+    static __device__ __forceinline__ void read(const char *lds, int m, int kk, float (&x)[D / 4])
+    {
+#pragma unroll
+        for (int i = 0; i < PIECES / 4; ++i) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(lds + m * ROW_B + (((kk * (PIECES / 4) + i) ^ swizzle(m)) * 16));
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (DTYPE == KVS_F32) x[4 * i + u] = __uint_as_float(w[u]);
+                else { x[8 * i + 2 * u] = bf16_lo(w[u]); x[8 * i + 2 * u + 1] = bf16_hi(w[u]); }
+            }
+        }
+    }
+};
+
 // 16 x 16 dot products of D channels: entry r of a lane is row 4 kk + r of `a` with row m of `b`.  Two chains, so that an
 // instruction does not wait for the one before.
 template <int D>
