@@ -5,11 +5,15 @@
 // its eight waves deal the keys among themselves, 16 or 64 at a time, each with its own running maximum; their results meet in
 // LDS at the end.  Both products run on v_mfma_f32_16x16x4_f32 (fp32 in, fp32 out): S^T = K Q^T leaves a lane with four
 // keys of one query, which is the layout the second product, O^T += V^T P^T, wants its P in, so P stays in registers.
-// Operands come straight from global memory: the layers that come here are small, and what they are bound by is the
-// latency of one chain of loads and products, so the keys are spread over as many waves as there are.
+// The layers that come here are small, and what they are bound by is one chain of loads and products on a few compute units (12
+// workgroups for 47 rows of 4 heads), so the keys are spread over as many waves as there are, K and Q go through LDS as
+// consecutive bytes (Rows16) before their positions are known, and a lane's V values are consecutive channels: any order of the
+// output's channels over the matrix rows is as good, so lane m16 has the four channels 4 m16 .. of each 64, one load for all.
 //
-// Measured: 47 rows of 4 heads over 512 fp32 tokens, head_dim 64: 39 -> 12.4 us (before: one token per workgroup, its
-// keys in turn, dot products on the vector units).
+// Measured: 47 rows of 4 heads over 512 fp32 tokens, head_dim 64: 12.3 -> 11.1 us with K and Q through LDS, V in wide loads and the
+// waves' weights made once a row; 50 rows of 32:8 heads of 128, 512 tokens, 21.6 -> 17.5, 300 of 64, 3000 tokens, 273 -> 224.  (V asked for
+// before the scores: the same, and 12 % slower on 1200 bf16 rows of head_dim 64.)
+// (one token per workgroup, its keys in turn, dot products on the vector units: 39 us).
 #include "attention.h"
 #include "f32_tiles.h"
 
@@ -23,12 +27,28 @@ namespace {
 constexpr int kF32Waves = 8;
 constexpr int kF32Threads = kF32Waves * 64;
 constexpr int kF32Rows = 16;
+constexpr int kF32Tiles = 4;                           // tiles of 16 keys that a wave takes at a time (one in contexts where that leaves waves without)
+template <int DTYPE, int D>
+constexpr int kF32Flight = Rows16<DTYPE, D>::BYTES <= 4096 ? 4 : 2;   // of them, in LDS together: what fits beside the query rows
 
 template <int DTYPE>
 __device__ __forceinline__ float load_elem(const void *p, int64_t i)
 {
     if (DTYPE == KVS_F32) return ((const float *)p)[i];
     return __uint_as_float((uint32_t)((const uint16_t *)p)[i] << 16);
+}
+
+// four consecutive elements, widened
+template <int DTYPE>
+__device__ __forceinline__ void load_four(const void *p, int64_t i, float *x)
+{
+    if (DTYPE == KVS_F32) {
+        const float4 v = *reinterpret_cast<const float4 *>((const float *)p + i);
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else {
+        const uint2 v = *reinterpret_cast<const uint2 *>((const uint16_t *)p + i);
+        x[0] = bf16_lo(v.x); x[1] = bf16_hi(v.x); x[2] = bf16_lo(v.y); x[3] = bf16_hi(v.y);
+    }
 }
 
 template <int DTYPE, int D>
@@ -38,10 +58,10 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const void *__restrict__ k_cache, const void *__restrict__ v_cache, float scale,
     void *__restrict__ out, float *__restrict__ lse_out)
 {
-    constexpr int DB = D / 16;                         // 16-channel blocks of the output
-    __shared__ float m_s[kF32Waves][kF32Rows], l_s[kF32Waves][kF32Rows];
-    constexpr int OC = 64;                             // channels that meet in LDS at a time
-    __shared__ float o_s[kF32Waves][kF32Rows][OC + 4];
+    constexpr int DB = D / 16;                         // matrix tiles of the output: tile db, row i is channel 64 (db / 4) + 4 i + db % 4
+    using Rows = Rows16<DTYPE, D>;
+    extern __shared__ __attribute__((aligned(16))) char rows_s[];  // the query rows, then kF32Flight tiles of keys a wave; the results afterwards
+    __shared__ float m_s[kF32Waves][kF32Rows], l_s[kF32Waves][kF32Rows], x_s[kF32Waves][kF32Rows];
     const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % n_kv_heads;
@@ -54,17 +74,33 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const int row0 = (tile_lin - td.tile_begin[b]) * kF32Rows;
 
     // this lane's query (the four lanes of a column share it)
-    const int rq = min(row0 + m16, n_rows - 1);
-    const int64_t s_glob = sel0 + rq / grp;
-    const int head = g * grp + rq % grp;
-    const int pos = min(max(sel_pos[s_glob], 0), ctx_len - 1);       // memory safety; the caller guarantees the range
-    float qv[D / 4];
-    load_quarter<DTYPE, D>(q_sel, (s_glob * n_q_heads + head) * (int64_t)D, kk, qv);
+    auto q_row = [&](int r) {
+        const int rq = min(row0 + r, n_rows - 1);
+        return ((sel0 + rq / grp) * n_q_heads + g * grp + rq % grp) * (int64_t)D;
+    };
+    const int pos = min(max(sel_pos[sel0 + min(row0 + m16, n_rows - 1) / grp], 0), ctx_len - 1);       // memory safety; the caller guarantees the range
+    if (wave < Rows::LOADS) Rows::load(q_sel, q_row, rows_s, wave, lane);
+    char *const mine = rows_s + Rows::BYTES * (1 + kF32Flight<DTYPE, D> * wave);
+    // tile i of the wave's keys from k0 on (keys past `last` are clamped and not used)
+    auto fetch = [&](int k0, int i, int last) {
+#pragma unroll
+        for (int l = 0; l < Rows::LOADS; ++l)
+            Rows::load(k_cache, [&](int r) { return ((ctx_off + min(k0 + 16 * i + r, last)) * n_kv_heads + g) * (int64_t)D; }, mine + i * Rows::BYTES, l, lane);
+    };
+    // the first keys do not wait for the positions
+    const bool small = ctx_len <= kF32Waves * 16;
+    const int first_k0 = wave * 16 * (small ? 1 : kF32Tiles);
+#pragma unroll
+    for (int i = 0; i < kF32Flight<DTYPE, D>; ++i)
+        if ((i == 0 || !small) && first_k0 + 16 * i < ctx_len) fetch(first_k0, i, ctx_len - 1);
     int pmin = pos, pmax = pos;
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) { pmin = min(pmin, __shfl_xor(pmin, o)); pmax = max(pmax, __shfl_xor(pmax, o)); }
     pmin = __builtin_amdgcn_readfirstlane(pmin);
     pmax = __builtin_amdgcn_readfirstlane(pmax);
+    __syncthreads();
+    float qv[D / 4];
+    Rows::read(rows_s, m16, kk, qv);
 
     f32x4 acc[DB];
 #pragma unroll
@@ -72,7 +108,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     float m_run = kLowest, l_run = 0.f;               // l_run: this lane's keys only
     // the wave's keys, TILES tiles of 16 at a time: one where that leaves no wave without (64 fp32 tokens of 8 heads of 128: 13.2 -> 9.8 us)
     auto sweep = [&](auto tiles) {
-        constexpr int TILES = decltype(tiles)::value;
+        constexpr int TILES = decltype(tiles)::value, FLIGHT = TILES < kF32Flight<DTYPE, D> ? TILES : kF32Flight<DTYPE, D>;
         for (int k0 = wave * 16 * TILES; k0 <= pmax; k0 += kF32Waves * 16 * TILES) {
             f32x4 s[TILES];
             float mx = -INFINITY;
@@ -84,21 +120,32 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
                     for (int r = 0; r < 4; ++r) {
                         const int key = k0 + 16 * t + 4 * kq + r;
                         const float p = __shfl(s[t][r], 16 * kq + m16);
-                        const int64_t vrow = ((ctx_off + min(key, pmax)) * n_kv_heads + g) * (int64_t)D + 4 * kk;
+                        const int64_t vrow = ((ctx_off + min(key, pmax)) * n_kv_heads + g) * (int64_t)D + 16 * kk;
 #pragma unroll
-                        for (int c = 0; c < D / 4; ++c) {              // acc[c / 4][c % 4] is channel 16 (c / 4) + 4 kk + c % 4
-                            const float v = load_elem<DTYPE>(v_cache, vrow + 16 * (c >> 2) + (c & 3));
+                        for (int c = 0; c < D / 4; ++c) {              // acc[c / 4][c % 4] is channel 64 (c / 16) + 16 kk + 4 (c % 4) + c / 4 % 4
+                            const float v = load_elem<DTYPE>(v_cache, vrow + 64 * (c >> 4) + 4 * (c & 3) + (c >> 2 & 3));
                             if (key <= pos && !(fabsf(v) < INFINITY)) acc[c >> 2][c & 3] += p * v;
                         }
                     }
                 }
             };
 #pragma unroll
+            for (int t0 = 0; t0 < TILES; t0 += FLIGHT) {
+                if (k0 != first_k0 || t0 > 0) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // what lay there has been read
+#pragma unroll
+                    for (int i = 0; i < FLIGHT; ++i) fetch(k0 + 16 * t0, i, pmax);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                }
+#pragma unroll
+                for (int i = 0; i < FLIGHT; ++i) {
+                    float kv[D / 4];
+                    Rows::read(mine + i * Rows::BYTES, m16, kk, kv);
+                    s[t0 + i] = dots<D>(kv, qv);
+                }
+            }
+#pragma unroll
             for (int t = 0; t < TILES; ++t) {
-                float kv[D / 4];
-                const int key = min(k0 + 16 * t + m16, pmax);          // (nothing past the last row's position is read)
-                load_quarter<DTYPE, D>(k_cache, ((ctx_off + key) * n_kv_heads + g) * (int64_t)D, kk, kv);
-                s[t] = dots<D>(kv, qv);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     s[t][r] = k0 + 16 * t + 4 * kk + r <= pos ? s[t][r] * scale : -INFINITY;
@@ -122,10 +169,10 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
                 float v[4][DB];
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int key = min(k0 + 16 * t + 4 * kk + r, pmax);
-                    const int64_t vrow = ((ctx_off + key) * n_kv_heads + g) * (int64_t)D + m16;
+                    const int key = min(k0 + 16 * t + 4 * kk + r, pmax);       // (nothing past the last row's position is read)
+                    const int64_t vrow = ((ctx_off + key) * n_kv_heads + g) * (int64_t)D + 4 * m16;
 #pragma unroll
-                    for (int db = 0; db < DB; ++db) v[r][db] = load_elem<DTYPE>(v_cache, vrow + 16 * db);
+                    for (int db = 0; db < DB; db += 4) load_four<DTYPE>(v_cache, vrow + 16 * db, &v[r][db]);
                 }
                 bool odd = false;
                 if (!all_seen) {
@@ -149,37 +196,77 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
             }
         }
     };
-    if (pmax < kF32Waves * 16) sweep(std::integral_constant<int, 1>{});
-    else sweep(std::integral_constant<int, 4>{});
+    if (small) sweep(std::integral_constant<int, 1>{});
+    else sweep(std::integral_constant<int, kF32Tiles>{});
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
     if (kk == 0) { m_s[wave][m16] = m_run; l_s[wave][m16] = l_run; }
-    // the waves' shares in wave order
+    // the waves' shares in wave order: their weights, one a thread, then four channels of a row a thread
+    float *const o_s = reinterpret_cast<float *>(rows_s);          // [waves][rows][64 + 4], over the keys
+    constexpr int OC = 64, OP = OC + 4;                            // channels that meet in LDS at a time, and a row's pitch
 #pragma unroll
     for (int c0 = 0; c0 < D; c0 += OC) {
-        if (c0 > 0) __syncthreads();
+        __syncthreads();                                           // the keys, or the channels before, have been read
 #pragma unroll
-        for (int db = 0; db < OC / 16; ++db) *reinterpret_cast<f32x4 *>(&o_s[wave][m16][16 * db + 4 * kk]) = acc[c0 / 16 + db];
+        for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f32x4 *>(o_s + (wave * kF32Rows + m16) * OP + 16 * kk + 4 * r) =
+                f32x4{acc[c0 / 16][r], acc[c0 / 16 + 1][r], acc[c0 / 16 + 2][r], acc[c0 / 16 + 3][r]};
+        if (c0 == 0 && tid < kF32Waves * kF32Rows) {
+            const int w = tid / kF32Rows, r = tid % kF32Rows;
+            float mt = m_s[0][r];
+#pragma unroll
+            for (int v = 1; v < kF32Waves; ++v) mt = fmaxf(mt, m_s[v][r]);
+            x_s[w][r] = expf(m_s[w][r] - mt);
+        }
         __syncthreads();
-        for (int e = tid; e < kF32Rows * OC; e += kF32Threads) {
-            const int r = e / OC, c = e % OC;
-            if (row0 + r >= n_rows) continue;
+        const int r = tid / (OC / 4), c = tid % (OC / 4) * 4;
+        if (r >= kF32Rows || row0 + r >= n_rows) continue;
+        float l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) {
+            const float x = x_s[w][r];
+            const f32x4 ow = *reinterpret_cast<const f32x4 *>(o_s + (w * kF32Rows + r) * OP + c);
+            l += x * l_s[w][r];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] += x * ow[u];
+        }
+        const int64_t orow = (sel0 + (row0 + r) / grp) * n_q_heads + g * grp + (row0 + r) % grp, at = orow * D + c0 + c;
+        if (DTYPE == KVS_F32) {
+            *reinterpret_cast<f32x4 *>((float *)out + at) = f32x4{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
+        } else {
+            uint2 w2;
+            w2.x = f32_to_bf16_bits(o[0] / l) | f32_to_bf16_bits(o[1] / l) << 16;
+            w2.y = f32_to_bf16_bits(o[2] / l) | f32_to_bf16_bits(o[3] / l) << 16;
+            *reinterpret_cast<uint2 *>((uint16_t *)out + at) = w2;
+        }
+        if (lse_out && c0 + c == 0) {
             float mt = m_s[0][r];
 #pragma unroll
             for (int w = 1; w < kF32Waves; ++w) mt = fmaxf(mt, m_s[w][r]);
-            float l = 0.f, o = 0.f;
-#pragma unroll
-            for (int w = 0; w < kF32Waves; ++w) {
-                const float x = expf(m_s[w][r] - mt);
-                l += x * l_s[w][r];
-                o += x * o_s[w][r][c];
-            }
-            const int64_t orow = (sel0 + (row0 + r) / grp) * n_q_heads + g * grp + (row0 + r) % grp;
-            if (DTYPE == KVS_F32) ((float *)out)[orow * D + c0 + c] = o / l;
-            else ((uint16_t *)out)[orow * D + c0 + c] = (uint16_t)f32_to_bf16_bits(o / l);
-            if (lse_out && c0 + c == 0) lse_out[orow] = mt + logf(l);
+            lse_out[orow] = mt + logf(l);
         }
     }
+}
+
+template <int DTYPE, int D>
+kvs_status launch_f32(dim3 grid, const AttnTiles &td, const kvs_shape *shape, int tiles, const void *q_sel, const int32_t *sel_pos,
+                      const void *k_cache, const void *v_cache, float scale, void *out, float *lse_out, hipStream_t st)
+{
+    using Rows = Rows16<DTYPE, D>;
+    static_assert(Rows::LOADS <= kF32Waves, "a wave loads one share of the query rows");
+    constexpr int keys = Rows::BYTES * (1 + kF32Flight<DTYPE, D> * kF32Waves), results = kF32Waves * kF32Rows * (64 + 4) * (int)sizeof(float);
+    constexpr int lds_bytes = keys > results ? keys : results;
+    static DeviceOnce attr_once;
+    const kvs_status ast = once_per_device(attr_once, [] {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_f32_kernel<DTYPE, D>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_partial_attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
+    });
+    if (ast != KVS_OK) return ast;
+    hipLaunchKernelGGL((attn_f32_kernel<DTYPE, D>), grid, dim3(kF32Threads), lds_bytes, st, td, shape->n_q_heads, shape->n_kv_heads, tiles,
+                       q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out);
+    return check_launch("kvs_partial_attention(f32)");
 }
 
 } // namespace
@@ -194,17 +281,14 @@ kvs_status launch_attention_f32(const kvs_shape *shape, const AttnBatch &bd, int
     const int64_t tiles = build_attn_tiles(shape, bd, kF32Rows, td);
     if (tiles < 0) return fail(KVS_EINVAL, "kvs_partial_attention: too many row tiles");
     if (tiles == 0) return KVS_OK;
-    const dim3 grid((unsigned)(tiles * shape->n_kv_heads)), block(kF32Threads);
-#define KVS_ATT_CASE(DT, DD)                                                                              \
-    hipLaunchKernelGGL((attn_f32_kernel<DT, DD>), grid, block, 0, st, td, shape->n_q_heads,                \
-                       shape->n_kv_heads, (int)tiles, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out)
+    const dim3 grid((unsigned)(tiles * shape->n_kv_heads));
+#define KVS_ATT_CASE(DT, DD) return launch_f32<DT, DD>(grid, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, st)
     if (shape->dtype == KVS_F32 && shape->head_dim == 64) KVS_ATT_CASE(KVS_F32, 64);
-    else if (shape->dtype == KVS_F32 && shape->head_dim == 128) KVS_ATT_CASE(KVS_F32, 128);
-    else if (shape->dtype == KVS_BF16 && shape->head_dim == 64) KVS_ATT_CASE(KVS_BF16, 64);
-    else if (shape->dtype == KVS_BF16 && shape->head_dim == 128) KVS_ATT_CASE(KVS_BF16, 128);
-    else return fail(KVS_EUNSUPPORTED, "kvs_partial_attention: head_dim %d", shape->head_dim);
+    if (shape->dtype == KVS_F32 && shape->head_dim == 128) KVS_ATT_CASE(KVS_F32, 128);
+    if (shape->dtype == KVS_BF16 && shape->head_dim == 64) KVS_ATT_CASE(KVS_BF16, 64);
+    if (shape->dtype == KVS_BF16 && shape->head_dim == 128) KVS_ATT_CASE(KVS_BF16, 128);
 #undef KVS_ATT_CASE
-    return check_launch("kvs_partial_attention(f32)");
+    return fail(KVS_EUNSUPPORTED, "kvs_partial_attention: head_dim %d", shape->head_dim);
 }
 
 } // namespace kvs
