@@ -44,6 +44,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 #endif
 
 constexpr int kAttnBigTileMinGrid = KVS_ATTN_BIG_MIN_GRID;
+constexpr int kAttnWholeFrom = 312;
 constexpr int D = 128;            // head_dim
 constexpr int BN = 64;            // keys per LDS tile
 constexpr int K_LD = D + 8;       // K tile row pitch in bf16 (272 B: 16-byte reads of 16 rows hit 16 bank groups)
@@ -527,15 +528,19 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     }
     // with fewer 256-row tiles than compute units the large kernel still wins if the caller's
     // workspace lets it cut the key ranges and its tiles are not mostly padding
-    AttnSplitPlan plan2 = {1, 0, 0, 0, false};
+    AttnSplitPlan plan2 = {1, 0, false};
     if (fits32) plan2 = attention_mfma2_plan(shape, bd, workspace ? workspace_bytes : 0);
     const int splits2 = plan2.n_splits;
-    const bool fills = big_tiles * shape->n_kv_heads >= kAttnBigTileMinGrid;
     const bool dense_tiles = rows * 10 >= big_tiles * 256 * 6;
+    const bool fills = big_tiles * shape->n_kv_heads >= kAttnBigTileMinGrid;
+    // Somewhat more tiles than units are as long as the longest tile, which most units wait for: pieces are shorter.  2161 of 24000 tokens on
+    // 32:8 heads (272 tiles) 547 us whole, 449 in pieces; 268 and 300 tiles of 9000 and 100000 tokens on 32:4 222 and 203, 2210 and 1805;
+    // 320, 324 and 352 tiles 197 and 204, 226 and 228, 550 and 594: the line lies between.
+    const bool whole = big_tiles * shape->n_kv_heads >= kAttnWholeFrom || !dense_tiles || splits2 < 2;
     // (below ~50 such tiles the per-workgroup start-up of the large kernel costs more than it gains)
     const bool big = fits32 && (forced ? forced == 2 : fills || (splits2 >= 2 && dense_tiles && big_tiles * shape->n_kv_heads >= 48));
     if (big) {
-        if (fills && !forced) plan2 = {1, 0, 0, 0, plan2.recentre};   // fills the chip: whole key ranges
+        if (fills && whole && !forced) plan2 = {1, 0, plan2.recentre};
         return launch_attention_mfma2(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, workspace, plan2, st);
     }
     return launch_mfma_variant<KVS_ATTN_NWAVES>(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out,

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
     const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     float scale_log2, uint16_t *__restrict__ out, float *__restrict__ lse_out,
-    int n_splits, const int4 *__restrict__ split_plan, const uint16_t *__restrict__ piece_list,
+    int n_splits, const int2 *__restrict__ split_plan, const uint16_t *__restrict__ piece_list,
     float *__restrict__ part_o, float4 *__restrict__ part_ml, int share_units)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // K ring, then V^T ring
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // neighbouring blocks a wave it would where block 6 has, which is three blocks later.
     auto block_row = [&](int nb) { return 32 * (nb == 0 ? wave : 2 * NWAVES - 1 - wave); };
 
-    // the plan: (pieces per row tile in use, key tiles per large piece, per small piece, small pieces)
-    int4 plan = make_int4(1, 0, 0, 0);
+    // the plan: (pieces per row tile in use, key tiles per piece)
+    int2 plan = make_int2(1, 0);
     if (SPLIT) {
         plan = *split_plan;
         if (split >= plan.x) {   // a piece slot the plan does not use: mark it empty for the merge
@@ -339,12 +339,10 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // this workgroup's share of the key tiles: [t_lo, t_hi)
     int t_lo = 0, t_hi = n_kv_tiles;
     if (SPLIT) {
-        // piece 0 is the top of the context; counted from the bottom, the first plan.w pieces are
-        // plan.z key tiles long and the others plan.y
-        const int j = plan.x - 1 - split;
-        const int lo = j < plan.w ? j * plan.z : plan.w * plan.z + (j - plan.w) * plan.y;
+        // piece 0 is the top of the context
+        const int lo = (plan.x - 1 - split) * plan.y;
         t_lo = min(n_kv_tiles, lo);
-        t_hi = min(n_kv_tiles, lo + (j < plan.w ? plan.z : plan.y));
+        t_hi = min(n_kv_tiles, lo + plan.y);
     }
     if (SPLIT && t_lo >= t_hi) {   // nothing of this tile in this key range: mark the piece empty
 #pragma unroll
@@ -865,14 +863,17 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
 
 namespace {
 
-// Plans a split launch on the device, where the positions are: the size of the large pieces and
+// Plans a split launch on the device, where the positions are: the size of the pieces and
 // the order in which the workgroups take the pieces.
 //
-// Size.  The large pieces run in rounds of one per compute unit, each round as long as the chunk,
+// Size.  Pieces run in rounds of one per compute unit, each round as long as the chunk,
 // and a piece costs about piece_overhead key tiles on top of its own: so for 1, 2, ... rounds the
 // best chunk is the smallest one whose pieces just fit, and the round count with the shortest
-// predicted time wins (fewer, longer rounds win ties through the overhead).  round_fill < 1 leaves
-// head-room.  Thread i tries chunk c_min + i * step over the lengths of all row tiles (taken from
+// predicted time wins (fewer, longer rounds win ties through the overhead).  A round is filled to the last
+// unit: leaving 8 % of them free, and two short pieces at the bottom of the context to level out the finish, made
+// pieces longer or a round more (20 launches of 44 to 192 tiles, 2500 to 100000 tokens: geometric mean 127.0 -> 115.6 us; 738 of 8192
+// tokens on 32:8 heads 94.9 -> 81.9, 481 of 12000 on 28:4 92.2 -> 70.4, 720 of 30000 194.7 -> 170.9; at worst 48.1 -> 49.3).
+// Thread i tries chunk c_min + i * step over the lengths of all row tiles (taken from
 // each tile's last row, i.e. exact for positions in ascending order; any other order costs speed
 // only: the attention kernel finds its own key range).
 //
@@ -885,15 +886,13 @@ constexpr int PLAN_MAX_TILES = kAttnPlanMaxTiles;
 constexpr int PLAN_MAX_ROUNDS = 4;
 __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const AttnTiles td, int grp, int n_kv_heads, int total_tiles, const int32_t *__restrict__ sel_pos,
-    int s_max, int ctx_tiles, int small_chunk, int n_small, float round_fill, float piece_overhead,
-    int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
+    int s_max, int ctx_tiles, float piece_overhead, int2 *__restrict__ plan, uint16_t *__restrict__ piece_list)
 {
     __shared__ int len[PLAN_MAX_TILES];       // key tiles of each row tile
     __shared__ int first_fit[PLAN_MAX_ROUNDS];
-    __shared__ int4 chosen;
+    __shared__ int2 chosen;
     __shared__ int wave_total[PLAN_NT / 64];
     const int tid = threadIdx.x;
-    const int bottom = n_small * small_chunk;
     for (int t = tid; t < total_tiles; t += PLAN_NT) {
         int b = 0;
         while (b + 1 < td.n_req && t >= td.tile_begin[b + 1]) ++b;
@@ -906,8 +905,8 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     }
     if (tid < PLAN_MAX_ROUNDS) first_fit[tid] = 0x7fffffff;
     __syncthreads();
-    const int c_min = max(1, (ctx_tiles - bottom + (s_max - n_small) - 1) / (s_max - n_small));
-    const int c_max = max(c_min, ctx_tiles - bottom);
+    const int c_min = max(1, (ctx_tiles + s_max - 1) / s_max);
+    const int c_max = max(c_min, ctx_tiles);
     const int step = (c_max - c_min + PLAN_NT - 1) / PLAN_NT;
     const int c = c_min + tid * step;
     const bool tries = c <= c_max && (step > 0 || tid == 0);
@@ -915,40 +914,38 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     if (tries) {
         const float rc = 1.0f / (float)c;
         pieces = 0;
-        for (int t = 0; t < total_tiles; ++t) pieces += (int)ceilf((float)max(0, len[t] - bottom) * rc - 1.0e-4f);
+        for (int t = 0; t < total_tiles; ++t) pieces += (int)ceilf((float)len[t] * rc - 1.0e-4f);
         pieces *= n_kv_heads;
     }
     // the piece count falls as the chunk grows, so per round count the first thread that fits is
     // the answer: one LDS atomic per wave instead of one per thread
     for (int r = 0; r < PLAN_MAX_ROUNDS; ++r) {
-        const bool fits = tries && (float)pieces <= round_fill * (float)(kAttnSplitCus * (r + 1));
+        const bool fits = tries && pieces <= kAttnSplitCus * (r + 1);
         const unsigned long long m = __ballot(fits);
         if (m != 0 && (tid & 63) == __ffsll((long long)m) - 1) atomicMin(&first_fit[r], c);
     }
     __syncthreads();
     if (tid == 0) {
-        int best_c = c_max;                 // one large piece per row tile always "fits"
+        int best_c = c_max;                 // one piece per row tile always "fits"
         float best_t = 3.0e38f;
         for (int r = 0; r < PLAN_MAX_ROUNDS; ++r) {
             if (first_fit[r] == 0x7fffffff) continue;
             const float time = (float)(r + 1) * ((float)first_fit[r] + piece_overhead);
             if (time < best_t) { best_t = time; best_c = first_fit[r]; }
         }
-        chosen = make_int4(n_small + (ctx_tiles - bottom + best_c - 1) / best_c, best_c, small_chunk, n_small);
+        chosen = make_int2((ctx_tiles + best_c - 1) / best_c, best_c);
         *plan = chosen;
     }
     __syncthreads();
     // the list: a stable partition of the piece ids into those with keys and the rest
-    const int4 pl = chosen;
+    const int2 pl = chosen;
     const int n_ids = s_max * total_tiles;
     const int per = (n_ids + PLAN_NT - 1) / PLAN_NT;
     const int e0 = min(n_ids, tid * per), e1 = min(n_ids, e0 + per);
     auto has_keys = [&](int e) {
         const int split = e / total_tiles, tile_lin = total_tiles - 1 - e % total_tiles;
         if (split >= pl.x) return false;
-        const int j = pl.x - 1 - split;
-        const int lo = j < pl.w ? j * pl.z : pl.w * pl.z + (j - pl.w) * pl.y;
-        return len[tile_lin] > lo;
+        return len[tile_lin] > (pl.x - 1 - split) * pl.y;
     };
     int mine = 0;
     for (int e = e0; e < e1; ++e) mine += has_keys(e) ? 1 : 0;
@@ -978,7 +975,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
 template <bool WANT_LSE, bool SPLIT, bool RECENTRE>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
-                      float scale_log2, void *out, float *lse_out, int n_splits, const int4 *split_plan,
+                      float scale_log2, void *out, float *lse_out, int n_splits, const int2 *split_plan,
                       const uint16_t *piece_list, float *part_o, float4 *part_ml, int share_units)
 {
     static DeviceOnce attr_once;
@@ -1024,7 +1021,7 @@ int share_units_for(const kvs_shape *shape, int64_t tiles)
 
 AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, size_t workspace_bytes)
 {
-    const AttnSplitPlan whole = {1, 0, 0, 0, false};
+    const AttnSplitPlan whole = {1, 0, false};
     const int grp = shape->n_q_heads / shape->n_kv_heads;
     int64_t tiles = 0, max_ctx = 0, kv_bytes = 0;
     for (int i = 0; i < bd.n_req; ++i) {
@@ -1036,7 +1033,7 @@ AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, 
         }
     }
     const int64_t wgs = tiles * shape->n_kv_heads;
-    if (wgs >= kAttnSplitBelowWgs) return AttnSplitPlan{1, 0, 0, 0, kv_bytes > kAttnRecentreBytes};
+    if (wgs >= kAttnSplitBelowWgs) return AttnSplitPlan{1, 0, kv_bytes > kAttnRecentreBytes};
     if (wgs <= 0 || tiles > kAttnPlanMaxTiles) return whole;
     const int64_t ctx_tiles = (max_ctx + BN - 1) / BN;
     const int64_t n_rows_total = (bd.cu_sel[bd.n_req] - bd.cu_sel[0]) * shape->n_q_heads;
@@ -1047,11 +1044,7 @@ AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, 
     const int64_t by_ws = (int64_t)((workspace_bytes - kAttnPlanBytes) / (kAttnPartBytesPerSlot * (size_t)(n_rows_total > 0 ? n_rows_total : 1)));
     if (s_max > by_ws) s_max = by_ws;
     if (s_max < 2) return whole;
-    // Small pieces at the bottom of the context (every row tile has them, and they start last)
-    // fill the gaps the large ones leave; they pay off once the large pieces can be several times
-    // their size.
-    const bool taper = s_max >= 6 && ctx_tiles >= 8 * kAttnSmallChunk;
-    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, kAttnSmallChunk, taper ? kAttnSmallPieces : 0, false};
+    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, false};
 }
 
 kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, const void *q_sel,
@@ -1084,13 +1077,11 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     float *part_o = (float *)workspace - row0 * n_splits * D;
     float4 *ml_base = (float4 *)((char *)workspace + (size_t)n_rows_total * n_splits * D * sizeof(float));
     float4 *part_ml = ml_base - row0 * n_splits;
-    int4 *split_plan = (int4 *)(ml_base + n_rows_total * n_splits);
+    int2 *split_plan = (int2 *)(ml_base + n_rows_total * n_splits);
     uint16_t *piece_list = (uint16_t *)(split_plan + 1);
-    float round_fill = kAttnRoundFill, piece_overhead = kAttnPieceOverhead;
-    int small_chunk = plan.small_chunk, n_small = plan.n_small;
+    const float piece_overhead = kAttnPieceOverhead;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(PLAN_NT), 0, st, td, shape->n_q_heads / shape->n_kv_heads,
-                       shape->n_kv_heads, (int)tiles, sel_pos, n_splits, plan.ctx_tiles, small_chunk, n_small, round_fill,
-                       piece_overhead, split_plan, piece_list);
+                       shape->n_kv_heads, (int)tiles, sel_pos, n_splits, plan.ctx_tiles, piece_overhead, split_plan, piece_list);
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));

@@ -1,0 +1,37 @@
+"""Launches around the line between pieces and whole key ranges: 256 to 311 row tiles of 256 in pieces, 312 whole; every row
+against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from attn_check import check_attention
+from paper_2503_16525_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hk,k,order", [(64, 1000, "ascending"), (64, 1024, "shuffled"), (62, 1280, "ascending"), (78, 1024, "ascending"), (52, 1281, "ascending")])
+def test_tiles_around_the_line(hk, k, order):
+    n = 1300
+    print(f"attention: {hk} heads, {k} of {n} tokens, {(k + 255) // 256 * hk} tiles, positions {order}", flush=True)
+    rng = np.random.default_rng(hk + k)
+    pos = np.sort(rng.permutation(n)[:k]).astype(np.int32)
+    if order == "shuffled":
+        pos = rng.permutation(pos)
+    gen = torch.Generator().manual_seed(k)
+    q = (torch.randn((k, hk, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16)
+    kk = torch.randn((n, hk, 128), generator=gen).to(torch.bfloat16)
+    v = torch.randn((n, hk, 128), generator=gen).to(torch.bfloat16)
+    kn, vn = oracle._as_np(kk), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0)
+    sh = B.make_shape(hk, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, 1, n, k),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full((k + 2, hk, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((k, hk), 7.0, device="cuda")
+    B.kvs_partial_attention(sh, [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), kk.cuda(), v.cuda(), 1.0, out, lse, ws)
+    got = out.float().cpu().numpy()
+    assert np.all(got[k:] == 7.0)
+    check_attention(got[:k], ref, mag, "bf16", f"{(k + 255) // 256 * hk} tiles {order}")
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
