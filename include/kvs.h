@@ -204,7 +204,9 @@ KVS_API kvs_status kvs_scatter_kv(const kvs_shape *shape, int64_t n_rows,
  *         (few selected tokens over long contexts, e.g. the decode-stage recompute) cut each row tile's
  *         key range into up to 16 pieces handled by separate workgroups and merge them; results are the
  *         same up to fp32 summation order.  With less, such launches take fewer pieces or keep whole key
- *         ranges.  Launches that fill the chip keep whole key ranges and do not touch it.  The size
+ *         ranges.  Launches that fill the chip keep whole key ranges; where they hold several requests
+ *         their workgroups draw work from counters in it (without it they take it in a fixed order).  As
+ *         every workspace it is one call's until that call has ended on its stream.  The size
  *         asked for stays below 0.56 GB for one request (528 bytes a row and piece).
  * bf16 inputs (head_dim 128, scale > 0) are contracted on the matrix cores with fp32 accumulation
  * and an fp32 softmax, the softmax weights entering the second product as bf16; every other case

@@ -80,7 +80,7 @@ static_assert(kAttnSplitMax * kAttnPlanMaxTiles <= 65536, "piece ids are 16 bits
 AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, size_t workspace_bytes);
 kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, const void *q_sel,
                                   const int32_t *sel_pos, const void *k_cache, const void *v_cache,
-                                  float scale, void *out, float *lse_out, void *workspace,
+                                  float scale, void *out, float *lse_out, void *workspace, size_t workspace_bytes,
                                   const AttnSplitPlan &plan, hipStream_t st);
 
 kvs_status launch_attention_f32(const kvs_shape *shape, const AttnBatch &bd, int64_t n_sel,

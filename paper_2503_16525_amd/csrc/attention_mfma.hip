@@ -541,7 +541,7 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     const bool big = fits32 && (forced ? forced == 2 : fills || (splits2 >= 2 && dense_tiles && big_tiles * shape->n_kv_heads >= 48));
     if (big) {
         if (fills && whole && !forced) plan2 = {1, 0, plan2.recentre};
-        return launch_attention_mfma2(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, workspace, plan2, st);
+        return launch_attention_mfma2(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, workspace, workspace_bytes, plan2, st);
     }
     return launch_mfma_variant<KVS_ATTN_NWAVES>(shape, bd, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out,
                                                 workspace, workspace_bytes, st);

@@ -1,0 +1,56 @@
+"""Ragged batches with more row tiles than fixed shares take: one workgroup a compute unit draws its tiles.  Around the line between the two,
+requests without and with few selected tokens, head counts that leave units over, more requests than one launch describes, a request
+beyond the last-level cache; every row against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from attn_check import check_attention
+from paper_2503_16525_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(rng, kind):
+    if kind == "15 tiles":        # 64 heads, 4 units each: 14 tiles are shares
+        return [(int(rng.integers(300, 900)), int(k)) for k in (256, 1, 300, 0, 255, 257, 40, 256, 256, 290, 3)]
+    if kind == "14 tiles":
+        return [(int(rng.integers(300, 900)), int(k)) for k in (256, 1, 300, 0, 255, 257, 40, 256, 256, 290)]
+    if kind == "70 requests":
+        return [(int(rng.integers(20, 200)), int(rng.integers(1, 20))) for _ in range(70)]
+    return [(6200, 10)] + [(int(rng.integers(50, 100)), int(rng.integers(1, 40))) for _ in range(16)]
+
+
+@pytest.mark.parametrize("kind,hk,want_lse", [("15 tiles", 64, True), ("15 tiles", 52, False), ("14 tiles", 64, True), ("70 requests", 64, False), ("large", 64, True),
+                                              ("large", 64, False)])
+def test_drawn_tiles(kind, hk, want_lse):
+    print(f"attention: {kind}, {hk} heads, lse {want_lse}", flush=True)
+    rng = np.random.default_rng(hk + len(kind))
+    off, length, cu, pos = [], [], [0], []
+    rows = 0
+    for n, k in _batch(rng, kind):
+        off.append(rows)
+        length.append(n)
+        rows += n + 3
+        pos.append(np.sort(rng.permutation(n)[:k]).astype(np.int32))
+        cu.append(cu[-1] + k)
+    pos = np.concatenate(pos)
+    gen = torch.Generator().manual_seed(hk)
+    q = (torch.randn((cu[-1], hk, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16)
+    k = torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16)
+    v = torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16)
+    kn, vn = oracle._as_np(k), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0, off, length, cu)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0, off, length, cu)
+    sh = B.make_shape(hk, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, len(off), rows, cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+    for _ in range(2):            # the second call finds the first one's queues
+        out = torch.full((cu[-1] + 2, hk, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+        lse = torch.full((cu[-1], hk), 7.0, device="cuda") if want_lse else None
+        B.kvs_partial_attention(sh, off, length, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, ws)
+        got = out.float().cpu().numpy()
+        assert np.all(got[cu[-1]:] == 7.0)
+        check_attention(got[:cu[-1]], ref, mag, "bf16", f"{kind}, {hk} heads")
+        if want_lse:
+            np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
