@@ -45,13 +45,21 @@ constexpr int kAttnSplitBelowWgs = 384;    // launches with fewer workgroups tha
 // start-up (6 us), write-out (4 us) and merge share of a piece, in key tiles; between 18 and 40 it does not matter (12 loses 7 % on 590 of
 // 32768 tokens)
 constexpr double kAttnPieceOverhead = 18.0;
+// Pieces of the 256-row kernel, as the merge sees them: piece s is keys [kAttnPieceKeys * y * (x - 1 - s), kAttnPieceKeys * y * (x - s)) with x, y of
+// what attn_plan_kernel left, and only pieces that begin at or before a row's position have left anything for it.
+struct AttnMergePlan {
+    const int4 *plan;          // nullptr: every one of n_splits slots is filled in, without keys with sum 0
+    const int32_t *sel_pos;    // of the first row's token
+    int n_q_heads, max_ctx;
+};
+constexpr int kAttnPieceKeys = 32;
 // out = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m); pieces with l = 0 drop out;
 // the log-sum-exp comes from the unrounded sums
 kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *part_o, const float4 *part_ml,
-                                  uint16_t *out, float *lse_out, hipStream_t st);
+                                  uint16_t *out, float *lse_out, hipStream_t st, const AttnMergePlan &pieces = {nullptr, nullptr, 1, 1});
 
 // What the host fixes for a split launch of the 256-row kernel: piece slots per row tile (1: no
-// cutting, nothing else is read) and the longest context in key tiles.  Launches too small to fill the chip
+// cutting, nothing else is read) and the longest context.  Launches too small to fill the chip
 // are cut: the size of the pieces is chosen on the device, from the positions, so that the
 // pieces just fill whole rounds of the compute units.  Pieces are started from the top of the
 // context down, range by range.
@@ -66,7 +74,7 @@ kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *par
 // more sweeps, and shorter contexts, most of whose launches meet none, keep the plain speed.
 struct AttnSplitPlan {
     int n_splits;
-    int ctx_tiles;
+    int max_ctx;
     bool recentre;
 };
 constexpr int64_t kAttnRecentreBytes = (int64_t)192 << 20;   // K + V of a launch's largest request

@@ -348,11 +348,13 @@ __global__ __launch_bounds__(NWAVES * 64, 2) void attn_mfma_kernel(
 
 // combines the split pieces of every row: out = sum_s w_s O_s / sum_s w_s l_s with
 // w_s = 2^(m_s - max m); pieces that saw no key carry l = 0 and drop out.  32 lanes per row, four
-// channels per lane, all pieces' loads issued before they are used.
+// channels per lane, all pieces' loads issued before they are used.  PLANNED: the row's position says which pieces there are, and their
+// sums and rows are asked for together.
+template <bool PLANNED>
 __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_splits,
                                                          const float *__restrict__ part_o,
                                                          const float4 *__restrict__ part_ml,
-                                                         uint16_t *__restrict__ out, float *__restrict__ lse_out)
+                                                         uint16_t *__restrict__ out, float *__restrict__ lse_out, const AttnMergePlan pieces)
 {
     const int64_t row = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
     const int c = (threadIdx.x % 32) * 4;
@@ -361,21 +363,32 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_s
     const float *po = part_o + row * n_splits * D + c;
     float4 v[kAttnSplitMax];
     float4 p[kAttnSplitMax];
+    int first = 0, end = n_splits;
+    if (PLANNED) {
+        const int pos = min(max(pieces.sel_pos[row / pieces.n_q_heads], 0), pieces.max_ctx - 1);   // memory safety, as in the attention kernel
+        const int4 plan = *pieces.plan;
+        end = min(plan.x, n_splits);
+        first = max(0, end - 1 - pos / (kAttnPieceKeys * plan.y));
+    }
+    auto there = [&](int s) { return s >= first && s < end; };
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (s < n_splits) p[s] = ml[s];
+        if (there(s)) {
+            p[s] = ml[s];
+            if (PLANNED) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
+        }
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (s < n_splits && p[s].y > 0.f) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
+        if (!PLANNED && there(s) && p[s].y > 0.f) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
     float m = -1.0e30f;
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (s < n_splits && p[s].y > 0.f) m = fmaxf(m, p[s].x);
+        if (there(s) && p[s].y > 0.f) m = fmaxf(m, p[s].x);
     float l = 0.f, l_exact = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (s < n_splits && p[s].y > 0.f) {
+        if (there(s) && p[s].y > 0.f) {
             const float w = __builtin_amdgcn_exp2f(p[s].x - m);
             l += w * p[s].y;
             l_exact += w * p[s].z;
@@ -461,11 +474,11 @@ kvs_status launch_mfma_variant(const kvs_shape *shape, const AttnBatch &bd, cons
 } // namespace
 
 kvs_status launch_attention_merge(int64_t n_rows, int n_splits, const float *part_o, const float4 *part_ml,
-                                  uint16_t *out, float *lse_out, hipStream_t st)
+                                  uint16_t *out, float *lse_out, hipStream_t st, const AttnMergePlan &pieces)
 {
     if (n_rows <= 0) return KVS_OK;
-    hipLaunchKernelGGL(attn_merge_kernel, dim3((unsigned)((n_rows + 7) / 8)), dim3(256), 0, st, n_rows, n_splits,
-                       part_o, part_ml, out, lse_out);
+    hipLaunchKernelGGL(pieces.plan ? attn_merge_kernel<true> : attn_merge_kernel<false>, dim3((unsigned)((n_rows + 7) / 8)), dim3(256), 0, st,
+                       n_rows, n_splits, part_o, part_ml, out, lse_out, pieces);
     return check_launch("kvs_partial_attention(merge)");
 }
 

@@ -48,7 +48,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
 constexpr int D = 128;             // head_dim
-constexpr int BN = 32;             // keys per tile
+constexpr int BN = kAttnPieceKeys; // keys per tile
 constexpr int NWAVES = 4;
 constexpr int NB = 2;              // 32-row query blocks per wave
 constexpr int NT = NWAVES * 64;
@@ -108,16 +108,6 @@ __device__ __forceinline__ int request_of(const int32_t *tile_begin, int n_req, 
     return b;
 }
 
-// Key tiles up to the position of row tile t's last row (the tiles are aligned to the end of their request's rows): the length of
-// its sweep for positions in ascending order.
-__device__ __forceinline__ int tile_reach(const int32_t *begin, const int32_t *n_sel, const int32_t *ctx_len, const int64_t *sel_lo, int n_req, int grp,
-                                          int t, const int32_t *__restrict__ sel_pos)
-{
-    const int b = request_of(begin, n_req, t);
-    const int last_row = n_sel[b] * grp - (begin[b + 1] - 1 - t) * ROWS - 1;
-    return min(max(sel_pos[sel_lo[b] + last_row / grp], 0), ctx_len[b] - 1) / BN + 1;
-}
-
 // The requests' geometry in LDS, where lanes of a wave ask for different requests.
 struct TileTable {
     int32_t begin[kAttnMaxReq + 1], n_sel[kAttnMaxReq], ctx_len[kAttnMaxReq];
@@ -165,11 +155,24 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     TileTable *const table = reinterpret_cast<TileTable *>(scratch + 16384);
     static_assert(MAXT * (2 * sizeof(float) + (1 + NWAVES) * sizeof(uint16_t)) + NWAVES * sizeof(int) <= 16384, "the table lies behind the lists");
-    table->load(td, tid);
-    __syncthreads();
+    const bool one = td.n_req == 1;           // its geometry stays in scalar registers: 256 workgroups that each read
+                                              // the argument block's whole table cost 15 % of 32768 tokens 10 us
+    if (!one) {
+        table->load(td, tid);
+        __syncthreads();
+    }
     const int padded = (total_tiles + 3) & ~3;
-    for (int t = tid; t < padded; t += NT)    // (the kernel's requests are below 4 GiB: reaches below 2^20)
-        key[t] = t < total_tiles ? (uint32_t)(tile_reach(table->begin, table->n_sel, table->ctx_len, table->sel_lo, td.n_req, grp, t, sel_pos) + kAttnTileOverhead) * MAXT + (uint32_t)t : 0u;
+    for (int t = tid; t < padded; t += NT) {
+        uint32_t k = 0;
+        if (t < total_tiles) {
+            const int b = one ? 0 : request_of(table->begin, td.n_req, t);
+            const int end = one ? total_tiles : table->begin[b + 1], n_sel = one ? td.n_sel[0] : table->n_sel[b], ctx_len = one ? td.ctx_len[0] : table->ctx_len[b];
+            const int last_row = n_sel * grp - (end - 1 - t) * ROWS - 1;     // the tiles end with their request's rows
+            const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : table->sel_lo[b]) + last_row / grp], 0), ctx_len - 1) / BN + 1;
+            k = (uint32_t)(reach + kAttnTileOverhead) * MAXT + (uint32_t)t;  // (the kernel's requests are below 4 GiB: reaches below 2^20)
+        }
+        key[t] = k;
+    }
     __syncthreads();
     static_assert(MAXT <= 2 * NT, "two tiles a thread");
     const uint32_t mine0 = tid < total_tiles ? key[tid] : 0u, mine1 = tid + NT < total_tiles ? key[tid + NT] : 0u;
@@ -262,7 +265,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const uint16_t *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
     const uint16_t *__restrict__ k_cache, const uint16_t *__restrict__ v_cache,
     float scale_log2, uint16_t *__restrict__ out, float *__restrict__ lse_out,
-    int n_splits, const int2 *__restrict__ split_plan, const uint16_t *__restrict__ piece_list,
+    int n_splits, const int4 *__restrict__ split_plan, const uint16_t *__restrict__ piece_list,
     float *__restrict__ part_o, float4 *__restrict__ part_ml, int share_units, int32_t *__restrict__ queue)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // K ring, then V^T ring
@@ -289,8 +292,13 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const int first_pass = RECENTRE && again ? 1 : 0;
     again = false;
     const int rest = it;
-    // split launches walk the list of pieces the plan kernel wrote: the pieces that have keys first,
-    // from the top of the context down, then the empty ones (which only mark their slot)
+    // split launches walk the list of pieces the plan kernel wrote, from the top of the context down.
+    // The plan: pieces per row tile in use, key tiles per piece, pieces that have keys
+    int4 plan = make_int4(1, 0, 0, 0);
+    if (SPLIT) {
+        plan = *split_plan;
+        if (rest >= plan.z) return;        // (see attn_plan_kernel)
+    }
     const int piece = SPLIT ? piece_list[rest] : rest;
     const int split = SPLIT ? piece / total_tiles : 0;
     const int tile_lin = __builtin_amdgcn_readfirstlane(SPLIT ? total_tiles - 1 - piece % total_tiles
@@ -311,22 +319,6 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     // as the slowest wave's: it shortens where the last lower block (block 3) has ended and every wave works on one block.  With two
     // neighbouring blocks a wave it would where block 6 has, which is three blocks later.
     auto block_row = [&](int nb) { return 32 * (nb == 0 ? wave : 2 * NWAVES - 1 - wave); };
-
-    // the plan: (pieces per row tile in use, key tiles per piece)
-    int2 plan = make_int2(1, 0);
-    if (SPLIT) {
-        plan = *split_plan;
-        if (split >= plan.x) {   // a piece slot the plan does not use: mark it empty for the merge
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int rq = row0 + block_row(nb) + ln;
-                const int t_sel = rq / grp, hh = rq - t_sel * grp;
-                if (rq >= 0 && hf == 0)
-                    part_ml[((sel0 + t_sel) * n_q_heads + g * grp + hh) * (int64_t)n_splits + split] = make_float4(-1.0e30f, 0.f, 0.f, 0.f);
-            }
-            return;
-        }
-    }
 
     // this lane's query rows, one per 32-row block (both half-waves hold the same queries)
     bool row_ok[NB];
@@ -385,12 +377,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         t_lo = min(n_kv_tiles, lo);
         t_hi = min(n_kv_tiles, lo + plan.y);
     }
-    if (SPLIT && t_lo >= t_hi) {   // nothing of this tile in this key range: mark the piece empty
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            if (row_ok[nb] && hf == 0) part_ml[row_idx[nb] * (int64_t)n_splits + split] = make_float4(-1.0e30f, 0.f, 0.f, 0.f);
-        return;
-    }
+    if (SPLIT && t_lo >= t_hi) return;      // (not reached: a listed piece has keys)
 
     // ---- global -> LDS staging of one K/V tile ---------------------------------------------------------
     // Buffer loads that write straight into LDS: no registers, no LDS store instructions, and the
@@ -922,28 +909,54 @@ namespace {
 // unit: leaving 8 % of them free, and two short pieces at the bottom of the context to level out the finish, made
 // pieces longer or a round more (20 launches of 44 to 192 tiles, 2500 to 100000 tokens: geometric mean 127.0 -> 115.6 us; 738 of 8192
 // tokens on 32:8 heads 94.9 -> 81.9, 481 of 12000 on 28:4 92.2 -> 70.4, 720 of 30000 194.7 -> 170.9; at worst 48.1 -> 49.3).
-// Thread i tries chunk c_min + i * step over the lengths of all row tiles (taken from
-// each tile's last row, i.e. exact for positions in ascending order; any other order costs speed
-// only: the attention kernel finds its own key range).
+// Thread i tries chunk c_min + i * step over the lengths of all row tiles.
 //
-// Order.  piece id = split * total_tiles + (row tiles from the last one down).  A workgroup that
-// finds its piece empty still holds a compute unit for a few microseconds, and the dispatcher
-// hands out workgroups strictly in order, so empty pieces in between starve the pieces behind
-// them: the list names the pieces with keys first and all empty slots after them.
+// Order.  piece id = split * total_tiles + (row tiles from the last one down).  The list names the pieces that have keys; there are as many
+// workgroups as ids, and those beyond the list end at once: marking their slots empty, which took each its positions and 2 us of a
+// compute unit after the last round, is not needed, since the merge tells from a row's position which pieces it is in (738
+// of 8192 tokens on 32:8 heads 84.6 -> 79.6 us, 481 of 12000 on 28:4 72.9 -> 68.7).  So a tile's length is the largest reach of its rows, in
+// whatever order their positions are.
 constexpr int PLAN_NT = 256;
 constexpr int PLAN_MAX_TILES = kAttnPlanMaxTiles;
 constexpr int PLAN_MAX_ROUNDS = 4;
 __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     const AttnTiles td, int grp, int n_kv_heads, int total_tiles, const int32_t *__restrict__ sel_pos,
-    int s_max, int ctx_tiles, float piece_overhead, int2 *__restrict__ plan, uint16_t *__restrict__ piece_list)
+    int s_max, int ctx_tiles, float piece_overhead, int4 *__restrict__ plan, uint16_t *__restrict__ piece_list)
 {
     __shared__ int len[PLAN_MAX_TILES];       // key tiles of each row tile
     __shared__ int first_fit[PLAN_MAX_ROUNDS];
     __shared__ int2 chosen;
     __shared__ int wave_total[PLAN_NT / 64];
+    __shared__ TileTable table;
+    __shared__ int first_token[kAttnMaxReq + 1];   // of each request, in the table's order
     const int tid = threadIdx.x;
-    // (the table of requests stays where it is: a copy in LDS costs one request 0.8 us)
-    for (int t = tid; t < total_tiles; t += PLAN_NT) len[t] = tile_reach(td.tile_begin, td.n_sel, td.ctx_len, td.sel_lo, td.n_req, grp, t, sel_pos);
+    const bool one = td.n_req == 1;                // (its geometry stays in scalar registers)
+    if (!one) {
+        table.load(td, tid);
+        if (tid < 64) {
+            int upto = tid < td.n_req ? td.n_sel[tid] : 0;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int v = __shfl_up(upto, o);
+                if (tid >= o) upto += v;
+            }
+            first_token[tid + 1] = upto;
+            if (tid == 0) first_token[0] = 0;
+        }
+    }
+    for (int t = tid; t < total_tiles; t += PLAN_NT) len[t] = 0;
+    __syncthreads();
+    const int n_tokens = one ? td.n_sel[0] : first_token[td.n_req];
+    // from the last token down: in ascending order few find a tile whose length they raise
+#pragma unroll 4
+    for (int i = n_tokens - 1 - tid; i >= 0; i -= PLAN_NT) {
+        const int b = one ? 0 : request_of(first_token, td.n_req, i);
+        const int at = one ? i : i - first_token[b], n_sel = one ? td.n_sel[0] : table.n_sel[b], ctx_len = one ? td.ctx_len[0] : table.ctx_len[b];
+        const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : table.sel_lo[b]) + at], 0), ctx_len - 1) / BN + 1;
+        const int to_end = (n_sel - at) * grp, last = (one ? total_tiles : table.begin[b + 1]) - 1;   // the token's rows and those behind it; the tiles end with them
+        for (int t = last - (to_end - 1) / ROWS; t <= last - (to_end - grp) / ROWS; ++t)
+            if (len[t] < reach) atomicMax(&len[t], reach);
+    }
     if (tid < PLAN_MAX_ROUNDS) first_fit[tid] = 0x7fffffff;
     __syncthreads();
     const int c_min = max(1, (ctx_tiles + s_max - 1) / s_max);
@@ -975,10 +988,9 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
             if (time < best_t) { best_t = time; best_c = first_fit[r]; }
         }
         chosen = make_int2((ctx_tiles + best_c - 1) / best_c, best_c);
-        *plan = chosen;
     }
     __syncthreads();
-    // the list: a stable partition of the piece ids into those with keys and the rest
+    // the list: the piece ids that have keys, in order
     const int2 pl = chosen;
     const int n_ids = s_max * total_tiles;
     const int per = (n_ids + PLAN_NT - 1) / PLAN_NT;
@@ -1006,11 +1018,9 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
         before += w < wave ? wave_total[w] : 0;
         total += wave_total[w];
     }
-    int full = before, empty = total + (e0 - before);
-    for (int e = e0; e < e1; ++e) {
-        if (has_keys(e)) piece_list[full++] = (uint16_t)e;
-        else piece_list[empty++] = (uint16_t)e;
-    }
+    if (tid == 0) *plan = make_int4(pl.x, pl.y, total, 0);
+    for (int e = e0; e < e1; ++e)
+        if (has_keys(e)) piece_list[before++] = (uint16_t)e;
 }
 
 // Queues, for whole key ranges of several requests with more than 3.5 tiles a unit: one workgroup a unit, which draws the KV head's next tile
@@ -1028,7 +1038,7 @@ __global__ void attn_queue_kernel(int n_kv_heads, int units, int32_t *__restrict
 template <bool WANT_LSE, bool SPLIT, bool RECENTRE, bool QUEUE>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
-                      float scale_log2, void *out, float *lse_out, int n_splits, const int2 *split_plan,
+                      float scale_log2, void *out, float *lse_out, int n_splits, const int4 *split_plan,
                       const uint16_t *piece_list, float *part_o, float4 *part_ml, int share_units, int32_t *queue)
 {
     static DeviceOnce attr_once;
@@ -1099,7 +1109,7 @@ AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, 
     const int64_t by_ws = (int64_t)((workspace_bytes - kAttnPlanBytes) / (kAttnPartBytesPerSlot * (size_t)(n_rows_total > 0 ? n_rows_total : 1)));
     if (s_max > by_ws) s_max = by_ws;
     if (s_max < 2) return whole;
-    return AttnSplitPlan{(int)s_max, (int)ctx_tiles, false};
+    return AttnSplitPlan{(int)s_max, (int)max_ctx, false};
 }
 
 kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, const void *q_sel,
@@ -1147,11 +1157,11 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     float *part_o = (float *)workspace - row0 * n_splits * D;
     float4 *ml_base = (float4 *)((char *)workspace + (size_t)n_rows_total * n_splits * D * sizeof(float));
     float4 *part_ml = ml_base - row0 * n_splits;
-    int2 *split_plan = (int2 *)(ml_base + n_rows_total * n_splits);
+    int4 *split_plan = (int4 *)(ml_base + n_rows_total * n_splits);
     uint16_t *piece_list = (uint16_t *)(split_plan + 1);
     const float piece_overhead = kAttnPieceOverhead;
     hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(PLAN_NT), 0, st, td, shape->n_q_heads / shape->n_kv_heads,
-                       shape->n_kv_heads, (int)tiles, sel_pos, n_splits, plan.ctx_tiles, piece_overhead, split_plan, piece_list);
+                       shape->n_kv_heads, (int)tiles, sel_pos, n_splits, (plan.max_ctx + BN - 1) / BN, piece_overhead, split_plan, piece_list);
     kvs_status stt = check_launch("kvs_partial_attention(plan)");
     if (stt != KVS_OK) return stt;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads * n_splits));
@@ -1161,7 +1171,8 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
                                             scale_log2, out, lse_out, n_splits, split_plan, piece_list, part_o, part_ml, 0, nullptr);
     if (stt != KVS_OK) return stt;
     return launch_attention_merge(n_rows_total, n_splits, (const float *)workspace, ml_base,
-                                  (uint16_t *)out + row0 * D, lse_out ? lse_out + row0 : nullptr, st);
+                                  (uint16_t *)out + row0 * D, lse_out ? lse_out + row0 : nullptr, st,
+                                  AttnMergePlan{split_plan, sel_pos + bd.cu_sel[0], shape->n_q_heads, plan.max_ctx});
 }
 
 } // namespace kvs

@@ -35,3 +35,43 @@ def test_tiles_around_the_line(hk, k, order):
     assert np.all(got[k:] == 7.0)
     check_attention(got[:k], ref, mag, "bf16", f"{(k + 255) // 256 * hk} tiles {order}")
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
+
+
+@pytest.mark.parametrize("grp,order", [(7, "ascending"), (7, "shuffled"), (3, "descending"), (8, "edges")])
+def test_pieces_of_a_batch(grp, order):
+    """Tokens whose rows lie in two tiles, a request without any, positions at the first and last key of key tiles, in orders that put a
+    tile's longest row anywhere."""
+    print(f"attention: pieces of a batch, {grp} heads a group, positions {order}", flush=True)
+    rng = np.random.default_rng(grp)
+    hk, hq = 8, 8 * grp
+    length, count = [1500, 1100, 2050, 1025], [770 // grp, 0, 560 // grp, 500 // grp]
+    off, cu, pos, rows = [], [0], [], 0
+    for n, k in zip(length, count):
+        p = np.sort(rng.permutation(n)[:k])
+        if order == "edges":
+            p = np.sort(np.minimum(n - 1, 32 * rng.integers(0, n // 32 + 1, k) - rng.integers(0, 2, k)).clip(0))
+        elif order == "shuffled":
+            p = rng.permutation(p)
+        elif order == "descending":
+            p = p[::-1]
+        off.append(rows)
+        rows += n + 1
+        pos.append(p.astype(np.int32))
+        cu.append(cu[-1] + k)
+    pos = np.concatenate(pos)
+    gen = torch.Generator().manual_seed(grp)
+    q = (torch.randn((cu[-1], hq, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16)
+    k = torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16)
+    v = torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16)
+    kn, vn = oracle._as_np(k), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0, off, length, cu)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0, off, length, cu)
+    sh = B.make_shape(hq, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, len(off), rows, cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full((cu[-1] + 2, hq, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((cu[-1], hq), 7.0, device="cuda")
+    B.kvs_partial_attention(sh, off, length, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, ws)
+    got = out.float().cpu().numpy()
+    assert np.all(got[cu[-1]:] == 7.0)
+    check_attention(got[:cu[-1]], ref, mag, "bf16", f"pieces of a batch, {grp} heads a group, {order}")
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
