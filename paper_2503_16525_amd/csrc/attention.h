@@ -31,6 +31,21 @@ struct AttnTiles {
     int32_t n_req;
 };
 
+// The last request that begins at or before tile t (requests without tiles begin where the next one does): six loads
+// one after another where a walk through a full table is up to 64 in every workgroup (decode checks of 64 requests of 1024 tokens
+// 43.0 -> 38.4 us, of 40 of 2000 32.6 -> 29.3, of 50 of 4000 with the attention output 156 -> 147).
+__device__ __forceinline__ int request_of(const int32_t *tile_begin, int n_req, int t)
+{
+    static_assert(kAttnMaxReq <= 64, "six halvings");
+    int b = 0;
+    if (n_req > 1) {
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1)
+            if (b + s < n_req && tile_begin[b + s] <= t) b += s;
+    }
+    return b;
+}
+
 // fills `td` for row tiles of `rows_per_tile` flattened (token, head-in-group) rows; returns the
 // number of row tiles, or -1 if the grid would overflow
 int64_t build_attn_tiles(const kvs_shape *shape, const AttnBatch &bd, int rows_per_tile, AttnTiles &td);

@@ -66,8 +66,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % n_kv_heads;
     const int tile_lin = total_tiles - 1 - (int)(blockIdx.x / n_kv_heads);         // longest contexts, last rows first
-    int b = 0;
-    while (b + 1 < td.n_req && tile_lin >= td.tile_begin[b + 1]) ++b;
+    const int b = request_of(td.tile_begin, td.n_req, tile_lin);
     const int grp = n_q_heads / n_kv_heads;
     const int n_rows = td.n_sel[b] * grp, ctx_len = td.ctx_len[b];
     const int64_t sel0 = td.sel_lo[b], ctx_off = td.ctx_off[b];

@@ -90,8 +90,7 @@ __global__ __launch_bounds__(NWAVES * 64, 2) void attn_mfma_kernel(
     const int rest = (int)(blockIdx.x / n_kv_heads);
     const int split = SPLIT ? rest % n_splits : 0;
     const int tile_lin = total_tiles - 1 - (SPLIT ? rest / n_splits : rest);
-    int b = 0;
-    while (b + 1 < td.n_req && tile_lin >= td.tile_begin[b + 1]) ++b;
+    const int b = request_of(td.tile_begin, td.n_req, tile_lin);
     const int tile = tile_lin - td.tile_begin[b];
     const int grp = n_q_heads / n_kv_heads;
     const int64_t sel0 = td.sel_lo[b];

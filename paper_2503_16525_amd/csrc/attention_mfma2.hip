@@ -97,17 +97,6 @@ __device__ __forceinline__ float add_rounded_pair(uint32_t w, float acc)   // ac
 }
 
 
-// The last request that begins at or before row tile t (requests without tiles begin where the next one does).
-__device__ __forceinline__ int request_of(const int32_t *tile_begin, int n_req, int t)
-{
-    static_assert(kAttnMaxReq <= 64, "six halvings");
-    int b = 0;
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1)
-        if (b + s < n_req && tile_begin[b + s] <= t) b += s;
-    return b;
-}
-
 // The requests' geometry in LDS, where lanes of a wave ask for different requests.
 struct TileTable {
     int32_t begin[kAttnMaxReq + 1], n_sel[kAttnMaxReq], ctx_len[kAttnMaxReq];

@@ -78,8 +78,7 @@ __global__ __launch_bounds__(kThreads) void decode_logits_kernel(
     float *lg_s = lds;                             // [n_q_heads][kTok]
     float *q_s = lds + n_q_heads * kTok;           // [n_q_heads][D], pre-multiplied by scale (GRP == 0 only)
 
-    int b = 0;
-    while (b + 1 < bd.n_req && (int)blockIdx.x >= bd.tile_begin[b + 1]) ++b;
+    const int b = request_of(bd.tile_begin, bd.n_req, (int)blockIdx.x);
     const int tile = blockIdx.x - bd.tile_begin[b];
     const int len = bd.ctx_len[b];
     const int tok0 = tile * kTok;
@@ -316,8 +315,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_logits_mfma_kernel(
         for (int r = 0; r < RU; ++r) asm volatile("buffer_store_dword %0, %1, %2, 0 offen" :: "v"(lg[r]), "v"(lg_off[r]), "s"(lrs) : "memory");
     };
 
-    Cursor ahead = {first, 0, 0}, cur;
-    settle(ahead);
+    Cursor ahead = {first, 0, request_of(bd.tile_begin, bd.n_req, first)}, cur;
     cur = ahead;
     load_q(cur.b, 0);
     if (n_heads_w == 2) load_q(cur.b, 1);
@@ -453,8 +451,7 @@ __global__ __launch_bounds__((score_threads(HIST, SPREAD))) void decode_score_ke
     const bool mine = (int)blockIdx.x * TILES + tile_here < n_tiles;      // (a tile too many is computed and dropped)
     if (HIST && SPREAD)
         for (int x = threadIdx.x; x < kKeyHistBins; x += score_threads(HIST, SPREAD)) count_s[x] = 0u;
-    int b = 0;
-    while (b + 1 < bd.n_req && tile_id >= bd.tile_begin[b + 1]) ++b;
+    const int b = request_of(bd.tile_begin, bd.n_req, tile_id);
     const int tile = tile_id - bd.tile_begin[b];
     const int i = tile * kTok + lane;
     const bool live = mine && i < bd.ctx_len[b];
@@ -555,8 +552,7 @@ __global__ __launch_bounds__(kThreads) void decode_attn_partial_kernel(
     static_assert(kAttTok == kThreads, "one token per thread in the weights step");
     const int g = blockIdx.x % n_kv_heads;
     const int tile_id = blockIdx.x / n_kv_heads;
-    int b = 0;
-    while (b + 1 < bd.n_req && tile_id >= bd.tile_begin[b + 1]) ++b;
+    const int b = request_of(bd.tile_begin, bd.n_req, tile_id);
     const int tok0 = (tile_id - bd.tile_begin[b]) * kAttTok;
     const int ntok = min(kAttTok, bd.ctx_len[b] - tok0);
     const int64_t row0 = bd.ctx_off[b] + tok0;
