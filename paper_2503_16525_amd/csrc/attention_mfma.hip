@@ -547,8 +547,9 @@ kvs_status launch_attention_mfma(const kvs_shape *shape, const AttnBatch &bd, in
     const bool fills = big_tiles * shape->n_kv_heads >= kAttnBigTileMinGrid;
     // Somewhat more tiles than units are as long as the longest tile, which most units wait for: pieces are shorter.  2161 of 24000 tokens on
     // 32:8 heads (272 tiles) 547 us whole, 449 in pieces; 268 and 300 tiles of 9000 and 100000 tokens on 32:4 222 and 203, 2210 and 1805;
-    // 320, 324 and 352 tiles 197 and 204, 226 and 228, 550 and 594: the line lies between.
-    const bool whole = big_tiles * shape->n_kv_heads >= kAttnWholeFrom || !dense_tiles || splits2 < 2;
+    // 320, 324 and 352 tiles 197 and 204, 226 and 228, 550 and 594: the line lies between.  Not for several requests, whose tiles are of all
+    // lengths: 58 requests of 1450 tokens (292 tiles on 28:4 heads) 55.5 us whole, 86.7 in pieces, 41 of 2910 (272) 85.7 and 108.8.
+    const bool whole = bd.n_req > 1 || big_tiles * shape->n_kv_heads >= kAttnWholeFrom || !dense_tiles || splits2 < 2;
     // (below ~50 such tiles the per-workgroup start-up of the large kernel costs more than it gains)
     const bool big = fits32 && (forced ? forced == 2 : fills || (splits2 >= 2 && dense_tiles && big_tiles * shape->n_kv_heads >= 48));
     if (big) {

@@ -112,6 +112,7 @@ struct TileTable {
 // head; every workgroup packs the head's row tiles onto the head's units by itself, from the
 // tiles' actual reach in the context, and runs its own unit's share (see plan_shares).
 constexpr int kAttnShareMaxTiles = 512;
+constexpr int kAttnShareMaxReq = 8;        // more requests: attn_order_kernel
 constexpr int kAttnShareMaxUnits = 64;     // one lane of a wavefront per unit
 constexpr int kAttnTileOverhead = 8;       // key-tile steps a tile costs before its first
 
@@ -128,8 +129,7 @@ constexpr int kAttnTileOverhead = 8;       // key-tile steps a tile costs before
 // share per unit loses nothing against a queue.
 //
 // How: weight of a tile = key tiles up to its last row's position (read from sel_pos: exact) plus
-// a fixed cost; tiles ranked by weight (requests looked up in LDS, four keys compared at a time: 64 requests of 1024 tokens
-// 75 -> 68 us with the write-back, where lookups chained up to 64 loads); first fit decreasing under a capacity, one lane per unit
+// a fixed cost; tiles ranked by weight; first fit decreasing under a capacity, one lane per unit
 // (a ballot finds the first unit with room); the four waves try four capacities at a time, from
 // 0.5 % above the mean load upwards, and the smallest that works is taken.
 __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int total_tiles, const int32_t *__restrict__ sel_pos,
@@ -142,23 +142,14 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
     uint16_t *found = st + MAXT;                                         // [NWAVES][MAXT] ranks that fall to `unit`, per trial
     int *n_found = reinterpret_cast<int *>(found + NWAVES * MAXT);       // [NWAVES], -1: the capacity did not work
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    TileTable *const table = reinterpret_cast<TileTable *>(scratch + 16384);
-    static_assert(MAXT * (2 * sizeof(float) + (1 + NWAVES) * sizeof(uint16_t)) + NWAVES * sizeof(int) <= 16384, "the table lies behind the lists");
-    const bool one = td.n_req == 1;           // its geometry stays in scalar registers: 256 workgroups that each read
-                                              // the argument block's whole table cost 15 % of 32768 tokens 10 us
-    if (!one) {
-        table->load(td, tid);
-        __syncthreads();
-    }
     const int padded = (total_tiles + 3) & ~3;
     for (int t = tid; t < padded; t += NT) {
         uint32_t k = 0;
         if (t < total_tiles) {
-            const int b = one ? 0 : request_of(table->begin, td.n_req, t);
-            const int end = one ? total_tiles : table->begin[b + 1], n_sel = one ? td.n_sel[0] : table->n_sel[b], ctx_len = one ? td.ctx_len[0] : table->ctx_len[b];
-            const int last_row = n_sel * grp - (end - 1 - t) * ROWS - 1;     // the tiles end with their request's rows
-            const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : table->sel_lo[b]) + last_row / grp], 0), ctx_len - 1) / BN + 1;
-            k = (uint32_t)(reach + kAttnTileOverhead) * MAXT + (uint32_t)t;  // (the kernel's requests are below 4 GiB: reaches below 2^20)
+            const int b = request_of(td.tile_begin, td.n_req, t);
+            const int last_row = td.n_sel[b] * grp - (td.tile_begin[b + 1] - 1 - t) * ROWS - 1;     // the tiles end with their request's rows
+            const int reach = min(max(sel_pos[td.sel_lo[b] + last_row / grp], 0), td.ctx_len[b] - 1) / BN + 1;
+            k = (uint32_t)(reach + kAttnTileOverhead) * MAXT + (uint32_t)t;                 // (the kernel's requests are below 4 GiB: reaches below 2^20)
         }
         key[t] = k;
     }
@@ -291,7 +282,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const int piece = SPLIT ? piece_list[rest] : rest;
     const int split = SPLIT ? piece / total_tiles : 0;
     const int tile_lin = __builtin_amdgcn_readfirstlane(SPLIT ? total_tiles - 1 - piece % total_tiles
-                                                              : (listed ? (int)my_tiles[rest] : total_tiles - 1 - rest));
+                                                              : (listed ? (int)my_tiles[rest] : QUEUE && piece_list ? (int)piece_list[rest] : total_tiles - 1 - rest));
     const int b = request_of(td.tile_begin, td.n_req, tile_lin);
     const int tile = tile_lin - td.tile_begin[b];
     const int grp = n_q_heads / n_kv_heads;
@@ -1024,6 +1015,40 @@ __global__ void attn_queue_kernel(int n_kv_heads, int units, int32_t *__restrict
     if ((int)threadIdx.x < n_kv_heads) queue[threadIdx.x] = units;
 }
 
+// The same for up to 3.5 tiles a unit, with the tiles by the length of their sweep, longest first: a request's tiles hardly run together there in
+// any order.  One workgroup reads the table of requests, where fixed shares had every workgroup read it, and the argument block lies
+// in host memory.  With the write-back, shares against this: 24 requests of 3798 tokens 123 -> 111 us, 41 of 2910 98.5 -> 88.6, 58 of 1450 64.0
+// -> 58.6, 15 of 10325 269 -> 253; 7 of 13738 347 and 350, 5 of 16000 287 and 293, which are left to shares.
+constexpr int ORDER_NT = 256;
+static_assert(kAttnShareMaxUnits * KVS_ATTN_SHARE_MAX_X2 / 2 <= ORDER_NT, "a tile a thread");
+__global__ __launch_bounds__(ORDER_NT) void attn_order_kernel(const AttnTiles td, int grp, int n_kv_heads, int units, int total_tiles,
+                                                              const int32_t *__restrict__ sel_pos, int32_t *__restrict__ queue, uint16_t *__restrict__ order)
+{
+    __shared__ TileTable table;
+    __shared__ __attribute__((aligned(16))) uint32_t key[ORDER_NT];
+    const int tid = threadIdx.x;
+    if (tid < n_kv_heads) queue[tid] = units;
+    table.load(td, tid);
+    __syncthreads();
+    uint32_t mine = 0;
+    if (tid < total_tiles) {
+        const int b = request_of(table.begin, td.n_req, tid);
+        const int last_row = table.n_sel[b] * grp - (table.begin[b + 1] - 1 - tid) * ROWS - 1;     // the tiles end with their request's rows
+        const int reach = min(max(sel_pos[table.sel_lo[b] + last_row / grp], 0), table.ctx_len[b] - 1) / BN + 1;
+        mine = (uint32_t)reach * ORDER_NT + (uint32_t)tid;     // (the kernel's requests are below 4 GiB: reaches below 2^20)
+    }
+    key[tid] = mine;
+    __syncthreads();
+    if (tid >= total_tiles) return;
+    int before = 0;
+#pragma unroll 4
+    for (int j = 0; j < (total_tiles + 3) / 4 * 4; j += 4) {
+        const u32x4_t o = *reinterpret_cast<const u32x4_t *>(key + j);
+        before += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
+    }
+    order[before] = (uint16_t)tid;
+}
+
 template <bool WANT_LSE, bool SPLIT, bool RECENTRE, bool QUEUE>
 kvs_status launch_one(const dim3 grid, size_t lds_bytes, hipStream_t st, const AttnTiles &td, const kvs_shape *shape,
                       int tiles, const void *q_sel, const int32_t *sel_pos, const void *k_cache, const void *v_cache,
@@ -1064,13 +1089,6 @@ int units_per_head(const kvs_shape *shape)
     return device_cus == kAttnSplitCus ? kAttnSplitCus / shape->n_kv_heads : 0;
 }
 
-// Whether a launch runs fixed shares.  Few tiles per unit is where the dispatcher does badly; from ~3.5 per unit on its one-by-one hand-out of
-// one request's tiles evens out as well as fixed shares do (3 % above the mean load at 4.5 per unit).
-bool runs_shares(int units, int64_t tiles)
-{
-    if (units < 1 || units > kAttnShareMaxUnits || tiles > kAttnShareMaxTiles) return false;
-    return tiles > units && 2 * tiles <= KVS_ATTN_SHARE_MAX_X2 * units;
-}
 } // namespace
 
 AttnSplitPlan attention_mfma2_plan(const kvs_shape *shape, const AttnBatch &bd, size_t workspace_bytes)
@@ -1115,20 +1133,27 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     const int n_splits = plan.n_splits;
     if (n_splits <= 1 || !workspace) {
         const int units = units_per_head(shape);
-        const int share_units = runs_shares(units, tiles) ? units : 0;
-        // One request's tiles are left to the dispatcher: 131072 Yi-shaped tokens 11.65 ms against 11.85 with a queue, 30 % of 32768 the same.
-        // With up to 3.5 tiles a unit shares are better than a queue for 8 requests of 16384 (541 us, 579) and 40 of 3000 (100, 108), worse for
-        // 64 of 1024 (68, 62) and 64 of 2800 (107, 100).
+        const bool few = units <= kAttnShareMaxUnits && 2 * tiles <= KVS_ATTN_SHARE_MAX_X2 * units;
+        const int share_units = few && tiles > units && bd.n_req <= kAttnShareMaxReq ? units : 0;
+        // One request's tiles beyond that are left to the dispatcher: 131072 Yi-shaped tokens 11.65 ms against 11.85 with a queue, 30 % of
+        // 32768 the same.
         int32_t *queue = nullptr;
-        if (share_units == 0 && units > 0 && tiles > units && bd.n_req > 1 && workspace && workspace_bytes >= kAttnPlanBytes) {
+        uint16_t *order = nullptr;
+        if (share_units == 0 && bd.n_req > 1 && tiles > units && units > 0 && workspace && workspace_bytes >= kAttnPlanBytes) {
             queue = (int32_t *)workspace;
-            hipLaunchKernelGGL(attn_queue_kernel, dim3(1), dim3(kAttnSplitCus), 0, st, shape->n_kv_heads, units, queue);
+            if (few) {
+                order = (uint16_t *)(queue + kAttnSplitCus);
+                hipLaunchKernelGGL(attn_order_kernel, dim3(1), dim3(ORDER_NT), 0, st, td, shape->n_q_heads / shape->n_kv_heads, shape->n_kv_heads, units,
+                                   (int)tiles, sel_pos, queue, order);
+            } else {
+                hipLaunchKernelGGL(attn_queue_kernel, dim3(1), dim3(kAttnSplitCus), 0, st, shape->n_kv_heads, units, queue);
+            }
             const kvs_status stt = check_launch("kvs_partial_attention(queue)");
             if (stt != KVS_OK) return stt;
         }
         const dim3 grid((unsigned)((share_units > 0 || queue ? units : tiles) * shape->n_kv_heads));
 #define KVS_ATTN_WHOLE(LSE, RC, Q) launch_one<LSE, false, RC, Q>(grid, lds_bytes, st, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, \
-                                                          scale_log2, out, lse_out, 1, nullptr, nullptr, nullptr, nullptr, share_units, queue)
+                                                          scale_log2, out, lse_out, 1, nullptr, order, nullptr, nullptr, share_units, queue)
         if (queue) {
             if (lse_out) return plan.recentre ? KVS_ATTN_WHOLE(true, true, true) : KVS_ATTN_WHOLE(true, false, true);
             return plan.recentre ? KVS_ATTN_WHOLE(false, true, true) : KVS_ATTN_WHOLE(false, false, true);

@@ -1,5 +1,5 @@
-"""Ragged batches with more row tiles than fixed shares take: one workgroup a compute unit draws its tiles.  Around the line between the two,
-requests without and with few selected tokens, head counts that leave units over, more requests than one launch describes, a request
+"""Ragged batches with more row tiles than compute units: one workgroup a unit draws its tiles, in the order of their lengths up to 3.5 tiles a unit.
+Around that line and the one to fixed shares (8 requests), requests without and with few selected tokens, head counts that leave units over, more requests than one launch describes, a request
 beyond the last-level cache; every row against the oracle."""
 import numpy as np
 import pytest
@@ -13,16 +13,18 @@ pytestmark = pytest.mark.gpu
 
 
 def _batch(rng, kind):
-    if kind == "15 tiles":        # 64 heads, 4 units each: 14 tiles are shares
+    if kind == "15 tiles":        # 64 heads, 4 units each: up to 14 tiles are put in order
         return [(int(rng.integers(300, 900)), int(k)) for k in (256, 1, 300, 0, 255, 257, 40, 256, 256, 290, 3)]
     if kind == "14 tiles":
         return [(int(rng.integers(300, 900)), int(k)) for k in (256, 1, 300, 0, 255, 257, 40, 256, 256, 290)]
+    if kind == "8 requests":      # shares
+        return [(int(rng.integers(300, 900)), int(k)) for k in (256, 1, 0, 255, 257, 40, 290, 3)]
     if kind == "70 requests":
         return [(int(rng.integers(20, 200)), int(rng.integers(1, 20))) for _ in range(70)]
     return [(6200, 10)] + [(int(rng.integers(50, 100)), int(rng.integers(1, 40))) for _ in range(16)]
 
 
-@pytest.mark.parametrize("kind,hk,want_lse", [("15 tiles", 64, True), ("15 tiles", 52, False), ("14 tiles", 64, True), ("70 requests", 64, False), ("large", 64, True),
+@pytest.mark.parametrize("kind,hk,want_lse", [("15 tiles", 64, True), ("15 tiles", 52, False), ("14 tiles", 64, True), ("14 tiles", 52, False), ("8 requests", 64, True), ("70 requests", 64, False), ("large", 64, True),
                                               ("large", 64, False)])
 def test_drawn_tiles(kind, hk, want_lse):
     print(f"attention: {kind}, {hk} heads, lse {want_lse}", flush=True)
