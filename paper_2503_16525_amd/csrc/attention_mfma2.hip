@@ -1134,12 +1134,14 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     if (n_splits <= 1 || !workspace) {
         const int units = units_per_head(shape);
         const bool few = units <= kAttnShareMaxUnits && 2 * tiles <= KVS_ATTN_SHARE_MAX_X2 * units;
-        const int share_units = few && tiles > units && bd.n_req <= kAttnShareMaxReq ? units : 0;
+        const bool draws = bd.n_req > 1 && tiles > units && units > 0 && workspace && workspace_bytes >= kAttnPlanBytes;
+        const int share_units = few && tiles > units && (bd.n_req <= kAttnShareMaxReq || !draws) ? units : 0;
+        // (batches of any size keep shares where there is no workspace to draw from)
         // One request's tiles beyond that are left to the dispatcher: 131072 Yi-shaped tokens 11.65 ms against 11.85 with a queue, 30 % of
         // 32768 the same.
         int32_t *queue = nullptr;
         uint16_t *order = nullptr;
-        if (share_units == 0 && bd.n_req > 1 && tiles > units && units > 0 && workspace && workspace_bytes >= kAttnPlanBytes) {
+        if (share_units == 0 && draws) {
             queue = (int32_t *)workspace;
             if (few) {
                 order = (uint16_t *)(queue + kAttnSplitCus);
