@@ -146,9 +146,11 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
     for (int t = tid; t < padded; t += NT) {
         uint32_t k = 0;
         if (t < total_tiles) {
-            const int b = request_of(td.tile_begin, td.n_req, t);
-            const int last_row = td.n_sel[b] * grp - (td.tile_begin[b + 1] - 1 - t) * ROWS - 1;     // the tiles end with their request's rows
-            const int reach = min(max(sel_pos[td.sel_lo[b] + last_row / grp], 0), td.ctx_len[b] - 1) / BN + 1;
+            const bool one = td.n_req == 1;                            // its geometry stays in scalar registers
+            const int b = one ? 0 : request_of(td.tile_begin, td.n_req, t);
+            const int end = one ? total_tiles : td.tile_begin[b + 1], n_sel = one ? td.n_sel[0] : td.n_sel[b], ctx_len = one ? td.ctx_len[0] : td.ctx_len[b];
+            const int last_row = n_sel * grp - (end - 1 - t) * ROWS - 1;                            // the tiles end with their request's rows
+            const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : td.sel_lo[b]) + last_row / grp], 0), ctx_len - 1) / BN + 1;
             k = (uint32_t)(reach + kAttnTileOverhead) * MAXT + (uint32_t)t;                 // (the kernel's requests are below 4 GiB: reaches below 2^20)
         }
         key[t] = k;
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     const int it_begin = listed ? 0 : wg, it_end = listed ? n_my_tiles : QUEUE ? total_tiles : wg + 1;
     int it_next = it_begin;
     bool again = false;                    // RECENTRE: the same tile once more, with its rows' exact maxima
-    for (int it = it_begin; it < it_end; it = it_next) {
+    for (int it = it_begin; it < it_end; it = QUEUE ? it_next : it + (RECENTRE && again ? 0 : 1)) {
     if (it != it_begin || (RECENTRE && again)) __syncthreads();   // every wave has left the previous tile: rings and tables are free
     const int first_pass = RECENTRE && again ? 1 : 0;
     again = false;
@@ -281,9 +283,12 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     }
     const int piece = SPLIT ? piece_list[rest] : rest;
     const int split = SPLIT ? piece / total_tiles : 0;
-    const int tile_lin = __builtin_amdgcn_readfirstlane(SPLIT ? total_tiles - 1 - piece % total_tiles
-                                                              : (listed ? (int)my_tiles[rest] : QUEUE && piece_list ? (int)piece_list[rest] : total_tiles - 1 - rest));
-    const int b = request_of(td.tile_begin, td.n_req, tile_lin);
+    const int tile_lin = SPLIT ? total_tiles - 1 - piece % total_tiles
+                               : QUEUE ? __builtin_amdgcn_readfirstlane(piece_list ? (int)piece_list[rest] : total_tiles - 1 - rest)
+                                       : (listed ? (int)my_tiles[rest] : total_tiles - 1 - rest);
+    int b = 0;
+    if (SPLIT || QUEUE) b = request_of(td.tile_begin, td.n_req, tile_lin);
+    else while (b + 1 < td.n_req && tile_lin >= td.tile_begin[b + 1]) ++b;
     const int tile = tile_lin - td.tile_begin[b];
     const int grp = n_q_heads / n_kv_heads;
     const int64_t sel0 = td.sel_lo[b];
@@ -819,8 +824,6 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         if (tid == 0) drawn = atomicAdd(queue + g, 1);
         __syncthreads();
         it_next = __builtin_amdgcn_readfirstlane(drawn);
-    } else {
-        it_next = it + 1;
     }
 
     // ---- epilogue: normalise, convert, store ----------------------------------------------------------
