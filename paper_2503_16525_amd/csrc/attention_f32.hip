@@ -97,6 +97,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     for (int o = 1; o < 16; o <<= 1) { pmin = min(pmin, __shfl_xor(pmin, o)); pmax = max(pmax, __shfl_xor(pmax, o)); }
     pmin = __builtin_amdgcn_readfirstlane(pmin);
     pmax = __builtin_amdgcn_readfirstlane(pmax);
+    Rows::landed();                                    // (also in waves whose first keys lie past pmax: results go over them)
     __syncthreads();
     float qv[D / 4];
     Rows::read(rows_s, m16, kk, qv);
@@ -134,7 +135,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // what lay there has been read
 #pragma unroll
                     for (int i = 0; i < FLIGHT; ++i) fetch(k0 + 16 * t0, i, pmax);
-                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                    Rows::landed();
                 }
 #pragma unroll
                 for (int i = 0; i < FLIGHT; ++i) {

@@ -161,6 +161,7 @@ __global__ __launch_bounds__(kCfThreads, 2) void colsum_f32_rows_kernel(int n, i
     float s[MAXT][4], m[4], z[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) { m[r] = kLowest; z[r] = 0.f; }
+    Rows::landed();
     __syncthreads();
     float fx[D / 4];
     Rows::read(rows_s, m16, kk, fx);
@@ -170,7 +171,7 @@ __global__ __launch_bounds__(kCfThreads, 2) void colsum_f32_rows_kernel(int n, i
         if (i0 > 0) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // what lay there has been read
             fetch(i0);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            Rows::landed();
         }
 #pragma unroll
         for (int i = 0; i < FETCH; ++i) {

@@ -43,7 +43,9 @@ template <int DTYPE, int D>
 struct Rows16 {
     static constexpr int ROW_B = D * (DTYPE == KVS_F32 ? 4 : 2), PIECES = ROW_B / 16, BYTES = 16 * ROW_B, LOADS = BYTES / 1024, ROWS_A_LOAD = 1024 / ROW_B;
     static __device__ __forceinline__ int swizzle(int r) { return PIECES >= 16 ? r : r >> 1; }
-    // a wave's load `i` of LOADS into the 16 rows at `lds`; row(r) is row r's first element in `base`
+    // a wave's load `i` of LOADS into the 16 rows at `lds`; row(r) is row r's first element in `base`.  It is under way when this returns:
+    // before the rows are read, or their place is used for something else, the wave that asked waits (landed()), and
+    // waves that read what another asked for meet it at a barrier after that.
     template <class Row>
     static __device__ __forceinline__ void load(const void *__restrict__ base, Row row, char *lds, int i, int lane)
     {
@@ -51,6 +53,7 @@ struct Rows16 {
         const char *src = reinterpret_cast<const char *>(base) + row(r) * (ROW_B / D) + piece * 16;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)(lds + i * 1024), 16, 0, 0);
     }
+    static __device__ __forceinline__ void landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
     // the kk-th quarter of row m's channels, widened
     static __device__ __forceinline__ void read(const char *lds, int m, int kk, float (&x)[D / 4])
     {

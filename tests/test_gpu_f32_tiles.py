@@ -43,6 +43,27 @@ def test_attention(dtype, hq, hk, d, n, k):
 
 
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
+@pytest.mark.parametrize("n,lo,k", [(600, 0, 40), (600, 60, 70), (1100, 100, 60), (2500, 0, 300)])
+def test_attention_low_in_a_long_context(dtype, hq, hk, d, n, lo, k):
+    """Selected tokens that reach a part of the first keys only: most waves have asked for rows that no query sees."""
+    print(f"fp32 attention: {dtype} {hq}x{hk} heads, head_dim {d}, tokens {lo}..{lo + k - 1} of {n}", flush=True)
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    pos = np.arange(lo, lo + k, dtype=np.int32)
+    q = lay["q"][lo:lo + k].contiguous()
+    scale = -0.7 if d == 128 and dtype == "bf16" else 1.0
+    ref, lse_ref = oracle.partial_attention(q, pos, oracle._as_np(lay["k_cache"]), oracle._as_np(lay["v_cache"]), scale)
+    out, lse = torch.full((k + 3, hq, d), 7.0, dtype=w.torch_dtype, device="cuda"), torch.full((k + 3, hq), 7.0, device="cuda")
+    B.kvs_partial_attention(B.shape_of(w), [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), lay["k_cache"].cuda(), lay["v_cache"].cuda(), scale, out, lse)
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.all(got[k:] == 7.0) and bool((lse[k:] == 7.0).all()), "rows past the last one were written"
+    # as above: fp32 products and sums of up to 300 weights; a bf16 result adds its own rounding
+    tol = 1e-5 * (1.0 + np.abs(ref).max()) + (2.0 ** -8 * np.abs(ref) if dtype == "bf16" else 0.0)
+    assert np.all(np.abs(got[:k] - ref) <= tol), np.abs(got[:k] - ref).max()
+    np.testing.assert_allclose(lse[:k].cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
 @pytest.mark.parametrize("at", [0, 15, 16, 50, 130, 400])
 def test_attention_hides_what_a_row_does_not_see(dtype, hq, hk, d, at):
     """An Inf or NaN in K or V reaches the rows whose position is at or past it, and no other: bit for bit."""
