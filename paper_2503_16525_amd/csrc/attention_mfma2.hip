@@ -840,13 +840,20 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             constexpr int PITCH = D + 4;                     // floats: 16 lanes' stores at one channel hit all banks
             static_assert(NWAVES * 32 * PITCH * (int)sizeof(float) <= LDS_BYTES, "a block of rows of every wave");
             float *const own = reinterpret_cast<float *>(lds_b) + wave_u * 32 * PITCH;
+            // Lanes read what other lanes of the wave stored.  The wave's LDS requests are handled in order, so this takes no instruction: it keeps
+            // the compiler, which looks at one lane, from moving the one past the other.
+            auto handed_over = [] {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            };
+            if (nb > 0) handed_over();                       // the block before has been read
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4)
                     *reinterpret_cast<float4 *>(own + ln * PITCH + 32 * db + 8 * r4 + 4 * hf) =
                         make_float4(o_acc[db][nb][4 * r4 + 0], o_acc[db][nb][4 * r4 + 1], o_acc[db][nb][4 * r4 + 2], o_acc[db][nb][4 * r4 + 3]);
-            // (a wave's LDS requests are handled in order: no barrier)
+            handed_over();
             const int rel = row_ok[nb] ? (int)(row_idx[nb] - sel0 * n_q_heads) : -1;   // of the request's rows
 #pragma unroll 4
             for (int i = 0; i < 16; ++i) {

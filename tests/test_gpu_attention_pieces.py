@@ -75,3 +75,26 @@ def test_pieces_of_a_batch(grp, order):
     assert np.all(got[cu[-1]:] == 7.0)
     check_attention(got[:cu[-1]], ref, mag, "bf16", f"pieces of a batch, {grp} heads a group, {order}")
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
+
+
+@pytest.mark.parametrize("hq,hk,n,k", [(64, 64, 1300, 1000), (32, 8, 2050, 700), (21, 3, 3000, 1201)])
+def test_rows_leave_whole(hq, hk, n, k):
+    """Every row gives one key, another for each row and head, all of its weight: its result is that key's V, bit for bit."""
+    print(f"attention: one key a row, {hq}x{hk} heads, {k} of {n} tokens", flush=True)
+    rng = np.random.default_rng(hq + k)
+    pos = np.sort(rng.permutation(n)[:k]).astype(np.int32)
+    gen = torch.Generator().manual_seed(k)
+    kk = (torch.randint(0, 2, (n, hk, 128), generator=gen) * 2 - 1).to(torch.bfloat16)
+    v = torch.randn((n, hk, 128), generator=gen).to(torch.bfloat16)
+    v[v == 0] = 1.0                       # (beside an exact 0 the other keys' e^-40 would show)
+    key = torch.from_numpy(rng.integers(0, pos[:, None] + 1, (k, hq)))
+    head = torch.arange(hq)[None].expand(k, hq) // (hq // hk)
+    q = kk[key, head].contiguous()
+    # a score is 128 for the row's key and below 70 for every other of some thousand random signs: with 0.7 as scale their weights are e^-40 at most
+    assert max(float((q[:, h].float() @ kk[:, h // (hq // hk)].float().t()).scatter_(1, key[:, h:h + 1], 0).max()) for h in range(hq)) < 70
+    sh = B.make_shape(hq, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, 1, n, k),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full((k + 2, hq, 128), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.kvs_partial_attention(sh, [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), kk.cuda(), v.cuda(), 0.7, out, None, ws)
+    assert bool((out[k:] == 7.0).all())
+    assert torch.equal(out[:k].cpu(), v[key, head])
