@@ -370,6 +370,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_s
         first = max(0, end - 1 - pos / (kAttnPieceKeys * plan.y));
     }
     auto there = [&](int s) { return s >= first && s < end; };
+    auto some = [&](int s) { return there(s) && !(p[s].y == 0.f); };     // (a NaN sum is some: it has to reach the row)
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
         if (there(s)) {
@@ -378,16 +379,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_s
         }
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (!PLANNED && there(s) && p[s].y > 0.f) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
+        if (!PLANNED && some(s)) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
     float m = -1.0e30f;
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (there(s) && p[s].y > 0.f) m = fmaxf(m, p[s].x);
+        if (some(s)) m = fmaxf(m, p[s].x);
     float l = 0.f, l_exact = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int s = 0; s < kAttnSplitMax; ++s)
-        if (there(s) && p[s].y > 0.f) {
+        if (some(s)) {
             const float w = __builtin_amdgcn_exp2f(p[s].x - m);
             l += w * p[s].y;
             l_exact += w * p[s].z;

@@ -702,6 +702,9 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) m_ref[nb] = fmaxf(m_ref[nb], row_max(s[nb]));
             }
+            // a row whose keys in this piece all score -inf: as in pass 0
+#pragma unroll
+            for (int nb = 0; SPLIT && nb < NB; ++nb) m_ref[nb] = fmaxf(m_ref[nb], -1.0e30f);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();   // every wave is done with the ring before the sweep refills it
         }
