@@ -147,7 +147,7 @@ __device__ __forceinline__ void plan_shares(const AttnTiles &td, int grp, int to
         uint32_t k = 0;
         if (t < total_tiles) {
             const bool one = td.n_req == 1;                            // its geometry stays in scalar registers
-            const int b = one ? 0 : request_of(td.tile_begin, td.n_req, t);
+            const int b = one ? 0 : request_of_lane(td.tile_begin, td.n_req, t);
             const int end = one ? total_tiles : td.tile_begin[b + 1], n_sel = one ? td.n_sel[0] : td.n_sel[b], ctx_len = one ? td.ctx_len[0] : td.ctx_len[b];
             const int last_row = n_sel * grp - (end - 1 - t) * ROWS - 1;                            // the tiles end with their request's rows
             const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : td.sel_lo[b]) + last_row / grp], 0), ctx_len - 1) / BN + 1;
@@ -943,7 +943,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     // from the last token down: in ascending order few find a tile whose length they raise
 #pragma unroll 4
     for (int i = n_tokens - 1 - tid; i >= 0; i -= PLAN_NT) {
-        const int b = one ? 0 : request_of(first_token, td.n_req, i);
+        const int b = one ? 0 : request_of_lane(first_token, td.n_req, i);
         const int at = one ? i : i - first_token[b], n_sel = one ? td.n_sel[0] : table.n_sel[b], ctx_len = one ? td.ctx_len[0] : table.ctx_len[b];
         const int reach = min(max(sel_pos[(one ? td.sel_lo[0] : table.sel_lo[b]) + at], 0), ctx_len - 1) / BN + 1;
         const int to_end = (n_sel - at) * grp, last = (one ? total_tiles : table.begin[b + 1]) - 1;   // the token's rows and those behind it; the tiles end with them
@@ -1045,7 +1045,7 @@ __global__ __launch_bounds__(ORDER_NT) void attn_order_kernel(const AttnTiles td
     __syncthreads();
     uint32_t mine = 0;
     if (tid < total_tiles) {
-        const int b = request_of(table.begin, td.n_req, tid);
+        const int b = request_of_lane(table.begin, td.n_req, tid);
         const int last_row = table.n_sel[b] * grp - (table.begin[b + 1] - 1 - tid) * ROWS - 1;     // the tiles end with their request's rows
         const int reach = min(max(sel_pos[table.sel_lo[b] + last_row / grp], 0), table.ctx_len[b] - 1) / BN + 1;
         mine = (uint32_t)reach * ORDER_NT + (uint32_t)tid;     // (the kernel's requests are below 4 GiB: reaches below 2^20)
