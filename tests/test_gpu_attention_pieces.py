@@ -98,3 +98,34 @@ def test_rows_leave_whole(hq, hk, n, k):
     B.kvs_partial_attention(sh, [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), kk.cuda(), v.cuda(), 0.7, out, None, ws)
     assert bool((out[k:] == 7.0).all())
     assert torch.equal(out[:k].cpu(), v[key, head])
+
+
+@pytest.mark.parametrize("hq,hk,lens,counts", [(1, 1, [13000], [12500]), (2, 1, [4000, 9000], [3000, 7000]),
+                                               (16, 2, [900 + 7 * i for i in range(64)], [0 if i in (0, 31, 63) else 17 + i % 15 for i in range(64)]),
+                                               (8, 8, [1100 + 50 * i for i in range(9)], [160 + 33 * i for i in range(9)])],
+                         ids=["12500 tokens", "10000 tokens of two", "64 requests", "9 requests"])
+@pytest.mark.parametrize("order", ["ascending", "shuffled"])
+def test_every_position_is_in_the_plan(hq, hk, lens, counts, order):
+    """More tokens than the plan reads at once, more requests, some of them without tokens: a row whose reach the plan missed has no top piece."""
+    print(f"attention: {sum(counts)} tokens of {len(lens)} requests in pieces, {hq}x{hk} heads, {order}", flush=True)
+    rng = np.random.default_rng(sum(counts))
+    off, cu, pos, rows = [], [0], [], 0
+    for n, k in zip(lens, counts):
+        off.append(rows)
+        rows += n + 1
+        p = np.sort(rng.permutation(n)[:k]).astype(np.int32)
+        pos.append(rng.permutation(p) if order == "shuffled" else p)
+        cu.append(cu[-1] + k)
+    pos = np.concatenate(pos)
+    gen = torch.Generator().manual_seed(cu[-1])
+    q = (torch.randn((cu[-1], hq, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16)
+    k, v = (torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16) for _ in range(2))
+    kn, vn = oracle._as_np(k), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0, off, lens, cu)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0, off, lens, cu)
+    sh = B.make_shape(hq, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, len(lens), rows, cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+    out, lse = torch.full((cu[-1], hq, 128), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((cu[-1], hq), 7.0, device="cuda")
+    B.kvs_partial_attention(sh, off, lens, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, ws)
+    check_attention(out.float().cpu().numpy(), ref, mag, "bf16", f"{sum(counts)} tokens of {len(lens)} requests, {order}")
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
