@@ -26,6 +26,8 @@
 // keys (coalesced 256 B per wave load), repack in registers, and write two 16-byte rows of V^T.
 #include "attention.h"
 
+#include <type_traits>
+
 #include <math.h>
 #include <stdlib.h>
 #include <string.h>
@@ -345,58 +347,65 @@ __global__ __launch_bounds__(NWAVES * 64, 2) void attn_mfma_kernel(
 }
 
 
+// f(0), f(1), ... with the number as a compile-time constant, for `n` of them
+template <int S = 0, class F>
+__device__ __forceinline__ void for_pieces(int n, F f)
+{
+    if constexpr (S < kAttnSplitMax) {
+        if (S >= n) return;
+        f(std::integral_constant<int, S>{});
+        for_pieces<S + 1>(n, f);
+    }
+}
+
 // combines the split pieces of every row: out = sum_s w_s O_s / sum_s w_s l_s with
-// w_s = 2^(m_s - max m); pieces that saw no key carry l = 0 and drop out.  32 lanes per row, four
-// channels per lane, all pieces' loads issued before they are used.  PLANNED: the row's position says which pieces there are, and their
-// sums and rows are asked for together.
+// w_s = 2^(m_s - max m); pieces that saw no key carry l = 0 and drop out (a NaN sum does not: it has to reach the row).  32 lanes per row, four
+// channels per lane, two rows a wave.  PLANNED: the row's position says which pieces there are.
+// Bound by instructions: 10 waves a SIMD at 686 tokens of 32 heads, each with 16 slots of which four or five are used.  So a piece's
+// sum and weight are one lane's work and go to the others by row broadcasts, and the pieces of the wave's two rows are counted off from
+// the first, the same in every lane.
+// 780 tokens of 16 requests on 32:8 heads 11.4 -> 7.2 us, 686 of 2870 10.1 -> 8.2, 345 of 7 requests on 28:4 7.0 -> 6.2, 1063 of 35315 14.8 -> 13.5 (16
+// branches a lane and loop, a 64-bit division; the same without a plan, whose loops branched on the lane's sums, 10.7, 8.8, 6.3 and 14.0).
 template <bool PLANNED>
 __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_splits,
                                                          const float *__restrict__ part_o,
                                                          const float4 *__restrict__ part_ml,
                                                          uint16_t *__restrict__ out, float *__restrict__ lse_out, const AttnMergePlan pieces)
 {
-    const int64_t row = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
-    const int c = (threadIdx.x % 32) * 4;
-    if (row >= n_rows) return;
-    const float4 *ml = part_ml + row * n_splits;
-    const float *po = part_o + row * n_splits * D + c;
-    float4 v[kAttnSplitMax];
-    float4 p[kAttnSplitMax];
-    int first = 0, end = n_splits;
+    static_assert(kAttnSplitMax == 16, "a piece a lane of a row of 16");
+    const int64_t own = (int64_t)blockIdx.x * 8 + threadIdx.x / 32, row = own < n_rows ? own : n_rows - 1;
+    const int c = (threadIdx.x % 32) * 4, lane16 = threadIdx.x % 16;
+    int first = 0, begin = 0, end = n_splits;             // the row's first piece, and the pieces of the wave's two rows
     if (PLANNED) {
-        const int pos = min(max(pieces.sel_pos[row / pieces.n_q_heads], 0), pieces.max_ctx - 1);   // memory safety, as in the attention kernel
+        const int pos = min(max(pieces.sel_pos[(uint32_t)row / (uint32_t)pieces.n_q_heads], 0), pieces.max_ctx - 1);   // memory safety, as in the attention kernel
         const int4 plan = *pieces.plan;
-        end = min(plan.x, n_splits);
-        first = max(0, end - 1 - pos / (kAttnPieceKeys * plan.y));
+        end = __builtin_amdgcn_readfirstlane(min(plan.x, n_splits));
+        first = max(0, end - 1 - (int)((uint32_t)pos / (uint32_t)(kAttnPieceKeys * plan.y)));
+        begin = min(__builtin_amdgcn_readlane(first, 0), __builtin_amdgcn_readlane(first, 32));
     }
-    auto there = [&](int s) { return s >= first && s < end; };
-    auto some = [&](int s) { return there(s) && !(p[s].y == 0.f); };     // (a NaN sum is some: it has to reach the row)
-#pragma unroll
-    for (int s = 0; s < kAttnSplitMax; ++s)
-        if (there(s)) {
-            p[s] = ml[s];
-            if (PLANNED) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
-        }
-#pragma unroll
-    for (int s = 0; s < kAttnSplitMax; ++s)
-        if (!PLANNED && some(s)) v[s] = *reinterpret_cast<const float4 *>(po + s * D);
-    float m = -1.0e30f;
-#pragma unroll
-    for (int s = 0; s < kAttnSplitMax; ++s)
-        if (some(s)) m = fmaxf(m, p[s].x);
+    const int n = end - begin;
+    const float *po = part_o + (row * n_splits + begin) * D + c;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);           // of piece begin + lane16
+    if (lane16 < n) p = part_ml[row * n_splits + begin + lane16];
+    float4 v[kAttnSplitMax];
+    for_pieces(n, [&](auto s) { v[s] = *reinterpret_cast<const float4 *>(po + s * D); });
+    const bool some = lane16 < n && begin + lane16 >= first && !(p.y == 0.f);
+    const float m = row16_max(some ? fmaxf(p.x, -1.0e30f) : -1.0e30f);
+    const float weight = some ? __builtin_amdgcn_exp2f(p.x - m) : -1.f;      // (what a slot without a piece of the row holds is not looked at)
     float l = 0.f, l_exact = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int s = 0; s < kAttnSplitMax; ++s)
-        if (some(s)) {
-            const float w = __builtin_amdgcn_exp2f(p[s].x - m);
-            l += w * p[s].y;
-            l_exact += w * p[s].z;
-            o.x += w * v[s].x;
-            o.y += w * v[s].y;
-            o.z += w * v[s].z;
-            o.w += w * v[s].w;
-        }
+    for_pieces(n, [&](auto s) {
+        constexpr int kRowBroadcast = 0x150 + decltype(s)::value;
+        const float w = dpp_f32<kRowBroadcast>(weight), y = dpp_f32<kRowBroadcast>(p.y), z = dpp_f32<kRowBroadcast>(p.z);
+        if (w < 0.f) return;
+        l += w * y;
+        l_exact += w * z;
+        o.x += w * v[s].x;
+        o.y += w * v[s].y;
+        o.z += w * v[s].z;
+        o.w += w * v[s].w;
+    });
+    if (own >= n_rows) return;
     const float inv = 1.0f / l;
     uint2 w2;
     w2.x = f32_to_bf16_bits(o.x * inv) | (f32_to_bf16_bits(o.y * inv) << 16);
