@@ -913,8 +913,9 @@ namespace {
 // Positions.  All are read, 64 consecutive tokens of one request a wave at a time and PLAN_IN_FLIGHT such units asked for together: what this
 // kernel waits for is trips to memory, and one token a thread and trip made up to five of them, after a search for its request in
 // LDS.  Lane e of every wave has request e's geometry, so a unit's request is a count over the lanes and its geometry a lane's registers.
-// 16 requests of up to 1819 tokens, 4 % picked, 8.8 -> 5.6 us; 1063 of 35315 tokens on 28:4 heads 7.9 -> 5.5; 686 of 2870 on 32:8 4.9 -> 4.7.
-constexpr int PLAN_NT = 1024;
+// 16 requests of up to 1819 tokens, 4 % picked, 8.8 -> 5.3 us; 1063 of 35315 tokens on 28:4 heads 7.9 -> 5.2; 1508 of 14122 10.3 -> 7.0; 686 of
+// 2870 on 32:8 4.9 -> 4.3.  (16 waves instead of 8: 5.4, 5.5, 6.8 and 4.7.)
+constexpr int PLAN_NT = 512;
 constexpr int PLAN_TRIALS = 256;              // chunk sizes, one a thread
 constexpr int PLAN_IN_FLIGHT = 4;
 constexpr int PLAN_MAX_TILES = kAttnPlanMaxTiles;
@@ -962,7 +963,12 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
             if (at[f] < 0) continue;
             const int reach = min(max(p[f], 0), ctx_len - 1) / BN + 1;
             const int to_end = (n_sel - at[f]) * grp;                 // the token's rows and those behind it; the tiles end with them
-            for (int t = last - (to_end - 1) / ROWS; t <= last - (to_end - grp) / ROWS; ++t)
+            const int t0 = last - (to_end - 1) / ROWS, t1 = last - (to_end - grp) / ROWS;
+            // A tile's last token of the unit first, alone (64 lanes at one place in LDS take their turns): in ascending order the others then find
+            // nothing to raise.
+            const int next = lane == 63 || to_end == grp ? t1 + 1 : last - (to_end - grp - 1) / ROWS;
+            for (int t = t0; t < next && t <= t1; ++t) atomicMax(&len[t], reach);
+            for (int t = t0; t <= t1; ++t)
                 if (len[t] < reach) atomicMax(&len[t], reach);
         }
     }
