@@ -1167,11 +1167,17 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
     if (n_splits <= 1 || !workspace) {
         const int units = units_per_head(shape);
         const bool few = units <= kAttnShareMaxUnits && 2 * tiles <= KVS_ATTN_SHARE_MAX_X2 * units;
-        const bool draws = bd.n_req > 1 && tiles > units && units > 0 && workspace && workspace_bytes >= kAttnPlanBytes;
+        // Beyond 3.5 tiles a unit a workgroup a tile uses all units of the chip, which a draw a unit does not for head counts that do not divide
+        // their number: us against a workgroup a tile, with the write-back, 30 requests of up to 8000 tokens, 5 % picked, 52 heads of one query head (48
+        // units idle) 1000 and 966, 44 (36) 827 and 821, 56 (32) 1060 and 1041; 48, 40, 24 and 20 (16) 876 and 905, 733 and 755, 448 and 459, 375 and 384.
+        const bool all_units = units * shape->n_kv_heads * 16 >= kAttnSplitCus * 15;
+        const bool draws = bd.n_req > 1 && tiles > units && units > 0 && (few || all_units) && workspace && workspace_bytes >= kAttnPlanBytes;
         const int share_units = few && tiles > units && (bd.n_req <= kAttnShareMaxReq || !draws) ? units : 0;
         // (batches of any size keep shares where there is no workspace to draw from)
         // One request's tiles beyond that are left to the dispatcher: 131072 Yi-shaped tokens 11.65 ms against 11.85 with a queue, 30 % of
-        // 32768 the same.
+        // 32768 the same.  Several long ones gain as much as they lose, or more: us a workgroup a tile and drawn, with the write-back, on 32:8 heads
+        // 2 of 32000 tokens, 15 % picked, 2324 and 2328, 4 of 25000, 10 %, 1884 and 1869, 6 of 18000 1613 and 1625, 16 of 8500, 8 %, 855 and 831; on
+        // 32:4 3 of 32000, 12 %, 2742 and 2714; on 28:4 5 of 16000, 15 %, 1088 and 1063.
         int32_t *queue = nullptr;
         uint16_t *order = nullptr;
         if (share_units == 0 && draws) {
