@@ -822,7 +822,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
         if (RECENTRE || redo_flag == 0) break;
     }
     if (RECENTRE && again) continue;
-    // the next tile: its number is on its way while the rows leave
+    // the next tile (all waves wait for its number before the rows leave: a round trip to the counter a tile)
     if (QUEUE) {
         if (tid == 0) drawn = atomicAdd(queue + g, 1);
         __syncthreads();

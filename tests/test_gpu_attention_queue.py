@@ -1,6 +1,6 @@
 """Ragged batches with more row tiles than compute units: one workgroup a unit draws its tiles, in the order of their lengths up to 3.5 tiles a unit.
-Around that line and the one to fixed shares (8 requests), requests without and with few selected tokens, head counts that leave units over, more requests than one launch describes, a request
-beyond the last-level cache; every row against the oracle."""
+Around that line and the one to fixed shares (8 requests), requests without and with few selected tokens, head counts that leave units over (52: a workgroup
+a tile beyond 3.5), more requests than one launch describes, a request beyond the last-level cache; every row against the oracle.  Tiles that run again."""
 import numpy as np
 import pytest
 import torch
@@ -56,3 +56,51 @@ def test_drawn_tiles(kind, hk, want_lse):
         check_attention(got[:cu[-1]], ref, mag, "bf16", f"{kind}, {hk} heads")
         if want_lse:
             np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
+
+
+@pytest.mark.parametrize("kind,hk", [("15 tiles", 64), ("14 tiles", 64), ("large", 64)])
+@pytest.mark.parametrize("what", ["band", "first"])
+def test_drawn_tiles_that_run_again(kind, hk, what):
+    """Keys of 60 times the size in every other request (band), or a first tile far below the rest (first), in some of a workgroup's tiles: those run a
+    second time, or move their reference, before the next is drawn.  As without a workspace bit for bit, where nothing is drawn."""
+    print(f"attention: {kind}, {hk} heads, {what}", flush=True)
+    rng = np.random.default_rng(hk + len(kind))
+    off, length, cu, pos, rows = [], [], [0], [], 0
+    for n, k in _batch(rng, kind):
+        off.append(rows)
+        length.append(n)
+        rows += n + 3
+        pos.append(np.sort(rng.permutation(n)[:k]).astype(np.int32))
+        cu.append(cu[-1] + k)
+    pos = np.concatenate(pos)
+    gen = torch.Generator().manual_seed(hk)
+    q = torch.randn((cu[-1], hk, 128), generator=gen) / 128 ** 0.5
+    k = torch.randn((rows, hk, 128), generator=gen)
+    v = torch.randn((rows, hk, 128), generator=gen).to(torch.bfloat16)
+    checked = np.ones(cu[-1], bool)
+    if what == "first":
+        q[..., 127], k[..., 127] = 1.0, 0.0
+    for r, (o, n) in enumerate(zip(off, length)):
+        if r % 2:
+            continue
+        if what == "band":
+            k[o + n // 2 : o + n // 2 + 20] *= 60
+        else:
+            k[o : o + 32, :, 127] = -4e9
+            checked[cu[r] : cu[r + 1]] = pos[cu[r] : cu[r + 1]] >= 32        # (before that a row sees nothing but equals, up to rounding)
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    kn, vn = oracle._as_np(k), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0, off, length, cu)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0, off, length, cu)
+    sh = B.make_shape(hk, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, len(off), rows, cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+    got = []
+    for workspace in (ws, None):
+        out, lse = torch.full((cu[-1] + 2, hk, 128), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((cu[-1], hk), 7.0, device="cuda")
+        B.kvs_partial_attention(sh, off, length, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, workspace)
+        got.append((out, lse))
+    out, lse = got[0]
+    assert bool((out[cu[-1]:] == 7.0).all())
+    check_attention(out[: cu[-1]].float().cpu().numpy()[checked], ref[checked], mag[checked], "bf16", f"{kind}, {hk} heads, {what}")
+    np.testing.assert_allclose(lse.cpu().numpy()[checked], lse_ref[checked], rtol=1e-5, atol=2e-3)
+    assert torch.equal(out, got[1][0]) and torch.equal(lse, got[1][1])
