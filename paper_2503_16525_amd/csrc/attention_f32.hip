@@ -196,7 +196,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
             }
         }
     };
-    if (small) sweep(std::integral_constant<int, 1>{});
+    if (pmax < kF32Waves * 16) sweep(std::integral_constant<int, 1>{});      // (by the rows' reach: all but wave 0 ask again in a long context)
     else sweep(std::integral_constant<int, kF32Tiles>{});
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
