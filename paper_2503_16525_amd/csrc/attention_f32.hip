@@ -28,8 +28,18 @@ constexpr int kF32Waves = 8;
 constexpr int kF32Threads = kF32Waves * 64;
 constexpr int kF32Rows = 16;
 constexpr int kF32Tiles = 4;                           // tiles of 16 keys that a wave takes at a time (one in contexts where that leaves waves without)
+// Of them, in LDS together: as many as fit beside the query rows.  Of fp32 rows of 64 that leaves a compute unit one workgroup (the other kinds'
+// registers do so in any case, or two have room): with two tiles together it has two, which is the faster way for launches of many workgroups,
+// and of short contexts, where start and end are most of a workgroup's time.  us with four and two tiles together: 64:8 heads, 300 of 3000 tokens
+// (1200 workgroups) 114 and 96, 8:8 heads, 3000 tokens, 1400, 1100 and 760 of them (704, 552, 384) 74.2 and 65.8, 57.9 and 60.8, 44.3 and
+// 51.9; 4:4, 6000 tokens, 3000 and 2200 (752, 552) 143 and 126, 104 and 115; 8:8, 760 of 1250 (384) 25.1 and 26.1, 900 and 700 of 1000 (456, 352) 25.1
+// and 23.2, 21.5 and 23.1, 520 of 700 (264) 15.9 and 14.6; 16:16, 300 of 500 (304) 16.2 and 12.3.
 template <int DTYPE, int D>
-constexpr int kF32Flight = Rows16<DTYPE, D>::BYTES <= 4096 ? 4 : 2;   // of them, in LDS together: what fits beside the query rows
+constexpr int kF32Flight = Rows16<DTYPE, D>::BYTES <= 4096 ? 4 : 2;
+template <int DTYPE, int D>
+constexpr int kF32FlightShared = DTYPE == KVS_F32 && D == 64 ? 2 : kF32Flight<DTYPE, D>;
+// workgroups from which on two share a unit, by the longest context
+inline int64_t shared_from(int64_t max_ctx) { return max_ctx <= 768 ? 257 : max_ctx <= 1536 ? 451 : 641; }
 
 template <int DTYPE>
 __device__ __forceinline__ float load_elem(const void *p, int64_t i)
@@ -51,7 +61,7 @@ __device__ __forceinline__ void load_four(const void *p, int64_t i, float *x)
     }
 }
 
-template <int DTYPE, int D>
+template <int DTYPE, int D, int IN_FLIGHT>
 __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const AttnTiles td, int n_q_heads, int n_kv_heads, int total_tiles,
     const void *__restrict__ q_sel, const int32_t *__restrict__ sel_pos,
@@ -60,7 +70,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
 {
     constexpr int DB = D / 16;                         // matrix tiles of the output: tile db, row i is channel 64 (db / 4) + 4 i + db % 4
     using Rows = Rows16<DTYPE, D>;
-    extern __shared__ __attribute__((aligned(16))) char rows_s[];  // the query rows, then kF32Flight tiles of keys a wave; the results afterwards
+    extern __shared__ __attribute__((aligned(16))) char rows_s[];  // the query rows, then IN_FLIGHT tiles of keys a wave; the results afterwards
     __shared__ float m_s[kF32Waves][kF32Rows], l_s[kF32Waves][kF32Rows], x_s[kF32Waves][kF32Rows];
     const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kk = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -79,7 +89,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     };
     const int pos = min(max(sel_pos[sel0 + min(row0 + m16, n_rows - 1) / grp], 0), ctx_len - 1);       // memory safety; the caller guarantees the range
     if (wave < Rows::LOADS) Rows::load(q_sel, q_row, rows_s, wave, lane);
-    char *const mine = rows_s + Rows::BYTES * (1 + kF32Flight<DTYPE, D> * wave);
+    char *const mine = rows_s + Rows::BYTES * (1 + IN_FLIGHT * wave);
     // tile i of the wave's keys from k0 on (keys past `last` are clamped and not used)
     auto fetch = [&](int k0, int i, int last) {
 #pragma unroll
@@ -90,7 +100,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     const bool small = ctx_len <= kF32Waves * 16;
     const int first_k0 = wave * 16 * (small ? 1 : kF32Tiles);
 #pragma unroll
-    for (int i = 0; i < kF32Flight<DTYPE, D>; ++i)
+    for (int i = 0; i < IN_FLIGHT; ++i)
         if ((i == 0 || !small) && first_k0 + 16 * i < ctx_len) fetch(first_k0, i, ctx_len - 1);
     int pmin = pos, pmax = pos;
 #pragma unroll
@@ -108,7 +118,7 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     float m_run = kLowest, l_run = 0.f;               // l_run: this lane's keys only
     // the wave's keys, TILES tiles of 16 at a time: one where that leaves no wave without (64 fp32 tokens of 8 heads of 128: 13.2 -> 9.8 us)
     auto sweep = [&](auto tiles) {
-        constexpr int TILES = decltype(tiles)::value, FLIGHT = TILES < kF32Flight<DTYPE, D> ? TILES : kF32Flight<DTYPE, D>;
+        constexpr int TILES = decltype(tiles)::value, FLIGHT = TILES < IN_FLIGHT ? TILES : IN_FLIGHT;
         for (int k0 = wave * 16 * TILES; k0 <= pmax; k0 += kF32Waves * 16 * TILES) {
             f32x4 s[TILES];
             float mx = -INFINITY;
@@ -249,22 +259,22 @@ __global__ __launch_bounds__(kF32Threads, 2) void attn_f32_kernel(
     }
 }
 
-template <int DTYPE, int D>
+template <int DTYPE, int D, int IN_FLIGHT>
 kvs_status launch_f32(dim3 grid, const AttnTiles &td, const kvs_shape *shape, int tiles, const void *q_sel, const int32_t *sel_pos,
                       const void *k_cache, const void *v_cache, float scale, void *out, float *lse_out, hipStream_t st)
 {
     using Rows = Rows16<DTYPE, D>;
     static_assert(Rows::LOADS <= kF32Waves, "a wave loads one share of the query rows");
-    constexpr int keys = Rows::BYTES * (1 + kF32Flight<DTYPE, D> * kF32Waves), results = kF32Waves * kF32Rows * (64 + 4) * (int)sizeof(float);
+    constexpr int keys = Rows::BYTES * (1 + IN_FLIGHT * kF32Waves), results = kF32Waves * kF32Rows * (64 + 4) * (int)sizeof(float);
     constexpr int lds_bytes = keys > results ? keys : results;
     static DeviceOnce attr_once;
     const kvs_status ast = once_per_device(attr_once, [] {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_f32_kernel<DTYPE, D>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_f32_kernel<DTYPE, D, IN_FLIGHT>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         return e == hipSuccess ? KVS_OK : fail(KVS_EHIP, "kvs_partial_attention: hipFuncSetAttribute: %s", hipGetErrorString(e));
     });
     if (ast != KVS_OK) return ast;
-    hipLaunchKernelGGL((attn_f32_kernel<DTYPE, D>), grid, dim3(kF32Threads), lds_bytes, st, td, shape->n_q_heads, shape->n_kv_heads, tiles,
+    hipLaunchKernelGGL((attn_f32_kernel<DTYPE, D, IN_FLIGHT>), grid, dim3(kF32Threads), lds_bytes, st, td, shape->n_q_heads, shape->n_kv_heads, tiles,
                        q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out);
     return check_launch("kvs_partial_attention(f32)");
 }
@@ -282,12 +292,17 @@ kvs_status launch_attention_f32(const kvs_shape *shape, const AttnBatch &bd, int
     if (tiles < 0) return fail(KVS_EINVAL, "kvs_partial_attention: too many row tiles");
     if (tiles == 0) return KVS_OK;
     const dim3 grid((unsigned)(tiles * shape->n_kv_heads));
-#define KVS_ATT_CASE(DT, DD) return launch_f32<DT, DD>(grid, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, st)
+    int64_t max_ctx = 0;
+    for (int i = 0; i < bd.n_req; ++i) max_ctx = bd.ctx_len[i] > max_ctx ? bd.ctx_len[i] : max_ctx;
+    const bool shared = (int64_t)grid.x >= shared_from(max_ctx);
+#define KVS_ATT_CASE_(DT, DD, FL) launch_f32<DT, DD, FL>(grid, td, shape, (int)tiles, q_sel, sel_pos, k_cache, v_cache, scale, out, lse_out, st)
+#define KVS_ATT_CASE(DT, DD) return shared ? KVS_ATT_CASE_(DT, DD, (kF32FlightShared<DT, DD>)) : KVS_ATT_CASE_(DT, DD, (kF32Flight<DT, DD>))
     if (shape->dtype == KVS_F32 && shape->head_dim == 64) KVS_ATT_CASE(KVS_F32, 64);
     if (shape->dtype == KVS_F32 && shape->head_dim == 128) KVS_ATT_CASE(KVS_F32, 128);
     if (shape->dtype == KVS_BF16 && shape->head_dim == 64) KVS_ATT_CASE(KVS_BF16, 64);
     if (shape->dtype == KVS_BF16 && shape->head_dim == 128) KVS_ATT_CASE(KVS_BF16, 128);
 #undef KVS_ATT_CASE
+#undef KVS_ATT_CASE_
     return fail(KVS_EUNSUPPORTED, "kvs_partial_attention: head_dim %d", shape->head_dim);
 }
 

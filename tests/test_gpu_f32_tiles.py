@@ -63,6 +63,26 @@ def test_attention_low_in_a_long_context(dtype, hq, hk, d, n, lo, k):
     np.testing.assert_allclose(lse[:k].cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64)])
+@pytest.mark.parametrize("hq,hk,n,k", [(32, 32, 150, 128), (32, 32, 150, 129), (30, 30, 769, 240), (41, 41, 769, 171), (40, 40, 1537, 256), (40, 40, 1537, 257)])
+def test_attention_of_many_workgroups(dtype, d, hq, hk, n, k):
+    """On both sides of 256 workgroups with a short context, of 450 and 640 with longer ones: a wave's tiles in flight change."""
+    print(f"fp32 attention: {dtype} {hq}x{hk} heads, head_dim {d}, {k} of {n} tokens, {(k + 15) // 16 * hk} workgroups", flush=True)
+    w = layer(dtype, hq, hk, d, n)
+    lay = synth.make_layer(w)
+    pos = np.sort(np.random.default_rng(n + k).permutation(n)[:k]).astype(np.int32)
+    q = lay["q"][torch.from_numpy(pos.astype(np.int64))].contiguous()
+    ref, lse_ref = oracle.partial_attention(q, pos, oracle._as_np(lay["k_cache"]), oracle._as_np(lay["v_cache"]), 1.0)
+    out, lse = torch.full((k + 3, hq, d), 7.0, dtype=w.torch_dtype, device="cuda"), torch.full((k + 3, hq), 7.0, device="cuda")
+    B.kvs_partial_attention(B.shape_of(w), [0], [n], [0, k], q.cuda(), torch.from_numpy(pos).cuda(), lay["k_cache"].cuda(), lay["v_cache"].cuda(), 1.0, out, lse)
+    got = out.float().cpu().numpy().astype(np.float64)
+    assert np.all(got[k:] == 7.0) and bool((lse[k:] == 7.0).all()), "rows past the last one were written"
+    # as above: fp32 products and sums of up to 1537 weights; a bf16 result adds its own rounding
+    tol = 1e-5 * (1.0 + np.abs(ref).max()) + (2.0 ** -8 * np.abs(ref) if dtype == "bf16" else 0.0)
+    assert np.all(np.abs(got[:k] - ref) <= tol), np.abs(got[:k] - ref).max()
+    np.testing.assert_allclose(lse[:k].cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("dtype,hq,hk,d", SHAPES)
 @pytest.mark.parametrize("at", [0, 15, 16, 50, 130, 400])
 def test_attention_hides_what_a_row_does_not_see(dtype, hq, hk, d, at):
