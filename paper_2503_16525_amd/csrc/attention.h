@@ -75,7 +75,8 @@ constexpr int kAttnSplitBelowWgs = 384;    // launches with fewer workgroups tha
 // 32768 tokens)
 constexpr double kAttnPieceOverhead = 18.0;
 // Pieces of the 256-row kernel, as the merge sees them: piece s is keys [kAttnPieceKeys * y * (x - 1 - s), kAttnPieceKeys * y * (x - s)) with x, y of
-// what attn_plan_kernel left, and only pieces that begin at or before a row's position have left anything for it.
+// what attn_plan_kernel left, and only pieces that begin at or before a row's position have left anything for it (a position past its request's context: empty
+// records above the context's last piece).
 struct AttnMergePlan {
     const int4 *plan;          // nullptr: every one of n_splits slots is filled in, without keys with sum 0
     const int32_t *sel_pos;    // of the first row's token

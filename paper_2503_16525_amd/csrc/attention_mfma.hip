@@ -377,7 +377,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(int64_t n_rows, int n_s
     const int c = (threadIdx.x % 32) * 4, lane16 = threadIdx.x % 16;
     int first = 0, begin = 0, end = n_splits;             // the row's first piece, and the pieces of the wave's two rows
     if (PLANNED) {
-        const int pos = min(max(pieces.sel_pos[(uint32_t)row / (uint32_t)pieces.n_q_heads], 0), pieces.max_ctx - 1);   // memory safety, as in the attention kernel
+        const int pos = min(max(pieces.sel_pos[(uint32_t)row / (uint32_t)pieces.n_q_heads], 0), pieces.max_ctx - 1);   // (past its own context: see the attention kernel's epilogue)
         const int4 plan = *pieces.plan;
         end = __builtin_amdgcn_readfirstlane(min(plan.x, n_splits));
         first = max(0, end - 1 - (int)((uint32_t)pos / (uint32_t)(kAttnPieceKeys * plan.y)));

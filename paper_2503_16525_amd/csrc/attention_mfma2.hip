@@ -275,7 +275,7 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
     again = false;
     const int rest = it;
     // split launches walk the list of pieces the plan kernel wrote, from the top of the context down.
-    // The plan: pieces per row tile in use, key tiles per piece, pieces that have keys
+    // The plan: pieces per row tile in use, key tiles per piece, pieces that have keys, whether a position lies past its context
     int4 plan = make_int4(1, 0, 0, 0);
     if (SPLIT) {
         plan = *split_plan;
@@ -867,6 +867,10 @@ __global__ __launch_bounds__(NT, 1) void attn_mfma2_kernel(
             }
             if (row_ok[nb] && hf == 0)
                 part_ml[row_idx[nb] * (int64_t)n_splits + split] = make_float4(m_ref[nb], l_tot[nb], WANT_LSE ? l_exact_tot : l_tot[nb], 0.f);
+            // A position past its request's context counts as the context's last.  The merge does not know the requests: where there are such
+            // positions (plan.w), a row's top piece leaves an empty record for each piece above it.
+            if (plan.w != 0 && row_ok[nb] && hf == 0 && pos[nb] >= t_lo * BN && pos[nb] < t_hi * BN && sel_pos[row_idx[nb] / n_q_heads] > pos[nb])
+                for (int above = 0; above < split; ++above) part_ml[row_idx[nb] * (int64_t)n_splits + above] = make_float4(-1.0e30f, 0.f, 0.f, 0.f);
             continue;
         }
         if (row_ok[nb]) {
@@ -928,12 +932,13 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
     __shared__ int len[PLAN_MAX_TILES];       // key tiles of each row tile
     __shared__ int first_fit[PLAN_MAX_ROUNDS];
     __shared__ int2 chosen;
-    __shared__ int wave_total[PLAN_NT / 64];
+    __shared__ int wave_total[PLAN_NT / 64], past_context;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_sel_l = td.n_sel[lane], ctx_len_l = td.ctx_len[lane], tile_end_l = td.tile_begin[lane + 1];   // (no tokens past n_req)
     const int64_t sel_lo_l = td.sel_lo[lane];
     for (int t = tid; t < total_tiles; t += PLAN_NT) len[t] = 0;
     if (tid < PLAN_MAX_ROUNDS) first_fit[tid] = 0x7fffffff;
+    if (tid == 0) past_context = 0;
     int units_upto = (n_sel_l + 63) / 64;     // of this lane's request and those before it
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -961,6 +966,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
             const int n_sel = __builtin_amdgcn_readlane(n_sel_l, req[f]), ctx_len = __builtin_amdgcn_readlane(ctx_len_l, req[f]);
             const int last = __builtin_amdgcn_readlane(tile_end_l, req[f]) - 1;
             if (at[f] < 0) continue;
+            if (p[f] >= ctx_len) past_context = 1;
             const int reach = min(max(p[f], 0), ctx_len - 1) / BN + 1;
             const int to_end = (n_sel - at[f]) * grp;                 // the token's rows and those behind it; the tiles end with them
             const int t0 = last - (to_end - 1) / ROWS, t1 = last - (to_end - grp) / ROWS;
@@ -1031,7 +1037,7 @@ __global__ __launch_bounds__(PLAN_NT) void attn_plan_kernel(
         before += w < wave ? wave_total[w] : 0;
         total += wave_total[w];
     }
-    if (tid == 0) *plan = make_int4(pl.x, pl.y, total, 0);
+    if (tid == 0) *plan = make_int4(pl.x, pl.y, total, past_context);
     for (int e = e0; e < e1; ++e)
         if (has_keys(e)) piece_list[before++] = (uint16_t)e;
 }

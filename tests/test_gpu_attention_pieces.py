@@ -129,3 +129,29 @@ def test_every_position_is_in_the_plan(hq, hk, lens, counts, order):
     B.kvs_partial_attention(sh, off, lens, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, ws)
     check_attention(out.float().cpu().numpy(), ref, mag, "bf16", f"{sum(counts)} tokens of {len(lens)} requests, {order}")
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
+
+
+def test_positions_past_a_short_context():
+    """A position past its own request's context, but not past the longest one, is taken as the context's last: the pieces that such a context does not have
+    are not read for it."""
+    print("attention: positions past a short context, pieces of a batch", flush=True)
+    hq, hk, lens, counts = 32, 8, [1100, 3000], [120, 200]
+    rng = np.random.default_rng(5)
+    off, cu = [0, lens[0] + 1], [0, counts[0], sum(counts)]
+    pos = np.concatenate([np.sort(rng.permutation(n)[:k]) for n, k in zip(lens, counts)]).astype(np.int32)
+    past = [7, 60, counts[0] - 1]
+    pos[past] = lens[0] - 1
+    gen = torch.Generator().manual_seed(5)
+    q = (torch.randn((cu[-1], hq, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16).cuda()
+    k, v = (torch.randn((sum(lens) + 1, hk, 128), generator=gen).to(torch.bfloat16).cuda() for _ in range(2))
+    sh = B.make_shape(hq, hk, 128, B.BF16)
+    got = []
+    for over in (0, 1, 700, 10 ** 9):
+        p = pos.copy()
+        p[past] += over
+        ws = torch.full((B.kvs_workspace_size("partial_attention", sh, 2, sum(lens) + 1, cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+        out, lse = torch.full((cu[-1], hq, 128), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((cu[-1], hq), 7.0, device="cuda")
+        B.kvs_partial_attention(sh, off, lens, cu, q, torch.from_numpy(p).cuda(), k, v, 1.0, out, lse, ws)
+        got.append((out, lse))
+        assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(lse).all()), over
+    assert all(torch.equal(o, got[0][0]) and torch.equal(s, got[0][1]) for o, s in got[1:])
