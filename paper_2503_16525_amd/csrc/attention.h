@@ -39,7 +39,8 @@ struct AttnTiles {
 // attention, 2 requests 28.7, 28.9, 28.6; 8: 39.8, 40.4, 39.5 to 40.2; 64: 72.5, 61.6, 61.4.
 __device__ __forceinline__ int request_of(const int32_t *tile_begin, int n_req, int t)
 {
-    static_assert(kAttnMaxReq == 64, "four blocks of 16");
+    static_assert(kAttnMaxReq == 64, "three quarterings");
+    if (n_req <= 1) return 0;
     auto upto_t = [t](int begin) { return (int)((uint32_t)(begin - (t + 1)) >> 31); };     // begin <= t, without a detour over vector registers
     int b = 0;
 #pragma unroll
