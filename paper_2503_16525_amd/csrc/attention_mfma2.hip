@@ -59,7 +59,7 @@ constexpr int TILE_B = BN * ROW_B;      // a K or V tile in LDS: 32 rows of 256 
 // Tiles are requested AHEAD steps before their softmax; the barrier of a step lets the
 // 4 * (AHEAD - 3) staging instructions of the younger tiles stay in flight.
 #ifndef KVS_ATTN_SHARE_MAX_X2
-#define KVS_ATTN_SHARE_MAX_X2 7      // launches run per-unit shares up to this many half-tiles per unit (7 = 3.5 tiles)
+#define KVS_ATTN_SHARE_MAX_X2 7      // half-tiles per unit (7 = 3.5 tiles) up to which launches run per-unit shares, and batches draw tiles put in order
 #endif
 #ifndef KVS_ATTN_AHEAD
 #define KVS_ATTN_AHEAD 4
