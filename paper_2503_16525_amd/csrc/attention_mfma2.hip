@@ -1176,8 +1176,10 @@ kvs_status launch_attention_mfma2(const kvs_shape *shape, const AttnBatch &bd, c
         // Beyond 3.5 tiles a unit a workgroup a tile uses all units of the chip, which a draw a unit does not for head counts that do not divide
         // their number: us against a workgroup a tile, with the write-back, 30 requests of up to 8000 tokens, 5 % picked, 52 heads of one query head (48
         // units idle) 1000 and 966, 44 (36) 827 and 821, 56 (32) 1060 and 1041; 48, 40, 24 and 20 (16) 876 and 905, 733 and 755, 448 and 459, 375 and 384.
+        // Where no shares are made (more than 64 units a head) a draw pays from 1.5 tiles a unit on: 32:1 heads, 1.4, 1.8 and 2.1 tiles a unit 202 and 194,
+        // 387 and 401, 117 and 135; 24:3, 1.5 and 1.8, 201 and 196, 112 and 128.
         const bool all_units = units * shape->n_kv_heads * 16 >= kAttnSplitCus * 15;
-        const bool draws = bd.n_req > 1 && tiles > units && units > 0 && (few || all_units) && workspace && workspace_bytes >= kAttnPlanBytes;
+        const bool draws = bd.n_req > 1 && units > 0 && (few ? tiles > units : all_units && 2 * tiles > 3 * units) && workspace && workspace_bytes >= kAttnPlanBytes;
         const int share_units = few && tiles > units && (bd.n_req <= kAttnShareMaxReq || !draws) ? units : 0;
         // (batches of any size keep shares where there is no workspace to draw from)
         // One request's tiles beyond that are left to the dispatcher: 131072 Yi-shaped tokens 11.65 ms against 11.85 with a queue, 30 % of

@@ -58,6 +58,29 @@ def test_drawn_tiles(kind, hk, want_lse):
             np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
 
 
+@pytest.mark.parametrize("hq,hk,n_req", [(32, 1, 11), (32, 1, 13), (24, 3, 15), (24, 3, 17)])
+def test_drawn_tiles_of_few_heads(hq, hk, n_req):
+    """No shares are made for more than 64 units a head: on both sides of 1.5 tiles a unit, where the draw begins."""
+    n_tokens = 256 if hk == 1 else 248
+    print(f"attention: {n_req} requests of {n_tokens} tokens, {hq}x{hk} heads, {n_tokens * hq // hk / 256 * n_req / (256 // hk):.2f} tiles a unit", flush=True)
+    rng = np.random.default_rng(hq + n_req)
+    lens = [int(n) for n in rng.integers(300, 700, n_req)]
+    off, cu = np.cumsum([0] + [n + 3 for n in lens]).tolist(), [n_tokens * i for i in range(n_req + 1)]
+    pos = np.concatenate([np.sort(rng.permutation(n)[:n_tokens]) for n in lens]).astype(np.int32)
+    gen = torch.Generator().manual_seed(hq)
+    q = (torch.randn((cu[-1], hq, 128), generator=gen) / 128 ** 0.5).to(torch.bfloat16)
+    k, v = (torch.randn((off[-1], hk, 128), generator=gen).to(torch.bfloat16) for _ in range(2))
+    kn, vn = oracle._as_np(k), oracle._as_np(v)
+    ref, lse_ref = oracle.partial_attention(q, pos, kn, vn, 1.0, off[:-1], lens, cu)
+    mag, _ = oracle.partial_attention(q, pos, kn, vn & np.uint16(0x7FFF), 1.0, off[:-1], lens, cu)
+    sh = B.make_shape(hq, hk, 128, B.BF16)
+    ws = torch.full((B.kvs_workspace_size("partial_attention", sh, n_req, off[-1], cu[-1]),), 255, dtype=torch.uint8, device="cuda")
+    out, lse = torch.full((cu[-1], hq, 128), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((cu[-1], hq), 7.0, device="cuda")
+    B.kvs_partial_attention(sh, off[:-1], lens, cu, q.cuda(), torch.from_numpy(pos).cuda(), k.cuda(), v.cuda(), 1.0, out, lse, ws)
+    check_attention(out.float().cpu().numpy(), ref, mag, "bf16", f"{n_req} requests, {hq}x{hk} heads")
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, atol=2e-3)
+
+
 @pytest.mark.parametrize("kind,hk", [("15 tiles", 64), ("14 tiles", 64), ("large", 64)])
 @pytest.mark.parametrize("what", ["band", "first"])
 def test_drawn_tiles_that_run_again(kind, hk, what):
